@@ -37,7 +37,8 @@
  *     break the precondition makes the accumulator wrap silently (two's complement), where the
  *     CPU oracle reports an overflow.  F8_ERR_ACC_OVERFLOW is reserved for checkers that see the data.
  *   - x, w, y must not overlap.  q->res may be any tensor of y's shape except y itself.
- *   - The single-layer dense calls keep a small device scratch buffer per (device, stream):
+ *   - The single-layer dense calls that do not take the K-sharing kernel (small outputs and odd channel
+ *     counts do: one launch, no scratch) keep a small device scratch buffer per (device, stream):
  *     256 bytes of zeros (the kernels' stand-in for padding) plus the folded accumulator
  *     start value, 4 bytes per output channel rounded up to 256 channels, at least 64 KiB.
  *     It is allocated (hipMalloc) on the first call on a stream and when a call needs more
@@ -109,7 +110,7 @@ f8_status f8_conv2d_fixed(const void *x, const int8_t *w, const int32_t *bias, v
  * into a HIP graph and issued from any number of host threads and streams at once, as long as
  * calls that may overlap use different workspaces.  `workspace` is device memory, 256-byte
  * aligned, of at least f8_conv_workspace_bytes(Cout) bytes (F8_ERR_ALIGN / F8_ERR_SHAPE otherwise);
- * the call overwrites it (256 bytes of zeros, then the folded accumulator start values) and
+ * the call may overwrite it (256 bytes of zeros, then the folded accumulator start values) and
  * later calls on the same stream may reuse it. */
 size_t f8_conv_workspace_bytes(int Cout);
 f8_status f8_conv2d_fixed_ws(const void *x, const int8_t *w, const int32_t *bias, void *y,
@@ -369,7 +370,8 @@ f8_status f8_mfma_i8_yardstick(int32_t *sink, int iters, double *ops, void *stre
 f8_status f8_mfma_i8_yardstick_operands(int32_t *sink, int iters, uint32_t seed, double *ops, void *stream);
 /* Tuning switches: kernel choices only, never results (the parity tests force every tile variant
  * through them).  Names and defaults: "conv_variant" (-1 = automatic; >= 0 forces that tile
- * variant of the LDS-direct dense kernel), "conv_ws", "conv_ws_min" (768: smallest layer, in blocks
+ * variant of the LDS-direct dense kernel), "wavek" (0: the K-sharing kernel only for layers no other kernel
+ * takes), "wavek_variant" (-1 = automatic; >= 0 forces that tile shape of it), "conv_ws", "conv_ws_min" (768: smallest layer, in blocks
  * of 128 pixels, that takes the weights-stationary 3x3 kernel), "pw_ws", "pw_small", "xcd_remap",
  * "pw_wide", "pw_mid" (1: the 1x1 128 -> 512 kernel only together with the 512 -> 128 layer behind it, 2: also
  * alone), "stem_pool", "conv_tail", "conv_img" (1 = on), "conv_img_min" (96: fewest images, or

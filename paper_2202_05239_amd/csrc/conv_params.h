@@ -37,14 +37,6 @@ struct ConvParams {
   FastDiv fd_pq, fd_q, fd_c, fd_s, fd_cpt, fd_cpt2;   // by P*Q, Q, C, S, C / 64, C / 128
 };
 
-// Launches the implicit-GEMM kernel.  vec is the widest of 16, 4, 1 bytes that divides C
-// and the alignment of x and w.  Returns a hipError_t as int.
-int launch_conv_igemm(const ConvParams &p, int vec, hipStream_t stream);
-
-// Which tile shape launch_conv_igemm picks for N output channels, and its name.
-int conv_variant(int N);
-const char *conv_variant_name(int variant);
-
 // Fast path (conv_fast.hip): Cin % 16 == 0, 8-bit output and residual, Cout % 4 == 0,
 // 16-byte aligned x and w.  conv_fast_variant picks the tile shape.
 bool conv_fast_applicable(const ConvParams &p);

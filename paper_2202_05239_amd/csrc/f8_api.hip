@@ -12,6 +12,7 @@ namespace {
 struct TuningName { const char *name; const char *env; std::atomic<int> Tuning::*field; };
 const TuningName kTuningNames[] = {
     {"conv_variant", "F8_CONV_VARIANT", &Tuning::conv_variant}, {"conv_ws", "F8_CONV_WS", &Tuning::conv_ws},
+    {"wavek", "F8_WAVEK", &Tuning::wavek}, {"wavek_variant", "F8_WAVEK_VARIANT", &Tuning::wavek_variant},
     {"conv_ws_min", "F8_CONV_WS_MIN", &Tuning::conv_ws_min},
     {"pw_ws", "F8_PW_WS", &Tuning::pw_ws},                       {"pw_small", "F8_PW_SMALL", &Tuning::pw_small},
     {"xcd_remap", "F8_XCD_REMAP", &Tuning::xcd_remap},           {"stem_pool", "F8_STEM_POOL", &Tuning::stem_pool},
@@ -87,13 +88,6 @@ f8_status check_align(const int32_t *bias, const void *y, const f8_quant &q, con
   return F8_OK;
 }
 
-static int widest_vec(int C, const void *a, const void *b) {
-  const uintptr_t bits = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | (uintptr_t)C;
-  if ((bits & 15) == 0) return 16;
-  if ((bits & 3) == 0) return 4;
-  return 1;
-}
-
 // The 3x3 64 -> 64 layers have a kernel of their own (weights in registers, input patch in LDS).
 static bool use_conv_ws(const void *x, const int8_t *w, const void *y, const void *res, const Geom &g,
                         const f8_quant &q, const void *y2) {
@@ -141,6 +135,57 @@ static bool use_pw_small(const void *x, const int8_t *w, const void *y, const vo
   if (!tuning().pw_small.load(std::memory_order_relaxed) || res || y2 || q.y_type == F8_S32) return false;
   if ((long long)g.B * g.H * g.W < 65536) return false;
   return pw_small_applicable(g.Cin, g.Cout, g.R, g.S, g.sh, g.sw, g.ph, g.pw, q.fl_x + q.fl_w - q.fl_y, x, w, y);
+}
+
+// Launch parameters of the general dense kernels (conv_fast, conv_wavek).
+static ConvParams conv_params(const void *x, const int8_t *w, const int32_t *acc0, const void *zero, void *y, const void *res,
+                              const Geom &g, const f8_quant &q, const f8_requant2 *q2, void *y2) {
+  ConvParams p;
+  p.y2 = nullptr;
+  p.shift2 = p.lo2 = p.hi2 = p.add2 = 0;
+  if (q2 && y2) {
+    p.y2 = y2;
+    p.shift2 = q.fl_x + q.fl_w - q2->fl_y;
+    p.lo2 = q2->clip_lo; p.hi2 = q2->clip_hi;
+    p.add2 = (p.shift2 > 0 ? (1 << (p.shift2 - 1)) : 0) - rounding_addend(q);
+  }
+  p.zero = static_cast<const uint8_t *>(zero);
+  {
+    const uintptr_t xa = reinterpret_cast<uintptr_t>(x), za = reinterpret_cast<uintptr_t>(zero);
+    const uintptr_t lo = xa < za ? xa : za;
+    const unsigned long long xbytes = (unsigned long long)g.B * g.H * g.W * g.Cin;
+    p.lo_base = reinterpret_cast<const uint8_t *>(lo);
+    p.x_delta = (uint32_t)(xa - lo);
+    p.z_delta = (uint32_t)(za - lo);
+    p.near = (xa - lo) + xbytes + 64 < 0x7fffffffULL && (za - lo) + 64 < 0x7fffffffULL;
+  }
+  p.x = static_cast<const uint8_t *>(x);
+  p.w = w;
+  p.acc0 = acc0;
+  p.y = y;
+  p.res = res;
+  p.B = g.B; p.H = g.H; p.W = g.W; p.C = g.Cin; p.N = g.Cout; p.R = g.R; p.S = g.S;
+  p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.P = g.P; p.Q = g.Q;
+  p.M = g.B * g.P * g.Q;
+  p.K = g.R * g.S * g.Cin;
+  p.xor_mask = q.x_type == F8_U8 ? 0x80808080u : 0u;
+  p.shift = q.y_type == F8_S32 ? 0 : q.fl_x + q.fl_w - q.fl_y;
+  p.lo = q.clip_lo; p.hi = q.clip_hi;
+  p.y_type = q.y_type;
+  p.res_type = q.res_type;
+  p.res_d = q.fl_x + q.fl_w - q.fl_res;
+  p.fd_pq = FastDiv((uint32_t)(g.P * g.Q));
+  p.fd_q = FastDiv((uint32_t)g.Q);
+  p.fd_c = FastDiv((uint32_t)g.Cin);
+  p.fd_cpt = FastDiv((uint32_t)((g.Cin & 63) == 0 ? g.Cin / 64 : 1));
+  p.fd_cpt2 = FastDiv((uint32_t)((g.Cin & 127) == 0 ? g.Cin / 128 : 1));
+  p.remap = tuning().xcd_remap.load(std::memory_order_relaxed) != 0;
+  p.gemm = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
+  p.fd_s = FastDiv((uint32_t)g.S);
+  p.tap_rep = 0;
+  if (g.R * g.S <= 32)
+    for (int r = 0; r < g.R; ++r) p.tap_rep |= 1u << (r * g.S);
+  return p;
 }
 
 f8_status enqueue_conv(const void *x, const int8_t *w, const int32_t *acc0, const void *zero, void *y,
@@ -232,55 +277,30 @@ f8_status enqueue_conv(const void *x, const int8_t *w, const int32_t *acc0, cons
     wp.tiles_per_image = wp.ntiles = wp.nrows = wp.pitch = wp.nchunks = 0;
     return launch_conv_ws(wp, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
   }
-  ConvParams p;
-  p.y2 = nullptr;
-  p.shift2 = p.lo2 = p.hi2 = p.add2 = 0;
-  if (q2 && y2) {
-    p.y2 = y2;
-    p.shift2 = q.fl_x + q.fl_w - q2->fl_y;
-    p.lo2 = q2->clip_lo; p.hi2 = q2->clip_hi;
-    p.add2 = (p.shift2 > 0 ? (1 << (p.shift2 - 1)) : 0) - rounding_addend(q);
-  }
-  p.zero = static_cast<const uint8_t *>(zero);
-  {
-    const uintptr_t xa = reinterpret_cast<uintptr_t>(x), za = reinterpret_cast<uintptr_t>(zero);
-    const uintptr_t lo = xa < za ? xa : za;
-    const unsigned long long xbytes = (unsigned long long)g.B * g.H * g.W * g.Cin;
-    p.lo_base = reinterpret_cast<const uint8_t *>(lo);
-    p.x_delta = (uint32_t)(xa - lo);
-    p.z_delta = (uint32_t)(za - lo);
-    p.near = (xa - lo) + xbytes + 64 < 0x7fffffffULL && (za - lo) + 64 < 0x7fffffffULL;
-  }
-  p.x = static_cast<const uint8_t *>(x);
-  p.w = w;
-  p.acc0 = acc0;
-  p.y = y;
-  p.res = res;
-  p.B = g.B; p.H = g.H; p.W = g.W; p.C = g.Cin; p.N = g.Cout; p.R = g.R; p.S = g.S;
-  p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.P = g.P; p.Q = g.Q;
-  p.M = g.B * g.P * g.Q;
-  p.K = g.R * g.S * g.Cin;
-  p.xor_mask = q.x_type == F8_U8 ? 0x80808080u : 0u;
-  p.shift = q.y_type == F8_S32 ? 0 : q.fl_x + q.fl_w - q.fl_y;
-  p.lo = q.clip_lo; p.hi = q.clip_hi;
-  p.y_type = q.y_type;
-  p.res_type = q.res_type;
-  p.res_d = q.fl_x + q.fl_w - q.fl_res;
-  const int vec = widest_vec(g.Cin, x, w);
-  p.fd_pq = FastDiv((uint32_t)(g.P * g.Q));
-  p.fd_q = FastDiv((uint32_t)g.Q);
-  p.fd_c = FastDiv((uint32_t)g.Cin);
-  p.fd_cpt = FastDiv((uint32_t)((g.Cin & 63) == 0 ? g.Cin / 64 : 1));
-  p.fd_cpt2 = FastDiv((uint32_t)((g.Cin & 127) == 0 ? g.Cin / 128 : 1));
-  p.remap = tuning().xcd_remap.load(std::memory_order_relaxed) != 0;
-  p.gemm = g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
-  p.fd_s = FastDiv((uint32_t)g.S);
-  p.tap_rep = 0;
-  if (g.R * g.S <= 32)
-    for (int r = 0; r < g.R; ++r) p.tap_rep |= 1u << (r * g.S);
+  const ConvParams p = conv_params(x, w, acc0, zero, y, res, g, q, q2, y2);
   if (p.M == 0 || p.N == 0) return F8_OK;
-  if (conv_fast_applicable(p)) return launch_conv_fast(p, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
-  return launch_conv_igemm(p, vec, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
+  const bool fast = conv_fast_applicable(p);
+  const int wk = conv_wavek_variant(p, !fast);
+  if (wk >= 0) return launch_conv_wavek(p, wk, false, nullptr, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
+  return launch_conv_fast(p, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
+}
+
+// Which kernel a dense layer takes does not depend on acc0 and the page of zeros, so the layers that
+// conv_wavek takes are known before anything is folded; it forms the start values itself.
+static bool takes_own_kernel(const void *x, const int8_t *w, const void *y, const void *res, const Geom &g, const f8_quant &q, void *y2) {
+  return use_pw_small(x, w, y, res, g, q, y2) || use_pw_ws(x, w, y, res, g, q, y2) || use_pw_mid(x, w, y, res, g, q, y2, false) ||
+         use_pw_wide(x, w, y, res, g, q, y2) || use_conv_ws(x, w, y, res, g, q, y2);
+}
+
+bool enqueue_conv_folding(const void *x, const int8_t *w, const int32_t *bias, void *y, const void *res, const Geom &g,
+                          const f8_quant &q, hipStream_t stream, const f8_requant2 *q2, void *y2, f8_status *st) {
+  if (takes_own_kernel(x, w, y, res, g, q, (q2 && y2) ? y2 : nullptr)) return false;
+  ConvParams p = conv_params(x, w, nullptr, nullptr, y, res, g, q, q2, y2);
+  p.near = 1;                           // (only conv_fast reads the page of zeros)
+  const int wk = conv_wavek_variant(p, !conv_fast_applicable(p));
+  if (wk < 0) return false;
+  *st = launch_conv_wavek(p, wk, true, bias, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
+  return true;
 }
 
 bool conv_reads_narrow_rows(const Geom &g, const f8_quant &q, bool has_res) {
@@ -315,8 +335,9 @@ const char *conv_kernel_name(const Geom &g, const f8_quant &q, bool has_res) {
   p.P = g.P; p.Q = g.Q;
   p.M = (g.B > 0 ? g.B : 1) * g.P * g.Q;
   p.K = g.R * g.S * g.Cin;
-  if (conv_fast_applicable(p)) return conv_fast_variant_name(conv_fast_variant(p));
-  return conv_variant_name(conv_variant(g.Cout));
+  const bool fast = conv_fast_applicable(p);
+  const int wk = conv_wavek_variant(p, !fast);
+  return wk >= 0 ? conv_wavek_name(wk, conv_wavek_direct(p)) : conv_fast_variant_name(conv_fast_variant(p));
 }
 
 f8_status enqueue_fold(const int8_t *w, const int32_t *bias, int32_t *acc0, const Geom &g,
@@ -408,6 +429,8 @@ int32_t *scratch_for(hipStream_t stream, size_t ints) {
 // Fold + layer of one single-layer dense call on the stream's own scratch.
 f8_status dense_on_stream_scratch(const void *x, const int8_t *w, const int32_t *bias, void *y, const Geom &g,
                                   const f8_quant &q, hipStream_t s, const f8_requant2 *q2, void *y2) {
+  f8_status done;
+  if (enqueue_conv_folding(x, w, bias, y, q.res, g, q, s, q2, y2, &done)) return done;
   std::lock_guard<std::mutex> lock(g_mu);
   int32_t *scratch = scratch_for(s, 64 + acc0_padded(g.Cout));
   if (!scratch) return F8_ERR_DEVICE;
@@ -483,6 +506,7 @@ f8_status f8_conv2d_fixed_ws(const void *x, const int8_t *w, const int32_t *bias
   if (workspace_bytes < f8_conv_workspace_bytes(Cout)) return F8_ERR_SHAPE;
   if ((long long)g.B * g.P * g.Q * g.Cout == 0) return F8_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (enqueue_conv_folding(x, w, bias, y, q->res, g, *q, s, nullptr, nullptr, &st)) return st;
   // the first 256 bytes are the kernels' page of zeros (cleared by a kernel, so the call can be captured),
   // the folded start values follow
   int32_t *base = static_cast<int32_t *>(workspace);
@@ -507,9 +531,10 @@ f8_status f8_conv2d_fixed_noalloc(const void *x, const int8_t *w, const int32_t 
   if (q->res == y) return F8_ERR_UNSUPPORTED;
   if (Cout > kStaticMaxCout || acc0_padded(Cout) > (size_t)kStaticMaxCout) return F8_ERR_UNSUPPORTED;
   if ((long long)g.B * g.P * g.Q * g.Cout == 0) return F8_OK;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (enqueue_conv_folding(x, w, bias, y, q->res, g, *q, s, nullptr, nullptr, &st)) return st;
   int32_t *base = static_scratch();
   if (!base) return F8_ERR_DEVICE;
-  hipStream_t s = static_cast<hipStream_t>(stream);
   int32_t *acc0 = base + 64;
   st = enqueue_fold(w, bias, acc0, g, *q, s);
   if (st != F8_OK) return st;

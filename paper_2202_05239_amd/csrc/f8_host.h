@@ -8,7 +8,8 @@
 #include <atomic>
 
 #include "../../include/f8.h"
-#include "conv_igemm.h"
+#include "conv_params.h"
+#include "conv_wavek.h"
 #include "conv_ws.h"
 #include "pw_ws.h"
 #include "pw_wide.h"
@@ -23,6 +24,8 @@ namespace f8 {
 // the C header) and afterwards only through f8_tuning_set; the launch paths read these ints.
 struct Tuning {
   std::atomic<int> conv_variant{-1};   // >= 0: force this tile variant of the LDS-direct dense kernel
+  std::atomic<int> wavek{1};           // K-sharing kernel where it is the faster one (0: only for layers no other kernel takes)
+  std::atomic<int> wavek_variant{-1};  // >= 0: force this tile shape of it
   std::atomic<int> conv_ws{1};         // weights-stationary 3x3 kernel
   std::atomic<int> conv_ws_min{768};    // ... from this many 128-pixel (64 channels) or 64-pixel (128 channels) blocks on
   std::atomic<int> pw_ws{1};           // weights-stationary 1x1 kernel (64 -> 256)
@@ -78,6 +81,11 @@ struct ConvTail {
 f8_status enqueue_conv(const void *x, const int8_t *w, const int32_t *acc0, const void *zero, void *y,
                        const void *res, const Geom &g, const f8_quant &q, hipStream_t stream,
                        const f8_requant2 *q2 = nullptr, void *y2 = nullptr, const ConvTail *tail = nullptr);
+// The same from the weights and the bias, without start values or scratch, where the kernel that would take
+// the layer can form them itself: one launch, nothing kept.  Returns false, with nothing enqueued, where it
+// cannot (the caller then folds and calls enqueue_conv).
+bool enqueue_conv_folding(const void *x, const int8_t *w, const int32_t *bias, void *y, const void *res, const Geom &g,
+                          const f8_quant &q, hipStream_t stream, const f8_requant2 *q2, void *y2, f8_status *st);
 // Whether enqueue_conv can take a tail of Cout2 channels behind this layer at this batch (operands
 // assumed 16-byte aligned, one output format, 8-bit residual if any).
 bool conv_tail_ok(const Geom &g, const f8_quant &q, int Cout2);

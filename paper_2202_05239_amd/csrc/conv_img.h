@@ -26,7 +26,7 @@ bool conv_img_applicable(int Cin, int Cout, int R, int S, int sh, int sw, int ph
                          const void *x, const void *y);
 // Work units of a launch (images, or bands of 28 rows): the kernel pays once they fill the CUs.
 int conv_img_units(int C, int B, int H);
-// [C][3][3][C] weights into the order the kernel streams them in.  A hipError_t as int.
+// [C][3][3][C] weights (C a multiple of 32) into the order the kernels stream them in.  A hipError_t as int.
 int launch_conv_img_weights(const int8_t *w, int8_t *wf, int C, hipStream_t stream);
 // A hipError_t as int.
 int launch_conv_img(const ConvImgParams &p, hipStream_t stream);

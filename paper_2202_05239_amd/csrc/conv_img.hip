@@ -370,7 +370,7 @@ bool conv_img_applicable(int Cin, int Cout, int R, int S, int sh, int sw, int ph
 int conv_img_units(int C, int B, int H) { return C == IMG_C ? B : B * ((H + BandShape<128>::BR - 1) / BandShape<128>::BR); }
 
 int launch_conv_img_weights(const int8_t *w, int8_t *wf, int C, hipStream_t stream) {
-  if (!w || !wf || (C != IMG_C && C != 128) || ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(wf)) & 15))
+  if (!w || !wf || C < 32 || (C & 31) || ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(wf)) & 15))
     return (int)hipErrorInvalidValue;
   const int pieces = C * 9 * C / 16;
   hipLaunchKernelGGL(conv_img_weights_kernel, dim3((pieces + 255) / 256), dim3(256), 0, stream, w, wf, C);

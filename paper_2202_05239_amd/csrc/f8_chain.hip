@@ -35,6 +35,7 @@
 #include "block_fused.h"
 #include "stem_pool.h"
 #include "conv_img.h"
+#include "conv_imgk.h"
 #include "f8_host.h"
 
 using namespace f8;
@@ -94,9 +95,43 @@ struct f8_chain {
   std::vector<size_t> img_w_off;       // per layer
   bool conv_img = true;
   int conv_img_min = 96;
-  bool img_role(size_t i, int batch) const {
-    return conv_img && img_w_off[i] != 0 && !(use_fusion() && fused[i].role != 0) &&
-           conv_img_units(layers[i].Cin, batch, geom[i].H) >= conv_img_min;
+  int imgk = 1;
+  // 0: neither, 1: an image (or band) per workgroup, 1 + n: fewer channels per workgroup, n waves share K
+  int img_role(size_t i, int batch) const {
+    if (img_w_off[i] == 0 || (use_fusion() && fused[i].role != 0)) return 0;
+    const f8_layer_desc &L = layers[i];
+    const Geom &g = geom[i];
+    const int shift = L.q.fl_x + L.q.fl_w - L.q.fl_y;
+    const bool img_ok = conv_img && L.res < 0 &&
+                        conv_img_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, nullptr, nullptr) &&
+                        conv_img_units(L.Cin, batch, g.H) >= conv_img_min;
+    if (img_ok && conv_img_min != 96) return 1;      // tuning aid: a limit of the caller's
+    if (imgk != 0 && conv_imgk_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift,
+                                          nullptr, nullptr, nullptr)) {
+      const int wk = imgk_waves(L, g, batch);
+      if (wk != 0) return 1 + wk;
+    }
+    if (img_ok) return 1;
+    return 0;
+  }
+  // Waves that share K in the image-stationary kernel, or 0 where another kernel is faster.  The fewer channels a
+  // workgroup computes, the more often its pixels are loaded and the more sums meet in LDS, but the layer
+  // lasts as long as its last round of workgroups: as many channels as give three quarters of the CUs one.
+  // Measured (us; 1, 2, 4 waves / the best other kernel):
+  //   256 channels, 14 x 14: batch 24 13.5, 10.4, 8.4 / 12.8; 32 13.5, 10.6, 9.1 / 12.9; 64 14.4, 12.4, 16.7 / 16.2;
+  //     128 18.3, 23.7, 32.5 / 22.4; 192 27.2, -, - / 25.7 (conv_img); 16 13.5, 10.3, 8.1 / 7.3 (conv_wavek)
+  //   512 channels, 7 x 7: batch 24 15.2, 10.8, 8.1 / 9.6; 64 16.2, 12.3, 16.0 / 22.2; 128 19.7, 23.7, 31.0 / 27.9;
+  //     256 37.6, -, - / 38.5; 16 15.1, 10.6, 7.9 / 7.1 (conv_wavek)
+  //   128 channels, 28 x 28: batch 16 9.6, 8.4 / 8.8; 32 10.0, 8.9 / 10.7; 128 19.2, 31.7 / 23.9; 192 26.1, - / 28.1;
+  //     256 33.8, - / 33.2 (conv_img)
+  int imgk_waves(const f8_layer_desc &L, const Geom &g, int batch) const {
+    if (imgk >= 10) return imgk - 10;                // tuning aid: force it
+    const long long most = L.Cin == 256 ? 256 : L.Cin == 128 ? 768 : 0x7fffffffLL;
+    for (int wk = 1; wk <= (L.Cin == 128 ? 2 : 4); wk *= 2) {
+      const long long wgs = conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk);
+      if (wgs >= (L.Cin == 128 && wk == 2 ? 128 : 176)) return wgs <= most ? wk : 0;
+    }
+    return 0;
   }
   bool tail_in_fused_block(size_t i) const {
     const size_t a = tail[i] == 1 ? i : (size_t)tail_peer[i], b = tail[i] == 1 ? (size_t)tail_peer[i] : i;
@@ -317,15 +352,32 @@ struct f8_chain {
     switch (L.op) {
       case F8_OP_CONV: {
         const int32_t *acc0 = reinterpret_cast<const int32_t *>(static_cast<uint8_t *>(workspace) + acc0_off[i]);
-        if (img_role(i, batch) && conv_img_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W,
-                                               L.q.fl_x + L.q.fl_w - L.q.fl_y, src, dst)) {
+        const int img = img_role(i, batch);
+        const int shift = L.q.fl_x + L.q.fl_w - L.q.fl_y;
+        const int8_t *wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + img_w_off[i]);
+        if (img > 1 && conv_imgk_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, src, dst, res)) {
+          ConvImgkParams ip;
+          ip.x = static_cast<const uint8_t *>(src);
+          ip.wf = wf;
+          ip.acc0 = acc0;
+          ip.y = static_cast<uint8_t *>(dst);
+          ip.res = static_cast<const uint8_t *>(res);
+          ip.B = batch; ip.H = g.H; ip.W = g.W; ip.C = L.Cin;
+          ip.shift = shift; ip.lo = L.q.clip_lo; ip.hi = L.q.clip_hi;
+          ip.x_xor = L.q.x_type == F8_U8 ? 0x80808080u : 0u;
+          ip.res_signed = L.q.res_type == F8_S8;
+          ip.res_d = res ? L.q.fl_x + L.q.fl_w - L.q.fl_res : 0;
+          ip.wk = img - 1;
+          return launch_conv_imgk(ip, s) == 0 ? F8_OK : F8_ERR_DEVICE;
+        }
+        if (img == 1 && conv_img_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, src, dst)) {
           ConvImgParams ip;
           ip.x = static_cast<const uint8_t *>(src);
-          ip.wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + img_w_off[i]);
+          ip.wf = wf;
           ip.acc0 = acc0;
           ip.y = static_cast<uint8_t *>(dst);
           ip.B = batch; ip.H = g.H; ip.W = g.W; ip.C = L.Cin;
-          ip.shift = L.q.fl_x + L.q.fl_w - L.q.fl_y; ip.lo = L.q.clip_lo; ip.hi = L.q.clip_hi;
+          ip.shift = shift; ip.lo = L.q.clip_lo; ip.hi = L.q.clip_hi;
           ip.x_xor = L.q.x_type == F8_U8 ? 0x80808080u : 0u;
           return launch_conv_img(ip, s) == 0 ? F8_OK : F8_ERR_DEVICE;
         }
@@ -476,12 +528,15 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
       }
     }
     size_t img_off = 0;
-    if (L.op == F8_OP_CONV && !sm.on && L.res < 0 && L.dst2 <= 0 && L.q.y_type != F8_S32 &&
-        (reinterpret_cast<uintptr_t>(L.w) & 15) == 0 &&
-        conv_img_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W,
-                            L.q.fl_x + L.q.fl_w - L.q.fl_y, nullptr, nullptr)) {
-      img_off = c->const_bytes;
-      c->const_bytes += round256(conv_img_weight_bytes(L.Cin));
+    if (L.op == F8_OP_CONV && !sm.on && L.dst2 <= 0 && L.q.y_type != F8_S32 && !(L.res >= 0 && L.q.res_type == F8_S32) &&
+        (reinterpret_cast<uintptr_t>(L.w) & 15) == 0) {
+      const int shift = L.q.fl_x + L.q.fl_w - L.q.fl_y;
+      if (conv_imgk_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, nullptr, nullptr, nullptr) ||
+          (L.res < 0 &&
+           conv_img_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, nullptr, nullptr))) {
+        img_off = c->const_bytes;
+        c->const_bytes += round256(conv_img_weight_bytes(L.Cin));
+      }
     }
     c->img_w_off.push_back(img_off);
     c->stem.push_back(sm);
@@ -495,6 +550,7 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
   c->stem_pool = tuning().stem_pool.load() != 0;
   c->conv_img = tuning().conv_img.load() != 0;
   c->conv_img_min = tuning().conv_img_min.load();
+  c->imgk = tuning().imgk.load();
   // a stem whose only reader is a 3x3 stride-2 pad-1 max pool: both in one kernel
   for (size_t i = 0; i + 1 < c->layers.size(); ++i) {
     const f8_layer_desc &L = c->layers[i], &M = c->layers[i + 1];
@@ -832,9 +888,10 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       Geom gk = c->narrow_rows((size_t)layer, batch) ? g : c->conv_geom(layer, batch);
       gk.B = batch;
       gk.P = g.P; gk.Q = g.Q;
-      name = c->img_role((size_t)layer, batch)
-                 ? (L.Cin == 256 ? "conv3x3_img<256x256>" : "conv3x3_img<128x128>")
-                 : conv_kernel_name(gk, L.q, L.res >= 0);
+      const int img = c->img_role((size_t)layer, batch);
+      if (img > 1) name = L.Cin == 128 ? "conv3x3_wavek<128>" : L.Cin == 256 ? "conv3x3_wavek<256>" : "conv3x3_wavek<512>";
+      else if (img == 1) name = L.Cin == 256 ? "conv3x3_img<256x256>" : "conv3x3_img<128x128>";
+      else name = conv_kernel_name(gk, L.q, L.res >= 0);
       ops = 2.0 * M * g.R * g.S * g.Cin * g.Cout;
       bytes += (double)g.R * g.S * g.Cin * g.Cout + 4.0 * g.Cout;
       if (with_tail) {

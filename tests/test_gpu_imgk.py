@@ -1,0 +1,67 @@
+"""The image-stationary 3x3 kernel whose waves share K (csrc/conv_imgk.hip), forced with 1, 2 and 4 waves sharing K
+on whole images, several images per workgroup (the last one partly empty), bands of rows and the smallest and
+widest images, with and without residual, against the oracle.  Integer work: the bar is equality."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2202_05239_amd import binding as f8
+from paper_2202_05239_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# C, B, H, W, x type, first y type, second y type, residual scale relative to the accumulator (None: no residual)
+CASES = [
+    (128, 2, 28, 28, "u8", "u8", "u8", 2), (128, 3, 5, 30, "s8", "u8", "s8", None), (128, 2, 23, 17, "u8", "s8", "u8", -1),
+    (128, 5, 3, 2, "u8", "u8", "u8", 0), (128, 1, 1, 1, "s8", "s8", "u8", 3),
+    (256, 2, 14, 14, "u8", "u8", "u8", 1), (256, 6, 7, 7, "u8", "s8", "u8", -2), (256, 1, 21, 14, "s8", "u8", "s8", None),
+    (256, 3, 2, 9, "u8", "u8", "s8", 2),
+    (512, 3, 7, 7, "u8", "u8", "u8", 2), (512, 2, 8, 8, "s8", "s8", "s8", None), (512, 1, 19, 6, "u8", "u8", "u8", -1),
+    (512, 4, 1, 3, "u8", "u8", "s8", 0),
+]
+
+
+@pytest.mark.parametrize("wk", [1, 2, 4])
+def test_image_stationary_3x3_with_shared_k(oracle, wk):
+    for k, (C, B, H, W, xt, yt, yt2, rd) in enumerate(CASES):
+        if C == 128 and wk == 4:
+            continue
+        rng = np.random.default_rng(9000 + k)
+        x, L1, _ = wl.random_conv_case(rng, B, H, W, C, C, 3, 3, 1, 1, xt, yt, None, shift=8)
+        _, L2, _ = wl.random_conv_case(rng, 1, H, W, C, C, 3, 3, 1, 1, yt, yt2, None, shift=9)
+        # the second layer reads the first one's output and, as residual, the network's input
+        L1.src, L1.dst, L1.res = 0, 1, -1
+        L2.src, L2.dst, L2.res = 1, 2, -1
+        L2.fl_x = L1.fl_y
+        L2.fl_y = L2.fl_x + L2.fl_w - 9
+        if rd is not None:
+            L2.res, L2.res_type = 0, xt
+            L2.fl_w = L1.fl_x + rd - L2.fl_x          # residual scale: fl_x + fl_w - fl_res = rd
+            L2.fl_res = L1.fl_x
+            L2.fl_y = L2.fl_x + L2.fl_w - 9
+        net = wl.Net("imgk", (H, W), C, xt, L1.fl_x, [L1, L2])
+        want = oracle.run_network(net, x, keep_all=True)
+        f8.f8_tuning_set("imgk", 10 + wk)
+        try:
+            chain = f8.Chain(net, keep_all=True).prepare(B)
+            assert [chain.layer_info(i, B)[0] for i in range(2)] == ["conv3x3_wavek<%d>" % C] * 2
+            out = chain.run(torch.from_numpy(x).cuda())
+            torch.cuda.synchronize()
+        finally:
+            f8.f8_tuning_set("imgk", 1)
+        for got, w, what in ((chain.tensor(1), want[1], "first"), (out, want[2], "second")):
+            got = got.cpu().numpy()
+            assert got.dtype == w.dtype and np.array_equal(got, w), "case %d, %d waves, %s layer: %d of %d differ" % (
+                k, wk, what, int((got != w).sum()), w.size)
+        assert len(np.unique(want[2])) > 4 or want[2].size < 200, "degenerate draw"
+
+
+def test_waves_sharing_k_follow_the_batch():
+    """ResNet-18's 3x3 layers: which batch takes the kernel, and with how many images the others do."""
+    _, net = wl.config3(batch=1)
+    chain = f8.Chain(net)
+
+    def count(batch):
+        return sum(chain.layer_info(i, batch)[0].startswith("conv3x3_wavek<") for i in range(len(net.layers)))
+
+    assert count(1) == 0 and count(64) == 9 and count(128) == 9

@@ -12,16 +12,22 @@
 // computes only a part of the output channels, which makes workgroups out of few images: wave wn has 32
 // channels of its own, and where that still leaves CUs idle, WK waves share K instead (wave kg takes the input
 // channels kg * C / WK onwards of every tap) and their sums meet in LDS at the end.
+//   C = 64: a band of up to 224 pixels, two waves of 32 channels, every weight of a wave in its registers;
 //   C = 256: a whole image of up to 224 pixels (7 blocks of 32); C = 512: two 7 x 7 images (4 blocks);
 //   C = 128: a band of up to 224 pixels.
-// Now 12.2 us for 256 channels on 64 images and 12.2 us for 512 (two waves share K), 17.7 / 19.2 us on 128 images
-// (22.4 / 28.6 before); 9.5 k cycles of a workgroup's 19.5 k are the loop (8.1 k of matrix instructions),
-// 5.3 k the patch (82 - 92 KiB at the 60 bytes per clock a CU gets from L2, then memory latency), 4 k the sums in
+// Now 12.1 us for 256 channels on 64 images and 12.0 us for 512 (two waves share K), 16.4 / 18.5 us on 128 images
+// (22.4 / 28.0 before); 9.3 k cycles of a workgroup's 19.7 k are the loop (8.1 k of matrix instructions),
+// 6 k the patch (82 - 92 KiB at the 60 bytes per clock a CU gets from L2, then memory latency), 4 k the sums in
 // LDS and the stores.  With 64 channels per wave and four waves sharing K the loop reads half as much from LDS
-// but the sums take twice as long: 12.8 us.
+// but the sums take twice as long: 12.8 us.  64 channels on 64 images of 56 x 56 with a residual: 13.5 us (18.9 in
+// conv_fast).
+// NAT (64 channels, single-layer calls): the weights are read as they are, 32 bytes of 32 rows per instruction, and
+// summed for the start values on the way, so that the call is one launch: 10.5 us a call on 32 images of
+// 56 x 56 against 11.9 us for fold and conv_ws.
 #include "conv_imgk.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace f8 {
 namespace {
@@ -30,14 +36,14 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) const v4i lds_v4i;
 typedef __attribute__((address_space(3))) const uint8_t lds_u8;
 
-constexpr int NT = 256;
 constexpr int PART_PITCH = 32 * 4 + 16;              // a pixel's 32 partial sums
 
-// MB: 32-pixel blocks of a workgroup; a wave's part of the patch is RPW rows of up to NI KiB.
+// NW waves, MB 32-pixel blocks; a wave's part of the patch is RPW rows of up to NI KiB.
 template <int C> struct Shape;
-template <> struct Shape<128> { static constexpr int MB = 7, RPW = 3, NI = 4; };
-template <> struct Shape<256> { static constexpr int MB = 7, RPW = 5, NI = 4; };
-template <> struct Shape<512> { static constexpr int MB = 4, RPW = 5, NI = 5; };
+template <> struct Shape<64> { static constexpr int NW = 2, MB = 7, RPW = 5, NI = 4; };
+template <> struct Shape<128> { static constexpr int NW = 4, MB = 7, RPW = 3, NI = 4; };
+template <> struct Shape<256> { static constexpr int NW = 4, MB = 7, RPW = 5, NI = 4; };
+template <> struct Shape<512> { static constexpr int NW = 4, MB = 4, RPW = 5, NI = 5; };
 
 // How the batch is cut into units of one workgroup: whole images, or bands of rows of one image.
 struct Units {
@@ -53,7 +59,7 @@ struct Units {
 
 template <int C> Units cut(int B, int H, int W, int WK) {
   using S = Shape<C>;
-  constexpr int cap = S::MB * 32, max_rows = 4 * S::RPW;
+  constexpr int cap = S::MB * 32, max_rows = S::NW * S::RPW;
   const int gpitch = C / WK + 16;
   Units u{};
   if (H < 1 || W < 1 || W > cap || (W + 2) * C > S::NI * 1024) return u;
@@ -79,21 +85,23 @@ template <int C> Units cut(int B, int H, int W, int WK) {
   return u;
 }
 
-// Channel fed as row r of a 32-channel block: see conv_img.hip (the fragment order has it built in).
+// Channel fed as row r of a 32-channel block (the fragment order of launch_conv_img_weights has it built in).
+__device__ __forceinline__ int frag_channel(int r) { return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3); }
 
-template <int C, int WK>
-__global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const ConvImgkParams p, const Units u, const FastDiv fd_w, const FastDiv fd_px,
+template <int C, int WK, bool NAT>
+__global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_kernel(const ConvImgkParams p, const Units u, const FastDiv fd_w, const FastDiv fd_px,
                                                           const FastDiv fd_prows, const FastDiv fd_units) {
   using S = Shape<C>;
-  constexpr int MB = S::MB, WN = 4 / WK;
+  constexpr int NT = 64 * S::NW, MB = S::MB, WN = S::NW / WK;
   constexpr int KPT = C / 32;                        // K slices per tap
   constexpr int KSW = KPT / WK;                      // of which a wave takes this many
   constexpr int KS = 9 * KPT;
   constexpr int CG = C / WK, GP = CG + 16;           // bytes of a patch pixel in one K group
   constexpr int PIECES = C / 16;                     // 16-byte pieces per pixel
   constexpr int ROW_SLICES = 3 * KSW;                // K slices per window row
-  constexpr int RING = MB == 7 ? (ROW_SLICES % 8 == 0 ? 8 : 6) : 12;
-  static_assert(ROW_SLICES % RING == 0 && ROW_SLICES % 2 == 0, "slots and fragment sets repeat from row to row");
+  constexpr int RING = C == 64 ? KS : MB == 7 ? (ROW_SLICES % 8 == 0 ? 8 : 6) : 12;      // slices of weights in flight
+  constexpr bool ALL = RING == KS;                   // every slice is requested before the loop
+  static_assert((ALL || ROW_SLICES % RING == 0) && ROW_SLICES % 2 == 0, "slots and fragment sets repeat from row to row");
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -119,12 +127,23 @@ __global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const Co
   // ---- this wave's weights: channel block n0 / 32 + wn, K slices kg * KSW .. + KSW of every tap.  Slice sc of window
   // row r is requested RING slices ahead.
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<int8_t *>(p.wf) + (size_t)(n0 / 32 + wn) * (KS * 1024), 0, KS * 1024, 0x00027000);
+      const_cast<int8_t *>(p.w) + (size_t)(n0 / 32 + wn) * (KS * 1024), 0, NAT ? 0 : KS * 1024, 0x00027000);
   const int lane16 = lane * 16, wbase = kg * (KSW * 1024);
   auto slice_at = [](int sc) { return ((sc / KSW) * KPT + sc % KSW) * 1024; };
-  v4i bq[RING];
+  // start values of this lane's 16 channels (registers 0..15 of a block): the wave that takes the first share of K
+  // starts its accumulators there
+  v4i a0[4];
 #pragma unroll
-  for (int sc = 0; sc < RING; ++sc) bq[sc] = __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, wbase + slice_at(sc), 0);
+  for (int g = 0; g < 4; ++g) {
+    const int n = n0 + 32 * wn + 16 * half + 4 * g;
+    if (!NAT) a0[g] = kg == 0 ? *reinterpret_cast<const v4i *>(p.acc0 + n) : v4i{0, 0, 0, 0};
+    else a0[g] = p.acc0 ? v4i{p.acc0[n], p.acc0[n + 1], p.acc0[n + 2], p.acc0[n + 3]} : v4i{0, 0, 0, 0};
+  }
+  v4i bq[RING];
+  const int8_t *w_row = p.w + (size_t)(n0 + 32 * wn + frag_channel(l32)) * (9 * C) + 16 * half;
+#pragma unroll
+  for (int sc = 0; sc < RING; ++sc)
+    bq[sc] = NAT ? *reinterpret_cast<const v4i *>(w_row + 32 * sc) : __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, wbase + slice_at(sc), 0);      // (ALL: slices of all rows; KSW == KPT then)
 
   // ---- the input pixels and a border of zeros into LDS, xor 0x80 when unsigned.  A wave takes the patch rows
   // wave, wave + 4, ...; a row's pixels are consecutive in memory, so a lane's 16-byte pieces of a row lie at
@@ -141,13 +160,32 @@ __global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const Co
   }
 #pragma unroll
   for (int k = 0; k < S::RPW; ++k) {
-    const int row = wave + 4 * k;                    // uniform
+    const int row = wave + S::NW * k;                    // uniform
     const int img = (int)fd_prows.div((uint32_t)row), y = y0 + row - img * u.prows - 1;
     const bool in = img < nimg && (unsigned)y < (unsigned)p.H;
+    if (row >= u.all_rows) continue;
     const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(xbase, 0, in ? nimg * (int)image_bytes : 0, 0x00027000);
     const int at = in ? (img * p.H + y) * p.W * C : 0;
 #pragma unroll
     for (int i = 0; i < S::NI; ++i) px[k][i] = __builtin_amdgcn_raw_buffer_load_b128(xres, x_at[i], at, 0);
+  }
+  // the residual pieces this thread will need at the end: WK == 1: its lane's 16 channels of every block; otherwise
+  // piece tid % (2 WN) of the pixels tid / (2 WN) + k * IPP
+  constexpr int IPP = NT / (2 * WN), ITEMS = WK == 1 ? MB : (MB * 32 + IPP - 1) / IPP;
+  const int piece = tid % (2 * WN), pixel0 = WK == 1 ? l32 : tid / (2 * WN);
+  const int n_out = WK == 1 ? n0 + 32 * wn + 16 * half : n0 + piece * 16;
+  constexpr int ITEM_STEP = WK == 1 ? 32 : IPP;
+  // (pixels past the unit: an offset the descriptors reject: loads return zeros, stores are dropped)
+  const int out_bytes = npx * C;
+  v4i rv[ITEMS];
+  uint32_t out_at[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k)
+    out_at[k] = pixel0 + k * ITEM_STEP < npx ? (uint32_t)((pixel0 + k * ITEM_STEP) * C + n_out) : 0x80000000u;
+  if (p.res) {
+    const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.res) + px0 * C, 0, out_bytes, 0x00027000);
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) rv[k] = __builtin_amdgcn_raw_buffer_load_b128(rres, out_at[k], 0, 0);
   }
   __builtin_amdgcn_sched_barrier(0);
 
@@ -166,11 +204,6 @@ __global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const Co
     }
     ar[j] = (lds_u8 *)lds + kg * u.group + at * GP + 16 * half;
   }
-  v16i acc[MB];
-#pragma unroll
-  for (int j = 0; j < MB; ++j)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[j][i] = 0;
   int to[S::NI];
 #pragma unroll
   for (int i = 0; i < S::NI; ++i) {
@@ -178,12 +211,27 @@ __global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const Co
     // (pieces past the last column are fetched as zeros and not kept)
     to[i] = col < u.pcols ? (piece / (CG / 16)) * u.group + col * GP + (piece % (CG / 16)) * 16 : -1;
   }
+  if (NAT) {
+    int wsum = 0;
+    // the sum of this lane's weights: with the other half's, 128 times it belongs in the start value
+#pragma unroll
+    for (int sc = 0; sc < RING; ++sc)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) wsum = __builtin_amdgcn_sdot4(bq[sc][d], 0x01010101, wsum, false);
+    wsum += __shfl_xor(wsum, 32, 64);
+    // lane r holds the sum of channel frag_channel(r): channels 16 half + 4 g .. + 3 are rows 8 g + 4 half ..
+    const int rnd = p.shift > 0 ? 1 << (p.shift - 1) : 0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a0[g][i] += rnd + (p.x_xor ? 128 * __shfl(wsum, 8 * g + 4 * half + i, 64) : 0);
+  }
   static_assert(64 % PIECES == 0, "a lane keeps its piece of a pixel");
   __builtin_amdgcn_sched_barrier(0);
   const int zx = (int)p.x_xor;
 #pragma unroll
   for (int k = 0; k < S::RPW; ++k) {
-    const int row = wave + 4 * k;
+    const int row = wave + S::NW * k;
     if (row < u.all_rows) {
 #pragma unroll
       for (int i = 0; i < S::NI; ++i)
@@ -195,11 +243,16 @@ __global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const Co
 
   // ---- K loop: a pass is a row of the window, 3 taps x KSW slices; activation fragments one slice ahead,
   // one request at a time behind the matrix instructions
+  v16i acc[MB];
+#pragma unroll
+  for (int j = 0; j < MB; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[j][i] = a0[i >> 2][i & 3];
   v4i xf[2][MB];
 #pragma unroll
   for (int j = 0; j < MB; ++j) xf[0][j] = *(lds_v4i *)(ar[j]);
   const int row_step = u.pcols * GP;
-#pragma unroll 1
+#pragma unroll ALL ? 3 : 1
   for (int r = 0; r < 3; ++r) {
     const int wrow = wbase + r * (3 * KPT * 1024);
 #pragma unroll
@@ -213,12 +266,13 @@ __global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const Co
       }
 #pragma unroll
       for (int j = 0; j < MB; ++j) {
-        acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bq[sc % RING], xf[cur][j], acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bq[ALL ? r * ROW_SLICES + sc : sc % RING], xf[cur][j], acc[j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         xf[nxt][j] = *(lds_v4i *)(ar[j] + off);
         __builtin_amdgcn_sched_barrier(0);
       }
       const int ahead = sc + RING;
+      if (ALL) continue;
       if (ahead < ROW_SLICES)
         bq[sc % RING] = __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, wrow + slice_at(ahead), 0);
       else if (r < 2)
@@ -228,49 +282,56 @@ __global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const Co
   }
 
   const ScaledClip c1 = scaled_clip(p.lo, p.hi, p.shift);
-  const int sh = p.shift;
-  auto finish = [&](int (&v)[16], const v4i &rv) {
-    if (p.res) {
+  const int sh = p.shift, d = p.res_d;
+  const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(p.y + px0 * C, 0, out_bytes, 0x00027000);
+  // One instance for each residual kind (RK: 0 none, 1 unsigned, 2 signed) and direction (RLEFT: shifted left, else
+  // rounded right); the choice is uniform.
+  auto finish = [&](auto rk_tag, auto rleft_tag) {
+    constexpr int RK = decltype(rk_tag)::value;
+    constexpr bool RLEFT = decltype(rleft_tag)::value;
+    const int rhalf = RLEFT ? 0 : 1 << (-d - 1);
+    auto store = [&](int (&v)[16], int k) {
+      if (RK != 0) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] += align_res(byte_of((uint32_t)rv[i >> 2], i & 3, p.res_signed != 0), p.res_d);
+        for (int i = 0; i < 16; ++i) {
+          const int b = RK == 2 ? (int)__builtin_amdgcn_sbfe(rv[k][i >> 2], 8 * (i & 3), 8)
+                                : (int)__builtin_amdgcn_ubfe((uint32_t)rv[k][i >> 2], 8 * (i & 3), 8);
+          v[i] += RLEFT ? (b << d) : ((b + rhalf) >> (-d));
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = clamp_med3(v[i], c1.lo, c1.hi);
+      __builtin_amdgcn_raw_buffer_store_b128(shift_pack16(v, sh), yres, out_at[k], 0, 0);
+    };
+    if constexpr (WK == 1) {
+      // every wave has its sums complete: a lane's 16 channels of a pixel are a 16-byte piece of an output row
+#pragma unroll
+      for (int j = 0; j < MB; ++j) {
+        settle_matrix_result(acc[j]);
+        int v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = acc[j][i];
+        store(v, j);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < ITEMS; ++k) {
+        const int m = pixel0 + k * IPP;              // (past the last block: reads sums of other pixels, drops the store)
+        const uint8_t *from = lds + (piece >> 1) * (WK * MB * 32 * PART_PITCH) + (m < MB * 32 ? m : 0) * PART_PITCH + (piece & 1) * 64;
+        int v[16];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          v4i a = *reinterpret_cast<const v4i *>(from + g * 16);
+#pragma unroll
+          for (int w = 1; w < WK; ++w) a += *reinterpret_cast<const v4i *>(from + w * (MB * 32 * PART_PITCH) + g * 16);
+          v[4 * g] = a.x; v[4 * g + 1] = a.y; v[4 * g + 2] = a.z; v[4 * g + 3] = a.w;
+        }
+        store(v, k);
+      }
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = clamp_med3(v[i], c1.lo, c1.hi);
-    return shift_pack16(v, sh);
   };
-  if constexpr (WK == 1) {
-    // every wave has its sums complete: a lane's 16 channels of a pixel are a 16-byte piece of an output row
-    const int n = n0 + 32 * wn + 16 * half;
-    v4i a0[4], rv[MB];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) a0[g] = *reinterpret_cast<const v4i *>(p.acc0 + n + 4 * g);
-#pragma unroll
-    for (int j = 0; j < MB; ++j) {
-      rv[j] = v4i{0, 0, 0, 0};
-      if (p.res && 32 * j + l32 < npx) rv[j] = *reinterpret_cast<const v4i *>(p.res + (px0 + 32 * j + l32) * C + n);
-    }
-#pragma unroll
-    for (int j = 0; j < MB; ++j) {
-      settle_matrix_result(acc[j]);
-      int v[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = acc[j][i] + a0[i >> 2][i & 3];
-      const v4i out = finish(v, rv[j]);
-      if (32 * j + l32 < npx) *reinterpret_cast<v4i *>(p.y + (px0 + 32 * j + l32) * C + n) = out;
-    }
-  } else {
-    // the waves' sums meet; thread -> piece of 16 channels of the pixels tid / (2 WN) + k * IPP
-    constexpr int IPP = NT / (2 * WN), ITEMS = (MB * 32 + IPP - 1) / IPP;
-    const int piece = tid % (2 * WN), pixel0 = tid / (2 * WN);
-    const int n = n0 + piece * 16;
-    v4i rv[ITEMS], a0[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) a0[g] = *reinterpret_cast<const v4i *>(p.acc0 + n + 4 * g);
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-      rv[k] = v4i{0, 0, 0, 0};
-      if (p.res && pixel0 + k * IPP < npx) rv[k] = *reinterpret_cast<const v4i *>(p.res + (px0 + pixel0 + k * IPP) * C + n);
-    }
+  if constexpr (WK > 1) {
+    // the waves' sums meet
     __syncthreads();                                 // the patch is no longer read
     uint8_t *part = lds + wave * (MB * 32 * PART_PITCH) + l32 * PART_PITCH + half * 64;
 #pragma unroll
@@ -280,33 +341,23 @@ __global__ __launch_bounds__(NT, WK == 1 ? 2 : 1) void conv_imgk_kernel(const Co
         *reinterpret_cast<v4i *>(part + j * (32 * PART_PITCH) + g * 16) =
             v4i{acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]};
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-      const int m = pixel0 + k * IPP;
-      if (m >= npx) continue;
-      const uint8_t *from = lds + (piece >> 1) * (WK * MB * 32 * PART_PITCH) + m * PART_PITCH + (piece & 1) * 64;
-      int v[16];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        v4i a = a0[g];
-#pragma unroll
-        for (int w = 0; w < WK; ++w) a += *reinterpret_cast<const v4i *>(from + w * (MB * 32 * PART_PITCH) + g * 16);
-        v[4 * g] = a.x; v[4 * g + 1] = a.y; v[4 * g + 2] = a.z; v[4 * g + 3] = a.w;
-      }
-      *reinterpret_cast<v4i *>(p.y + (px0 + m) * C + n) = finish(v, rv[k]);
-    }
   }
+  using std::integral_constant;
+  if (!p.res) finish(integral_constant<int, 0>{}, std::true_type{});
+  else if (p.res_signed) { if (d >= 0) finish(integral_constant<int, 2>{}, std::true_type{}); else finish(integral_constant<int, 2>{}, std::false_type{}); }
+  else { if (d >= 0) finish(integral_constant<int, 1>{}, std::true_type{}); else finish(integral_constant<int, 1>{}, std::false_type{}); }
 }
 
-template <int C, int WK> int launch_c(const ConvImgkParams &p, hipStream_t stream) {
+template <int C, int WK, bool NAT> int launch_c(const ConvImgkParams &p, hipStream_t stream) {
+  using S = Shape<C>;
   const Units u = cut<C>(p.B, p.H, p.W, WK);
   if (u.images < 1) return (int)hipErrorInvalidValue;
-  const long long grid = u.units * (C / (32 * (4 / WK)));
+  const long long grid = u.units * (C / (32 * (S::NW / WK)));
   if (grid > 0x7fffffffLL) return (int)hipErrorInvalidValue;
   // up to one workgroup per CU: ask for more than half of the LDS, or two of them may share a CU while
   // another stays idle (256 workgroups for 128 channels on 64 images: 13.3 us, with this 10.6 us)
   const int lds = grid <= 256 && u.lds < 84 * 1024 ? 84 * 1024 : u.lds;
-  const void *fn = reinterpret_cast<const void *>(conv_imgk_kernel<C, WK>);
+  const void *fn = reinterpret_cast<const void *>(conv_imgk_kernel<C, WK, NAT>);
   static std::atomic<unsigned long long> done_mask{0};         // devices whose LDS limit has been raised
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return (int)hipErrorInvalidDevice;
@@ -315,40 +366,53 @@ template <int C, int WK> int launch_c(const ConvImgkParams &p, hipStream_t strea
     if (e != hipSuccess) return (int)e;
     if (dev >= 0 && dev <= 63) done_mask.fetch_or(1ull << dev, std::memory_order_relaxed);
   }
-  hipLaunchKernelGGL((conv_imgk_kernel<C, WK>), dim3((unsigned)grid), dim3(NT), lds, stream, p, u, FastDiv((uint32_t)p.W),
+  hipLaunchKernelGGL((conv_imgk_kernel<C, WK, NAT>), dim3((unsigned)grid), dim3(64 * S::NW), lds, stream, p, u, FastDiv((uint32_t)p.W),
                      FastDiv((uint32_t)(u.rows * p.W)), FastDiv((uint32_t)u.prows), FastDiv((uint32_t)u.units));
   return (int)hipGetLastError();
 }
 
-Units cut_any(int C, int B, int H, int W, int WK) { return C == 128 ? cut<128>(B, H, W, WK) : C == 256 ? cut<256>(B, H, W, WK) : cut<512>(B, H, W, WK); }
+Units cut_any(int C, int B, int H, int W, int WK) {
+  return C == 64 ? cut<64>(B, H, W, WK) : C == 128 ? cut<128>(B, H, W, WK) : C == 256 ? cut<256>(B, H, W, WK) : cut<512>(B, H, W, WK);
+}
 
 }  // namespace
 
+bool conv_imgk_fills(int C, int H, int W) {
+  const Units u = cut_any(C, 1, H, W, 1);
+  return u.images * u.rows * W * 3 >= (C == 512 ? 4 : 7) * 32 * 2;
+}
+
+int conv_imgk_most_waves(int C) { return C == 64 ? 1 : C == 128 ? 2 : 4; }
+
 bool conv_imgk_applicable(int Cin, int Cout, int R, int S, int sh, int sw, int ph, int pw, int H, int W, int shift,
                           const void *x, const void *y, const void *res) {
-  if (Cin != Cout || (Cin != 128 && Cin != 256 && Cin != 512) || R != 3 || S != 3 || sh != 1 || sw != 1 || ph != 1 || pw != 1) return false;
+  if (Cin != Cout || (Cin != 64 && Cin != 128 && Cin != 256 && Cin != 512) || R != 3 || S != 3 || sh != 1 || sw != 1 || ph != 1 || pw != 1) return false;
   if (shift < 0 || H < 1 || W < 1 || (long long)H * W * Cin * 8 > 0x7fffffffLL) return false;
-  for (int wk = 1; wk <= 4; wk *= 2)
+  for (int wk = 1; wk <= conv_imgk_most_waves(Cin); wk *= 2)
     if (cut_any(Cin, 1, H, W, wk).images < 1) return false;
   return ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(res)) & 15) == 0;
 }
 
-long long conv_imgk_workgroups(int C, int B, int H, int W, int wk) { return cut_any(C, B, H, W, wk).units * (C / (32 * (4 / wk))); }
+long long conv_imgk_workgroups(int C, int B, int H, int W, int wk) {
+  return cut_any(C, B, H, W, wk).units * (C / (32 * ((C == 64 ? 2 : 4) / wk)));
+}
 
 int launch_conv_imgk(const ConvImgkParams &p, hipStream_t stream) {
   if (p.B <= 0) return 0;
   if (!conv_imgk_applicable(p.C, p.C, 3, 3, 1, 1, 1, 1, p.H, p.W, p.shift, p.x, p.y, p.res) || p.lo > p.hi ||
-      ((reinterpret_cast<uintptr_t>(p.wf) | reinterpret_cast<uintptr_t>(p.acc0)) & 15))
+      (reinterpret_cast<uintptr_t>(p.w) & 15) || (reinterpret_cast<uintptr_t>(p.acc0) & (p.fold ? 3 : 15)))
     return (int)hipErrorInvalidValue;
+  if (p.fold) return p.C == 64 && p.wk == 1 ? launch_c<64, 1, true>(p, stream) : (int)hipErrorInvalidValue;
   switch (p.C * 8 + p.wk) {
-    case 128 * 8 + 1: return launch_c<128, 1>(p, stream);
-    case 128 * 8 + 2: return launch_c<128, 2>(p, stream);
-    case 256 * 8 + 1: return launch_c<256, 1>(p, stream);
-    case 256 * 8 + 2: return launch_c<256, 2>(p, stream);
-    case 256 * 8 + 4: return launch_c<256, 4>(p, stream);
-    case 512 * 8 + 1: return launch_c<512, 1>(p, stream);
-    case 512 * 8 + 2: return launch_c<512, 2>(p, stream);
-    case 512 * 8 + 4: return launch_c<512, 4>(p, stream);
+    case 64 * 8 + 1: return launch_c<64, 1, false>(p, stream);
+    case 128 * 8 + 1: return launch_c<128, 1, false>(p, stream);
+    case 128 * 8 + 2: return launch_c<128, 2, false>(p, stream);
+    case 256 * 8 + 1: return launch_c<256, 1, false>(p, stream);
+    case 256 * 8 + 2: return launch_c<256, 2, false>(p, stream);
+    case 256 * 8 + 4: return launch_c<256, 4, false>(p, stream);
+    case 512 * 8 + 1: return launch_c<512, 1, false>(p, stream);
+    case 512 * 8 + 2: return launch_c<512, 2, false>(p, stream);
+    case 512 * 8 + 4: return launch_c<512, 4, false>(p, stream);
     default: return (int)hipErrorInvalidValue;
   }
 }

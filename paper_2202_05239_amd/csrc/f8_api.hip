@@ -4,6 +4,7 @@
 #include <mutex>
 #include <unordered_map>
 
+#include "conv_imgk.h"
 #include "f8_host.h"
 
 namespace f8 {
@@ -292,8 +293,35 @@ static bool takes_own_kernel(const void *x, const int8_t *w, const void *y, cons
          use_pw_wide(x, w, y, res, g, q, y2) || use_conv_ws(x, w, y, res, g, q, y2);
 }
 
+// The 3x3 64 -> 64 layers: the image-stationary kernel reads the weights as they are.
+static bool use_imgk_folding(const void *x, const int8_t *w, const void *y, const void *res, const Geom &g, const f8_quant &q, const void *y2) {
+  if (tuning().imgk.load(std::memory_order_relaxed) == 0 || tuning().conv_variant.load(std::memory_order_relaxed) >= 0 || g.Cin != 64 ||
+      y2 || q.y_type == F8_S32 || (res && q.res_type == F8_S32) || (reinterpret_cast<uintptr_t>(w) & 15))
+    return false;
+  if (!conv_imgk_applicable(g.Cin, g.Cout, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.H, g.W, q.fl_x + q.fl_w - q.fl_y, x, y, res)) return false;
+  // (us a call, here / fold and the best other kernel: batch 16 9.1 / 11.4, 32 10.5 / 11.9, 64 14.1 / 17.3, 256 40.3 / 40.6;
+  // with a residual 32 11.1 / 14.1, 256 44 / 64)
+  return conv_imgk_fills(g.Cin, g.H, g.W) && conv_imgk_workgroups(g.Cin, g.B, g.H, g.W, 1) >= 176;
+}
+
 bool enqueue_conv_folding(const void *x, const int8_t *w, const int32_t *bias, void *y, const void *res, const Geom &g,
                           const f8_quant &q, hipStream_t stream, const f8_requant2 *q2, void *y2, f8_status *st) {
+  if (use_imgk_folding(x, w, y, res, g, q, (q2 && y2) ? y2 : nullptr)) {
+    ConvImgkParams ip;
+    ip.x = static_cast<const uint8_t *>(x);
+    ip.w = w;
+    ip.acc0 = bias;
+    ip.y = static_cast<uint8_t *>(y);
+    ip.res = static_cast<const uint8_t *>(res);
+    ip.B = g.B; ip.H = g.H; ip.W = g.W; ip.C = g.Cin;
+    ip.shift = q.fl_x + q.fl_w - q.fl_y; ip.lo = q.clip_lo; ip.hi = q.clip_hi;
+    ip.x_xor = q.x_type == F8_U8 ? 0x80808080u : 0u;
+    ip.res_signed = q.res_type == F8_S8;
+    ip.res_d = res ? q.fl_x + q.fl_w - q.fl_res : 0;
+    ip.wk = 1; ip.fold = 1;
+    *st = launch_conv_imgk(ip, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
+    return true;
+  }
   if (takes_own_kernel(x, w, y, res, g, q, (q2 && y2) ? y2 : nullptr)) return false;
   ConvParams p = conv_params(x, w, nullptr, nullptr, y, res, g, q, q2, y2);
   p.near = 1;                           // (only conv_fast reads the page of zeros)

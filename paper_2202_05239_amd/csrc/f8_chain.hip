@@ -118,16 +118,19 @@ struct f8_chain {
   // workgroup computes, the more often its pixels are loaded and the more sums meet in LDS, but the layer
   // lasts as long as its last round of workgroups: as many channels as give three quarters of the CUs one.
   // Measured (us; 1, 2, 4 waves / the best other kernel):
-  //   256 channels, 14 x 14: batch 24 13.5, 10.4, 8.4 / 12.8; 32 13.5, 10.6, 9.1 / 12.9; 64 14.4, 12.4, 16.7 / 16.2;
-  //     128 18.3, 23.7, 32.5 / 22.4; 192 27.2, -, - / 25.7 (conv_img); 16 13.5, 10.3, 8.1 / 7.3 (conv_wavek)
-  //   512 channels, 7 x 7: batch 24 15.2, 10.8, 8.1 / 9.6; 64 16.2, 12.3, 16.0 / 22.2; 128 19.7, 23.7, 31.0 / 27.9;
-  //     256 37.6, -, - / 38.5; 16 15.1, 10.6, 7.9 / 7.1 (conv_wavek)
-  //   128 channels, 28 x 28: batch 16 9.6, 8.4 / 8.8; 32 10.0, 8.9 / 10.7; 128 19.2, 31.7 / 23.9; 192 26.1, - / 28.1;
-  //     256 33.8, - / 33.2 (conv_img)
+  //   64 channels, 56 x 56: batch 16 6.9 / 7.8; 32 9.4 / 9.2; 64 12.5 / 14.5; 128 22.3 / 22.6 (conv_ws; with two halves of
+  //     128 side by side, as ResNet-50 runs at batch 256, conv_ws is ahead by 10 us a layer); with a residual: batch 32 9.9 / 12.2; 64 13.5 / 18.9; 256 41.5 / 65.0
+  //   128 channels, 28 x 28: batch 16 8.9, 8.2 / 8.7; 32 9.4, 8.7 / 10.7; 64 10.4, - / 16.7; 128 17.7, - / 23.0;
+  //     192 24.2, - / 28.5; 256 30.7, - / 32.4 (conv_img, held to by the tests)
+  //   256 channels, 14 x 14: batch 16 12.6, 10.3, 8.1 / 7.2 (conv_wavek); 24 12.9, 10.4, 8.4 / 12.7; 32 12.8, 10.6,
+  //     8.6 / 13.0; 64 13.7, 12.1, 16.7 / 16.6; 128 16.4, 23.7, - / 22.4; 192 25.3, -, - / 24.8 (conv_img)
+  //   512 channels, 7 x 7: batch 16 14.9, 10.6, 7.9 / 7.1 (conv_wavek); 24 15.3, 10.8, 8.2 / 9.7; 64 16.1, 12.0, 16.0 /
+  //     22.3; 128 18.5, 23.7, - / 28.0; 256 35.0, -, - / 38.0
   int imgk_waves(const f8_layer_desc &L, const Geom &g, int batch) const {
-    if (imgk >= 10) return imgk - 10;                // tuning aid: force it
-    const long long most = L.Cin == 256 ? 256 : L.Cin == 128 ? 768 : 0x7fffffffLL;
-    for (int wk = 1; wk <= (L.Cin == 128 ? 2 : 4); wk *= 2) {
+    if (imgk >= 10) return imgk - 10 <= conv_imgk_most_waves(L.Cin) ? imgk - 10 : 0;      // tuning aid: force it
+    const long long most = L.Cin == 256 ? 256 : L.Cin == 128 ? 768 : L.Cin == 64 && L.res < 0 ? 1024 : 0x7fffffffLL;
+    if (!conv_imgk_fills(L.Cin, g.H, g.W)) return 0;
+    for (int wk = 1; wk <= conv_imgk_most_waves(L.Cin); wk *= 2) {
       const long long wgs = conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk);
       if (wgs >= (L.Cin == 128 && wk == 2 ? 128 : 176)) return wgs <= most ? wk : 0;
     }
@@ -358,7 +361,8 @@ struct f8_chain {
         if (img > 1 && conv_imgk_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, src, dst, res)) {
           ConvImgkParams ip;
           ip.x = static_cast<const uint8_t *>(src);
-          ip.wf = wf;
+          ip.w = wf;
+          ip.fold = 0;
           ip.acc0 = acc0;
           ip.y = static_cast<uint8_t *>(dst);
           ip.res = static_cast<const uint8_t *>(res);
@@ -889,7 +893,7 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       gk.B = batch;
       gk.P = g.P; gk.Q = g.Q;
       const int img = c->img_role((size_t)layer, batch);
-      if (img > 1) name = L.Cin == 128 ? "conv3x3_wavek<128>" : L.Cin == 256 ? "conv3x3_wavek<256>" : "conv3x3_wavek<512>";
+      if (img > 1) name = L.Cin == 64 ? "conv3x3_wavek<64>" : L.Cin == 128 ? "conv3x3_wavek<128>" : L.Cin == 256 ? "conv3x3_wavek<256>" : "conv3x3_wavek<512>";
       else if (img == 1) name = L.Cin == 256 ? "conv3x3_img<256x256>" : "conv3x3_img<128x128>";
       else name = conv_kernel_name(gk, L.q, L.res >= 0);
       ops = 2.0 * M * g.R * g.S * g.Cin * g.Cout;

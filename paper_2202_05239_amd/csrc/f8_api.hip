@@ -123,11 +123,42 @@ static bool use_pw_mid(const void *x, const int8_t *w, const void *y, const void
 // And the 1x1 layers with 256 or 512 input channels and at least as many output channels per workgroup
 // as its four waves hold weights for (the closing layers of the third and fourth ResNet stage).
 static bool use_pw_wide(const void *x, const int8_t *w, const void *y, const void *res, const Geom &g,
-                        const f8_quant &q, const void *y2) {
-  if (!tuning().pw_wide.load(std::memory_order_relaxed) || y2 || q.y_type == F8_S32 || (res && q.res_type == F8_S32)) return false;
-  // it pays once every workgroup walks over several blocks of 32 pixels: blocks x channel slices >= 4 x 512
-  if ((g.Cin != 256 && g.Cin != 512) || (long long)g.B * g.H * g.W / 32 * (g.Cout / (4 * (16384 / g.Cin))) < 2048) return false;
+                        const f8_quant &q, const f8_requant2 *q2, const void *y2, bool folding = false) {
+  if (!tuning().pw_wide.load(std::memory_order_relaxed) || q.y_type == F8_S32 || (res && q.res_type == F8_S32)) return false;
+  if (y2 && q2 && (q.fl_x + q.fl_w - q2->fl_y < 0 || (reinterpret_cast<uintptr_t>(y2) & 15))) return false;
+  // it pays once every workgroup walks over several blocks of 32 pixels: blocks x channel slices >= 4 x 512; in single
+  // calls, where it also saves the fold's launch, from 300 on (us a call, here / fold and conv_fast: 256 -> 1024 with
+  // residual and two formats at 392 8.3 / 10.0, 784 11.1 / 12.3, 1568 14.4 / 17.8, 3136 21.7 / 27.2; 512 -> 2048 at 96
+  // 8.4 / 6.3, 384 8.6 / 9.9, 1568 13.3 / 15.6)
+  const long long units = (g.Cin != 256 && g.Cin != 512) ? 0 : (long long)g.B * g.H * g.W / 32 * (g.Cout / (4 * (16384 / g.Cin)));
+  if (units < (folding ? 300 : 2048)) return false;
   return pw_wide_applicable(g.Cin, g.Cout, g.R, g.S, g.sh, g.sw, g.ph, g.pw, q.fl_x + q.fl_w - q.fl_y, x, w, y, res);
+}
+
+static PwWideParams pw_wide_params(const void *x, const int8_t *w, const int32_t *acc0, void *y, const void *res, const Geom &g,
+                                   const f8_quant &q, const f8_requant2 *q2, void *y2, int fold) {
+  PwWideParams pp;
+  pp.x = static_cast<const uint8_t *>(x);
+  pp.w = w;
+  pp.acc0 = acc0;
+  pp.res = static_cast<const uint8_t *>(res);
+  pp.y = static_cast<uint8_t *>(y);
+  pp.M = (long long)g.B * g.H * g.W;
+  pp.K = g.Cin; pp.N = g.Cout;
+  pp.shift = q.fl_x + q.fl_w - q.fl_y; pp.lo = q.clip_lo; pp.hi = q.clip_hi;
+  pp.res_signed = q.res_type == F8_S8;
+  pp.res_d = res ? q.fl_x + q.fl_w - q.fl_res : 0;
+  pp.x_xor = q.x_type == F8_U8 ? 0x80808080u : 0u;
+  pp.fold = fold;
+  pp.y2 = nullptr;
+  pp.shift2 = pp.lo2 = pp.hi2 = pp.add2 = 0;
+  if (q2 && y2) {
+    pp.y2 = static_cast<uint8_t *>(y2);
+    pp.shift2 = q.fl_x + q.fl_w - q2->fl_y;
+    pp.lo2 = q2->clip_lo; pp.hi2 = q2->clip_hi;
+    pp.add2 = (pp.shift2 > 0 ? (1 << (pp.shift2 - 1)) : 0) - rounding_addend(q);
+  }
+  return pp;
 }
 
 // And the 1x1 layers with 16 or 32 input and 96 / 144 / 192 output channels (MobileNetV2's first expand layers).
@@ -251,21 +282,8 @@ f8_status enqueue_conv(const void *x, const int8_t *w, const int32_t *acc0, cons
     pp.x_xor = q.x_type == F8_U8 ? 0x80808080u : 0u;
     return launch_pw_ws(pp, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
   }
-  if (use_pw_wide(x, w, y, res, g, q, (q2 && y2) ? y2 : nullptr) && (reinterpret_cast<uintptr_t>(acc0) & 15) == 0) {
-    PwWideParams pp;
-    pp.x = static_cast<const uint8_t *>(x);
-    pp.w = w;
-    pp.acc0 = acc0;
-    pp.res = static_cast<const uint8_t *>(res);
-    pp.y = static_cast<uint8_t *>(y);
-    pp.M = (long long)g.B * g.H * g.W;
-    pp.K = g.Cin; pp.N = g.Cout;
-    pp.shift = q.fl_x + q.fl_w - q.fl_y; pp.lo = q.clip_lo; pp.hi = q.clip_hi;
-    pp.res_signed = q.res_type == F8_S8;
-    pp.res_d = res ? q.fl_x + q.fl_w - q.fl_res : 0;
-    pp.x_xor = q.x_type == F8_U8 ? 0x80808080u : 0u;
-    return launch_pw_wide(pp, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
-  }
+  if (use_pw_wide(x, w, y, res, g, q, q2, y2) && (reinterpret_cast<uintptr_t>(acc0) & 15) == 0)
+    return launch_pw_wide(pw_wide_params(x, w, acc0, y, res, g, q, q2, y2, 0), stream) == 0 ? F8_OK : F8_ERR_DEVICE;
   if (use_conv_ws(x, w, y, res, g, q, (q2 && y2) ? y2 : nullptr) && (reinterpret_cast<uintptr_t>(acc0) & 15) == 0) {
     ConvWsParams wp;
     wp.x = static_cast<const uint8_t *>(x);
@@ -290,7 +308,7 @@ f8_status enqueue_conv(const void *x, const int8_t *w, const int32_t *acc0, cons
 // conv_wavek takes are known before anything is folded; it forms the start values itself.
 static bool takes_own_kernel(const void *x, const int8_t *w, const void *y, const void *res, const Geom &g, const f8_quant &q, void *y2) {
   return use_pw_small(x, w, y, res, g, q, y2) || use_pw_ws(x, w, y, res, g, q, y2) || use_pw_mid(x, w, y, res, g, q, y2, false) ||
-         use_pw_wide(x, w, y, res, g, q, y2) || use_conv_ws(x, w, y, res, g, q, y2);
+         use_conv_ws(x, w, y, res, g, q, y2);
 }
 
 // The 3x3 64 -> 64 layers: the image-stationary kernel reads the weights as they are.
@@ -323,6 +341,10 @@ bool enqueue_conv_folding(const void *x, const int8_t *w, const int32_t *bias, v
     return true;
   }
   if (takes_own_kernel(x, w, y, res, g, q, (q2 && y2) ? y2 : nullptr)) return false;
+  if (use_pw_wide(x, w, y, res, g, q, q2, y2, true)) {
+    *st = launch_pw_wide(pw_wide_params(x, w, bias, y, res, g, q, q2, y2, 1), stream) == 0 ? F8_OK : F8_ERR_DEVICE;
+    return true;
+  }
   ConvParams p = conv_params(x, w, nullptr, nullptr, y, res, g, q, q2, y2);
   p.near = 1;                           // (only conv_fast reads the page of zeros)
   const int wk = conv_wavek_variant(p, !conv_fast_applicable(p));
@@ -351,7 +373,7 @@ const char *conv_kernel_name(const Geom &g, const f8_quant &q, bool has_res) {
   }
   if (!(has_res && q.res_type == F8_S32) && use_pw_ws(nullptr, nullptr, nullptr, nullptr, g, q, nullptr)) return "pw1x1_ws<64x256>";
   if (!(has_res && q.res_type == F8_S32) && use_pw_mid(nullptr, nullptr, nullptr, nullptr, g, q, nullptr, false)) return "pw1x1_mid<128x512>";
-  if (!(has_res && q.res_type == F8_S32) && use_pw_wide(nullptr, nullptr, nullptr, nullptr, g, q, nullptr))
+  if (!(has_res && q.res_type == F8_S32) && use_pw_wide(nullptr, nullptr, nullptr, nullptr, g, q, nullptr, nullptr))
     return g.Cin == 256 ? "pw1x1_wide<256>" : "pw1x1_wide<512>";
   if (use_conv_ws(nullptr, nullptr, nullptr, has_res ? &g : nullptr, g, q, nullptr)) return g.Cin == 64 ? "conv3x3_ws<64x64>" : "conv3x3_ws<128x128>";
   ConvParams p;

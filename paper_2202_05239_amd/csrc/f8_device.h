@@ -152,6 +152,56 @@ __device__ __forceinline__ uint32_t pack4(int v0, int v1, int v2, int v3) {
   return lo | hi;
 }
 
+// Between writes to LDS and other lanes' reads of them within one wave: the wave's LDS operations are served in
+// order, so nothing waits, but the compiler, which looks at one lane at a time, must not move them past here.
+__device__ __forceinline__ void lanes_meet() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Weight fragments of NB blocks of 32 channels, rows of ROWB bytes (a multiple of 128) one behind the other
+// from `rows` on, into a wave's registers: fa[nb][ks] = row weight_row(l32) of block nb, bytes 32 ks + 16 half ..
+// + 16.  The fragments themselves are 32 bytes of each of 32 rows, which the load unit takes a row at a time
+// (16 bytes per clock and CU, measured); so the rows are fetched as they lie in memory, 1 KiB per instruction
+// at 60 bytes per clock, and change places in `stage`, 4 KiB of LDS that only this wave uses, 16-byte aligned.
+// All loads are issued first.  lane: 0..63.
+__device__ __forceinline__ int weight_row(int r) { return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3); }
+
+template <int ROWB, int NB>
+struct FragmentLoad {
+  static_assert(ROWB % 128 == 0, "rows of whole 128 bytes");
+  static constexpr int IPB = 32 * ROWB / 1024;            // 1 KiB loads per block
+  static constexpr int PPR = ROWB / 16;                   // 16-byte pieces per row
+  v4i raw[NB * IPB];
+  __device__ __forceinline__ void issue(const int8_t *rows, int lane) {
+#pragma unroll
+    for (int i = 0; i < NB * IPB; ++i) raw[i] = *reinterpret_cast<const v4i *>(rows + (size_t)(i * 1024) + lane * 16);
+  }
+  // pieces of a row are permuted by the row number: no 8 rows' pieces share their banks
+  static __device__ __forceinline__ int at(int row, int piece) {
+    return row * 128 + ((piece ^ ((row >> 1) & 7)) * 16);
+  }
+  __device__ __forceinline__ void distribute(uint8_t *stage, int lane, v4i (&fa)[NB][ROWB / 32]) const {
+    constexpr int QUARTERS = ROWB / 128, KSQ = 4;            // 128 bytes of each row at a time
+    const int l32 = lane & 31, half = lane >> 5;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int kq = 0; kq < QUARTERS; ++kq) {
+#pragma unroll
+        for (int i = 0; i < IPB; ++i) {
+          const int row = (i * 64 + lane) / PPR, piece = (i * 64 + lane) % PPR;
+          if (piece / 8 == kq) *reinterpret_cast<v4i *>(stage + at(row, piece % 8)) = raw[nb * IPB + i];
+        }
+        lanes_meet();
+#pragma unroll
+        for (int t = 0; t < KSQ; ++t) fa[nb][kq * KSQ + t] = *reinterpret_cast<const v4i *>(stage + at(weight_row(l32), 2 * t + half));
+        lanes_meet();
+      }
+  }
+};
+
 // Residual operand brought to the accumulator scale (F8Net Sec. 4.3: sibling tensors
 // differ only by a power of two).  d >= 0: exact left shift; d < 0: rounding shift.
 __device__ __forceinline__ int align_res(int r, int d) {

@@ -69,21 +69,27 @@ __global__ __launch_bounds__(PM_NT, 1) void pw_mid_kernel(const PwMidParams p) {
   const int pb = wave >> 2, cg = wave & 3;                 // block of the pair, group of 128 channels
   uint8_t *tile = lds + PM_TILES + wave * PM_TILE;
 
-  // weights: fa[nb][ks] = channel 128 cg + 32 nb + frag_channel(l32), bytes 32 ks + 16 half .. + 16 of its 128
+  // weights: fa[nb][ks] = channel 128 cg + 32 nb + frag_channel(l32), bytes 32 ks + 16 half .. + 16 of its 128; the second
+  // layer's for this wave's 32 of its channels: 16 fragments, in registers as well.  Both by way of the wave's tile.
+  static_assert(PM_TILE >= 4096, "stage of the weights");
   v4i fa[4][4];
-#pragma unroll
-  for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      fa[nb][ks] = *reinterpret_cast<const v4i *>(p.w + (size_t)(128 * cg + 32 * nb + frag_channel(l32)) * PM_K + 32 * ks + 16 * half);
-  start[tid] = p.acc0[tid];
-  // the second layer's weights for this wave's 32 of its channels: 16 fragments, in registers as well
   v4i wt[TAIL ? 16 : 1];
-  if (TAIL) {
-    if (tid < PM_TN) start2[tid] = p.t_acc0[tid];
+  {
+    FragmentLoad<PM_K, 4> rows;
+    rows.issue(p.w + (size_t)(128 * cg) * PM_K, lane);
+    start[tid] = p.acc0[tid];
+    if constexpr (TAIL) {
+      FragmentLoad<PM_N, 1> trows;
+      trows.issue(p.t_w + (size_t)(32 * cg) * PM_N, lane);
+      if (tid < PM_TN) start2[tid] = p.t_acc0[tid];
+      rows.distribute(tile, lane, fa);
+      v4i t[1][16];
+      trows.distribute(tile, lane, t);
 #pragma unroll
-    for (int ks = 0; ks < 16; ++ks)
-      wt[ks] = *reinterpret_cast<const v4i *>(p.t_w + (size_t)(32 * cg + frag_channel(l32)) * PM_N + 32 * ks + 16 * half);
+      for (int ks = 0; ks < 16; ++ks) wt[ks] = t[0][ks];
+    } else {
+      rows.distribute(tile, lane, fa);
+    }
   }
 
   const long long npair = (p.M + 63) >> 6;

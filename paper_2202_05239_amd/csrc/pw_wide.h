@@ -10,7 +10,7 @@ namespace f8 {
 struct PwWideParams {
   const uint8_t *x;      // [M][K]
   const int8_t *w;       // [N][K]
-  const int32_t *acc0;   // [N] folded accumulator start values
+  const int32_t *acc0;   // [N] folded accumulator start values; fold: the bias, or null
   const uint8_t *res;    // [M][N] 8-bit residual, or null
   uint8_t *y;            // [M][N], unsigned or signed bytes
   long long M;           // pixels
@@ -18,6 +18,9 @@ struct PwWideParams {
   int shift, lo, hi;     // requantisation (shift >= 0)
   int res_signed, res_d; // residual type; its shift to the accumulator scale (left if >= 0, rounding right if < 0)
   uint32_t x_xor;        // 0x80808080 when x is unsigned
+  int fold;              // 1: form the start values here
+  uint8_t *y2;           // optional second output: clip((A + add2) >> shift2), shift2 >= 0; null for none
+  int shift2, lo2, hi2, add2;
 };
 
 // Geometry and operand checks (1x1, stride 1, no padding, 16-byte aligned tensors).

@@ -16,7 +16,9 @@
 // weight rows are fed in the order that leaves a lane with 16 consecutive channels of its pixel, so
 // each lane adds its accumulators to one 16-byte piece of the residual, requantises and writes the
 // piece back in place; finished rows leave as 16-byte pieces (whole 128- or 64-byte runs per row).
-// One barrier per block of 32 pixels.
+// One barrier per block of 32 pixels.  A second output format of the same accumulator takes the tile after the
+// first one's rows have left it.  In single-layer calls the start values come from the weights in the
+// registers (fold), so that the call is one launch.
 #include "pw_wide.h"
 
 namespace f8 {
@@ -47,7 +49,7 @@ template <int K> constexpr int pww_wgs_per_cu() { return 2; }
 
 // RK: residual kind (0 none, 1 unsigned, 2 signed); RLEFT: the residual is shifted left to the
 // accumulator's scale (else rounded right).  Both uniform, so the per-lane code carries no selects.
-template <int K, int RK, bool RLEFT>
+template <int K, int RK, bool RLEFT, bool DUAL>
 __global__ __launch_bounds__(PWW_NT, pww_wgs_per_cu<K>()) void pw_wide_kernel(const PwWideParams p) {
   constexpr bool HAS_RES = RK != 0;
   constexpr int KS = K / 32;                 // K slices
@@ -77,14 +79,40 @@ __global__ __launch_bounds__(PWW_NT, pww_wgs_per_cu<K>()) void pw_wide_kernel(co
   const int groups = (int)gridDim.x / slices;
   const int n0 = slice * WGCH + wave * WCH;  // this wave's first channel
 
-  // weights: fa[nb][ks] = channel n0 + 32 nb + frag_channel(l32), bytes 32 ks + 16 half .. + 16 of its K
+  // weights: fa[nb][ks] = channel n0 + 32 nb + frag_channel(l32), bytes 32 ks + 16 half .. + 16 of its K.  K = 256: by way
+  // of this wave's 4 KiB of the ring that the activations will use (14 x 14 256 -> 1024 at batch 128: 16.9 us, read
+  // straight into place 18.2 us); K = 512: straight into place (rows of 512 bytes change places 16 lanes at a
+  // time there: 17.1 us against 16.4 us for 7 x 7 512 -> 2048)
   v4i fa[NBW][KS];
+  if constexpr (K == 256) {
+    static_assert(sizeof(xring) >= 4 * 4096, "a stage per wave");
+    FragmentLoad<K, NBW> rows;
+    rows.issue(p.w + (size_t)n0 * K, lane);
+    rows.distribute(&xring[0][0] + wave * 4096, lane, fa);
+  } else {
 #pragma unroll
-  for (int nb = 0; nb < NBW; ++nb)
+    for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      fa[nb][ks] = *reinterpret_cast<const v4i *>(p.w + (size_t)(n0 + 32 * nb + frag_channel(l32)) * K + 32 * ks + 16 * half);
-  if (tid < WGCH) start[tid] = p.acc0[slice * WGCH + tid];
+      for (int ks = 0; ks < KS; ++ks)
+        fa[nb][ks] = *reinterpret_cast<const v4i *>(p.w + (size_t)(n0 + 32 * nb + frag_channel(l32)) * K + 32 * ks + 16 * half);
+  }
+  if (p.fold) {
+    // start values from the weights at hand: bias, rounding addend, 128 times their sum for unsigned activations
+    const int rnd = p.shift > 0 ? 1 << (p.shift - 1) : 0;
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+      int s = 0;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_sdot4(fa[nb][ks][i], 0x01010101, s, false);
+      s += __shfl_xor(s, 32, 64);
+      const int n = wave * WCH + 32 * nb + frag_channel(l32);
+      if (half == 0) start[n] = rnd + (p.acc0 ? p.acc0[slice * WGCH + n] : 0) + (p.x_xor ? 128 * s : 0);
+    }
+  } else if (tid < WGCH) {
+    start[tid] = p.acc0[slice * WGCH + tid];
+  }
   __syncthreads();
 
   const long long nblk = (p.M + 31) >> 5;
@@ -129,6 +157,8 @@ __global__ __launch_bounds__(PWW_NT, pww_wgs_per_cu<K>()) void pw_wide_kernel(co
   const ScaledClip c1 = scaled_clip(p.lo, p.hi, sh);
   const int d = RLEFT ? p.res_d : -p.res_d;            // shift distance, left or right
   const int rhalf = RLEFT ? 0 : (1 << (d - 1));
+  const int sh2 = p.shift2, a2 = p.add2;
+  const ScaledClip c2 = scaled_clip(p.lo2, p.hi2, DUAL ? sh2 : 0);
 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();                     // the first block's activations are in LDS
@@ -165,6 +195,7 @@ __global__ __launch_bounds__(PWW_NT, pww_wgs_per_cu<K>()) void pw_wide_kernel(co
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int nb = 0; nb < NBW; ++nb) acc[nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[nb][ks], xb[ks], acc[nb], 0, 0, 0);
+    v4i second[DUAL ? NBW : 1];
 #pragma unroll
     for (int nb = 0; nb < NBW; ++nb) {
       settle_matrix_result(acc[nb]);
@@ -181,6 +212,13 @@ __global__ __launch_bounds__(PWW_NT, pww_wgs_per_cu<K>()) void pw_wide_kernel(co
           v[i] += RLEFT ? (r << d) : ((r + rhalf) >> d);
         }
       }
+      if (DUAL) {
+        // the second format of the same accumulator: swap the rounding addend, clip, shift
+        int u[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) u[i] = clamp_med3(v[i] + a2, c2.lo, c2.hi);
+        second[nb] = shift_pack16(u, sh2);
+      }
       // clip at the accumulator's scale, then one shift-and-pack instruction per value
 #pragma unroll
       for (int i = 0; i < 16; ++i) v[i] = clamp_med3(v[i], c1.lo, c1.hi);
@@ -189,6 +227,16 @@ __global__ __launch_bounds__(PWW_NT, pww_wgs_per_cu<K>()) void pw_wide_kernel(co
     v4i out[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j) out[j] = *reinterpret_cast<const v4i *>(tile + (RPI * j + prow) * PITCH + 16 * ppiece);
+    v4i out2[DUAL ? NI : 1];
+    if (DUAL) {
+      // the second result takes the tile once the first one's rows are read
+      lanes_meet();
+#pragma unroll
+      for (int nb = 0; nb < NBW; ++nb) *reinterpret_cast<v4i *>(tile + l32 * PITCH + 32 * nb + 16 * half) = second[nb];
+      lanes_meet();
+#pragma unroll
+      for (int j = 0; j < NI; ++j) out2[j] = *reinterpret_cast<const v4i *>(tile + (RPI * j + prow) * PITCH + 16 * ppiece);
+    }
     // The wait for the next block's operands goes here, before this block's stores are issued: at the
     // top of the loop it would also wait for those stores (loads and stores share one counter).
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -202,22 +250,28 @@ __global__ __launch_bounds__(PWW_NT, pww_wgs_per_cu<K>()) void pw_wide_kernel(co
 #pragma unroll
       for (int j = 0; j < NI; ++j)
         if (m + RPI * j < p.M) *reinterpret_cast<v4i *>(dst + (size_t)j * RPI * p.N) = out[j];
+      if (DUAL) {
+        uint8_t *dst2 = p.y2 + m * p.N + n0 + 16 * ppiece;
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+          if (m + RPI * j < p.M) *reinterpret_cast<v4i *>(dst2 + (size_t)j * RPI * p.N) = out2[j];
+      }
     }
     // every wave has read this block's activations and has seen its share of the next block's land
     __syncthreads();
   }
 }
 
-template <int K>
+template <int K, bool DUAL>
 void launch_k(const PwWideParams &p, hipStream_t stream) {
   const int rk = !p.res ? 0 : (p.res_signed ? 2 : 1);
   const bool left = p.res_d >= 0;
   const dim3 grid(256 * pww_wgs_per_cu<K>()), block(PWW_NT);
-  if (rk == 0) hipLaunchKernelGGL((pw_wide_kernel<K, 0, true>), grid, block, 0, stream, p);
-  else if (rk == 1 && left) hipLaunchKernelGGL((pw_wide_kernel<K, 1, true>), grid, block, 0, stream, p);
-  else if (rk == 1) hipLaunchKernelGGL((pw_wide_kernel<K, 1, false>), grid, block, 0, stream, p);
-  else if (left) hipLaunchKernelGGL((pw_wide_kernel<K, 2, true>), grid, block, 0, stream, p);
-  else hipLaunchKernelGGL((pw_wide_kernel<K, 2, false>), grid, block, 0, stream, p);
+  if (rk == 0) hipLaunchKernelGGL((pw_wide_kernel<K, 0, true, DUAL>), grid, block, 0, stream, p);
+  else if (rk == 1 && left) hipLaunchKernelGGL((pw_wide_kernel<K, 1, true, DUAL>), grid, block, 0, stream, p);
+  else if (rk == 1) hipLaunchKernelGGL((pw_wide_kernel<K, 1, false, DUAL>), grid, block, 0, stream, p);
+  else if (left) hipLaunchKernelGGL((pw_wide_kernel<K, 2, true, DUAL>), grid, block, 0, stream, p);
+  else hipLaunchKernelGGL((pw_wide_kernel<K, 2, false, DUAL>), grid, block, 0, stream, p);
 }
 
 }  // namespace
@@ -239,10 +293,11 @@ bool pw_wide_applicable(int Cin, int Cout, int R, int S, int sh, int sw, int ph,
 int launch_pw_wide(const PwWideParams &p, hipStream_t stream) {
   if (p.M <= 0) return 0;
   if (!pw_wide_applicable(p.K, p.N, 1, 1, 1, 1, 0, 0, p.shift, p.x, p.w, p.y, p.res) || p.lo > p.hi || p.res_d > 24 ||
-      p.res_d < -24 || p.M > (1LL << 40) || (reinterpret_cast<uintptr_t>(p.acc0) & 15))
+      p.res_d < -24 || p.M > (1LL << 40) || (reinterpret_cast<uintptr_t>(p.acc0) & (p.fold ? 3 : 15)) ||
+      (reinterpret_cast<uintptr_t>(p.y2) & 15) || (p.y2 && (p.shift2 < 0 || p.lo2 > p.hi2)))
     return (int)hipErrorInvalidValue;
-  if (p.K == 256) launch_k<256>(p, stream);
-  else launch_k<512>(p, stream);
+  if (p.K == 256) p.y2 ? launch_k<256, true>(p, stream) : launch_k<256, false>(p, stream);
+  else p.y2 ? launch_k<512, true>(p, stream) : launch_k<512, false>(p, stream);
   return (int)hipGetLastError();
 }
 

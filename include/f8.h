@@ -371,14 +371,17 @@ f8_status f8_mfma_i8_yardstick_operands(int32_t *sink, int iters, uint32_t seed,
 /* Tuning switches: kernel choices only, never results (the parity tests force every tile variant
  * through them).  Names and defaults: "conv_variant" (-1 = automatic; >= 0 forces that tile
  * variant of the LDS-direct dense kernel), "wavek" (0: the K-sharing kernel only for layers no other kernel
- * takes), "wavek_variant" (-1 = automatic; >= 0 forces that tile shape of it), "conv_ws", "conv_ws_min" (768: smallest layer, in blocks
- * of 128 pixels, that takes the weights-stationary 3x3 kernel), "pw_ws", "pw_small", "xcd_remap",
- * "pw_wide", "pw_mid" (1: the 1x1 128 -> 512 kernel only together with the 512 -> 128 layer behind it, 2: also
- * alone), "stem_pool", "conv_tail", "conv_img", "imgk" (1 = on; 10 + n: the image-stationary 3x3 kernel with n waves sharing K wherever it fits), "conv_img_min" (96: fewest images, or
- * bands of 28 image rows, for which a chain takes the image-stationary 3x3 kernels).  The environment variables F8_<NAME IN CAPITALS> give the
- * initial values; they are read once, when the library first looks at a switch, never on the
- * launch path.  f8_tuning_set returns 0, or -1 for an unknown name; the chain switches
- * (the last five) are read by f8_chain_create.  f8_tuning_get returns the value (-1 for an unknown name). */
+ * takes), "wavek_variant" (-1 = automatic; >= 0 forces that tile shape of it), "conv_ws",
+ * "conv_ws_min" (768: smallest layer, in blocks of 128 pixels, that takes the weights-stationary 3x3
+ * kernel), "pw_ws", "pw_small", "xcd_remap", "pw_wide", "pw_mid" (1: the 1x1 128 -> 512 kernel only
+ * together with the 512 -> 128 layer behind it, 2: also alone), "stem_pool", "conv_tail", "conv_img",
+ * "imgk" (1 = on; 10 + n: the image-stationary 3x3 kernel with n waves sharing K wherever it fits),
+ * "dw_pw" (1 = on where it pays; 2: a depthwise layer and the 1x1 layer behind it in one launch wherever
+ * they fit), "conv_img_min" (96: fewest images, or bands of 28 image rows, for which a chain takes the
+ * image-stationary 3x3 kernels).  The environment variables F8_<NAME IN CAPITALS> give the initial
+ * values; they are read once, when the library first looks at a switch, never on the launch path.
+ * f8_tuning_set returns 0, or -1 for an unknown name; the chain switches ("stem_pool" to
+ * "conv_img_min") are read by f8_chain_create.  f8_tuning_get returns the value (-1 for an unknown name). */
 int f8_tuning_set(const char *name, int value);
 int f8_tuning_get(const char *name);
 /* Library version, for the binding to check that it loaded what it was built against. */

@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "block_fused.h"
+#include "dw_pw.h"
 #include "stem_pool.h"
 #include "conv_img.h"
 #include "conv_imgk.h"
@@ -136,6 +137,33 @@ struct f8_chain {
     }
     return 0;
   }
+  // A depthwise 3x3 layer and the 1x1 layer that is its only reader in one launch: dwp[i] = 1 for the depthwise one,
+  // 2 for the other; dwp_w_off: the 1x1 layer's weights in fragment order.  Whether the pair runs as one
+  // launch depends on the batch.
+  std::vector<int> dwp;                // per layer
+  std::vector<size_t> dwp_w_off;       // per layer (of the depthwise one)
+  int dw_pw = 1;
+  int dwp_role(size_t i, int batch) const {
+    if (dw_pw == 0 || keep_all || dwp[i] == 0) return 0;
+    const size_t head = dwp[i] == 1 ? i : i - 1;
+    if (use_fusion() && (fused[head].role != 0 || fused[head + 1].role != 0)) return 0;
+    if (dw_pw != 2 && !dw_pw_pays(head, batch)) return 0;
+    return dwp[i];
+  }
+  // Microseconds of the pair, apart -> together (the tail of the launch is what it saves; it pays for that with a
+  // depthwise part that gathers its columns one by one and holds only one or two workgroups per CU).  Rows of more than 64
+  // pixels: 112x112 C32, batch 4 (1.5 M elements) 8.3 -> 5.6, batch 8 (3.1 M) 7.7 -> 9.1.  Up to 64: 56x56 C96 stride 2 from 112,
+  // batch 8 (2.3 M) 9.5 -> 7.3; C64, batch 16 (3.1 M) 11.0 -> 13.4.  Up to 28: C144, batch 40 (4.3 M) 10.2 -> 9.7; C192, batch 40
+  // (5.7 M) 9.9 -> 11.2.  Up to 14: C576, batch 64 (6.9 M) 12.7 -> 11.9; C384, batch 100 (7.2 M) 11.8 -> 12.9.  Up to 7: C576
+  // stride 2, batch 64 (1.7 M) 9.6 -> 8.4; batch 100 (2.7 M) 11.2 -> 12.1.  And K not so long that the few waves per block
+  // of channels walk it one after the other: C576 -> 160, 18 slices of 32 each, batch 27, 8.9 -> 6.9; C960 -> 160, 30 slices
+  // each, 7.8 -> 8.1 at every batch.
+  bool dw_pw_pays(size_t i, int batch) const {
+    const Geom &g = geom[i];
+    const long long total = (long long)batch * g.P * g.Q * g.Cin;
+    const long long most = g.Q > 64 ? 2ll << 20 : g.Q > 28 ? 5ll << 19 : g.Q > 14 ? 9ll << 19 : g.Q > 7 ? 7ll << 20 : 2ll << 20;
+    return total <= most && dw_pw_slices(g.Cin, layers[i + 1].Cout) <= 20;
+  }
   bool tail_in_fused_block(size_t i) const {
     const size_t a = tail[i] == 1 ? i : (size_t)tail_peer[i], b = tail[i] == 1 ? (size_t)tail_peer[i] : i;
     return use_fusion() && (fused[a].role != 0 || fused[b].role != 0);
@@ -222,8 +250,14 @@ struct f8_chain {
       }
       if (stem[li].on) stem[li].x_off_per_image = alloc(round256(stem[li].x_bytes_per_image));
       Tensor &d = tensors[layers[li].dst];
+      const bool dwp_head = !keep_all && dwp[li] == 1, dwp_behind = !keep_all && dwp[li] == 2;
+      if (dwp_head) {
+        // written by this launch: must not share memory with what this layer reads
+        Tensor &dp = tensors[layers[li + 1].dst];
+        if (!dp.external) dp.offset_per_image = alloc(round256(dp.bytes_per_image));
+      }
       // (the output of a 1x1 layer that may run inside the previous launch got its place there)
-      if (!d.external && tail_plan(li) != 2) d.offset_per_image = alloc(round256(d.bytes_per_image));
+      if (!d.external && tail_plan(li) != 2 && !dwp_behind) d.offset_per_image = alloc(round256(d.bytes_per_image));
       if (tail_plan(li) == 1) {
         // written by this launch too: must not share memory with what this layer reads
         Tensor &dt = tensors[layers[tail_peer[li]].dst];
@@ -348,7 +382,39 @@ struct f8_chain {
       const BlockParams bp = block_params(i, x, out, workspace, batch);
       return launch_block_fused(bp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
-    if (tail_role(i, batch) == 2) return F8_OK;
+    if (tail_role(i, batch) == 2 || dwp_role(i, batch) == 2) return F8_OK;
+    if (dwp_role(i, batch) == 1) {
+      const f8_layer_desc &T = layers[i + 1];
+      const void *xs = tensor_ptr(L.src, x, out, workspace, batch);
+      void *yd = tensor_ptr(T.dst, x, out, workspace, batch);
+      const void *rs = T.res >= 0 ? tensor_ptr(T.res, x, out, workspace, batch) : nullptr;
+      const int d_shift = L.q.fl_x + L.q.fl_w - L.q.fl_y, t_shift = T.q.fl_x + T.q.fl_w - T.q.fl_y;
+      if (dw_pw_applicable(L.Cin, T.Cout, g.Q, d_shift, t_shift, xs, L.w, yd, rs)) {
+        DwPwParams dp;
+        dp.x = static_cast<const uint8_t *>(xs);
+        dp.wd = L.w;
+        dp.bias = L.bias;
+        dp.wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + dwp_w_off[i]);
+        dp.acc0 = reinterpret_cast<const int32_t *>(static_cast<uint8_t *>(workspace) + acc0_off[i + 1]);
+        dp.y = static_cast<uint8_t *>(yd);
+        dp.res = static_cast<const uint8_t *>(rs);
+        dp.B = batch; dp.H = g.H; dp.W = g.W; dp.C = L.Cin; dp.N = T.Cout; dp.P = g.P; dp.Q = g.Q; dp.stride = g.sh;
+        dp.x_xor = L.q.x_type == F8_U8 ? 0x80808080u : 0u;
+        dp.d_xor = L.q.y_type == F8_U8 ? 0x80808080u : 0u;
+        dp.d_shift = d_shift; dp.d_lo = L.q.clip_lo; dp.d_hi = L.q.clip_hi;
+        dp.shift = t_shift; dp.lo = T.q.clip_lo; dp.hi = T.q.clip_hi;
+        dp.res_signed = T.q.res_type == F8_S8;
+        dp.res_d = rs ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0;
+        return launch_dw_pw(dp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
+      }
+      // (a tensor of the caller's at an odd address: the two layers one after the other)
+      const f8_status st = enqueue_dwconv(xs, L.w, L.bias, tensor_ptr(L.dst, x, out, workspace, batch), nullptr, g, L.q, s);
+      if (st != F8_OK) return st;
+      Geom gt = geom[i + 1];
+      gt.B = batch;
+      return enqueue_conv(tensor_ptr(L.dst, x, out, workspace, batch), T.w,
+                          reinterpret_cast<const int32_t *>(static_cast<uint8_t *>(workspace) + acc0_off[i + 1]), workspace, yd, rs, gt, T.q, s);
+    }
     const void *src = tensor_ptr(L.src, x, out, workspace, batch);
     void *dst = tensor_ptr(L.dst, x, out, workspace, batch);
     const void *res = L.res >= 0 ? tensor_ptr(L.res, x, out, workspace, batch) : nullptr;
@@ -547,6 +613,8 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->fused.push_back(Fused());
     c->tail.push_back(0);
     c->tail_peer.push_back(-1);
+    c->dwp.push_back(0);
+    c->dwp_w_off.push_back(0);
   }
   if (st != F8_OK) { delete c; return st; }
   c->last_tensor = c->layers.back().dst;
@@ -598,6 +666,25 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
         break;
       }
     }
+  }
+  // a depthwise 3x3 layer and the 1x1 layer that is its only reader
+  c->dw_pw = tuning().dw_pw.load();
+  for (size_t i = 0; i + 1 < c->layers.size(); ++i) {
+    const f8_layer_desc &L = c->layers[i], &T = c->layers[i + 1];
+    const Geom &g = c->geom[i];
+    if (L.op != F8_OP_DWCONV || g.R != 3 || g.S != 3 || g.sh != g.sw || (g.sh != 1 && g.sh != 2) || g.ph != 1 || g.pw != 1 || L.res >= 0 ||
+        L.q.y_type == F8_S32 || (long long)g.H * g.W * g.Cin > 0x3fffffffLL || (reinterpret_cast<uintptr_t>(L.bias) & 3))
+      continue;
+    if (T.op != F8_OP_CONV || T.src != L.dst || T.R != 1 || T.S != 1 || T.stride_h != 1 || T.stride_w != 1 || T.pad_h != 0 || T.pad_w != 0 ||
+        T.dst2 > 0 || T.q.y_type == F8_S32 || (T.res >= 0 && T.q.res_type == F8_S32) || T.res == L.dst || c->stem[i + 1].on || c->tail[i + 1] != 0 ||
+        c->stem[i + 1].pool != 0)
+      continue;
+    if (c->tensors[L.dst].last_use != (int)i + 1 || L.dst == c->last_tensor) continue;
+    if (!dw_pw_applicable(L.Cin, T.Cout, g.Q, L.q.fl_x + L.q.fl_w - L.q.fl_y, T.q.fl_x + T.q.fl_w - T.q.fl_y, nullptr, L.w, nullptr, nullptr)) continue;
+    c->dwp[i] = 1;
+    c->dwp[i + 1] = 2;
+    c->dwp_w_off[i] = c->const_bytes;
+    c->const_bytes += round256(dw_pw_weight_bytes(L.Cin, T.Cout));
   }
   // inverted-residual blocks that can run as one kernel
   for (size_t i = 0; i + 2 < c->layers.size(); ++i) {
@@ -688,6 +775,8 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
     int32_t *acc0 = reinterpret_cast<int32_t *>(static_cast<uint8_t *>(workspace) + c->acc0_off[i]);
     const f8_status st = enqueue_fold(c->conv_weights(i, workspace), L.bias, acc0, c->conv_geom(i, 1), L.q, s);
     if (st != F8_OK) return st;
+    if (c->dwp[i] == 2 && launch_dw_pw_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->dwp_w_off[i - 1]), L.Cin, L.Cout, s) != 0)
+      return F8_ERR_DEVICE;
     if (c->img_w_off[i] != 0 &&
         launch_conv_img_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->img_w_off[i]), L.Cin, s) != 0)
       return F8_ERR_DEVICE;
@@ -773,7 +862,7 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
   if (!c->planned) const_cast<f8_chain *>(c)->plan();
   const Tensor &t = c->tensors[id];
   // tensors inside a fused block are never materialised
-  const bool elided = (t.producer >= 0 && c->pool_role((size_t)t.producer) == 1) ||
+  const bool elided = (t.producer >= 0 && (c->pool_role((size_t)t.producer) == 1 || c->dwp_role((size_t)t.producer, batch) == 1)) ||
                       (c->use_fusion() && t.producer >= 0 && c->fused[t.producer].role != 0 &&
                        !(c->fused[t.producer].role == 2 && t.producer >= 2 && c->fused[t.producer - 2].role == 1));
   // (with two streams the two halves of a tensor lie apart: not reported)
@@ -867,7 +956,7 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
     if (alg_bytes) *alg_bytes = fb;
     return F8_OK;
   }
-  if (c->tail_role((size_t)layer, batch) == 2) {
+  if (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2) {
     // accounted to the layer in front, whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {
@@ -908,6 +997,14 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       break;
     }
     case F8_OP_DWCONV:
+      if (c->dwp_role((size_t)layer, batch) == 1) {
+        // plus the 1x1 layer that reads it: what lies between them never leaves the chip
+        const f8_layer_desc &T = c->layers[layer + 1];
+        name = g.sh == 1 ? "dwconv3x3<s1>+1x1" : "dwconv3x3<s2>+1x1";
+        ops = 2.0 * M * (9.0 * L.Cout + (double)T.Cin * T.Cout);
+        bytes += M * (T.Cout - L.Cout) + (T.res >= 0 ? M * T.Cout : 0.0) + 13.0 * L.Cout + (double)T.Cin * T.Cout + 4.0 * T.Cout;
+        break;
+      }
       name = (g.R == 3 && g.S == 3 && g.sh == g.sw && (g.sh == 1 || g.sh == 2) && g.Cin % 4 == 0 && L.res < 0 &&
               c->tensors[L.dst].type != F8_S32 && L.q.fl_x + L.q.fl_w - L.q.fl_y >= 0)
                  ? (g.sh == 1 ? "dwconv3x3<s1>" : "dwconv3x3<s2>")

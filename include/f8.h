@@ -370,8 +370,8 @@ f8_status f8_mfma_i8_yardstick(int32_t *sink, int iters, double *ops, void *stre
 f8_status f8_mfma_i8_yardstick_operands(int32_t *sink, int iters, uint32_t seed, double *ops, void *stream);
 /* Tuning switches: kernel choices only, never results (the parity tests force every tile variant
  * through them).  Names and defaults: "conv_variant" (-1 = automatic; >= 0 forces that tile
- * variant of the LDS-direct dense kernel), "wavek" (0: the K-sharing kernel only for layers no other kernel
- * takes), "wavek_variant" (-1 = automatic; >= 0 forces that tile shape of it), "conv_ws",
+ * variant of the LDS-direct dense kernel), "wavek" (1 = the K-sharing kernel where it is the faster one,
+ * 0 = never), "wavek_variant" (-1 = automatic; >= 0 forces that tile shape of it), "conv_ws",
  * "conv_ws_min" (768: smallest layer, in blocks of 128 pixels, that takes the weights-stationary 3x3
  * kernel), "pw_ws", "pw_small", "xcd_remap", "pw_wide", "pw_mid" (1: the 1x1 128 -> 512 kernel only
  * together with the 512 -> 128 layer behind it, 2: also alone), "stem_pool", "conv_tail", "conv_img",

@@ -1,7 +1,7 @@
 // Fast path of the dense fixed-point convolution / GEMM (F8Net Eq. 6 in integer form) for
 // gfx950, for layers whose input channel count is a multiple of 16 (every layer of the
 // ResNet / MobileNet bodies) and for the re-laid-out stem.  Same arithmetic and operand
-// conventions as the generic kernel in conv_params.hip; what differs is how the data moves:
+// conventions as the generic kernel in conv_igemm.hip; what differs is how the data moves:
 //
 //  * v_mfma_i32_32x32x32_i8 (the full-rate int8 matrix instruction on this chip; the
 //    16x16x64 form issues at half that rate), weights as the row operand, im2col rows as

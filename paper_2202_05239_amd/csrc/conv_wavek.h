@@ -11,11 +11,11 @@ namespace f8 {
 enum { WK_32x32_W8 = 0, WK_32x32_W4 = 1, WK_64x32_W8 = 2, WK_64x64_W8 = 3, WK_VARIANTS = 4 };
 
 // x and w can be fetched in 16-byte units (whole channels of one tap, 16-byte aligned); otherwise the kernel
-// gathers them.  It takes every layer the entry points accept.
+// gathers them.  It can take every layer the entry points accept.
 bool conv_wavek_direct(const ConvParams &p);
-// The tile shape for this layer; -1 where conv_fast is the faster kernel (never if must is set: no other
-// kernel takes the layer).
-int conv_wavek_variant(const ConvParams &p, bool must);
+// The tile shape for this layer; -1 where another kernel is the faster one: conv_fast or, for layers that it does
+// not take (general), conv_igemm.
+int conv_wavek_variant(const ConvParams &p, bool general);
 const char *conv_wavek_name(int variant, bool direct);
 // fold == false: p.acc0 holds the folded start values.  fold == true: the kernel forms them itself from the
 // weights and the bias (null for none); p.acc0 is not read.  A hipError_t as int.

@@ -1,5 +1,6 @@
 // Dense fixed-point convolution / GEMM (F8Net Eq. 6 in integer form) for layers with few output tiles, and
-// for channel counts and alignments that the LDS-direct kernel (conv_fast_kernel.h) does not take.
+// for channel counts and alignments that the LDS-direct kernel (conv_fast_kernel.h) does not take, where K is long or
+// odd (conv_igemm.hip takes the others: what lies between the two is in conv_wavek_variant).
 //
 // What bounds such a layer is not bandwidth or the matrix pipes but one serial chain: a workgroup walks
 // along K a step at a time, and a step costs the latency of its operand loads however few workgroups
@@ -8,8 +9,9 @@
 //  * the tile is small (32 x 32 to 64 x 64), which makes workgroups out of a small output, and
 //  * the waves of a workgroup share the tile's K range instead of its area: wave w takes the 128-byte
 //    K chunks w, w + NW, ..., copies them into LDS of its own (no barrier in the loop, D chunks in flight
-//    per wave, 96 - 144 KiB in flight per CU) and accumulates the whole tile for them.  The partial sums
-//    meet in LDS once, at the end; integer sums do not depend on the order.
+//    per wave: 128 KiB in flight per workgroup, 96 for 64 x 32, 64 with four waves, of which two share a CU) and
+//    accumulates the whole tile for them.  The partial sums meet in LDS once, at the end; integer sums do not
+//    depend on the order.
 //  A wave's fragments are then shared by all of its tile (64 x 64: 16 KiB read from LDS per 16 matrix
 //  instructions, where four waves that share the area read twice that).
 //
@@ -20,14 +22,14 @@
 //  Gather: any channel count and any alignment.  The 16 bytes of a unit are taken from at most two runs of
 //  memory (a window row is one run of S * C bytes, of which the image border cuts off a part at either
 //  end), each fetched as one unaligned 16-byte load and masked; only units at the very ends of a tensor, or
-//  windows whose rows are shorter than 16 bytes, are put together byte by byte.  This replaced a kernel that
-//  gathered every byte on its own.
+//  windows whose rows are shorter than 16 bytes, are put together byte by byte.
 //
 // FOLD: the single-layer calls get their accumulator start values (bias, rounding addend, 128 * sum of the
 // weights for unsigned activations) from here too, so that a small call is one launch instead of two: the
 // weights of a tile pass through its waves anyway, and four packed dot products per fragment sum them.
 #include "conv_wavek.h"
 
+#include "conv_igemm.h"
 #include "f8_host.h"
 
 namespace f8 {
@@ -568,10 +570,39 @@ bool conv_wavek_direct(const ConvParams &p) {
   return (p.C & 15) == 0 || packed;
 }
 
-int conv_wavek_variant(const ConvParams &p, bool must) {
+// Up to how many 32 x 32 tiles this kernel is ahead of conv_igemm on layers that conv_fast does not take, by K and by the
+// width of that kernel's gather.  A tile costs more here (the sums of the waves), a chunk of K less; measured on 1900
+// layers of 1000 to 400000 pixels (us, here / there):
+//   16 bytes: 64 -> 255 on 3136 pixels (784 tiles) 6.2 / 10.8, on 12544 (3136) 17.5 / 11.4; K = 512 18.7 / 16.1; K = 1024 21.0 / 21.3;
+//     K = 2048 27 / 32, on 50176 pixels (12544) 86 / 79.  One tile wide (N <= 32): 256 -> 30 on 50176 pixels (1568) 10.5 / 9.0, K =
+//     1024 16.1 / 22.7, 2048 on 200704 (6272) 89 / 105;
+//   4 bytes: K = 108 -> 49 with a 32-bit residual on 9212 (576) 11.7 / 20.1, 60 -> 62 on 12544 (784) 14.5 / 10.7, 124 -> 130 there
+//     (1960) 21.0 / 12.0, 1800 -> 130 there 37 / 48, 1980 -> 256 on 7800 (1952) 28.7 / 51.5;
+//   single bytes, which keep that kernel's gather busy: 401 -> 255 on 200704 (50176) 293 / 576, 147 -> 62 there (12544) 82 / 85,
+//     75 -> 62 on 50176 (3136) 26.5 / 26.0, 27 -> 62 there 26.1 / 18.5, on 12544 (784) 14.4 / 17.7.
+static long long general_limit(const ConvParams &p) {
+  const int K = p.K;
+  const bool one = p.N <= 32;
+  const long long any = 1LL << 62;
+  const int vec = conv_igemm_vec(p);
+  // windows whose rows are shorter than 16 bytes: each wave gathers them byte by byte, one row of pixels after another
+  // (3x3 on three channels, 32 of them out of 12544 pixels, 16.7 / 14.5; 401408 pixels 331 / 51); ahead on few pixels of
+  // odd channel counts only (1 -> 62, 3136 pixels: 13.0 / 15.6)
+  if (p.R > 1 && p.S * p.C < 16) return vec == 1 && !one ? 768 : -1;
+  long long limit;
+  if (vec == 16) limit = one ? (K < 256 ? 512 : K < 1024 ? 1536 : K < 2048 ? 3072 : any) : (K < 64 ? 1024 : K < 256 ? 1536 : K < 1024 ? 2048 : 4096);
+  else if (vec == 4) limit = one ? (K < 128 ? 512 : K < 256 ? 768 : K < 1024 ? 1536 : K < 1536 ? 2048 : any) : (K < 128 ? 768 : K < 256 ? 1536 : K < 1536 ? 2048 : 8192);
+  else limit = K >= 256 ? any : K >= 128 ? (p.R == 1 && p.S == 1 ? 16384 : 6144) : one ? 1024 : K < 64 ? 1536 : 2048;
+  // a residual or a second format of odd rows goes byte by byte in conv_igemm's epilogue (16 -> 102 with both on 8954 pixels,
+  // 1120 tiles: 12.0 / 19.0; 400 -> 473 with both, 2265: 20.5 / 25.4)
+  return (p.N & 3) != 0 && (p.res || p.y2) && limit < any ? limit + limit / 2 : limit;
+}
+
+int conv_wavek_variant(const ConvParams &p, bool general) {
   const int f = tuning().wavek_variant.load(std::memory_order_relaxed);      // tuning aid: force one tile shape
   if (f >= 0 && f < WK_VARIANTS) return f;
-  if (!must && (tuning().wavek.load(std::memory_order_relaxed) == 0 || tuning().conv_variant.load(std::memory_order_relaxed) >= 0)) return -1;
+  if (tuning().wavek.load(std::memory_order_relaxed) == 0) return -1;
+  if (!general && tuning().conv_variant.load(std::memory_order_relaxed) >= 0) return -1;
   // Measured against each other and against conv_fast on the layers of ResNet-50 and MobileNetV2 at batch 1
   // to 64, where every CU has at most one workgroup (two of the 64 KiB shape):
   //  * up to one 32 x 32 tile per CU: eight waves share K when it is long (7 x 7 3x3 512 -> 512, one image:
@@ -584,12 +615,25 @@ int conv_wavek_variant(const ConvParams &p, bool must) {
   // keeps several tiles per CU in flight, is ahead (3x3 256 -> 256 at batch 32: 15.0 / 13.0).
   auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
   const long long t32 = tiles(32, 32);
+  if (general) {
+    if (t32 > general_limit(p)) return -1;
+    // gathered: 64 x 64 tiles, which halve the gathering, from four to six 32 x 32 tiles per CU on (us, 32 x 32 / 64 x 64: K =
+    // 900 -> 76 channels, 588 of them, 13.3 / 18.9; 612 -> 157, 980, 17.7 / 19.2; 459 -> 49, 1176, 16.8 / 16.3; 162 -> 50,
+    // 1520, 16.3 / 16.1; 558 -> 48, 1914, 28.7 / 21.5), earlier where one 64 x 64 tile per CU is all there is (157 -> 1208,
+    // 874 and 228 tiles: 14.0 / 12.4); where N is one tile wide 32 x 32 (900 -> 23, 1078: 20.9, 64 x 32 27.5), but for
+    // the fourth per CU (729 -> 30, 816: 20.1, 64 x 32 16.9)
+    if (!conv_wavek_direct(p)) {
+      if (t32 <= 256 && p.K >= 1024) return WK_32x32_W8;
+      if (p.N <= 32) return t32 > 768 && t32 <= 1024 ? WK_64x32_W8 : WK_32x32_W4;
+      return t32 <= 768 || (t32 <= (p.K < 256 ? 1536 : 1024) && tiles(64, 64) > 256) ? WK_32x32_W4 : WK_64x64_W8;
+    }
+  }
   if (t32 <= 256) return p.K >= 1024 ? WK_32x32_W8 : WK_32x32_W4;
   if (t32 <= 512 && p.K < 2048) return WK_32x32_W4;
   if (tiles(64, 32) <= 256) return WK_64x32_W8;
-  if (tiles(64, 64) <= 256 && p.K >= 512) return WK_64x64_W8;
-  if (!must) return -1;
-  return p.N <= 32 ? WK_64x32_W8 : WK_64x64_W8;
+  if (tiles(64, 64) <= 256 && (p.K >= 512 || (general && p.N > 32))) return WK_64x64_W8;
+  if (!general) return -1;
+  return p.N <= 32 || (t32 <= 1536 && p.K < 1024) ? WK_32x32_W4 : WK_64x64_W8;
 }
 
 const char *conv_wavek_name(int variant, bool direct) {

@@ -302,11 +302,11 @@ f8_status enqueue_conv(const void *x, const int8_t *w, const int32_t *acc0, cons
   const bool fast = conv_fast_applicable(p);
   const int wk = conv_wavek_variant(p, !fast);
   if (wk >= 0) return launch_conv_wavek(p, wk, false, nullptr, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
-  return launch_conv_fast(p, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
+  return (fast ? launch_conv_fast(p, stream) : launch_conv_igemm(p, false, nullptr, stream)) == 0 ? F8_OK : F8_ERR_DEVICE;
 }
 
 // Which kernel a dense layer takes does not depend on acc0 and the page of zeros, so the layers that
-// conv_wavek takes are known before anything is folded; it forms the start values itself.
+// conv_wavek and conv_igemm take are known before anything is folded; these form the start values themselves.
 static bool takes_own_kernel(const void *x, const int8_t *w, const void *y, const void *res, const Geom &g, const f8_quant &q, void *y2) {
   return use_pw_small(x, w, y, res, g, q, y2) || use_pw_ws(x, w, y, res, g, q, y2) || use_pw_mid(x, w, y, res, g, q, y2, false) ||
          use_conv_ws(x, w, y, res, g, q, y2);
@@ -348,9 +348,10 @@ bool enqueue_conv_folding(const void *x, const int8_t *w, const int32_t *bias, v
   }
   ConvParams p = conv_params(x, w, nullptr, nullptr, y, res, g, q, q2, y2);
   p.near = 1;                           // (only conv_fast reads the page of zeros)
-  const int wk = conv_wavek_variant(p, !conv_fast_applicable(p));
-  if (wk < 0) return false;
-  *st = launch_conv_wavek(p, wk, true, bias, stream) == 0 ? F8_OK : F8_ERR_DEVICE;
+  const bool fast = conv_fast_applicable(p);
+  const int wk = conv_wavek_variant(p, !fast);
+  if (wk < 0 && fast) return false;
+  *st = (wk >= 0 ? launch_conv_wavek(p, wk, true, bias, stream) : launch_conv_igemm(p, true, bias, stream)) == 0 ? F8_OK : F8_ERR_DEVICE;
   return true;
 }
 
@@ -388,7 +389,8 @@ const char *conv_kernel_name(const Geom &g, const f8_quant &q, bool has_res) {
   p.K = g.R * g.S * g.Cin;
   const bool fast = conv_fast_applicable(p);
   const int wk = conv_wavek_variant(p, !fast);
-  return wk >= 0 ? conv_wavek_name(wk, conv_wavek_direct(p)) : conv_fast_variant_name(conv_fast_variant(p));
+  if (wk >= 0) return conv_wavek_name(wk, conv_wavek_direct(p));
+  return fast ? conv_fast_variant_name(conv_fast_variant(p)) : conv_igemm_name(p.N);
 }
 
 f8_status enqueue_fold(const int8_t *w, const int32_t *bias, int32_t *acc0, const Geom &g,

@@ -9,6 +9,7 @@
 
 #include "../../include/f8.h"
 #include "conv_params.h"
+#include "conv_igemm.h"
 #include "conv_wavek.h"
 #include "conv_ws.h"
 #include "pw_ws.h"
@@ -24,7 +25,7 @@ namespace f8 {
 // the C header) and afterwards only through f8_tuning_set; the launch paths read these ints.
 struct Tuning {
   std::atomic<int> conv_variant{-1};   // >= 0: force this tile variant of the LDS-direct dense kernel
-  std::atomic<int> wavek{1};           // K-sharing kernel where it is the faster one (0: only for layers no other kernel takes)
+  std::atomic<int> wavek{1};           // K-sharing kernel where it is the faster one (0: never)
   std::atomic<int> wavek_variant{-1};  // >= 0: force this tile shape of it
   std::atomic<int> conv_ws{1};         // weights-stationary 3x3 kernel
   std::atomic<int> conv_ws_min{768};    // ... from this many 128-pixel (64 channels) or 64-pixel (128 channels) blocks on

@@ -202,6 +202,32 @@ def test_chain_pairs_a_1x1_layer_with_the_layer_in_front_host_side():
     L.f8_chain_destroy(h)
 
 
+def one_layer_kernel(C, N, k, hw, batch, y_type="u8"):
+    """Name of the kernel that a chain of one dense layer launches."""
+    rng = np.random.default_rng(1)
+    _, S, _ = wl.random_conv_case(rng, 1, hw, hw, C, N, k, k, 1, k // 2, "u8", y_type)
+    S.src, S.dst, S.res = 0, 1, -1
+    L, h, buf = f8.lib(), ctypes.c_void_p(), ctypes.create_string_buffer(64)
+    assert L.f8_chain_create(make_descs(wl.Net("one", (hw, hw), C, "u8", S.fl_x, [S])), 1, hw, hw, C, f8.F8_U8, ctypes.byref(h)) == 0
+    assert L.f8_chain_layer_info(h, 0, batch, buf, 64, None, None) == 0
+    L.f8_chain_destroy(h)
+    return buf.value.decode()
+
+
+def test_general_layers_with_many_tiles_do_not_share_k_host_side():
+    """Layers that the LDS-direct kernel does not take (odd channel counts, raw accumulators of them): few tiles or
+    long K go to the waves that share K, many tiles of short K to those that share the tile's area."""
+    assert one_layer_kernel(64, 62, 1, 56, 64) == "conv_igemm<256x64>"
+    assert one_layer_kernel(64, 255, 1, 56, 16, "s32") == "conv_igemm<128x128>"
+    assert one_layer_kernel(24, 30, 1, 56, 64, "s32") == "conv_igemm<256x32>"
+    assert one_layer_kernel(3, 10, 3, 112, 4, "s32") == "conv_igemm<256x16>"
+    assert one_layer_kernel(64, 62, 3, 56, 64) == "conv_igemm<256x64>"
+    for C, N, k, hw, batch, y_type in ((64, 62, 1, 56, 1, "u8"), (2048, 255, 1, 28, 16, "u8"), (401, 255, 1, 56, 64, "s32"),
+                                       (2048, 30, 1, 56, 64, "u8"), (147, 62, 1, 56, 16, "s32")):
+        name = one_layer_kernel(C, N, k, hw, batch, y_type)
+        assert "wavek" in name or "gather" in name, (name, C, N, k, hw, batch)
+
+
 def test_binding_refuses_to_run_without_library(monkeypatch):
     monkeypatch.setattr(f8, "_lib", None)
     monkeypatch.setattr(f8, "LIB_PATH", "/nonexistent/libf8.so")

@@ -128,7 +128,10 @@ struct f8_chain {
   //   512 channels, 7 x 7: batch 16 14.9, 10.6, 7.9 / 7.1 (conv_wavek); 24 15.3, 10.8, 8.2 / 9.7; 64 16.1, 12.0, 16.0 /
   //     22.3; 128 18.5, 23.7, - / 28.0; 256 35.0, -, - / 38.0
   int imgk_waves(const f8_layer_desc &L, const Geom &g, int batch) const {
-    if (imgk >= 10) return imgk - 10 <= conv_imgk_most_waves(L.Cin) ? imgk - 10 : 0;      // tuning aid: force it
+    if (imgk >= 10) {      // tuning aid: force it, with 1, 2 or 4 waves (there is no kernel for other counts)
+      const int wk = imgk - 10;
+      return (wk == 1 || wk == 2 || wk == 4) && wk <= conv_imgk_most_waves(L.Cin) ? wk : 0;
+    }
     const long long most = L.Cin == 256 ? 256 : L.Cin == 128 ? 768 : L.Cin == 64 && L.res < 0 ? 1024 : 0x7fffffffLL;
     if (!conv_imgk_fills(L.Cin, g.H, g.W)) return 0;
     for (int wk = 1; wk <= conv_imgk_most_waves(L.Cin); wk *= 2) {

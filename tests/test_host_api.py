@@ -228,6 +228,19 @@ def test_general_layers_with_many_tiles_do_not_share_k_host_side():
         assert "wavek" in name or "gather" in name, (name, C, N, k, hw, batch)
 
 
+def test_forced_wave_counts_without_a_kernel_take_another_kernel_host_side():
+    """The switch "imgk" forces a number of waves that share K; only 1, 2 and 4 exist (64 channels: 1, 128: up to 2).  Any
+    other value must not pick the image-stationary kernel, whose launch would be refused."""
+    try:
+        for n in range(0, 7):
+            f8.f8_tuning_set("imgk", 10 + n)
+            for C, hw, most in ((64, 56, 1), (128, 28, 2), (256, 14, 4), (512, 7, 4)):
+                forced = n in (1, 2, 4) and n <= most
+                assert one_layer_kernel(C, C, 3, hw, 64).startswith("conv3x3_wavek<") == forced, (n, C)
+    finally:
+        f8.f8_tuning_set("imgk", 1)
+
+
 def test_binding_refuses_to_run_without_library(monkeypatch):
     monkeypatch.setattr(f8, "_lib", None)
     monkeypatch.setattr(f8, "LIB_PATH", "/nonexistent/libf8.so")

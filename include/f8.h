@@ -374,8 +374,8 @@ f8_status f8_mfma_i8_yardstick_operands(int32_t *sink, int iters, uint32_t seed,
  * 0 = never), "wavek_variant" (-1 = automatic; >= 0 forces that tile shape of it), "conv_ws",
  * "conv_ws_min" (768: smallest layer, in blocks of 128 pixels, that takes the weights-stationary 3x3
  * kernel), "pw_ws", "pw_small", "xcd_remap", "pw_wide", "pw_mid" (1: the 1x1 128 -> 512 kernel only
- * together with the 512 -> 128 layer behind it, 2: also alone), "stem_pool", "conv_tail", "conv_img",
- * "imgk" (1 = on; 10 + n: the image-stationary 3x3 kernel with n = 1, 2 or 4 waves sharing K wherever it fits),
+ * together with the 512 -> 128 layer behind it, 2: also alone), "stem_pool", "conv_tail", "conv_img" (1 = the
+ * kernel with one image per workgroup where it is the faster one, 2 = before any other wherever it fits), "imgk" (1 = on; 10 + n: the image-stationary 3x3 kernel with n = 1, 2 or 4 waves sharing K wherever it fits),
  * "dw_pw" (1 = on where it pays; 2: a depthwise layer and the 1x1 layer behind it in one launch wherever
  * they fit), "conv_img_min" (96: fewest images, or bands of 28 image rows, for which a chain takes the
  * image-stationary 3x3 kernels).  The environment variables F8_<NAME IN CAPITALS> give the initial

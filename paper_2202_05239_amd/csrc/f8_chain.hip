@@ -94,7 +94,7 @@ struct f8_chain {
   // 3x3 layers the image-stationary kernel can take: byte offset of their weights in fragment order
   // in the constants region (0: not such a layer).
   std::vector<size_t> img_w_off;       // per layer
-  bool conv_img = true;
+  int conv_img = 1;
   int conv_img_min = 96;
   int imgk = 1;
   // 0: neither, 1: an image (or band) per workgroup, 1 + n: fewer channels per workgroup, n waves share K
@@ -103,10 +103,10 @@ struct f8_chain {
     const f8_layer_desc &L = layers[i];
     const Geom &g = geom[i];
     const int shift = L.q.fl_x + L.q.fl_w - L.q.fl_y;
-    const bool img_ok = conv_img && L.res < 0 &&
+    const bool img_ok = conv_img != 0 && L.res < 0 &&
                         conv_img_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, nullptr, nullptr) &&
                         conv_img_units(L.Cin, batch, g.H) >= conv_img_min;
-    if (img_ok && conv_img_min != 96) return 1;      // tuning aid: a limit of the caller's
+    if (img_ok && conv_img == 2) return 1;           // the caller's choice
     if (imgk != 0 && conv_imgk_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift,
                                           nullptr, nullptr, nullptr)) {
       const int wk = imgk_waves(L, g, batch);
@@ -623,7 +623,7 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
   c->last_tensor = c->layers.back().dst;
   c->tensors[c->last_tensor].external = true;
   c->stem_pool = tuning().stem_pool.load() != 0;
-  c->conv_img = tuning().conv_img.load() != 0;
+  c->conv_img = tuning().conv_img.load();
   c->conv_img_min = tuning().conv_img_min.load();
   c->imgk = tuning().imgk.load();
   // a stem whose only reader is a 3x3 stride-2 pad-1 max pool: both in one kernel

@@ -295,23 +295,28 @@ def test_image_stationary_3x3_256(oracle):
         b.conv("second", a, C, 3, 1, 1, relu=relu2)
         net = b.net
         x = wl.draw_u8(rng, (batch, hw, hw, C)) if x_type == "u8" else wl.draw_s8_normal(rng, (batch, hw, hw, C), 5)
+        f8.f8_tuning_set("conv_img", 2)          # (before the kernel that shares K)
         f8.f8_tuning_set("conv_img_min", 1)      # (also for fewer images than the kernel is normally chosen for)
         try:
             names = [f8.Chain(net).layer_info(i, batch)[0] for i in range(2)]
             assert names == ["conv3x3_img<%dx%d>" % (C, C)] * 2, names
             out = check_network(oracle, x, net, list(range(batch)), "image-stationary 3x3, case %d" % k, lean_is_smaller=False)
         finally:
+            f8.f8_tuning_set("conv_img", 1)
             f8.f8_tuning_set("conv_img_min", 96)
         assert not any(f8.Chain(net).layer_info(i, 1)[0].startswith("conv3x3_img") for i in range(2))
         f8.f8_tuning_set("conv_img", 0)
+        f8.f8_tuning_set("imgk", 0)
         try:
             plain = f8.Chain(net).prepare(batch)
-            assert not any(plain.layer_info(i, batch)[0].startswith("conv3x3_img") for i in range(2))
+            for i in range(2):
+                assert plain.layer_info(i, batch)[0].startswith(("conv_fast", "conv3x3_ws<")), plain.layer_info(i, batch)[0]
             other = plain.run(torch.from_numpy(x).to(DEV))
             torch.cuda.synchronize()
             assert torch.equal(other, out), "general kernel, case %d" % k
         finally:
             f8.f8_tuning_set("conv_img", 1)
+            f8.f8_tuning_set("imgk", 1)
     # the stride-1 3x3 layers of the full-size network's third (five) and second (three) stage
     _, net = wl.config4(batch=1)
     chain = f8.Chain(net)

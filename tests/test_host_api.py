@@ -241,6 +241,24 @@ def test_forced_wave_counts_without_a_kernel_take_another_kernel_host_side():
         f8.f8_tuning_set("imgk", 1)
 
 
+def test_conv_img_limit_is_a_limit_and_no_switch_host_side():
+    """"conv_img_min" says from how many images on the kernel with one image per workgroup is considered; which of two
+    applicable kernels wins does not depend on its value.  "conv_img" = 2 puts that kernel first."""
+    try:
+        for C, hw, batch in ((256, 14, 128), (128, 28, 128)):
+            for limit in (1, 95, 96, 97):
+                f8.f8_tuning_set("conv_img_min", limit)
+                assert one_layer_kernel(C, C, 3, hw, batch) == "conv3x3_wavek<%d>" % C, (C, limit)
+            f8.f8_tuning_set("conv_img", 2)
+            for limit, first in ((1, True), (batch, True), (batch + 1, False)):
+                f8.f8_tuning_set("conv_img_min", limit)
+                assert one_layer_kernel(C, C, 3, hw, batch).startswith("conv3x3_img<") == first, (C, limit)
+            f8.f8_tuning_set("conv_img", 1)
+    finally:
+        f8.f8_tuning_set("conv_img", 1)
+        f8.f8_tuning_set("conv_img_min", 96)
+
+
 def test_binding_refuses_to_run_without_library(monkeypatch):
     monkeypatch.setattr(f8, "_lib", None)
     monkeypatch.setattr(f8, "LIB_PATH", "/nonexistent/libf8.so")

@@ -121,8 +121,9 @@ struct f8_chain {
   // Measured (us; 1, 2, 4 waves / the best other kernel):
   //   64 channels, 56 x 56: batch 16 6.9 / 7.8; 32 9.4 / 9.2; 64 12.5 / 14.5; 128 22.3 / 22.6 (conv_ws; with two halves of
   //     128 side by side, as ResNet-50 runs at batch 256, conv_ws is ahead by 10 us a layer); with a residual: batch 32 9.9 / 12.2; 64 13.5 / 18.9; 256 41.5 / 65.0
-  //   128 channels, 28 x 28: batch 16 8.9, 8.2 / 8.7; 32 9.4, 8.7 / 10.7; 64 10.4, - / 16.7; 128 17.7, - / 23.0;
-  //     192 24.2, - / 28.5; 256 30.7, - / 32.4 (conv_img, held to by the tests)
+  //   128 channels, 28 x 28: batch 16 8.9, 8.2 / 8.7; 32 9.4, 8.7 / 10.7; 64 10.4, - / 16.7; 128 16.5, - / 21.5;
+  //     192 22.9, - / 26.8; 224 27.1, - / 28.0; 256 29.0, - / 29.9; 288 33.5, - / 38.5; 512 53.0, - / 57.1; 1024 100, - / 108 (conv_img,
+  //     conv_ws at 288); with a residual 256 31.7, - / 45.3; 768 84.0, - / 110.6; 20 x 20, batch 512: 29.2, - / 36.9
   //   256 channels, 14 x 14: batch 16 12.6, 10.3, 8.1 / 7.2 (conv_wavek); 24 12.9, 10.4, 8.4 / 12.7; 32 12.8, 10.6,
   //     8.6 / 13.0; 64 13.7, 12.1, 16.7 / 16.6; 128 16.4, 23.7, - / 22.4; 192 25.3, -, - / 24.8 (conv_img)
   //   512 channels, 7 x 7: batch 16 14.9, 10.6, 7.9 / 7.1 (conv_wavek); 24 15.3, 10.8, 8.2 / 9.7; 64 16.1, 12.0, 16.0 /
@@ -132,7 +133,7 @@ struct f8_chain {
       const int wk = imgk - 10;
       return (wk == 1 || wk == 2 || wk == 4) && wk <= conv_imgk_most_waves(L.Cin) ? wk : 0;
     }
-    const long long most = L.Cin == 256 ? 256 : L.Cin == 128 ? 768 : L.Cin == 64 && L.res < 0 ? 1024 : 0x7fffffffLL;
+    const long long most = L.Cin == 256 ? 256 : L.Cin == 64 && L.res < 0 ? 1024 : 0x7fffffffLL;
     if (!conv_imgk_fills(L.Cin, g.H, g.W)) return 0;
     for (int wk = 1; wk <= conv_imgk_most_waves(L.Cin); wk *= 2) {
       const long long wgs = conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk);

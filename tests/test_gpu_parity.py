@@ -267,13 +267,15 @@ def test_weights_stationary_3x3_64(oracle):
     chain = f8.Chain(net)
     assert [chain.layer_info(i, 256)[0] for i in range(len(net.layers))].count("conv3x3_ws<64x64>") == 3
     assert [chain.layer_info(i, 2)[0] for i in range(len(net.layers))].count("conv3x3_ws<64x64>") == 0
-    # (in a chain the 128-channel layers go to the image-stationary kernel unless that is switched off)
+    # (in a chain the 128-channel layers go to the image-stationary kernels unless these are switched off)
     f8.f8_tuning_set("conv_img", 0)
+    f8.f8_tuning_set("imgk", 0)
     try:
         chain = f8.Chain(net)
         assert [chain.layer_info(i, 256)[0] for i in range(len(net.layers))].count("conv3x3_ws<128x128>") == 3
     finally:
         f8.f8_tuning_set("conv_img", 1)
+        f8.f8_tuning_set("imgk", 1)
 
 
 def test_image_stationary_3x3_256(oracle):
@@ -317,11 +319,16 @@ def test_image_stationary_3x3_256(oracle):
         finally:
             f8.f8_tuning_set("conv_img", 1)
             f8.f8_tuning_set("imgk", 1)
-    # the stride-1 3x3 layers of the full-size network's third (five) and second (three) stage
+    # the stride-1 3x3 layers of the full-size network's third (five) and, where the kernel is put first, second (three) stage
     _, net = wl.config4(batch=1)
     chain = f8.Chain(net)
     assert [chain.layer_info(i, 256)[0] for i in range(len(net.layers))].count("conv3x3_img<256x256>") == 5
-    assert [chain.layer_info(i, 256)[0] for i in range(len(net.layers))].count("conv3x3_img<128x128>") == 3
+    f8.f8_tuning_set("conv_img", 2)
+    try:
+        first = f8.Chain(net)
+        assert [first.layer_info(i, 256)[0] for i in range(len(net.layers))].count("conv3x3_img<128x128>") == 3
+    finally:
+        f8.f8_tuning_set("conv_img", 1)
     assert not any(chain.layer_info(i, 32)[0].startswith("conv3x3_img") for i in range(len(net.layers)))
 
 

@@ -241,6 +241,12 @@ def test_forced_wave_counts_without_a_kernel_take_another_kernel_host_side():
         f8.f8_tuning_set("imgk", 1)
 
 
+def test_128_channel_layers_keep_the_image_stationary_kernel_at_any_batch_host_side():
+    for hw in (20, 24, 28):
+        for batch in (128, 192, 256, 300, 1024):
+            assert one_layer_kernel(128, 128, 3, hw, batch) == "conv3x3_wavek<128>", (hw, batch)
+
+
 def test_conv_img_limit_is_a_limit_and_no_switch_host_side():
     """"conv_img_min" says from how many images on the kernel with one image per workgroup is considered; which of two
     applicable kernels wins does not depend on its value.  "conv_img" = 2 puts that kernel first."""

@@ -638,8 +638,8 @@ int conv_wavek_variant(const ConvParams &p, bool general) {
 
 const char *conv_wavek_name(int variant, bool direct) {
   static const char *const names[2][WK_VARIANTS] = {
-      {"conv_gather<32x32,w8>", "conv_gather<32x32,w4>", "conv_gather<64x32,w4>", "conv_gather<64x64,w4>"},
-      {"conv_fast_wavek<32x32,w8>", "conv_fast_wavek<32x32,w4>", "conv_fast_wavek<64x32,w8>", "conv_fast_wavek<64x64,w8>"}};
+      {"conv_wavek_gather<32x32,w8>", "conv_wavek_gather<32x32,w4>", "conv_wavek_gather<64x32,w4>", "conv_wavek_gather<64x64,w4>"},
+      {"conv_wavek<32x32,w8>", "conv_wavek<32x32,w4>", "conv_wavek<64x32,w8>", "conv_wavek<64x64,w8>"}};
   return variant >= 0 && variant < WK_VARIANTS ? names[direct][variant] : "?";
 }
 

@@ -364,8 +364,12 @@ bool conv_tail_ok(const Geom &g, const f8_quant &q, int Cout2) {
   return (Cout2 == 64 || Cout2 == 128) && use_pw_ws(nullptr, nullptr, nullptr, nullptr, g, q, nullptr);
 }
 
-const char *conv_kernel_name(const Geom &g, const f8_quant &q, bool has_res) {
-  if (use_pw_small(nullptr, nullptr, nullptr, has_res ? &g : nullptr, g, q, nullptr)) {
+const char *conv_kernel_name(const Geom &g, const f8_quant &q, bool has_res, const f8_requant2 *q2) {
+  alignas(16) static const char stand_in[16] = {};      // for a residual or second output, 16-byte aligned
+  const void *res = has_res ? stand_in : nullptr;
+  const bool res8 = !(has_res && q.res_type == F8_S32);
+  void *y2 = q2 ? const_cast<char *>(stand_in) : nullptr;
+  if (use_pw_small(nullptr, nullptr, nullptr, res, g, q, y2)) {
     if (g.Cout == 16) return "pw1x1_small<32x16>";
     if (g.Cout == 64) return "pw1x1_small<32x64>";
     static const char *const names[3][3] = {{"pw1x1_small<16x96>", "pw1x1_small<16x144>", "pw1x1_small<16x192>"},
@@ -373,14 +377,14 @@ const char *conv_kernel_name(const Geom &g, const f8_quant &q, bool has_res) {
                                             {"pw1x1_small<32x96>", "pw1x1_small<32x144>", "pw1x1_small<32x192>"}};
     return names[g.Cin == 16 ? 0 : (g.Cin == 24 ? 1 : 2)][g.Cout == 96 ? 0 : (g.Cout == 144 ? 1 : 2)];
   }
-  if (!(has_res && q.res_type == F8_S32) && use_pw_ws(nullptr, nullptr, nullptr, nullptr, g, q, nullptr)) return "pw1x1_ws<64x256>";
-  if (!(has_res && q.res_type == F8_S32) && use_pw_mid(nullptr, nullptr, nullptr, nullptr, g, q, nullptr, false)) return "pw1x1_mid<128x512>";
-  if (!(has_res && q.res_type == F8_S32) && use_pw_wide(nullptr, nullptr, nullptr, nullptr, g, q, nullptr, nullptr))
+  if (res8 && use_pw_ws(nullptr, nullptr, nullptr, nullptr, g, q, y2)) return "pw1x1_ws<64x256>";
+  if (res8 && use_pw_mid(nullptr, nullptr, nullptr, nullptr, g, q, y2, false)) return "pw1x1_mid<128x512>";
+  if (res8 && use_pw_wide(nullptr, nullptr, nullptr, nullptr, g, q, q2, y2))
     return g.Cin == 256 ? "pw1x1_wide<256>" : "pw1x1_wide<512>";
-  if (use_conv_ws(nullptr, nullptr, nullptr, has_res ? &g : nullptr, g, q, nullptr)) return g.Cin == 64 ? "conv3x3_ws<64x64>" : "conv3x3_ws<128x128>";
+  if (use_conv_ws(nullptr, nullptr, nullptr, res, g, q, y2)) return g.Cin == 64 ? "conv3x3_ws<64x64>" : "conv3x3_ws<128x128>";
   ConvParams p;
-  p.x = nullptr; p.w = nullptr; p.y = nullptr; p.res = has_res ? &p : nullptr;   // aligned stand-ins
-  p.y2 = nullptr; p.shift2 = 0;
+  p.x = nullptr; p.w = nullptr; p.y = nullptr; p.res = res;
+  p.y2 = y2; p.shift2 = q2 ? q.fl_x + q.fl_w - q2->fl_y : 0;
   p.near = 1;
   p.C = g.Cin; p.N = g.Cout; p.y_type = q.y_type; p.res_type = q.res_type;
   p.H = g.H; p.W = g.W; p.R = g.R; p.S = g.S; p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw;

@@ -986,9 +986,9 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       gk.B = batch;
       gk.P = g.P; gk.Q = g.Q;
       const int img = c->img_role((size_t)layer, batch);
-      if (img > 1) name = L.Cin == 64 ? "conv3x3_wavek<64>" : L.Cin == 128 ? "conv3x3_wavek<128>" : L.Cin == 256 ? "conv3x3_wavek<256>" : "conv3x3_wavek<512>";
+      if (img > 1) name = L.Cin == 64 ? "conv3x3_imgk<64>" : L.Cin == 128 ? "conv3x3_imgk<128>" : L.Cin == 256 ? "conv3x3_imgk<256>" : "conv3x3_imgk<512>";
       else if (img == 1) name = L.Cin == 256 ? "conv3x3_img<256x256>" : "conv3x3_img<128x128>";
-      else name = conv_kernel_name(gk, L.q, L.res >= 0);
+      else name = conv_kernel_name(gk, L.q, L.res >= 0, L.dst2 > 0 ? &L.q2 : nullptr);
       ops = 2.0 * M * g.R * g.S * g.Cin * g.Cout;
       bytes += (double)g.R * g.S * g.Cin * g.Cout + 4.0 * g.Cout;
       if (with_tail) {

@@ -98,7 +98,7 @@ f8_status check_requant2(const f8_quant &q, const f8_requant2 *q2);
 // input channels, which also reads rows of 24 channels: the chain then skips its zero-padded copy.
 bool conv_reads_narrow_rows(const Geom &g, const f8_quant &q, bool has_res);
 // Name of the kernel enqueue_conv launches for this layer (operands assumed 16-byte aligned).
-const char *conv_kernel_name(const Geom &g, const f8_quant &q, bool has_res);
+const char *conv_kernel_name(const Geom &g, const f8_quant &q, bool has_res, const f8_requant2 *q2);
 // Enqueue the fold of (w, bias, rounding addend, sign correction) into acc0.
 f8_status enqueue_fold(const int8_t *w, const int32_t *bias, int32_t *acc0, const Geom &g,
                        const f8_quant &q, hipStream_t stream);

@@ -46,7 +46,7 @@ def test_image_stationary_3x3_with_shared_k(oracle, wk):
         f8.f8_tuning_set("imgk", 10 + wk)
         try:
             chain = f8.Chain(net, keep_all=True).prepare(B)
-            assert [chain.layer_info(i, B)[0] for i in range(2)] == ["conv3x3_wavek<%d>" % C] * 2
+            assert [chain.layer_info(i, B)[0] for i in range(2)] == ["conv3x3_imgk<%d>" % C] * 2
             out = chain.run(torch.from_numpy(x).cuda())
             torch.cuda.synchronize()
         finally:
@@ -65,11 +65,11 @@ def test_waves_sharing_k_follow_the_batch():
     chain = f8.Chain(net)
 
     def count(batch):
-        return sum(chain.layer_info(i, batch)[0].startswith("conv3x3_wavek<") for i in range(len(net.layers)))
+        return sum(chain.layer_info(i, batch)[0].startswith("conv3x3_imgk<") for i in range(len(net.layers)))
 
     assert count(1) == 0 and count(64) == 13 and count(128) == 11
     _, small = wl.config3(batch=1, hw=32)
-    assert not any(f8.Chain(small).layer_info(i, 300)[0] == "conv3x3_wavek<64>" for i in range(len(small.layers)))
+    assert not any(f8.Chain(small).layer_info(i, 300)[0] == "conv3x3_imgk<64>" for i in range(len(small.layers)))
 
 
 @pytest.mark.parametrize("case", [(16, 56, 56, "u8", "u8", None), (23, 28, 31, "s8", "s8", "u8"), (13, 61, 62, "u8", "u8", "s8")])

@@ -306,13 +306,13 @@ def test_image_stationary_3x3_256(oracle):
         finally:
             f8.f8_tuning_set("conv_img", 1)
             f8.f8_tuning_set("conv_img_min", 96)
-        assert not any(f8.Chain(net).layer_info(i, 1)[0].startswith("conv3x3_img") for i in range(2))
+        assert not any(f8.Chain(net).layer_info(i, 1)[0].startswith("conv3x3_img<") for i in range(2))
         f8.f8_tuning_set("conv_img", 0)
         f8.f8_tuning_set("imgk", 0)
         try:
             plain = f8.Chain(net).prepare(batch)
             for i in range(2):
-                assert plain.layer_info(i, batch)[0].startswith(("conv_fast", "conv3x3_ws<")), plain.layer_info(i, batch)[0]
+                assert plain.layer_info(i, batch)[0].startswith(("conv_fast<", "conv_wavek<", "conv3x3_ws<")), plain.layer_info(i, batch)[0]
             other = plain.run(torch.from_numpy(x).to(DEV))
             torch.cuda.synchronize()
             assert torch.equal(other, out), "general kernel, case %d" % k
@@ -329,7 +329,7 @@ def test_image_stationary_3x3_256(oracle):
         assert [first.layer_info(i, 256)[0] for i in range(len(net.layers))].count("conv3x3_img<128x128>") == 3
     finally:
         f8.f8_tuning_set("conv_img", 1)
-    assert not any(chain.layer_info(i, 32)[0].startswith("conv3x3_img") for i in range(len(net.layers)))
+    assert not any(chain.layer_info(i, 32)[0].startswith("conv3x3_img<") for i in range(len(net.layers)))
 
 
 def test_weights_stationary_1x1_64_to_256(oracle):
@@ -922,7 +922,8 @@ def test_chain_channel_padding(oracle):
     for L in net.layers[:-1]:
         assert_same(chain.tensor(L.dst).cpu().numpy(), want[L.dst], "padded chain " + L.name)
     assert_same(out.cpu().numpy(), want[net.layers[-1].dst], "padded chain output")
-    assert "conv_fast" in chain.layer_info(0, B)[0] and "conv_fast" in chain.layer_info(2, B)[0]
+    # the padded layers run in 16-byte units, gathered by no one
+    assert all(chain.layer_info(i, B)[0].startswith(("conv_fast<", "conv_wavek<")) for i in (0, 2)), [chain.layer_info(i, B)[0] for i in (0, 2)]
     t = {0: x}
     for L in net.layers:
         t[L.dst] = gpu_layer(L, t[L.src])

@@ -106,9 +106,9 @@ def test_k_sharing_kernel_is_chosen_by_size():
         L.src, L.dst, L.res = 0, 1, -1
         return f8.Chain(wl.Net("one", (hw, hw), C, "u8", L.fl_x, [L])).layer_info(0, batch)[0]
 
-    assert name(512, 512, 3, 7, 1) == "conv_fast_wavek<32x32,w8>"
-    assert name(512, 128, 1, 28, 1) == "conv_fast_wavek<32x32,w4>"
-    assert name(512, 512, 3, 7, 16) == "conv_fast_wavek<64x32,w8>"
-    assert name(256, 256, 3, 14, 16) == "conv_fast_wavek<64x64,w8>"
+    assert name(512, 512, 3, 7, 1) == "conv_wavek<32x32,w8>"
+    assert name(512, 128, 1, 28, 1) == "conv_wavek<32x32,w4>"
+    assert name(512, 512, 3, 7, 16) == "conv_wavek<64x32,w8>"
+    assert name(256, 256, 3, 14, 16) == "conv_wavek<64x64,w8>"
     assert name(2048, 512, 1, 7, 256).startswith("conv_fast<")
-    assert name(301, 10, 1, 14, 256, "s32").startswith("conv_gather<")
+    assert name(301, 10, 1, 14, 256, "s32").startswith("conv_wavek_gather<")

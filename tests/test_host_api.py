@@ -225,7 +225,7 @@ def test_general_layers_with_many_tiles_do_not_share_k_host_side():
     for C, N, k, hw, batch, y_type in ((64, 62, 1, 56, 1, "u8"), (2048, 255, 1, 28, 16, "u8"), (401, 255, 1, 56, 64, "s32"),
                                        (2048, 30, 1, 56, 64, "u8"), (147, 62, 1, 56, 16, "s32")):
         name = one_layer_kernel(C, N, k, hw, batch, y_type)
-        assert "wavek" in name or "gather" in name, (name, C, N, k, hw, batch)
+        assert name.startswith("conv_wavek"), (name, C, N, k, hw, batch)
 
 
 def test_forced_wave_counts_without_a_kernel_take_another_kernel_host_side():
@@ -236,15 +236,34 @@ def test_forced_wave_counts_without_a_kernel_take_another_kernel_host_side():
             f8.f8_tuning_set("imgk", 10 + n)
             for C, hw, most in ((64, 56, 1), (128, 28, 2), (256, 14, 4), (512, 7, 4)):
                 forced = n in (1, 2, 4) and n <= most
-                assert one_layer_kernel(C, C, 3, hw, 64).startswith("conv3x3_wavek<") == forced, (n, C)
+                assert one_layer_kernel(C, C, 3, hw, 64).startswith("conv3x3_imgk<") == forced, (n, C)
     finally:
         f8.f8_tuning_set("imgk", 1)
+
+
+def test_reported_names_are_those_of_the_kernels_that_run_host_side():
+    """Every kernel is reported under its own name, and a layer with two output formats never under that of a kernel that
+    writes one."""
+    assert one_layer_kernel(512, 512, 3, 7, 64).startswith("conv3x3_imgk<")
+    assert one_layer_kernel(512, 512, 3, 7, 1).startswith("conv_wavek<")
+    assert one_layer_kernel(301, 10, 1, 14, 256, "s32").startswith("conv_wavek_gather<")
+    L, h, buf = f8.lib(), ctypes.c_void_p(), ctypes.create_string_buffer(64)
+    _, net = wl.resnet50_private_fl(batch=1)
+    assert L.f8_chain_create(make_descs(net), len(net.layers), 224, 224, 3, f8.F8_S8, ctypes.byref(h)) == 0
+    dual = {}
+    for i, S in enumerate(net.layers):
+        if S.dst2 > 0:
+            assert L.f8_chain_layer_info(h, i, 256, buf, 64, None, None) == 0
+            dual[S.name] = buf.value.decode()
+    L.f8_chain_destroy(h)
+    assert len(dual) > 8 and any(n.startswith("pw1x1_wide<") for n in dual.values())
+    assert all(n.startswith(("pw1x1_wide<", "conv_fast<", "conv_wavek<")) for n in dual.values()), dual
 
 
 def test_128_channel_layers_keep_the_image_stationary_kernel_at_any_batch_host_side():
     for hw in (20, 24, 28):
         for batch in (128, 192, 256, 300, 1024):
-            assert one_layer_kernel(128, 128, 3, hw, batch) == "conv3x3_wavek<128>", (hw, batch)
+            assert one_layer_kernel(128, 128, 3, hw, batch) == "conv3x3_imgk<128>", (hw, batch)
 
 
 def test_conv_img_limit_is_a_limit_and_no_switch_host_side():
@@ -254,7 +273,7 @@ def test_conv_img_limit_is_a_limit_and_no_switch_host_side():
         for C, hw, batch in ((256, 14, 128), (128, 28, 128)):
             for limit in (1, 95, 96, 97):
                 f8.f8_tuning_set("conv_img_min", limit)
-                assert one_layer_kernel(C, C, 3, hw, batch) == "conv3x3_wavek<%d>" % C, (C, limit)
+                assert one_layer_kernel(C, C, 3, hw, batch) == "conv3x3_imgk<%d>" % C, (C, limit)
             f8.f8_tuning_set("conv_img", 2)
             for limit, first in ((1, True), (batch, True), (batch + 1, False)):
                 f8.f8_tuning_set("conv_img_min", limit)

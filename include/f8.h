@@ -205,7 +205,8 @@ typedef struct f8_chain f8_chain;
  * tensors share memory.  in_type is the type of tensor 0 (F8_U8 / F8_S8). */
 f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, int in_w,
                           int in_c, int in_type, f8_chain **out);
-/* Bytes of device workspace needed for `batch` images (activations + folded constants). */
+/* Bytes of device workspace needed for `batch` images: activations, folded constants, and the re-ordered copies of weights
+ * that the kernels chosen for this batch read. */
 f8_status f8_chain_workspace_bytes(const f8_chain *c, int batch, size_t *bytes);
 /* Writes the folded per-channel constants into the workspace; once per workspace and
  * batch size, before f8_chain_run. */

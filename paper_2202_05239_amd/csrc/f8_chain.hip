@@ -91,15 +91,15 @@ struct f8_chain {
   // tensors are still written).  Whether the kernel that can do this is chosen depends on the batch.
   std::vector<int> tail, tail_peer;    // per layer
   bool conv_tail = true;
-  // 3x3 layers the image-stationary kernel can take: byte offset of their weights in fragment order
-  // in the constants region (0: not such a layer).
-  std::vector<size_t> img_w_off;       // per layer
+  // 3x3 layers the image-stationary kernels can take: bytes of their weights in fragment order (0: not such a
+  // layer).
+  std::vector<size_t> img_w_bytes;     // per layer
   int conv_img = 1;
   int conv_img_min = 96;
   int imgk = 1;
   // 0: neither, 1: an image (or band) per workgroup, 1 + n: fewer channels per workgroup, n waves share K
   int img_role(size_t i, int batch) const {
-    if (img_w_off[i] == 0 || (use_fusion() && fused[i].role != 0)) return 0;
+    if (img_w_bytes[i] == 0 || (use_fusion() && fused[i].role != 0)) return 0;
     const f8_layer_desc &L = layers[i];
     const Geom &g = geom[i];
     const int shift = L.q.fl_x + L.q.fl_w - L.q.fl_y;
@@ -142,10 +142,10 @@ struct f8_chain {
     return 0;
   }
   // A depthwise 3x3 layer and the 1x1 layer that is its only reader in one launch: dwp[i] = 1 for the depthwise one,
-  // 2 for the other; dwp_w_off: the 1x1 layer's weights in fragment order.  Whether the pair runs as one
+  // 2 for the other; dwp_w_bytes: of the 1x1 layer's weights in fragment order.  Whether the pair runs as one
   // launch depends on the batch.
   std::vector<int> dwp;                // per layer
-  std::vector<size_t> dwp_w_off;       // per layer (of the depthwise one)
+  std::vector<size_t> dwp_w_bytes;     // per layer (of the depthwise one)
   int dw_pw = 1;
   int dwp_role(size_t i, int batch) const {
     if (dw_pw == 0 || keep_all || dwp[i] == 0) return 0;
@@ -167,6 +167,26 @@ struct f8_chain {
     const long long total = (long long)batch * g.P * g.Q * g.Cin;
     const long long most = g.Q > 64 ? 2ll << 20 : g.Q > 28 ? 5ll << 19 : g.Q > 14 ? 9ll << 19 : g.Q > 7 ? 7ll << 20 : 2ll << 20;
     return total <= most && dw_pw_slices(g.Cin, layers[i + 1].Cout) <= 20;
+  }
+  // Copies of weights in fragment order (img_w_bytes, dwp_w_bytes) lie behind the arena and only where this batch, or
+  // either half of it on two streams, takes their kernel: ResNet-18 at one image needs 0.7 MB of workspace, with every
+  // copy 10 MB.  frag_off: byte offset of layer i's copy in the workspace, 0 for none.  Returns the copies' bytes; off
+  // (one entry per layer) may be null.
+  std::vector<size_t> frag_off;        // per layer, as of the last f8_chain_prepare
+  size_t place_fragments(int batch, size_t *off) const {
+    const size_t base = const_bytes + arena_per_image * (size_t)batch;
+    size_t bytes = 0;
+    for (size_t i = 0; i < layers.size(); ++i) {
+      bool img = false, pair = false;
+      for (int b : {batch, batch / 2, batch - batch / 2}) {
+        if (b < 1) continue;
+        img = img || img_role(i, b) != 0;
+        pair = pair || dwp_role(i, b) == 1;
+      }
+      if (off) off[i] = img || pair ? base + bytes : 0;
+      if (img || pair) bytes += round256(img ? img_w_bytes[i] : dwp_w_bytes[i]);
+    }
+    return bytes;
   }
   bool tail_in_fused_block(size_t i) const {
     const size_t a = tail[i] == 1 ? i : (size_t)tail_peer[i], b = tail[i] == 1 ? (size_t)tail_peer[i] : i;
@@ -393,12 +413,12 @@ struct f8_chain {
       void *yd = tensor_ptr(T.dst, x, out, workspace, batch);
       const void *rs = T.res >= 0 ? tensor_ptr(T.res, x, out, workspace, batch) : nullptr;
       const int d_shift = L.q.fl_x + L.q.fl_w - L.q.fl_y, t_shift = T.q.fl_x + T.q.fl_w - T.q.fl_y;
-      if (dw_pw_applicable(L.Cin, T.Cout, g.Q, d_shift, t_shift, xs, L.w, yd, rs)) {
+      if (frag_off[i] != 0 && dw_pw_applicable(L.Cin, T.Cout, g.Q, d_shift, t_shift, xs, L.w, yd, rs)) {
         DwPwParams dp;
         dp.x = static_cast<const uint8_t *>(xs);
         dp.wd = L.w;
         dp.bias = L.bias;
-        dp.wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + dwp_w_off[i]);
+        dp.wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + frag_off[i]);
         dp.acc0 = reinterpret_cast<const int32_t *>(static_cast<uint8_t *>(workspace) + acc0_off[i + 1]);
         dp.y = static_cast<uint8_t *>(yd);
         dp.res = static_cast<const uint8_t *>(rs);
@@ -425,9 +445,9 @@ struct f8_chain {
     switch (L.op) {
       case F8_OP_CONV: {
         const int32_t *acc0 = reinterpret_cast<const int32_t *>(static_cast<uint8_t *>(workspace) + acc0_off[i]);
-        const int img = img_role(i, batch);
+        const int img = frag_off[i] != 0 ? img_role(i, batch) : 0;
         const int shift = L.q.fl_x + L.q.fl_w - L.q.fl_y;
-        const int8_t *wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + img_w_off[i]);
+        const int8_t *wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + frag_off[i]);
         if (img > 1 && conv_imgk_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, src, dst, res)) {
           ConvImgkParams ip;
           ip.x = static_cast<const uint8_t *>(src);
@@ -601,24 +621,23 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
         c->const_bytes += round256((size_t)L.Cout * g.R * g.S * sm.Cp);
       }
     }
-    size_t img_off = 0;
+    size_t img_bytes = 0;
     if (L.op == F8_OP_CONV && !sm.on && L.dst2 <= 0 && L.q.y_type != F8_S32 && !(L.res >= 0 && L.q.res_type == F8_S32) &&
         (reinterpret_cast<uintptr_t>(L.w) & 15) == 0) {
       const int shift = L.q.fl_x + L.q.fl_w - L.q.fl_y;
       if (conv_imgk_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, nullptr, nullptr, nullptr) ||
           (L.res < 0 &&
-           conv_img_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, nullptr, nullptr))) {
-        img_off = c->const_bytes;
-        c->const_bytes += round256(conv_img_weight_bytes(L.Cin));
-      }
+           conv_img_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, shift, nullptr, nullptr)))
+        img_bytes = conv_img_weight_bytes(L.Cin);
     }
-    c->img_w_off.push_back(img_off);
+    c->img_w_bytes.push_back(img_bytes);
     c->stem.push_back(sm);
     c->fused.push_back(Fused());
     c->tail.push_back(0);
     c->tail_peer.push_back(-1);
     c->dwp.push_back(0);
-    c->dwp_w_off.push_back(0);
+    c->dwp_w_bytes.push_back(0);
+    c->frag_off.push_back(0);
   }
   if (st != F8_OK) { delete c; return st; }
   c->last_tensor = c->layers.back().dst;
@@ -687,8 +706,7 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     if (!dw_pw_applicable(L.Cin, T.Cout, g.Q, L.q.fl_x + L.q.fl_w - L.q.fl_y, T.q.fl_x + T.q.fl_w - T.q.fl_y, nullptr, L.w, nullptr, nullptr)) continue;
     c->dwp[i] = 1;
     c->dwp[i + 1] = 2;
-    c->dwp_w_off[i] = c->const_bytes;
-    c->const_bytes += round256(dw_pw_weight_bytes(L.Cin, T.Cout));
+    c->dwp_w_bytes[i] = dw_pw_weight_bytes(L.Cin, T.Cout);
   }
   // inverted-residual blocks that can run as one kernel
   for (size_t i = 0; i + 2 < c->layers.size(); ++i) {
@@ -755,7 +773,7 @@ f8_status f8_chain_workspace_bytes(const f8_chain *cc, int batch, size_t *bytes)
       return F8_ERR_UNSUPPORTED;
   for (const Stem &sm : c->stem)
     if (sm.on && (long long)sm.x_bytes_per_image * batch > 0x7fffffffLL) return F8_ERR_UNSUPPORTED;
-  *bytes = c->const_bytes + c->arena_per_image * (size_t)batch + 256;
+  *bytes = c->const_bytes + c->arena_per_image * (size_t)batch + c->place_fragments(batch, nullptr) + 256;
   return F8_OK;
 }
 
@@ -765,6 +783,8 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
   if (reinterpret_cast<uintptr_t>(workspace) & 255) return F8_ERR_ALIGN;
   if (!c->planned) c->plan();
   hipStream_t s = static_cast<hipStream_t>(stream);
+  c->prepared_ws = nullptr;
+  c->place_fragments(batch, c->frag_off.data());
   if (hipMemsetAsync(workspace, 0, 256, s) != hipSuccess) return F8_ERR_DEVICE;
   for (size_t i = 0; i < c->layers.size(); ++i) {
     const f8_layer_desc &L = c->layers[i];
@@ -779,10 +799,11 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
     int32_t *acc0 = reinterpret_cast<int32_t *>(static_cast<uint8_t *>(workspace) + c->acc0_off[i]);
     const f8_status st = enqueue_fold(c->conv_weights(i, workspace), L.bias, acc0, c->conv_geom(i, 1), L.q, s);
     if (st != F8_OK) return st;
-    if (c->dwp[i] == 2 && launch_dw_pw_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->dwp_w_off[i - 1]), L.Cin, L.Cout, s) != 0)
+    if (c->dwp[i] == 2 && c->frag_off[i - 1] != 0 &&
+        launch_dw_pw_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->frag_off[i - 1]), L.Cin, L.Cout, s) != 0)
       return F8_ERR_DEVICE;
-    if (c->img_w_off[i] != 0 &&
-        launch_conv_img_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->img_w_off[i]), L.Cin, s) != 0)
+    if (c->frag_off[i] != 0 &&
+        launch_conv_img_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->frag_off[i]), L.Cin, s) != 0)
       return F8_ERR_DEVICE;
   }
   for (size_t i = 0; i < c->layers.size(); ++i) {

@@ -241,6 +241,42 @@ def test_forced_wave_counts_without_a_kernel_take_another_kernel_host_side():
         f8.f8_tuning_set("imgk", 1)
 
 
+def test_workspace_holds_weight_copies_only_for_kernels_the_batch_takes_host_side():
+    """Copies of weights in fragment order (3x3 layers, the 1x1 layers behind depthwise ones) are kept where the batch, or a
+    half of it on two streams, takes the kernel that reads them, and nowhere else."""
+    L = f8.lib()
+    for fn, small, large, mark in ((wl.config3, 1, 64, "conv3x3_im"), (wl.mobilenet_v2_forward, 256, 27, "+1x1")):
+        _, net = fn(batch=1)
+        h, n, buf = ctypes.c_void_p(), ctypes.c_size_t(), ctypes.create_string_buffer(64)
+        assert L.f8_chain_create(make_descs(net), len(net.layers), 224, 224, 3, f8.F8_S8, ctypes.byref(h)) == 0
+
+        def size(batch):
+            assert L.f8_chain_workspace_bytes(h, batch, ctypes.byref(n)) == 0
+            return n.value
+
+        def copies(batch):
+            total = 0
+            for i, S in enumerate(net.layers):
+                taken = False
+                for b in {batch, batch // 2, batch - batch // 2} - {0}:
+                    assert L.f8_chain_layer_info(h, i, b, buf, 64, None, None) == 0
+                    taken = taken or mark in buf.value.decode()
+                if taken:
+                    T = S if S.op == "conv" else net.layers[i + 1]
+                    total += (T.Cout + 31) // 32 * 32 * T.R * T.S * ((T.Cin + 31) // 32 * 32)
+            return total
+
+        # what does not depend on the batch, and what one image adds, from two batches without copies
+        a, b = (2, 3) if small == 1 else (1000, 1001)
+        assert copies(a) == copies(b) == 0 and copies(small) < 20000 and copies(large) > 100000
+        image = size(b) - size(a)
+        fixed = size(a) - a * image
+        assert fixed < 1 << 20 if small == 1 else fixed < 2 << 20
+        for batch in (small, large, 2 * large, 2 * large + 1):
+            assert size(batch) == fixed + batch * image + copies(batch), batch
+        L.f8_chain_destroy(h)
+
+
 def test_reported_names_are_those_of_the_kernels_that_run_host_side():
     """Every kernel is reported under its own name, and a layer with two output formats never under that of a kernel that
     writes one."""

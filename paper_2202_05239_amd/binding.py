@@ -176,10 +176,15 @@ def _check(rc, where):
         raise F8Error(rc, where)
 
 
+# The current stream's handle itself: a Stream object around it costs 2.6 us, as much as the launch of a small
+# layer (a 256 x 64 x 64 GEMM call 8.3 us with the object, 5.9 us without).  A torch without this function gets the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the current stream's handle itself: a Stream object around it costs 2.6 us, as much as the launch of a small
-    # layer (a 256 x 64 x 64 GEMM call 8.3 us with the object, 5.9 us without)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 def _ptr(t):

@@ -327,6 +327,20 @@ def test_binding_refuses_to_run_without_library(monkeypatch):
         f8.lib()
 
 
+def test_stream_handle_without_the_raw_getter(monkeypatch):
+    """The handle of the current stream comes from a torch internal; without it the public object serves."""
+    import importlib.util
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=0x1230))
+    spec = importlib.util.spec_from_file_location("paper_2202_05239_amd.binding_again", f8.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._stream().value == 0x1230
+
+
 def test_quant_tools_host_side():
     """Eq. 1 and Eq. 5 on the host against the oracle, and argument validation of the device
     entry points (every call below fails before anything is launched)."""

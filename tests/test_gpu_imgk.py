@@ -91,7 +91,9 @@ def test_copies_of_weights_for_the_halves_of_a_batch(oracle):
     assert torch.equal(later.run(x_t), got)
 
 
-@pytest.mark.parametrize("case", [(16, 56, 56, "u8", "u8", None), (23, 28, 31, "s8", "s8", "u8"), (13, 61, 62, "u8", "u8", "s8")])
+# (bands of 4 rows; of 7; of 6, the last of 5; of 3, the last of one)
+@pytest.mark.parametrize("case", [(16, 56, 56, "u8", "u8", None), (45, 28, 31, "s8", "s8", "u8"), (37, 29, 31, "s8", "u8", "s8"),
+                                  (13, 61, 62, "u8", "u8", "s8")])
 def test_single_call_of_the_64_channel_layer_folds_itself(oracle, case):
     """f8_conv2d_fixed on 64 -> 64 channels: weights as they are, with and without bias, one launch."""
     B, H, W, xt, yt, rt = case
@@ -105,3 +107,13 @@ def test_single_call_of_the_64_channel_layer_folds_itself(oracle, case):
         f8.f8_conv2d_fixed(x_t, w_t, None if bias is None else torch.from_numpy(bias).cuda(), y, L, (1, 1), (1, 1), r_t)
         torch.cuda.synchronize()
         assert np.array_equal(y.cpu().numpy(), want), case
+    # it is this kernel that takes the call: no start values are written to scratch, unless it is switched off
+    for on in (0, 1):
+        f8.f8_tuning_set("imgk", on)
+        n = f8.lib().f8_conv_workspace_bytes(64)
+        ws = torch.full((n + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        ws = ws[(-ws.data_ptr()) % 256:][:n]
+        f8.f8_conv2d_fixed_ws(x_t, w_t, None, y, L, ws, (1, 1), (1, 1), r_t)
+        torch.cuda.synchronize()
+        assert bool((ws == 0xA5).all()) == bool(on), (case, on)
+        assert np.array_equal(y.cpu().numpy(), want), (case, on)

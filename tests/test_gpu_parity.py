@@ -700,11 +700,37 @@ def test_pools(oracle):
         assert_same(gpu_layer(L, x), oracle.global_pool_fixed(x, L), "gpool")
 
 
-def test_repeatable_and_streams(oracle):
+@pytest.fixture(params=["one launch", "fold and layer"])
+def launches(request):
+    """The small single-layer calls form their start values in the layer's own kernel; with these switches off they are
+    folded into scratch memory first, as those of larger layers are."""
+    if request.param != "one launch":
+        for name in ("wavek", "imgk", "pw_wide"):
+            f8.f8_tuning_set(name, 0)
+    yield 1 if request.param == "one launch" else 2
+    for name in ("wavek", "imgk", "pw_wide"):
+        f8.f8_tuning_set(name, 1)
+
+
+def scratch_for(Cout):
+    """A workspace for f8_conv2d_fixed_ws, filled with a pattern that tells whether the call used it."""
+    n = f8.lib().f8_conv_workspace_bytes(Cout)
+    ws = torch.full((n + 256,), 0xA5, dtype=torch.uint8, device=DEV)
+    return ws[(-ws.data_ptr()) % 256:][:n]
+
+
+def scratch_used(ws):
+    return not bool((ws == 0xA5).all())
+
+
+def test_repeatable_and_streams(oracle, launches):
     """Same inputs, three runs, two streams: identical bits (the race detector)."""
     x, L = wl.config1(batch=4)
     xt, wt, bt = (torch.from_numpy(a).to(DEV) for a in (x, L.w, L.bias))
     want = oracle.conv2d_fixed(x, L.w, L.bias, L, (1, 1), (1, 1))
+    ws = scratch_for(64)
+    f8.f8_conv2d_fixed_ws(xt, wt, bt, torch.empty(want.shape, dtype=torch.uint8, device=DEV), L, ws, (1, 1), (1, 1))
+    assert scratch_used(ws) == (launches == 2)
     outs = []
     s2 = torch.cuda.Stream()
     for i in range(3):
@@ -722,7 +748,7 @@ def test_repeatable_and_streams(oracle):
         assert_same(o, want, "repeat")
 
 
-def test_caller_workspace_entry_point_from_two_threads_and_streams(oracle):
+def test_caller_workspace_entry_point_from_two_threads_and_streams(oracle, launches):
     """f8_conv2d_fixed_ws keeps no state in the library: four host threads, each with its own stream
     and workspace, issue different layers at the same time, repeatedly; every result is the
     oracle's.  The allocating entry point, called from the same threads on one shared stream,
@@ -737,9 +763,7 @@ def test_caller_workspace_entry_point_from_two_threads_and_streams(oracle):
         x, L, res = wl.random_conv_case(rng, B, H, W, Cin, Cout, R, S, st, pd, xt, yt, rt)
         want = oracle.conv2d_fixed(x, L.w, L.bias, L, (st, st), (pd, pd), res)
         dev = [torch.from_numpy(a).to(DEV) if a is not None else None for a in (x, L.w, L.bias, res)]
-        ws = torch.empty(f8.lib().f8_conv_workspace_bytes(Cout) + 256, dtype=torch.uint8, device=DEV)
-        ws = ws[(-ws.data_ptr()) % 256:][:f8.lib().f8_conv_workspace_bytes(Cout)]
-        jobs.append((L, dev, want, ws, torch.cuda.Stream(), (st, st), (pd, pd)))
+        jobs.append((L, dev, want, scratch_for(Cout), torch.cuda.Stream(), (st, st), (pd, pd)))
     torch.cuda.synchronize()
     errors = []
 
@@ -768,6 +792,7 @@ def test_caller_workspace_entry_point_from_two_threads_and_streams(oracle):
         for t in threads:
             t.join()
     assert not errors, errors
+    assert [scratch_used(job[3]) for job in jobs] == [launches == 2] * len(jobs)
     # validation of the workspace arguments happens before any launch
     L, (xd, wd, bd, rd), want, ws, stream, stride, pad = jobs[0]
     y = torch.empty(want.shape, dtype=torch.uint8, device=DEV)

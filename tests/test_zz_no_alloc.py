@@ -55,7 +55,33 @@ def both_ways(case, rng, oracle=None):
     return got
 
 
-# (first call, second and smaller call): the pair shares the library's scratch array
+@pytest.fixture(params=["one launch", "fold and layer"])
+def launches(request):
+    """Calls whose start values the layer's own kernel forms keep nothing in scratch; with these switches off, layers with
+    channel counts that the LDS-direct kernel takes are folded into it first, whatever their size."""
+    if request.param != "one launch":
+        for name in ("wavek", "imgk", "pw_wide"):
+            f8.f8_tuning_set(name, 0)
+    yield 1 if request.param == "one launch" else 2
+    for name in ("wavek", "imgk", "pw_wide"):
+        f8.f8_tuning_set(name, 1)
+
+
+def folds_into_scratch(case):
+    """Whether the call writes start values to scratch memory, seen on the entry point whose scratch is the caller's."""
+    B, H, W, Cin, Cout, R, S, st, pd, xty, yty, rty = case
+    x, L, res = wl.random_conv_case(np.random.default_rng(1), B, H, W, Cin, Cout, R, S, st, pd, xty, yty, rty)
+    xt, wt, bt = (torch.from_numpy(a).to(DEV) for a in (x, L.w, L.bias))
+    rt = torch.from_numpy(res).to(DEV) if res is not None else None
+    n = f8.lib().f8_conv_workspace_bytes(Cout)
+    ws = torch.full((n + 256,), 0xA5, dtype=torch.uint8, device=DEV)
+    ws = ws[(-ws.data_ptr()) % 256:][:n]
+    y = torch.empty((B,) + tuple(L.out_hw) + (Cout,), dtype=f8.TORCH_DTYPE[yty], device=DEV)
+    f8.f8_conv2d_fixed_ws(xt, wt, bt, y, L, ws, (st, st), (pd, pd), rt)
+    return not bool((ws == 0xA5).all())
+
+
+# (first call, second and smaller call): the pair shares the library's scratch array where both are folded into it
 PAIRS = [
     # large then small, both through the LDS-direct dense kernel
     ((2, 28, 28, 128, 512, 1, 1, 1, 0, "u8", "u8", "u8"), (1, 14, 14, 64, 64, 3, 3, 1, 1, "u8", "u8", None)),
@@ -63,20 +89,26 @@ PAIRS = [
     ((1, 7, 7, 256, 4096, 1, 1, 1, 0, "u8", "s8", None), (1, 9, 9, 7, 5, 3, 3, 1, 1, "u8", "s8", None)),
     # signed input (no sign correction in the start values) after unsigned, int32 logits after 8-bit
     ((2, 19, 23, 64, 192, 3, 3, 2, 1, "u8", "u8", None), (1, 1, 40, 512, 1000, 1, 1, 1, 0, "s8", "s32", None)),
+    # many channels, then few that are folded too
+    ((1, 7, 7, 256, 4096, 1, 1, 1, 0, "u8", "s8", None), (1, 9, 9, 16, 20, 3, 3, 1, 1, "u8", "s8", None)),
 ]
 
 
 @pytest.mark.parametrize("pair", PAIRS)
-def test_noalloc_entry_point_matches_the_allocating_one(pair):
+def test_noalloc_entry_point_matches_the_allocating_one(pair, launches):
+    if launches == 2:
+        # (odd channel counts are never folded into scratch)
+        assert [folds_into_scratch(case) for case in pair] == [case[3] % 16 == 0 for case in pair]
     rng = np.random.default_rng(zlib.crc32(repr(pair).encode()))
     for case in pair:          # two calls in a row, the second with the smaller input
         both_ways(case, rng)
 
 
-def test_noalloc_matches_the_oracle_on_a_ragged_layer():
+def test_noalloc_matches_the_oracle_on_a_ragged_layer(launches):
     # also pinned to the CPU oracle directly, not only to the other entry point
     from oracle import ref
     case = (3, 17, 17, 32, 160, 3, 3, 1, 1, "u8", "u8", "u8")
+    assert folds_into_scratch(case) == (launches == 2)
     rng = np.random.default_rng(7)
     B, H, W, Cin, Cout, R, S, st, pd, xty, yty, rty = case
     x, L, res = wl.random_conv_case(rng, B, H, W, Cin, Cout, R, S, st, pd, xty, yty, rty)

@@ -37,8 +37,12 @@
  *     break the precondition makes the accumulator wrap silently (two's complement), where the
  *     CPU oracle reports an overflow.  F8_ERR_ACC_OVERFLOW is reserved for checkers that see the data.
  *   - x, w, y must not overlap.  q->res may be any tensor of y's shape except y itself.
- *   - The single-layer dense calls that do not take the K-sharing kernel (small outputs and odd channel
- *     counts do: one launch, no scratch) keep a small device scratch buffer per (device, stream):
+ *   - Some single-layer dense calls are one launch without scratch, their kernel forms the accumulator's start
+ *     values itself: small outputs (the K-sharing kernel), everything the LDS-direct kernel does not take (odd
+ *     channel counts, odd addresses, 32-bit residuals), the 3x3 64 -> 64 layers from about 13 images of 56 x 56
+ *     on, and the 1x1 layers with 256 or 512 input channels and a wide output from about 13 images of 14 x 14
+ *     (256 -> 1024) or 7 x 7 (512 -> 2048) on.
+ *     The others keep a small device scratch buffer per (device, stream):
  *     256 bytes of zeros (the kernels' stand-in for padding) plus the folded accumulator
  *     start value, 4 bytes per output channel rounded up to 256 channels, at least 64 KiB.
  *     It is allocated (hipMalloc) on the first call on a stream and when a call needs more
@@ -218,8 +222,10 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
 f8_status f8_chain_run(f8_chain *c, const void *x, void *out, void *workspace, int batch,
                        void *stream);
 /* Where tensor `id` lives after a run (for per-layer checks): pointer inside the
- * workspace (or NULL for ids 0 and the last tensor), shape and type.  Tensors whose
- * memory was reused by a later layer are reported with *live_at_end = 0. */
+ * workspace (or NULL for ids 0 and the last tensor, and for tensors that a kernel computing two or three layers at
+ * this batch never writes: the stem's under its max pool, a depthwise layer's under the 1x1 layer behind it; with
+ * keep_all every tensor is written), shape and type.  Tensors whose memory was reused by a later layer are reported
+ * with *live_at_end = 0. */
 f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch, void **ptr,
                           int *h, int *w, int *ch, int *dtype, int *live_at_end);
 /* With keep_all != 0 no two tensors share memory (bigger workspace, every intermediate

@@ -20,7 +20,7 @@
 // long K go to conv_wavek.hip, whose waves share K instead; there a tile of 64 x 64 keeps a CU for 4.6 us
 // even when K is one chunk (sums of all waves through LDS), which over many tiles is 2 - 12 times slower: 65536 x 64
 // -> 1023 to 32 bits 142 us here, 297 us there; 3x3 stride 2 on 32 images of 224 x 224 x 3, 51 / 331 us; 64 -> 256
-// with a 32-bit residual on 50176 pixels 28 / 66 us.
+// with a 32-bit residual on 50176 pixels 25 / 66 us.
 //
 // FOLD (single-layer calls): the start values are formed from the weight fragments on the way, four packed dot
 // products per fragment, so that the call is one launch without scratch.

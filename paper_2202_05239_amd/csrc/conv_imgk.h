@@ -27,8 +27,8 @@ int conv_imgk_most_waves(int C);
 // Whether images of this size fill the accumulators of a workgroup to two thirds at least.  Below that the best number of
 // waves against the best other kernel measures, in us, at 64, 128, 256 images: 256 channels on 12 x 12 (64 % full) 11.1 / 15.9,
 // 15.4 / 20.7, 25.7 / 25.9; 10 x 10 (45 %) 10.5 / 12.8, 14.6 / 15.5, 24.0 / 21.5; 8 x 8 8.5 / 7.5, 11.1 / 13.2, 15.0 / 16.2; 512 on 5 x 5 11.0 /
-// 9.9, 15.9 / 22.0, 27.2 / 26.3; 128 on 16 x 16 8.3 / 8.5, 9.9 / 10.1, 15.4 / 16.8: ahead at some batches, behind at others, so the
-// line is where the kernel is ahead at every batch.
+// 9.9, 15.9 / 22.0, 27.2 / 26.3; 128 on 16 x 16 8.3 / 8.5, 9.9 / 10.1, 15.4 / 16.8: ahead at some batches and behind at others; the
+// line lies above all of them.
 bool conv_imgk_fills(int C, int H, int W);
 // Workgroups of a launch with wk waves sharing K.
 long long conv_imgk_workgroups(int C, int B, int H, int W, int wk);

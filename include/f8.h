@@ -210,7 +210,7 @@ typedef struct f8_chain f8_chain;
 f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, int in_w,
                           int in_c, int in_type, f8_chain **out);
 /* Bytes of device workspace needed for `batch` images: activations, folded constants, and the re-ordered copies of weights
- * that the kernels chosen for this batch read. */
+ * that the kernels chosen for this batch read.  Never less than for any smaller batch. */
 f8_status f8_chain_workspace_bytes(const f8_chain *c, int batch, size_t *bytes);
 /* Writes the folded per-channel constants into the workspace; once per workspace and
  * batch size, before f8_chain_run. */

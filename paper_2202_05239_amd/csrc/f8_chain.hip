@@ -773,7 +773,17 @@ f8_status f8_chain_workspace_bytes(const f8_chain *cc, int batch, size_t *bytes)
       return F8_ERR_UNSUPPORTED;
   for (const Stem &sm : c->stem)
     if (sm.on && (long long)sm.x_bytes_per_image * batch > 0x7fffffffLL) return F8_ERR_UNSUPPORTED;
-  *bytes = c->const_bytes + c->arena_per_image * (size_t)batch + c->place_fragments(batch, nullptr) + 256;
+  // A smaller batch may take kernels with copies that this one does not need; a workspace for the largest batch of a
+  // program has to hold every smaller one too.  Where a smaller arena saves more than all copies take, nothing more
+  // can be needed; a chain whose arena is next to nothing gets room for all of them instead of a long search.
+  size_t copies = 0, most = 0;
+  for (size_t i = 0; i < c->layers.size(); ++i) copies += round256(c->img_w_bytes[i]) + round256(c->dwp_w_bytes[i]);
+  for (int b = batch; b >= 0 && c->arena_per_image * (size_t)(batch - b) <= copies; --b) {
+    const bool far = batch - b >= 1024;
+    most = std::max(most, c->arena_per_image * (size_t)b + (far ? copies : c->place_fragments(b, nullptr)));
+    if (far) break;
+  }
+  *bytes = c->const_bytes + most + 256;
   return F8_OK;
 }
 

@@ -272,9 +272,28 @@ def test_workspace_holds_weight_copies_only_for_kernels_the_batch_takes_host_sid
         image = size(b) - size(a)
         fixed = size(a) - a * image
         assert fixed < 1 << 20 if small == 1 else fixed < 2 << 20
-        for batch in (small, large, 2 * large, 2 * large + 1):
-            assert size(batch) == fixed + batch * image + copies(batch), batch
+        need = [0] + [fixed + n_img * image + copies(n_img) for n_img in range(1, 2 * large + 2)]
+        sizes = [size(n_img) for n_img in range(len(need))]
+        # a workspace for the largest batch also holds every smaller one, whatever kernels that takes
+        for batch in range(1, len(need)):
+            assert sizes[batch] == max(need[:batch + 1]), batch
+        assert any(need[n_img] > need[n_img + 1] for n_img in range(1, len(need) - 1)) or small != 1
         L.f8_chain_destroy(h)
+
+
+def test_workspace_of_a_chain_without_arena_is_found_at_once_host_side():
+    """One 3x3 layer from the caller's input to the caller's output: no arena at all, a million images."""
+    rng = np.random.default_rng(1)
+    _, S, _ = wl.random_conv_case(rng, 1, 7, 7, 64, 64, 3, 3, 1, 1, "u8", "u8")
+    S.src, S.dst, S.res = 0, 1, -1
+    L, h, n = f8.lib(), ctypes.c_void_p(), ctypes.c_size_t()
+    assert L.f8_chain_create(make_descs(wl.Net("one", (7, 7), 64, "u8", S.fl_x, [S])), 1, 7, 7, 64, f8.F8_U8, ctypes.byref(h)) == 0
+    last = 0
+    for batch in (0, 1, 176, 1023, 1024, 1025, 2047, 5000, 600000):
+        assert L.f8_chain_workspace_bytes(h, batch, ctypes.byref(n)) == 0
+        assert last <= n.value < 100000
+        last = n.value
+    L.f8_chain_destroy(h)
 
 
 def test_reported_names_are_those_of_the_kernels_that_run_host_side():

@@ -58,6 +58,29 @@ def forced_variant():
     f8.f8_tuning_set("conv_variant", -1)
 
 
+@pytest.fixture(params=["one launch", "fold and layer"])
+def launches(request):
+    """The small single-layer calls go to kernels that share K and form their start values themselves; with these switches
+    off they take the kernels of larger layers, folded into scratch memory first where that is the LDS-direct one."""
+    if request.param != "one launch":
+        for name in ("wavek", "imgk", "pw_wide"):
+            f8.f8_tuning_set(name, 0)
+    yield 1 if request.param == "one launch" else 2
+    for name in ("wavek", "imgk", "pw_wide"):
+        f8.f8_tuning_set(name, 1)
+
+
+def scratch_for(Cout):
+    """A workspace for f8_conv2d_fixed_ws, filled with a pattern that tells whether the call used it."""
+    n = f8.lib().f8_conv_workspace_bytes(Cout)
+    ws = torch.full((n + 256,), 0xA5, dtype=torch.uint8, device=DEV)
+    return ws[(-ws.data_ptr()) % 256:][:n]
+
+
+def scratch_used(ws):
+    return not bool((ws == 0xA5).all())
+
+
 def assert_same(got, want, what=""):
     assert got.shape == want.shape and got.dtype == want.dtype, (what, got.shape, want.shape, got.dtype, want.dtype)
     if not np.array_equal(got, want):
@@ -261,7 +284,10 @@ def test_weights_stationary_3x3_64(oracle):
         with ThreadPoolExecutor(len(parts)) as ex:
             outs = list(ex.map(lambda idx: oracle.conv2d_fixed(np.ascontiguousarray(x[idx]), L.w, L.bias, L, (1, 1), (1, 1)), parts))
         want = np.concatenate(outs)
-        assert_same(gpu_layer(L, x), want, "ws 3x3 %s" % str((C, B, H, W, xt, yt, shift)))
+        # (single calls on 64 channels take the image-stationary kernel, where the images fill it, unless it is off)
+        for imgk in (0, 1):
+            f8.f8_tuning_set("imgk", imgk)
+            assert_same(gpu_layer(L, x), want, "ws 3x3 %s imgk %d" % (str((C, B, H, W, xt, yt, shift)), imgk))
     # in a chain the kernel's name shows: chosen at batch 256 of the full-size network, not for a few images
     _, net = wl.config4(batch=1)
     chain = f8.Chain(net)
@@ -587,7 +613,7 @@ DENSE_CASES = [
 
 
 @pytest.mark.parametrize("case", DENSE_CASES)
-def test_dense_layer_sweep(oracle, case):
+def test_dense_layer_sweep(oracle, case, launches):
     B, H, W, Cin, Cout, R, S, st, pd, xt, yt, rt, off = case
     rng = np.random.default_rng(zlib.crc32(repr(case).encode()))
     for trial in range(3):
@@ -600,7 +626,7 @@ def test_dense_layer_sweep(oracle, case):
         assert_same(got, want, "dense %s trial %d" % (str(case), trial))
 
 
-def test_residual_shift_directions(oracle):
+def test_residual_shift_directions(oracle, launches):
     """Residual finer than, equal to and coarser than the accumulator scale."""
     rng = np.random.default_rng(77)
     for fl_res in (0, 5, 9, 12, 14):
@@ -610,7 +636,7 @@ def test_residual_shift_directions(oracle):
         assert_same(gpu_layer(L, x, res), want, "fl_res %d" % fl_res)
 
 
-def test_shift_extremes(oracle):
+def test_shift_extremes(oracle, launches):
     rng = np.random.default_rng(78)
     for shift, fl in ((24, (12, 12, 0)), (-8, (0, 0, 8)), (1, (1, 0, 0))):
         x, L, _ = wl.random_conv_case(rng, 1, 8, 8, 64, 32, 3, 3, 1, 1, "u8", "u8", shift=shift,
@@ -623,7 +649,7 @@ def test_shift_extremes(oracle):
         assert len(np.unique(want)) > (1 if shift < 0 else 2)
 
 
-def test_degenerate_inputs(oracle):
+def test_degenerate_inputs(oracle, launches):
     rng = np.random.default_rng(79)
     x, L, _ = wl.random_conv_case(rng, 1, 8, 8, 16, 16, 3, 3, 1, 1)
     L.w[:] = 0                                                  # output = fix_quant(bias)
@@ -698,29 +724,6 @@ def test_pools(oracle):
         L = wl.LayerSpec(op="gpool", Cin=shape[3], Cout=shape[3], fl_x=4, fl_w=fl_w, fl_y=4, clip_lo=0,
                          clip_hi=255, x_type="u8", y_type="u8")
         assert_same(gpu_layer(L, x), oracle.global_pool_fixed(x, L), "gpool")
-
-
-@pytest.fixture(params=["one launch", "fold and layer"])
-def launches(request):
-    """The small single-layer calls form their start values in the layer's own kernel; with these switches off they are
-    folded into scratch memory first, as those of larger layers are."""
-    if request.param != "one launch":
-        for name in ("wavek", "imgk", "pw_wide"):
-            f8.f8_tuning_set(name, 0)
-    yield 1 if request.param == "one launch" else 2
-    for name in ("wavek", "imgk", "pw_wide"):
-        f8.f8_tuning_set(name, 1)
-
-
-def scratch_for(Cout):
-    """A workspace for f8_conv2d_fixed_ws, filled with a pattern that tells whether the call used it."""
-    n = f8.lib().f8_conv_workspace_bytes(Cout)
-    ws = torch.full((n + 256,), 0xA5, dtype=torch.uint8, device=DEV)
-    return ws[(-ws.data_ptr()) % 256:][:n]
-
-
-def scratch_used(ws):
-    return not bool((ws == 0xA5).all())
 
 
 def test_repeatable_and_streams(oracle, launches):
@@ -957,7 +960,7 @@ def test_chain_channel_padding(oracle):
 
 # ------------------------------------------------------------------------- random geometry
 
-def test_random_geometry_fuzz(oracle):
+def test_random_geometry_fuzz(oracle, launches):
     """Seeded random layer geometries (window, stride, padding, channel counts, types, residual
     kinds, shifts) against the oracle: dense and depthwise, every draw bit-exact."""
     rng = np.random.default_rng(20220205)

@@ -39,21 +39,25 @@ def test_single_calls_of_the_wide_1x1_layers(oracle, C, N, M):
             assert bool((t[:16] == 77).all()) and bool((t[16 + M * N:] == 77).all())
 
 
-@pytest.mark.parametrize("C,N,hw,batch", [(256, 1024, 27, 23), (512, 2048, 9, 102)])
-def test_two_formats_in_a_chain(oracle, C, N, hw, batch):
-    """The same kernel behind start values from the chain's workspace, with a residual and a ragged last block."""
+# residual: unsigned, signed, none
+@pytest.mark.parametrize("dual", [True, False])
+@pytest.mark.parametrize("C,N,hw,batch,relu", [(256, 1024, 27, 23, True), (512, 2048, 9, 102, True), (256, 1024, 27, 23, False), (512, 2048, 9, 102, None)])
+def test_layers_of_a_chain(oracle, C, N, hw, batch, relu, dual):
+    """The same kernel behind start values from the chain's workspace, with a ragged last block."""
     rng = np.random.default_rng(C)
     b = wl._NetBuilder("dual", rng, hw, 32, "u8", 5, (5, 9), (2, 6), True)
-    wide = b.conv("wide", 0, N, 1, 1, 0)
-    first, second = b.conv("closing", b.conv("narrow", 0, C, 1, 1, 0), N, 1, 1, 0, res=wide, dual=True)
-    b.conv("reader", second, 16, 1, 1, 0)
-    b.conv("last", first, 16, 1, 1, 0)
+    wide = b.conv("wide", 0, N, 1, 1, 0, relu=relu is not False)
+    out = b.conv("closing", b.conv("narrow", 0, C, 1, 1, 0), N, 1, 1, 0, res=-1 if relu is None else wide, dual=dual)
+    outs = out if dual else (out,)
+    for t in outs:
+        b.conv("reader", t, 16, 1, 1, 0)
+    b.conv("last", outs[0], 16, 1, 1, 0)
     x = wl.draw_u8(rng, (batch, hw, hw, 32))
     chain = f8.Chain(b.net, keep_all=True).prepare(batch)
     assert chain.layer_info(2, batch)[0] == "pw1x1_wide<%d>" % C
     chain.run(torch.from_numpy(x).cuda())
     pick = [0, batch // 2, batch - 1]
     want = oracle.run_network(b.net, np.ascontiguousarray(x[pick]), keep_all=True)
-    for t in (first, second):
+    for t in outs:
         got = chain.tensor(t)[pick].cpu().numpy()
         assert got.dtype == want[t].dtype and np.array_equal(got, want[t]), t

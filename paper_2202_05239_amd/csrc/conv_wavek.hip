@@ -48,8 +48,9 @@ constexpr int BK = 128;              // bytes of K per chunk
 enum { M_GEMM = 0, M_TAP = 1, M_ANY = 2, M_GATHER = 3 };
 
 struct WkTiling {
-  int tiles_m, tiles_n, ntiles;
+  int ntiles;
   int m_fast;                        // neighbouring workgroups share the channel tile (else the pixel tile)
+  FastDiv fd_fast;                   // by the tiles that neighbouring workgroups walk along
   int x_bytes;
   int run;                           // bytes of a window row: S * C
   int short_runs;                    // a unit can touch more than two window rows
@@ -141,14 +142,15 @@ __global__ __launch_bounds__(64 * NW, MODE == M_GATHER && NW == 4 ? 2 : 1) void 
 
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
+  pin_args(tl.ntiles, tl.fd_fast.mul, tl.fd_fast.shr, tl.fd_fast.d, tl.m_fast, tl.x_bytes, p.x, p.w, p.C, p.N, p.M, p.K, p.acc0, p.res);
+  if (MODE != M_GEMM) pin_args(p.fd_pq.mul, p.fd_pq.shr, p.fd_pq.d, p.fd_q.mul, p.fd_q.shr, p.fd_q.d, p.H, p.W, p.sh, p.sw, p.ph, p.pw);
+  if (MODE == M_TAP) pin_args(p.fd_c.mul, p.fd_c.shr, p.fd_c.d, p.fd_s.mul, p.fd_s.shr, p.fd_s.d, p.R, p.S, p.tap_rep);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const uint32_t tile = xcd_remap(blockIdx.x, (uint32_t)tl.ntiles);
-  int tile_m, tile_n;
-  if (tl.m_fast) { tile_n = (int)tile / tl.tiles_m; tile_m = (int)tile - tile_n * tl.tiles_m; }
-  else { tile_m = (int)tile / tl.tiles_n; tile_n = (int)tile - tile_m * tl.tiles_n; }
-  const int m0 = tile_m * TM, n0 = tile_n * TN;
+  const int slow = (int)tl.fd_fast.div(tile), fast = (int)tile - slow * (int)tl.fd_fast.d;
+  const int m0 = (tl.m_fast ? fast : slow) * TM, n0 = (tl.m_fast ? slow : fast) * TN;
 
   // ---- loader: row 8 i + lane / 8 of the tile, physical 16-byte piece lane % 8 of its 128 bytes.  The pieces
   // of a row are permuted by the row number (conflict-free fragment reads); rows 8 i with even and odd i hold
@@ -160,11 +162,12 @@ __global__ __launch_bounds__(64 * NW, MODE == M_GATHER && NW == 4 ? 2 : 1) void 
   // tile and the lanes that fetch the row get it from there.
   int x_off[XR], x_ih[XR], x_iw[XR];
   if (MODE == M_GEMM) {
+    // (rows past the last pixel lie past the end of the tensor)
+    const int first = (m0 + lrow) * p.C;
 #pragma unroll
     for (int i = 0; i < XR; ++i) {
-      const int m = m0 + 8 * i + lrow;
       x_ih[i] = x_iw[i] = 0;
-      x_off[i] = m < p.M ? m * p.C + piece[i & 1] * 16 : (int)0x80000000u;
+      x_off[i] = first + i * (8 * p.C) + piece[i & 1] * 16;
     }
   } else {
     // (a row past the last pixel: no tap inside)
@@ -199,13 +202,15 @@ __global__ __launch_bounds__(64 * NW, MODE == M_GATHER && NW == 4 ? 2 : 1) void 
     }
   }
   int w_off[WR];
+  // (from the tile's first channel on; row 8 i + lrow of a block of 32 is channel frag_channel(lrow) + 4 i, and rows past the
+  // last channel lie past the end of the tile's weights)
+  const int w_first = frag_channel(lrow) * p.K;
 #pragma unroll
   for (int i = 0; i < WR; ++i) {
-    const int r = 8 * i + lrow;
-    const int n = n0 + (r & ~31) + frag_channel(r & 31);
-    // (from the tile's first channel on)
-    if (GATHER) w_off[i] = n < p.N ? (n - n0) * p.K : -1;
-    else w_off[i] = n < p.N ? (n - n0) * p.K + piece[i & 1] * 16 : (int)0x80000000u;
+    const int n = n0 + 32 * (i >> 2) + 4 * (i & 3) + frag_channel(lrow);
+    const int off = w_first + (32 * (i >> 2) + 4 * (i & 3)) * p.K;
+    if (GATHER) w_off[i] = n < p.N ? off : -1;
+    else w_off[i] = off + piece[i & 1] * 16;
   }
   uint8_t *own = lds + wave * (D * STAGE);
   const uint32_t own_at = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint8_t *)own);
@@ -321,7 +326,29 @@ __global__ __launch_bounds__(64 * NW, MODE == M_GATHER && NW == 4 ? 2 : 1) void 
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the wave's own writes, read back below
   };
 
-  // ---- what the epilogue needs from memory, requested ahead of the operands: four channels n .. n + 3 per
+  // ---- K loop ------------------------------------------------------------------------------
+  v16i acc[NB][MB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[nb][mb][i] = 0;
+  int wsum[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) wsum[nb] = 0;
+  const int xm = (int)p.xor_mask;
+  uint32_t foff[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) foff[ks] = (uint32_t)(l32 * BK + (((2 * ks + half) ^ ((l32 >> 1) & 7)) * 16));
+
+  if (!GATHER) {
+#pragma unroll
+    for (int s = 0; s < D; ++s)
+      if (s < mine) copy_chunk(wave + s * NW, s);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // ---- what the epilogue needs from memory, requested behind the first operands: four channels n .. n + 3 per
   // thread, pixels row0 + k * (NT / GROW)
   const int n = n0 + (tid % GROW) * 4, row0 = tid / GROW;
   const bool n_vec = (p.N & 3) == 0;
@@ -355,28 +382,6 @@ __global__ __launch_bounds__(64 * NW, MODE == M_GATHER && NW == 4 ? 2 : 1) void 
     }
   }
   __builtin_amdgcn_sched_barrier(0);
-
-  // ---- K loop ------------------------------------------------------------------------------
-  v16i acc[NB][MB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[nb][mb][i] = 0;
-  int wsum[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) wsum[nb] = 0;
-  const int xm = (int)p.xor_mask;
-  uint32_t foff[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) foff[ks] = (uint32_t)(l32 * BK + (((2 * ks + half) ^ ((l32 >> 1) & 7)) * 16));
-
-  if (!GATHER) {
-#pragma unroll
-    for (int s = 0; s < D; ++s)
-      if (s < mine) copy_chunk(wave + s * NW, s);
-  }
   int stage = 0;
   for (int j = 0; j < mine; ++j) {
     if (GATHER) gather_chunk(wave + j * NW);
@@ -514,14 +519,14 @@ __global__ __launch_bounds__(64 * NW, MODE == M_GATHER && NW == 4 ? 2 : 1) void 
 template <int TM, int TN, int NW, int D, int MODE, bool FOLD>
 int launch_one(const ConvParams &p, const int32_t *bias, hipStream_t stream) {
   WkTiling tl;
-  tl.tiles_m = (p.M + TM - 1) / TM;
-  tl.tiles_n = (p.N + TN - 1) / TN;
-  const long long ntiles = (long long)tl.tiles_m * tl.tiles_n;
+  const int tiles_m = (p.M + TM - 1) / TM, tiles_n = (p.N + TN - 1) / TN;
+  const long long ntiles = (long long)tiles_m * tiles_n;
   if (ntiles > 0x7fffffffLL) return (int)hipErrorInvalidValue;
   tl.ntiles = (int)ntiles;
   tl.x_bytes = p.B * p.H * p.W * p.C;
   // neighbouring tiles run on one XCD: let them share the larger operand
   tl.m_fast = (long long)p.N * p.K > tl.x_bytes;
+  tl.fd_fast = FastDiv((uint32_t)(tl.m_fast ? tiles_m : tiles_n));
   tl.run = p.S * p.C;
   tl.short_runs = p.R > 1 && tl.run < 16;
   tl.fd_run = FastDiv((uint32_t)tl.run);

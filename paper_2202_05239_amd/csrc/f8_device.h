@@ -13,28 +13,36 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 
 enum { T_U8 = 0, T_S8 = 1, T_S32 = 2 };
 
-// Division of a non-negative 32-bit integer by a fixed divisor d >= 1, as a multiply-high
-// and a shift.  (Address arithmetic only: the layer arithmetic itself has no multiply
-// besides the 8-bit products.)
+// Division of an integer 0 <= n < 2^31 by a fixed divisor d >= 1, as a multiply-high and a shift: with l = ceil(log2 d)
+// and mul = floor(2^(31 + l) / d) + 1, which fits 32 bits, n * mul >> (31 + l) is exact for such n (mul * d exceeds
+// 2^(31 + l) by at most d <= 2^l).  No special case for d = 1: a branch here is a chain of scalar loads in every kernel's
+// prologue, one after the other, 100 to 500 cycles each (the arguments of a launch lie in memory that no cache holds yet).
+// (Address arithmetic only: the layer arithmetic itself has no multiply besides the 8-bit products.)
 struct FastDiv {
   uint32_t mul;
   uint32_t shr;
   uint32_t d;
-  __host__ FastDiv() : mul(0), shr(0), d(1) {}
-  __host__ explicit FastDiv(uint32_t div) : d(div) {
-    if (div <= 1) { mul = 0; shr = 0; d = 1; return; }
-    uint32_t l = 0;
-    while ((1ull << l) < div) ++l;                        // l = ceil(log2(div))
-    uint64_t m = ((1ull << 32) * ((1ull << l) - div)) / div + 1;
-    mul = (uint32_t)m;
-    shr = l;
+  __host__ FastDiv() : FastDiv(1) {}
+  __host__ explicit FastDiv(uint32_t div) : shr(0), d(div < 1 ? 1 : div) {
+    while ((1ull << shr) < d) ++shr;
+    mul = (uint32_t)((1ull << (31 + shr)) / d + 1);
   }
-  __device__ __forceinline__ uint32_t div(uint32_t n) const {
-    if (d == 1) return n;
-    uint32_t t = __umulhi(n, mul);
-    return (t + ((n - t) >> 1)) >> (shr - 1);
+  __host__ __device__ __forceinline__ uint32_t div(uint32_t n) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __umulhi(n << 1, mul) >> shr;
+#else
+    return (uint32_t)(((unsigned long long)(n << 1) * mul) >> 32) >> shr;
+#endif
   }
 };
+
+// Makes the given kernel arguments be loaded here, together.  Left to itself the compiler loads an argument where it is
+// first used, and a prologue becomes a chain of scalar loads, each 140 cycles (in a graph that ran before) to 550 cycles
+// (first touch of its 64 bytes by this launch).
+template <typename T>
+__device__ __forceinline__ void pin_arg(T v) { asm volatile("" ::"s"(v)); }
+template <typename... T>
+__device__ __forceinline__ void pin_args(T... v) { (pin_arg(v), ...); }
 
 // Workgroups are handed to the 8 XCDs round-robin by linear id.  Give every XCD a
 // contiguous range of logical tiles so that neighbouring tiles share one L2.

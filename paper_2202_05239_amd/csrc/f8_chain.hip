@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "block_fused.h"
+#include "bottleneck.h"
 #include "dw_pw.h"
 #include "stem_pool.h"
 #include "conv_img.h"
@@ -168,23 +169,58 @@ struct f8_chain {
     const long long most = g.Q > 64 ? 2ll << 20 : g.Q > 28 ? 5ll << 19 : g.Q > 14 ? 9ll << 19 : g.Q > 7 ? 7ll << 20 : 2ll << 20;
     return total <= most && dw_pw_slices(g.Cin, layers[i + 1].Cout) <= 20;
   }
-  // Copies of weights in fragment order (img_w_bytes, dwp_w_bytes) lie behind the arena and only where this batch, or
+  // A 3x3 layer, the 1x1 layer of four times its channels that is its only reader, and (where there is one) the 1x1 layer
+  // behind that in one launch: bn[i] = 1 for the first, 2 and 3 for the others; bn_head[i] = the first layer, bn_behind[i]
+  // (of the first) = the third or -1.  Whether the three run as one launch depends on the batch.
+  std::vector<int> bn, bn_head, bn_behind;   // per layer
+  int bottleneck = 1;
+  int bn_channels(size_t head) const { return bn_behind[head] < 0 ? 0 : layers[bn_behind[head]].Cout; }
+  size_t bn_w_bytes(size_t i) const { return bn[i] == 1 ? bottleneck_weight_bytes(layers[i].Cin, bn_channels(i)) : 0; }
+  bool bn_allowed(size_t head) const {
+    if (bottleneck == 0 || keep_all) return false;
+    return !use_fusion() || (fused[head].role == 0 && fused[head + 1].role == 0 && (bn_behind[head] < 0 || fused[bn_behind[head]].role == 0));
+  }
+  int bn_role(size_t i, int batch) const {
+    if (bn[i] == 0 || !bn_allowed((size_t)bn_head[i])) return 0;
+    return bottleneck >= 2 || bn_pays((size_t)bn_head[i], batch) ? bn[i] : 0;
+  }
+  // Microseconds of the three layers, apart -> together (apart the launches cost some 0.4 us each more in a forward than
+  // alone), ResNet-50:
+  //   64 channels, 56 x 56: batch 1 9.7 -> 7.0, 4 13.8 -> 7.9, 16 19 -> 13.4, 64 38 -> 34 - 36, 128 66 -> 59 (two formats: 103 -> 82), 192 104 -> 91
+  //   128 channels, 28 x 28: batch 1 9.3 -> 7.0, 16 19 -> 9.6, 64 32 -> 28, 128 50 -> 45, 192 64 -> 63, 256 79 -> 84; stride 2 from 56 x 56: batch
+  //     16 20 -> 11.4, 32 25 -> 20, 48 31.7 -> 30.6, 64 36 -> 42 (the patch leaves room for one workgroup per CU)
+  //   256 channels, 14 x 14: batch 1 9.8 -> 12.8, 4 11.7 -> 12.6, 8 13.5 -> 12.7, 16 17.9 -> 13.5, 32 22 -> 14.7, 64 30 -> 22, 96 37 -> 39, 128 42 -> 41
+  //     (two formats 45 -> 47); stride 2 from 28 x 28: batch 4 11.7 -> 12.1, 32 26.6 -> 14.7, 64 34.6 -> 29.6, 96 44 -> 44, 128 49 -> 59
+  // (Above 2^19 pixels, 64 channels gain too, but there the closing layers' own kernels have not been compared on anything
+  // but ResNet-50.)
+  bool bn_pays(size_t head, int batch) const {
+    const Geom &g = geom[head];
+    const long long M = (long long)batch * g.P * g.Q;
+    if (g.Cin == 64) return M < 1 << 19;
+    if (g.Cin == 128) return M <= (g.sh == 1 ? 131072 : 38000);
+    return M >= 1200 && M <= (g.sh == 1 ? 16384 : 13000);
+  }
+  // Copies of weights in fragment order (img_w_bytes, bn_w_bytes, dwp_w_bytes) lie behind the arena and only where this batch, or
   // either half of it on two streams, takes their kernel: ResNet-18 at one image needs 0.7 MB of workspace, with every
-  // copy 10 MB.  frag_off: byte offset of layer i's copy in the workspace, 0 for none.  Returns the copies' bytes; off
-  // (one entry per layer) may be null.
-  std::vector<size_t> frag_off;        // per layer, as of the last f8_chain_prepare
-  size_t place_fragments(int batch, size_t *off) const {
+  // copy 10 MB.  frag_off: byte offset of layer i's copy in the workspace, 0 for none (bn_off: the copy
+  // of the three layers it is the first of).  Returns the copies' bytes; off and boff (one entry per layer) may be null.
+  std::vector<size_t> frag_off, bn_off;   // per layer, as of the last f8_chain_prepare
+  size_t place_fragments(int batch, size_t *off, size_t *boff) const {
     const size_t base = const_bytes + arena_per_image * (size_t)batch;
     size_t bytes = 0;
     for (size_t i = 0; i < layers.size(); ++i) {
-      bool img = false, pair = false;
+      bool img = false, pair = false, three = false;
       for (int b : {batch, batch / 2, batch - batch / 2}) {
         if (b < 1) continue;
-        img = img || img_role(i, b) != 0;
+        const int role = bn_role(i, b);
+        three = three || role == 1;
+        img = img || (role == 0 && img_role(i, b) != 0);
         pair = pair || dwp_role(i, b) == 1;
       }
       if (off) off[i] = img || pair ? base + bytes : 0;
       if (img || pair) bytes += round256(img ? img_w_bytes[i] : dwp_w_bytes[i]);
+      if (boff) boff[i] = three ? base + bytes : 0;
+      if (three) bytes += round256(bn_w_bytes(i));
     }
     return bytes;
   }
@@ -249,6 +285,14 @@ struct f8_chain {
         free_list.erase(free_list.begin() + i);
       }
     };
+    // (a layer that may run inside an earlier layer's launch gets the place of its output there)
+    std::vector<char> placed(tensors.size(), 0);
+    auto place = [&](int id) {
+      Tensor &t = tensors[id];
+      if (t.external || placed[id]) return;
+      t.offset_per_image = alloc(round256(t.bytes_per_image));
+      placed[id] = 1;
+    };
     // tail candidates as the planner sees them: any batch, but not inside a fused block
     auto tail_plan = [&](size_t li) { return tail[li] == 0 || tail_in_fused_block(li) ? 0 : tail[li]; };
     for (size_t li = 0; li < layers.size(); ++li) {
@@ -273,23 +317,18 @@ struct f8_chain {
         continue;
       }
       if (stem[li].on) stem[li].x_off_per_image = alloc(round256(stem[li].x_bytes_per_image));
-      Tensor &d = tensors[layers[li].dst];
-      const bool dwp_head = !keep_all && dwp[li] == 1, dwp_behind = !keep_all && dwp[li] == 2;
-      if (dwp_head) {
-        // written by this launch: must not share memory with what this layer reads
-        Tensor &dp = tensors[layers[li + 1].dst];
-        if (!dp.external) dp.offset_per_image = alloc(round256(dp.bytes_per_image));
+      // written by this launch: must not share memory with what any of its layers reads
+      if (!keep_all && dwp[li] == 1) place(layers[li + 1].dst);
+      place(layers[li].dst);
+      if (bn[li] == 1 && bn_allowed(li)) {
+        place(layers[li + 1].dst);
+        if (layers[li + 1].dst2 > 0) place(layers[li + 1].dst2);
+        if (bn_behind[li] >= 0) place(layers[bn_behind[li]].dst);
       }
-      // (the output of a 1x1 layer that may run inside the previous launch got its place there)
-      if (!d.external && tail_plan(li) != 2 && !dwp_behind) d.offset_per_image = alloc(round256(d.bytes_per_image));
-      if (tail_plan(li) == 1) {
-        // written by this launch too: must not share memory with what this layer reads
-        Tensor &dt = tensors[layers[tail_peer[li]].dst];
-        if (!dt.external) dt.offset_per_image = alloc(round256(dt.bytes_per_image));
-      }
+      if (tail_plan(li) == 1) place(layers[tail_peer[li]].dst);
       if (layers[li].dst2 > 0) {
         Tensor &d2 = tensors[layers[li].dst2];
-        d2.offset_per_image = alloc(round256(d2.bytes_per_image));
+        place(layers[li].dst2);
         // never read: give the space back once this layer has run
         if (!keep_all && d2.last_use < 0) release(d2.offset_per_image, round256(d2.bytes_per_image));
       }
@@ -379,6 +418,41 @@ struct f8_chain {
     return p;
   }
 
+  // Parameters of the three layers that start at the 3x3 layer i.
+  BottleneckParams bottleneck_params(size_t i, const void *x, void *out, void *workspace, int batch) const {
+    const f8_layer_desc &L = layers[i], &T = layers[i + 1];
+    const Geom &g = geom[i];
+    const int a = bn_behind[i];
+    auto bytes = [&](int id) { return static_cast<uint8_t *>(tensor_ptr(id, x, out, workspace, batch)); };
+    auto sign = [](int type) { return type == F8_U8 ? 0x80808080u : 0u; };
+    BottleneckParams p;
+    p.x = bytes(L.src);
+    p.wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + bn_off[i]);
+    p.res = T.res >= 0 ? bytes(T.res) : nullptr;
+    p.y = bytes(T.dst);
+    p.y2 = T.dst2 > 0 ? bytes(T.dst2) : nullptr;
+    p.ya = a >= 0 ? bytes(layers[a].dst) : nullptr;
+    p.B = batch; p.H = g.H; p.W = g.W; p.C = g.Cin; p.P = g.P; p.Q = g.Q; p.stride = g.sh;
+    p.NA = bn_channels(i);
+    p.x_xor = sign(L.q.x_type); p.b_xor = sign(L.q.y_type); p.y_xor = sign(T.q.y_type);
+    p.shift_b = L.q.fl_x + L.q.fl_w - L.q.fl_y; p.lo_b = L.q.clip_lo; p.hi_b = L.q.clip_hi;
+    p.shift_c = T.q.fl_x + T.q.fl_w - T.q.fl_y; p.lo_c = T.q.clip_lo; p.hi_c = T.q.clip_hi;
+    p.shift_2 = p.lo_2 = p.hi_2 = p.add_2 = 0;
+    if (p.y2) {
+      p.shift_2 = T.q.fl_x + T.q.fl_w - T.q2.fl_y; p.lo_2 = T.q2.clip_lo; p.hi_2 = T.q2.clip_hi;
+      p.add_2 = (p.shift_2 > 0 ? 1 << (p.shift_2 - 1) : 0) - rounding_addend(T.q);
+    }
+    p.shift_a = p.lo_a = p.hi_a = 0;
+    if (a >= 0) {
+      const f8_quant &q = layers[a].q;
+      p.shift_a = q.fl_x + q.fl_w - q.fl_y; p.lo_a = q.clip_lo; p.hi_a = q.clip_hi;
+    }
+    p.res_signed = T.q.res_type == F8_S8;
+    p.res_d = p.res ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0;
+    p.force = bottleneck;
+    return p;
+  }
+
   f8_status launch_layer(size_t i, const void *x, void *out, void *workspace, int batch, hipStream_t s) const {
     const f8_layer_desc &L = layers[i];
     Geom g = geom[i];
@@ -405,6 +479,12 @@ struct f8_chain {
     if (use_fusion() && fused[i].role == 1) {
       const BlockParams bp = block_params(i, x, out, workspace, batch);
       return launch_block_fused(bp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
+    }
+    const int three = bn_role(i, batch);
+    if (three > 1) return F8_OK;
+    if (three == 1 && bn_off[i] != 0) {
+      const BottleneckParams bp = bottleneck_params(i, x, out, workspace, batch);
+      return launch_bottleneck(bp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
     if (tail_role(i, batch) == 2 || dwp_role(i, batch) == 2) return F8_OK;
     if (dwp_role(i, batch) == 1) {
@@ -638,6 +718,10 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->dwp.push_back(0);
     c->dwp_w_bytes.push_back(0);
     c->frag_off.push_back(0);
+    c->bn.push_back(0);
+    c->bn_head.push_back(-1);
+    c->bn_behind.push_back(-1);
+    c->bn_off.push_back(0);
   }
   if (st != F8_OK) { delete c; return st; }
   c->last_tensor = c->layers.back().dst;
@@ -689,6 +773,39 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
         break;
       }
     }
+  }
+  // a 3x3 layer, the 1x1 layer of four times its channels that is its only reader, and the 1x1 layer that opens the next
+  // block (the next layer, or the one after a new stage's shortcut projection); all tensors in the arena
+  c->bottleneck = tuning().bottleneck.load();
+  for (size_t i = 0; i + 1 < c->layers.size(); ++i) {
+    const f8_layer_desc &L = c->layers[i], &T = c->layers[i + 1];
+    const Geom &g = c->geom[i];
+    auto plain = [&](size_t l) {
+      const f8_layer_desc &D = c->layers[l];
+      return D.op == F8_OP_CONV && !c->stem[l].on && c->stem[l].pool == 0 && c->bn[l] == 0 && D.q.y_type != F8_S32 &&
+             (reinterpret_cast<uintptr_t>(D.w) & 15) == 0 && !c->tensors[D.src].external && !c->tensors[D.dst].external;
+    };
+    auto pointwise = [&](size_t l) {
+      const f8_layer_desc &D = c->layers[l];
+      return plain(l) && D.R == 1 && D.S == 1 && D.stride_h == 1 && D.stride_w == 1 && D.pad_h == 0 && D.pad_w == 0;
+    };
+    auto shift = [](const f8_layer_desc &D) { return D.q.fl_x + D.q.fl_w - D.q.fl_y; };
+    if (!plain(i) || !pointwise(i + 1) || L.R != 3 || L.S != 3 || L.stride_h != L.stride_w || L.pad_h != 1 || L.pad_w != 1 ||
+        L.Cout != L.Cin || L.res >= 0 || L.dst2 > 0 || T.src != L.dst || T.Cout != 4 * L.Cout || T.res == L.dst ||
+        (T.res >= 0 && (T.q.res_type == F8_S32 || c->tensors[T.res].external)) || c->tensors[L.dst].last_use != (int)i + 1)
+      continue;
+    int a = -1;
+    for (size_t j = i + 2; j <= i + 3 && j < c->layers.size() && a < 0; ++j) {
+      const f8_layer_desc &A = c->layers[j];
+      if (pointwise(j) && A.src == T.dst && A.res < 0 && A.dst2 <= 0 && (A.Cout == L.Cin || A.Cout == 2 * L.Cin) && shift(A) >= 0) a = (int)j;
+    }
+    if (!bottleneck_applicable(L.Cin, g.H, g.W, L.stride_h, a < 0 ? 0 : c->layers[a].Cout, shift(L), shift(T), a < 0 ? 0 : shift(c->layers[a]),
+                               T.dst2 > 0 ? T.q.fl_x + T.q.fl_w - T.q2.fl_y : 0, T.res >= 0 ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0))
+      continue;
+    c->bn[i] = 1; c->bn[i + 1] = 2;
+    c->bn_head[i] = c->bn_head[i + 1] = (int)i;
+    c->bn_behind[i] = a;
+    if (a >= 0) { c->bn[a] = 3; c->bn_head[a] = (int)i; }
   }
   // a depthwise 3x3 layer and the 1x1 layer that is its only reader
   c->dw_pw = tuning().dw_pw.load();
@@ -777,10 +894,10 @@ f8_status f8_chain_workspace_bytes(const f8_chain *cc, int batch, size_t *bytes)
   // program has to hold every smaller one too.  Where a smaller arena saves more than all copies take, nothing more
   // can be needed; a chain whose arena is next to nothing gets room for all of them instead of a long search.
   size_t copies = 0, most = 0;
-  for (size_t i = 0; i < c->layers.size(); ++i) copies += round256(c->img_w_bytes[i]) + round256(c->dwp_w_bytes[i]);
+  for (size_t i = 0; i < c->layers.size(); ++i) copies += round256(c->img_w_bytes[i]) + round256(c->dwp_w_bytes[i]) + round256(c->bn_w_bytes(i));
   for (int b = batch; b >= 0 && c->arena_per_image * (size_t)(batch - b) <= copies; --b) {
     const bool far = batch - b >= 1024;
-    most = std::max(most, c->arena_per_image * (size_t)b + (far ? copies : c->place_fragments(b, nullptr)));
+    most = std::max(most, c->arena_per_image * (size_t)b + (far ? copies : c->place_fragments(b, nullptr, nullptr)));
     if (far) break;
   }
   *bytes = c->const_bytes + most + 256;
@@ -794,7 +911,7 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
   if (!c->planned) c->plan();
   hipStream_t s = static_cast<hipStream_t>(stream);
   c->prepared_ws = nullptr;
-  c->place_fragments(batch, c->frag_off.data());
+  c->place_fragments(batch, c->frag_off.data(), c->bn_off.data());
   if (hipMemsetAsync(workspace, 0, 256, s) != hipSuccess) return F8_ERR_DEVICE;
   for (size_t i = 0; i < c->layers.size(); ++i) {
     const f8_layer_desc &L = c->layers[i];
@@ -814,6 +931,17 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
       return F8_ERR_DEVICE;
     if (c->frag_off[i] != 0 &&
         launch_conv_img_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->frag_off[i]), L.Cin, s) != 0)
+      return F8_ERR_DEVICE;
+  }
+  for (size_t i = 0; i < c->layers.size(); ++i) {
+    if (c->bn_off[i] == 0) continue;
+    const f8_layer_desc &L = c->layers[i], &T = c->layers[i + 1];
+    const int a = c->bn_behind[i];
+    uint8_t *cb = static_cast<uint8_t *>(workspace);
+    auto start = [&](size_t l) { return reinterpret_cast<const int32_t *>(cb + c->acc0_off[l]); };
+    const int res_bias = T.res >= 0 && T.q.res_type == F8_U8 ? 128 << (T.q.fl_x + T.q.fl_w - T.q.fl_res) : 0;
+    if (launch_bottleneck_weights(L.w, T.w, a < 0 ? nullptr : c->layers[a].w, start(i), start(i + 1), a < 0 ? nullptr : start(a),
+                                  reinterpret_cast<int8_t *>(cb + c->bn_off[i]), L.Cin, c->bn_channels(i), res_bias, s) != 0)
       return F8_ERR_DEVICE;
   }
   for (size_t i = 0; i < c->layers.size(); ++i) {
@@ -897,7 +1025,8 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
   if (!c->planned) const_cast<f8_chain *>(c)->plan();
   const Tensor &t = c->tensors[id];
   // tensors inside a fused block are never materialised
-  const bool elided = (t.producer >= 0 && (c->pool_role((size_t)t.producer) == 1 || c->dwp_role((size_t)t.producer, batch) == 1)) ||
+  const bool elided = (t.producer >= 0 && (c->pool_role((size_t)t.producer) == 1 || c->dwp_role((size_t)t.producer, batch) == 1 ||
+                                             c->bn_role((size_t)t.producer, batch) == 1)) ||
                       (c->use_fusion() && t.producer >= 0 && c->fused[t.producer].role != 0 &&
                        !(c->fused[t.producer].role == 2 && t.producer >= 2 && c->fused[t.producer - 2].role == 1));
   // (with two streams the two halves of a tensor lie apart: not reported)
@@ -991,7 +1120,8 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
     if (alg_bytes) *alg_bytes = fb;
     return F8_OK;
   }
-  if (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2) {
+  const int three = c->bn_role((size_t)layer, batch);
+  if (three > 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
     // accounted to the layer in front, whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {
@@ -1017,12 +1147,23 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       gk.B = batch;
       gk.P = g.P; gk.Q = g.Q;
       const int img = c->img_role((size_t)layer, batch);
-      if (img > 1) name = L.Cin == 64 ? "conv3x3_imgk<64>" : L.Cin == 128 ? "conv3x3_imgk<128>" : L.Cin == 256 ? "conv3x3_imgk<256>" : "conv3x3_imgk<512>";
+      if (three == 1) name = L.Cin == 64 ? "bottleneck<64>" : L.Cin == 128 ? "bottleneck<128>" : "bottleneck<256>";
+      else if (img > 1) name = L.Cin == 64 ? "conv3x3_imgk<64>" : L.Cin == 128 ? "conv3x3_imgk<128>" : L.Cin == 256 ? "conv3x3_imgk<256>" : "conv3x3_imgk<512>";
       else if (img == 1) name = L.Cin == 256 ? "conv3x3_img<256x256>" : "conv3x3_img<128x128>";
       else name = conv_kernel_name(gk, L.q, L.res >= 0, L.dst2 > 0 ? &L.q2 : nullptr);
       ops = 2.0 * M * g.R * g.S * g.Cin * g.Cout;
       bytes += (double)g.R * g.S * g.Cin * g.Cout + 4.0 * g.Cout;
-      if (with_tail) {
+      if (three == 1) {
+        // plus the closing layer (residual in, one or two formats out) and the layer behind it
+        const f8_layer_desc &T = c->layers[layer + 1];
+        ops += 2.0 * M * (double)T.Cin * T.Cout;
+        bytes += M * ((double)T.Cout * (1 + (T.res >= 0) + (T.dst2 > 0)) - L.Cout) + (double)T.Cin * T.Cout + 4.0 * T.Cout;
+        if (c->bn_behind[layer] >= 0) {
+          const f8_layer_desc &A = c->layers[c->bn_behind[layer]];
+          ops += 2.0 * M * (double)A.Cin * A.Cout;
+          bytes += M * A.Cout + (double)A.Cin * A.Cout + 4.0 * A.Cout;
+        }
+      } else if (with_tail) {
         // plus the 1x1 layer behind it: its output and weights; its input never leaves the chip
         const f8_layer_desc &T = c->layers[c->tail_peer[layer]];
         name = L.Cin == 128 ? "pw1x1_mid<128x512>+1x1<128>" : (T.Cout == 64 ? "pw1x1_ws<64x256>+1x1<64>" : "pw1x1_ws<64x256>+1x1<128>");

@@ -173,6 +173,9 @@ struct f8_chain {
   // behind that in one launch: bn[i] = 1 for the first, 2 and 3 for the others; bn_head[i] = the first layer, bn_behind[i]
   // (of the first) = the third or -1.  Whether the three run as one launch depends on the batch.
   std::vector<int> bn, bn_head, bn_behind;   // per layer
+  // Where the first layer's copy of the weights lies among the constants (64 and 128 channels, 70 and 278 KB, which almost every
+  // batch takes); 0: behind the arena, where the batch takes it (256 channels, 1.1 MB).
+  std::vector<size_t> bn_const_off;          // per layer
   int bottleneck = 1;
   int bn_channels(size_t head) const { return bn_behind[head] < 0 ? 0 : layers[bn_behind[head]].Cout; }
   size_t bn_w_bytes(size_t i) const { return bn[i] == 1 ? bottleneck_weight_bytes(layers[i].Cin, bn_channels(i)) : 0; }
@@ -219,8 +222,8 @@ struct f8_chain {
       }
       if (off) off[i] = img || pair ? base + bytes : 0;
       if (img || pair) bytes += round256(img ? img_w_bytes[i] : dwp_w_bytes[i]);
-      if (boff) boff[i] = three ? base + bytes : 0;
-      if (three) bytes += round256(bn_w_bytes(i));
+      if (boff) boff[i] = !three ? 0 : bn_const_off[i] != 0 ? bn_const_off[i] : base + bytes;
+      if (three && bn_const_off[i] == 0) bytes += round256(bn_w_bytes(i));
     }
     return bytes;
   }
@@ -722,6 +725,7 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->bn_head.push_back(-1);
     c->bn_behind.push_back(-1);
     c->bn_off.push_back(0);
+    c->bn_const_off.push_back(0);
   }
   if (st != F8_OK) { delete c; return st; }
   c->last_tensor = c->layers.back().dst;
@@ -806,6 +810,10 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->bn_head[i] = c->bn_head[i + 1] = (int)i;
     c->bn_behind[i] = a;
     if (a >= 0) { c->bn[a] = 3; c->bn_head[a] = (int)i; }
+    if (L.Cin <= 128) {
+      c->bn_const_off[i] = c->const_bytes;
+      c->const_bytes += round256(c->bn_w_bytes(i));
+    }
   }
   // a depthwise 3x3 layer and the 1x1 layer that is its only reader
   c->dw_pw = tuning().dw_pw.load();
@@ -894,7 +902,7 @@ f8_status f8_chain_workspace_bytes(const f8_chain *cc, int batch, size_t *bytes)
   // program has to hold every smaller one too.  Where a smaller arena saves more than all copies take, nothing more
   // can be needed; a chain whose arena is next to nothing gets room for all of them instead of a long search.
   size_t copies = 0, most = 0;
-  for (size_t i = 0; i < c->layers.size(); ++i) copies += round256(c->img_w_bytes[i]) + round256(c->dwp_w_bytes[i]) + round256(c->bn_w_bytes(i));
+  for (size_t i = 0; i < c->layers.size(); ++i) copies += round256(c->img_w_bytes[i]) + round256(c->dwp_w_bytes[i]) + (c->bn_const_off[i] == 0 ? round256(c->bn_w_bytes(i)) : 0);
   for (int b = batch; b >= 0 && c->arena_per_image * (size_t)(batch - b) <= copies; --b) {
     const bool far = batch - b >= 1024;
     most = std::max(most, c->arena_per_image * (size_t)b + (far ? copies : c->place_fragments(b, nullptr, nullptr)));

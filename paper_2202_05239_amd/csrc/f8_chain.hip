@@ -35,6 +35,7 @@
 #include "block_fused.h"
 #include "bottleneck.h"
 #include "dw_pw.h"
+#include "pw_dw_pw.h"
 #include "stem_pool.h"
 #include "conv_img.h"
 #include "conv_imgk.h"
@@ -168,6 +169,22 @@ struct f8_chain {
     const long long total = (long long)batch * g.P * g.Q * g.Cin;
     const long long most = g.Q > 64 ? 2ll << 20 : g.Q > 28 ? 5ll << 19 : g.Q > 14 ? 9ll << 19 : g.Q > 7 ? 7ll << 20 : 2ll << 20;
     return total <= most && dw_pw_slices(g.Cin, layers[i + 1].Cout) <= 20;
+  }
+  // The 1x1 layer in front of such a pair, whose only reader the depthwise layer is, in the same launch (an inverted-residual
+  // block): pdp[i] = 1 for the front one; its constants lie at pdp_off[i]: weights in fragment order, depthwise weights, start values.
+  std::vector<int> pdp;                // per layer
+  std::vector<size_t> pdp_off;         // per layer (of the front one)
+  int pw_dw_pw = 1;
+  // Wherever the pair is one launch the three are too: microseconds of front layer and pair, two launches -> one (two launches
+  // cost 1 - 2 us more in a forward than alone), MobileNetV2: 28 x 28 C192, batch 1 8.5 -> 6.7, 27 13.8 -> 8.5; 14 x 14 C384, batch 1 7.6 -> 5.4, 27 11.2 ->
+  // 6.6, 64 12.5 -> 9.0, 96 17.2 -> 11.2; C576, batch 1 8.9 -> 7.6, 27 12.8 -> 9.0, 64 17.5 -> 11.9; 28 x 28 C192 stride 2, batch 64 15.5 -> 8.2, 192 26.6 ->
+  // 18.8; 56 x 56 C144, batch 1 11.2 -> 5.7, stride 2, batch 27 14.6 -> 9.0, 40 16.1 -> 15.2.
+  // 1: front layer, 2: depthwise layer (which launches all three), 3: the one behind
+  int pdp_role(size_t i, int batch) const {
+    const int k = dwp[i];
+    const size_t front = k == 0 ? i : i - (size_t)k;
+    if ((k != 0 && i < (size_t)k) || pdp[front] == 0 || pw_dw_pw == 0 || dwp_role(front + 1, batch) != 1) return 0;
+    return 1 + k;
   }
   // A 3x3 layer, the 1x1 layer of four times its channels that is its only reader, and (where there is one) the 1x1 layer
   // behind that in one launch: bn[i] = 1 for the first, 2 and 3 for the others; bn_head[i] = the first layer, bn_behind[i]
@@ -321,6 +338,7 @@ struct f8_chain {
       }
       if (stem[li].on) stem[li].x_off_per_image = alloc(round256(stem[li].x_bytes_per_image));
       // written by this launch: must not share memory with what any of its layers reads
+      if (!keep_all && pdp[li] == 1) place(layers[li + 2].dst);
       if (!keep_all && dwp[li] == 1) place(layers[li + 1].dst);
       place(layers[li].dst);
       if (bn[li] == 1 && bn_allowed(li)) {
@@ -456,6 +474,29 @@ struct f8_chain {
     return p;
   }
 
+  // Parameters of the inverted-residual block that starts at layer i.
+  PwDwPwParams pdp_params(size_t i, const void *x, void *out, void *workspace, int batch) const {
+    const f8_layer_desc &L0 = layers[i], &L1 = layers[i + 1], &L2 = layers[i + 2];
+    const Geom &g = geom[i + 1];
+    uint8_t *cb = static_cast<uint8_t *>(workspace);
+    auto sign = [](int type) { return type == F8_U8 ? 0x80808080u : 0u; };
+    PwDwPwParams p;
+    p.x = static_cast<const uint8_t *>(tensor_ptr(L0.src, x, out, workspace, batch));
+    p.w1 = reinterpret_cast<const int8_t *>(cb + pdp_off[i]);
+    p.consts = p.w1 + round256(dw_pw_weight_bytes(L0.Cin, L0.Cout));
+    p.w2 = reinterpret_cast<const int8_t *>(cb + frag_off[i + 1]);
+    p.y = static_cast<uint8_t *>(tensor_ptr(L2.dst, x, out, workspace, batch));
+    p.B = batch; p.H = g.H; p.W = g.W; p.P = g.P; p.Q = g.Q; p.stride = g.sh;
+    p.Cin = L0.Cin; p.Ce = L0.Cout; p.Cout = L2.Cout;
+    p.x_xor = sign(L0.q.x_type); p.e_xor = sign(L0.q.y_type); p.d_xor = sign(L1.q.y_type);
+    p.shift1 = L0.q.fl_x + L0.q.fl_w - L0.q.fl_y; p.lo1 = L0.q.clip_lo; p.hi1 = L0.q.clip_hi;
+    p.shiftd = L1.q.fl_x + L1.q.fl_w - L1.q.fl_y; p.lod = L1.q.clip_lo; p.hid = L1.q.clip_hi;
+    p.shift2 = L2.q.fl_x + L2.q.fl_w - L2.q.fl_y; p.lo2 = L2.q.clip_lo; p.hi2 = L2.q.clip_hi;
+    p.has_res = L2.res >= 0;
+    p.res_d = p.has_res ? L2.q.fl_x + L2.q.fl_w - L2.q.fl_res : 0;
+    return p;
+  }
+
   f8_status launch_layer(size_t i, const void *x, void *out, void *workspace, int batch, hipStream_t s) const {
     const f8_layer_desc &L = layers[i];
     Geom g = geom[i];
@@ -488,6 +529,12 @@ struct f8_chain {
     if (three == 1 && bn_off[i] != 0) {
       const BottleneckParams bp = bottleneck_params(i, x, out, workspace, batch);
       return launch_bottleneck(bp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
+    }
+    const int block = pdp_role(i, batch);
+    if (block == 1 || block == 3) return F8_OK;
+    if (block == 2 && frag_off[i] != 0) {
+      const PwDwPwParams pp = pdp_params(i - 1, x, out, workspace, batch);
+      return launch_pw_dw_pw(pp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
     if (tail_role(i, batch) == 2 || dwp_role(i, batch) == 2) return F8_OK;
     if (dwp_role(i, batch) == 1) {
@@ -721,6 +768,8 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->dwp.push_back(0);
     c->dwp_w_bytes.push_back(0);
     c->frag_off.push_back(0);
+    c->pdp.push_back(0);
+    c->pdp_off.push_back(0);
     c->bn.push_back(0);
     c->bn_head.push_back(-1);
     c->bn_behind.push_back(-1);
@@ -833,6 +882,23 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->dwp[i + 1] = 2;
     c->dwp_w_bytes[i] = dw_pw_weight_bytes(L.Cin, T.Cout);
   }
+  // the 1x1 layer in front of such a pair; all tensors in the arena
+  c->pw_dw_pw = tuning().pw_dw_pw.load();
+  for (size_t i = 0; i + 2 < c->layers.size(); ++i) {
+    const f8_layer_desc &L = c->layers[i], &D = c->layers[i + 1], &T = c->layers[i + 2];
+    const Geom &g = c->geom[i + 1];
+    if (c->dwp[i] != 0 || c->dwp[i + 1] != 1 || L.op != F8_OP_CONV || D.src != L.dst || c->tensors[L.dst].last_use != (int)i + 1) continue;
+    if (L.R != 1 || L.S != 1 || L.stride_h != 1 || L.stride_w != 1 || L.pad_h != 0 || L.pad_w != 0 || L.res >= 0 || L.dst2 > 0 ||
+        L.q.y_type == F8_S32 || c->tail[i] != 0 || c->bn[i] != 0 || c->stem[i].pool != 0)
+      continue;
+    if (c->tensors[L.src].external || c->tensors[T.dst].external || (T.res >= 0 && T.res != L.src)) continue;
+    if (!pw_dw_pw_applicable(L.Cin, L.Cout, T.Cout, g.H, g.W, g.sh, L.q.fl_x + L.q.fl_w - L.q.fl_y, D.q.fl_x + D.q.fl_w - D.q.fl_y,
+                             T.q.fl_x + T.q.fl_w - T.q.fl_y, T.res >= 0, T.res >= 0 ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0, nullptr, nullptr))
+      continue;
+    c->pdp[i] = 1;
+    c->pdp_off[i] = c->const_bytes;
+    c->const_bytes += round256(dw_pw_weight_bytes(L.Cin, L.Cout)) + pw_dw_pw_const_bytes(L.Cout, T.Cout) + round256((size_t)(L.Cout + 31) / 32 * 128);
+  }
   // inverted-residual blocks that can run as one kernel
   for (size_t i = 0; i + 2 < c->layers.size(); ++i) {
     const f8_layer_desc &L0 = c->layers[i], &L1 = c->layers[i + 1], &L2 = c->layers[i + 2];
@@ -942,6 +1008,20 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
       return F8_ERR_DEVICE;
   }
   for (size_t i = 0; i < c->layers.size(); ++i) {
+    if (c->pdp[i] == 0) continue;
+    const f8_layer_desc &L = c->layers[i], &D = c->layers[i + 1], &T = c->layers[i + 2];
+    uint8_t *cb = static_cast<uint8_t *>(workspace);
+    int8_t *w1 = reinterpret_cast<int8_t *>(cb + c->pdp_off[i]);
+    int8_t *consts = w1 + round256(dw_pw_weight_bytes(L.Cin, L.Cout));
+    int32_t *accd = reinterpret_cast<int32_t *>(consts + pw_dw_pw_const_bytes(L.Cout, T.Cout));
+    auto start = [&](size_t l) { return reinterpret_cast<const int32_t *>(cb + c->acc0_off[l]); };
+    const int res_bias = T.res >= 0 && T.q.res_type == F8_U8 ? 128 << (T.q.fl_x + T.q.fl_w - T.q.fl_res) : 0;
+    int e = launch_dw_pw_weights(L.w, w1, L.Cin, L.Cout, s);
+    if (e == 0) e = launch_block_fold_dw(D.w, D.bias, accd, L.Cout, (L.Cout + 31) / 32 * 32, rounding_addend(D.q), D.q.x_type == F8_U8 ? 128 : 0, s);
+    if (e == 0) e = launch_pw_dw_pw_consts(D.w, start(i), accd, start(i + 2), consts, L.Cout, T.Cout, res_bias, s);
+    if (e != 0) return F8_ERR_DEVICE;
+  }
+  for (size_t i = 0; i < c->layers.size(); ++i) {
     if (c->bn_off[i] == 0) continue;
     const f8_layer_desc &L = c->layers[i], &T = c->layers[i + 1];
     const int a = c->bn_behind[i];
@@ -1034,6 +1114,7 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
   const Tensor &t = c->tensors[id];
   // tensors inside a fused block are never materialised
   const bool elided = (t.producer >= 0 && (c->pool_role((size_t)t.producer) == 1 || c->dwp_role((size_t)t.producer, batch) == 1 ||
+                                             c->pdp_role((size_t)t.producer, batch) == 1 ||
                                              c->bn_role((size_t)t.producer, batch) == 1)) ||
                       (c->use_fusion() && t.producer >= 0 && c->fused[t.producer].role != 0 &&
                        !(c->fused[t.producer].role == 2 && t.producer >= 2 && c->fused[t.producer - 2].role == 1));
@@ -1129,8 +1210,8 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
     return F8_OK;
   }
   const int three = c->bn_role((size_t)layer, batch);
-  if (three > 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
-    // accounted to the layer in front, whose launch computes this one
+  if (three > 1 || c->pdp_role((size_t)layer, batch) == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
+    // accounted to the layer in front (of the first layer of an inverted-residual block: behind), whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {
       int i = 0;
@@ -1187,6 +1268,14 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
         name = g.sh == 1 ? "dwconv3x3<s1>+1x1" : "dwconv3x3<s2>+1x1";
         ops = 2.0 * M * (9.0 * L.Cout + (double)T.Cin * T.Cout);
         bytes += M * (T.Cout - L.Cout) + (T.res >= 0 ? M * T.Cout : 0.0) + 13.0 * L.Cout + (double)T.Cin * T.Cout + 4.0 * T.Cout;
+        if (c->pdp_role((size_t)layer, batch) == 2) {
+          // and the 1x1 layer in front, all of whose pixels are needed; the shortcut is its input, read once
+          const f8_layer_desc &E = c->layers[layer - 1];
+          name = g.sh == 1 ? "1x1+dwconv3x3<s1>+1x1" : "1x1+dwconv3x3<s2>+1x1";
+          const double in = (double)batch * g.H * g.W;
+          ops += 2.0 * in * (double)E.Cin * E.Cout;
+          bytes += in * E.Cin - (double)batch * rows * cols * g.Cin - (T.res >= 0 ? M * T.Cout : 0.0) + (double)E.Cin * E.Cout + 4.0 * E.Cout;
+        }
         break;
       }
       name = (g.R == 3 && g.S == 3 && g.sh == g.sw && (g.sh == 1 || g.sh == 2) && g.Cin % 4 == 0 && L.res < 0 &&

@@ -1,0 +1,428 @@
+// An inverted-residual block (1x1 layer to Ce channels, depthwise 3x3 layer with stride 1 or 2, 1x1 layer back, identity
+// shortcut), F8Net Eq. 6 three times, in one launch.
+//
+// At small and medium batch the block's launches are bound by what a launch costs beyond its work (1.6 to 2.4 us behind
+// another one, cold operands, one wave's serial chain).  A workgroup of eight waves takes a few output rows of an image with
+// all channels: it computes the expanded rows under them (the rows above and below are computed by the neighbours
+// too: that is the price), keeps them in LDS with a border of zeros, runs the depthwise layer on them and the last layer on
+// that; only the block's input is read and its output written.
+//
+// The depthwise layer runs on the matrix cores: for 32 channels and one tap the left operand is the diagonal matrix of the
+// tap's weights (each lane masks its row's byte out of a replicated one), the right operand the pixels the tap meets, so a
+// block of 32 pixels x 32 channels takes nine matrix instructions on fragments that lie in LDS as they are.  The packed dot products
+// of dw_pw.hip need the bytes of neighbouring pixels side by side first: nine vector instructions per result where
+// this has six, of which none waits for a transposition.
+#include "pw_dw_pw.h"
+
+#include <atomic>
+
+namespace f8 {
+namespace {
+
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef __attribute__((address_space(3))) v4i lds_v4i;
+typedef __attribute__((address_space(3))) v2i lds_v2i;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+
+constexpr int NT = 512, NWAVE = NT / 64;
+constexpr int PART_PITCH = 32 * 4 + 16;
+
+// Division by a divisor that is known anyway.
+struct Div {
+  uint32_t mul, shr;
+  Div() = default;
+  __host__ explicit Div(int d) { const FastDiv f((uint32_t)d); mul = f.mul; shr = f.shr; }
+  __device__ __forceinline__ int of(int n) const { return (int)(__umulhi((uint32_t)n << 1, mul) >> shr); }
+};
+
+// What a launch needs, all of it loaded at once: a wave alone on its SIMD waits for every load of an argument.
+struct Args {
+  const uint8_t *x;
+  const int8_t *w1, *consts, *w2;
+  uint8_t *y;
+  int x_bytes, w1_bytes, const_bytes;
+  int H, W, P, Q, stride, c8, cout;    // c8: 8-byte pieces per input pixel
+  int rows, bands;           // output rows per workgroup, workgroups per image
+  int nb1, nb3;              // 32-channel blocks of Ce, Cout
+  int mb1, mb2;              // most blocks of 32 pixels: of expanded rows, of output rows
+  int m1, g1, m2, g2;        // in the first two layers: pixel blocks side by side, waves per pixel block
+  int xp, ep;                // bytes of a pixel in LDS: input; expanded and depthwise result
+  int at_const, at_e, at_d;  // LDS offsets (the input rows lie at 0)
+  int kg;                    // waves that share the last layer's K
+  int has_res, res_d;
+  uint32_t x_xor, e_xor, d_xor;
+  ScaledClip clip1, clipd;
+  int shift1, shiftd, shift2, lo2, hi2;
+  Div by_bands, by_m1, by_m2, by_w, by_q, by_c8, by_pe, by_np, by_u3, by_nb3;
+};
+
+// Behind the depthwise taps of a launch's constants: start values of the three layers.
+__host__ __device__ constexpr int tap_bytes(int nb1) { return nb1 * 32 * 9 * 4; }
+
+__device__ __forceinline__ v4i lds_read(uint32_t at) { return *(lds_v4i *)(uintptr_t)at; }
+__device__ __forceinline__ void lds_write(uint32_t at, v4i v) { *(lds_v4i *)(uintptr_t)at = v; }
+
+// 16 accumulators of a lane, already holding the rounding addend, to 16 bytes, in signed form.
+__device__ __forceinline__ v4i requant16(v16i &a, ScaledClip c, int shift, int x) {
+  settle_matrix_result(a);
+  int v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = clamp_med3(a[i], c.lo, c.hi);
+  const v4i r = shift_pack16(v, shift);
+  return v4i{r.x ^ x, r.y ^ x, r.z ^ x, r.w ^ x};
+}
+
+template <int KS1>
+__global__ __launch_bounds__(NT, 2) void pw_dw_pw_kernel(const Args a) {
+  pin_args(a.x, a.w1, a.consts, a.w2, a.y, a.x_bytes, a.w1_bytes, a.const_bytes, a.H, a.W, a.P, a.Q, a.stride, a.c8, a.cout, a.rows, a.bands,
+           a.nb1, a.nb3, a.mb1, a.mb2, a.m1, a.g1, a.m2, a.g2, a.xp, a.ep, a.at_const, a.at_e, a.at_d, a.kg, a.has_res, a.res_d, a.x_xor, a.e_xor, a.d_xor, a.clip1.lo,
+           a.clip1.hi, a.clipd.lo, a.clipd.hi, a.shift1, a.shiftd, a.shift2, a.lo2, a.hi2, a.by_bands.mul, a.by_bands.shr, a.by_m1.mul,
+           a.by_m1.shr, a.by_m2.mul, a.by_m2.shr, a.by_w.mul, a.by_w.shr, a.by_q.mul, a.by_q.shr, a.by_c8.mul, a.by_c8.shr, a.by_pe.mul,
+           a.by_pe.shr, a.by_np.mul, a.by_np.shr, a.by_u3.mul, a.by_u3.shr, a.by_nb3.mul, a.by_nb3.shr);
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const uint32_t base = (uint32_t)(uintptr_t)((lds_u8 *)lds);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  const int wg = (int)xcd_remap(blockIdx.x, gridDim.x);
+  const int img = a.by_bands.of(wg), p0 = (wg - img * a.bands) * a.rows;
+  const int out_rows = min(a.rows, a.P - p0);
+  const int ih0 = p0 * a.stride - 1, e_rows = (out_rows - 1) * a.stride + 3;
+  const int r_lo = max(ih0, 0), r_hi = min(ih0 + e_rows, a.H);        // input rows inside the image
+  const int npx = (r_hi - r_lo) * a.W, opx = out_rows * a.Q;
+
+  // ---- input rows: contiguous in memory, 8 bytes at a time (pixels of 24 bytes), into rows of whole fragments
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.x), 0, a.x_bytes, 0x00027000);
+  const int n8 = npx * a.c8, x_first = (img * a.H + r_lo) * a.W * a.c8 * 8;
+  constexpr int XU = 2;
+  v2i xv[XU];
+  auto fetch = [&](int i0) {
+#pragma unroll
+    for (int k = 0; k < XU; ++k) {
+      const int i = i0 + k * NT + tid;
+      xv[k] = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(xres, i < n8 ? (uint32_t)(x_first + i * 8) : 0x80000000u, 0, 0));
+    }
+  };
+  auto put = [&](int i0) {
+#pragma unroll
+    for (int k = 0; k < XU; ++k) {
+      const int i = i0 + k * NT + tid, px = a.by_c8.of(i);
+      if (i < n8) *(lds_v2i *)(uintptr_t)(base + px * a.xp + (i - px * a.c8) * 8) = v2i{xv[k].x ^ (int)a.x_xor, xv[k].y ^ (int)a.x_xor};
+    }
+  };
+  fetch(0);
+  // first weights of this wave
+  const __amdgpu_buffer_rsrc_t w1res = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(a.w1), 0, a.w1_bytes, 0x00027000);
+  const int slot1 = a.by_m1.of(wave), m1 = wave - slot1 * a.m1;
+  v4i wn[KS1];
+  auto load_w1 = [&](int nb) {
+#pragma unroll
+    for (int k = 0; k < KS1; ++k)
+      wn[k] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(w1res, lane * 16, (nb * KS1 + k) * 1024, 0));
+  };
+  load_w1(slot1);
+  // ---- depthwise weights and start values, straight into LDS
+  {
+    const __amdgpu_buffer_rsrc_t cres = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(a.consts), 0, a.const_bytes, 0x00027000);
+    for (int at = wave * 1024; at < a.const_bytes; at += NWAVE * 1024)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(cres, (lds_void *)(lds + a.at_const + at), 16, lane * 16, at, 0, 0);
+  }
+  // ---- zeros around the expanded rows: the columns beside the image, and whole rows above or below it
+  {
+    const int ez = (int)a.e_xor, pe = a.ep >> 4, ew = a.W + 2;
+    for (int i = tid; i < e_rows * 2 * pe; i += NT) {
+      const int cell = a.by_pe.of(i);
+      lds_write(base + a.at_e + ((cell >> 1) * ew + (cell & 1) * (ew - 1)) * a.ep + (i - cell * pe) * 16, v4i{ez, ez, ez, ez});
+    }
+    if (r_hi - r_lo < e_rows)
+      for (int i = tid; i < a.W * pe; i += NT) {
+        const int cell = a.by_pe.of(i);
+        const uint32_t to = base + a.at_e + (1 + cell) * a.ep + (i - cell * pe) * 16;
+        if (ih0 < 0) lds_write(to, v4i{ez, ez, ez, ez});
+        if (r_hi == a.H) for (int r = a.H - ih0; r < e_rows; ++r) lds_write(to + r * ew * a.ep, v4i{ez, ez, ez, ez});
+      }
+  }
+  put(0);
+  for (int i0 = XU * NT; i0 < n8; i0 += XU * NT) { fetch(i0); put(i0); }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the constants have arrived
+  __syncthreads();
+
+  auto start16 = [&](int block) {
+    v16i v;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const v4i s = lds_read(base + a.at_const + tap_bytes(a.nb1) + block * 128 + half * 64 + g * 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[4 * g + i] = s[i];
+    }
+    return v;
+  };
+
+  // ---- first layer: a wave keeps its block of pixels and takes every g1-th block of channels
+  if (slot1 < a.g1) {
+    for (int mb = m1; mb < a.mb1; mb += a.m1) {
+      const int i = mb * 32 + l32, r = a.by_w.of(i), c = i - r * a.W;
+      const uint32_t from = base + min(i, npx - 1) * a.xp + half * 16;
+      const uint32_t to = base + a.at_e + ((r + r_lo - ih0) * (a.W + 2) + c + 1) * a.ep + half * 16;
+      v4i xf[KS1];
+#pragma unroll
+      for (int k = 0; k < KS1; ++k) xf[k] = lds_read(from + k * 32);
+      for (int nb = slot1; nb < a.nb1; nb += a.g1) {
+        v16i acc = start16(nb);
+#pragma unroll
+        for (int k = 0; k < KS1; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wn[k], xf[k], acc, 0, 0, 0);
+        const int next = nb + a.g1 < a.nb1 ? nb + a.g1 : slot1;
+        load_w1(next);
+        const v4i v = requant16(acc, a.clip1, a.shift1, (int)a.e_xor);
+        if (i < npx) lds_write(to + nb * 32, v);
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- last layer's first weights, requested ahead of the depthwise layer
+  const int part = a.by_u3.of(wave), unit = wave - part * (a.nb3 * a.mb2);
+  const int mbi = a.by_nb3.of(unit), nbi = unit - mbi * a.nb3;
+  const bool active = part < a.kg;
+  const int8_t *wf = a.w2 + ((size_t)nbi * a.nb1 * 64 + lane) * 16;
+  constexpr int PF = 4;
+  v4i wq[PF];
+  if (active) {
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      const int s = part + i * a.kg;
+      wq[i] = *reinterpret_cast<const v4i *>(wf + (size_t)(s < a.nb1 ? s : part) * 1024);
+    }
+  }
+  // ---- depthwise layer: the same over output pixels.  (The nine products are one chain, each waiting 64 cycles for the last,
+  // half of them idle: the other wave of the SIMD has them.)
+  const int slot2 = a.by_m2.of(wave);
+  if (slot2 < a.g2) {
+    // the lane's row of the diagonal matrix: channel weight_row(l32) of the block, its byte among the lane's 16
+    const int ch = weight_row(l32);
+    uint32_t mask[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) mask[d] = (ch >> 4) == half && ((ch >> 2) & 3) == d ? 0xffu << (8 * (ch & 3)) : 0u;
+    for (int mb = wave - slot2 * a.m2; mb < a.mb2; mb += a.m2) {
+      const int j = mb * 32 + l32, jc = min(j, opx - 1), pr = a.by_q.of(jc), q = jc - pr * a.Q;
+      const uint32_t first = base + a.at_e + (pr * a.stride * (a.W + 2) + q * a.stride) * a.ep + half * 16;
+      const uint32_t to = base + a.at_d + j * a.ep + half * 16;
+      for (int cb = slot2; cb < a.nb1; cb += a.g2) {
+        const uint32_t taps = base + a.at_const + cb * (9 * 128) + ch * 4;
+        uint32_t t9[9], at = first + cb * 32;
+        v4i f[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          t9[t] = *(lds_u32 *)(uintptr_t)(taps + t * 128);
+          f[t] = lds_read(at);
+          at += t % 3 == 2 ? a.W * a.ep : a.ep;
+        }
+        v16i acc = start16(a.nb1 + cb);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          const v4i d = {(int)(t9[t] & mask[0]), (int)(t9[t] & mask[1]), (int)(t9[t] & mask[2]), (int)(t9[t] & mask[3])};
+          acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(d, f[t], acc, 0, 0, 0);
+        }
+        lds_write(to + cb * 32, requant16(acc, a.clipd, a.shiftd, (int)a.d_xor));
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- last layer: waves share the output blocks and, where there are fewer than waves, K
+  if (active) {
+    v16i acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0;
+    const uint32_t from = base + a.at_d + (mbi * 32 + l32) * a.ep + half * 16;
+    for (int s0 = part; s0 < a.nb1; s0 += PF * a.kg) {
+      v4i xf[PF];
+#pragma unroll
+      for (int i = 0; i < PF; ++i) {
+        const int s = s0 + i * a.kg;
+        xf[i] = lds_read(from + (s < a.nb1 ? s : part) * 32);
+      }
+#pragma unroll
+      for (int i = 0; i < PF; ++i) {
+        const int s = s0 + i * a.kg;
+        if (s < a.nb1) {                             // uniform
+          acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wq[i], xf[i], acc, 0, 0, 0);
+          const int ahead = s + PF * a.kg;
+          if (ahead < a.nb1) wq[i] = *reinterpret_cast<const v4i *>(wf + (size_t)ahead * 1024);
+        }
+      }
+    }
+    // (the expanded rows are no longer read: their place takes the sums)
+    const uint32_t to = base + a.at_e + ((part * a.mb2 + mbi) * a.nb3 + nbi) * (32 * PART_PITCH) + l32 * PART_PITCH + half * 64;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) lds_write(to + g * 16, v4i{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]});
+  }
+  __syncthreads();
+  const size_t y_first = ((size_t)img * a.P + p0) * a.Q;
+  const int shortcut = (p0 - r_lo) * a.W, np = a.cout >> 2;
+  for (int it = tid; it < opx * np; it += NT) {
+    const int m = a.by_np.of(it), n = (it - m * np) * 4;
+    v4i v = lds_read(base + a.at_const + tap_bytes(a.nb1) + 2 * a.nb1 * 128 + n * 4);
+    for (int k = 0; k < a.kg; ++k)
+      v += lds_read(base + a.at_e + ((k * a.mb2 + (m >> 5)) * a.nb3 + (n >> 5)) * (32 * PART_PITCH) + (m & 31) * PART_PITCH + (n & 31) * 4);
+    if (a.has_res) {
+      const uint32_t r = *(lds_u32 *)(uintptr_t)(base + (m + shortcut) * a.xp + n);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] += (int)(int8_t)(r >> (8 * i)) << a.res_d;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = requant<false>(v[i], a.shift2, a.lo2, a.hi2);
+    *reinterpret_cast<uint32_t *>(a.y + (y_first + m) * a.cout + n) = pack4(v.x, v.y, v.z, v.w);
+  }
+}
+
+// The constants: dword [block of 32 channels][tap][c] = the tap's weight of channel c in all four bytes (zeros past Ce), then the start values of
+// the three layers, the last with what makes an unsigned shortcut signed.
+__global__ __launch_bounds__(256) void pw_dw_pw_consts_kernel(const int8_t *__restrict__ wd, const int32_t *__restrict__ acc1,
+                                                              const int32_t *__restrict__ accd, const int32_t *__restrict__ acc2,
+                                                              int32_t *__restrict__ to, int Ce, int padded, int n3, int res_bias) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < 9 * padded) {
+    const int c = i / 288 * 32 + i % 32, tap = i / 32 % 9;
+    to[i] = c < Ce ? (int)((uint32_t)(uint8_t)wd[(size_t)tap * Ce + c] * 0x01010101u) : 0;
+  } else if (i < 10 * padded) {
+    to[i] = acc1[i - 9 * padded];
+  } else if (i < 11 * padded) {
+    to[i] = accd[i - 10 * padded];
+  } else if (i < 11 * padded + n3) {
+    to[i] = acc2[i - 11 * padded] + res_bias;
+  }
+}
+
+constexpr int LDS_MOST = 160 * 1024;
+constexpr int KS1_MOST = 6;
+
+struct Shape {
+  int rows, bands, mb1, mb2, xp, ep, at_const, at_e, at_d, bytes;
+};
+
+// LDS and blocks of a launch with `rows` output rows per workgroup.
+Shape shape_of(int Cin, int Ce, int Cout, int H, int W, int P, int Q, int stride, int rows) {
+  Shape s;
+  s.rows = rows;
+  s.bands = (P + rows - 1) / rows;
+  const int e_rows = (rows - 1) * stride + 3, in_rows = e_rows < H ? e_rows : H, nb1 = (Ce + 31) / 32, nb3 = (Cout + 31) / 32;
+  s.mb1 = (in_rows * W + 31) / 32;
+  s.mb2 = (rows * Q + 31) / 32;
+  s.xp = (Cin + 31) / 32 * 32 + 16;
+  s.ep = nb1 * 32 + 16;
+  s.at_const = (in_rows * W * s.xp + 15) / 16 * 16;
+  s.at_e = s.at_const + (int)pw_dw_pw_const_bytes(Ce, Cout);
+  const int kg = nb3 * s.mb2 <= NWAVE ? NWAVE / (nb3 * s.mb2) : 1;
+  const int e = e_rows * (W + 2) * s.ep, sums = kg * nb3 * s.mb2 * 32 * PART_PITCH;
+  s.at_d = s.at_e + (e > sums ? e : sums);
+  s.bytes = s.at_d + s.mb2 * 32 * s.ep;
+  return s;
+}
+
+// Rows per workgroup, by what a launch of them would take: set-up and the units of the first two layers that a wave works
+// through one after the other, in rounds of 256 workgroups, of which two share a CU at 0.8 of the time each where they fit.
+// 0: no number of rows fits.
+int rows_for(int Cin, int Ce, int Cout, int H, int W, int P, int Q, int stride, int B) {
+  const int nb1 = (Ce + 31) / 32, nb3 = (Cout + 31) / 32, ks1 = (Cin + 31) / 32;
+  int best = 0;
+  long long least = 0;
+  for (int rows = 1; rows <= P; ++rows) {
+    const Shape s = shape_of(Cin, Ce, Cout, H, W, P, Q, stride, rows);
+    if (s.bytes > LDS_MOST || nb3 * s.mb2 > NWAVE) break;
+    auto units = [&](int mb) {
+      const int m = mb < NWAVE ? mb : NWAVE, g = NWAVE / m;
+      return (long long)((mb + m - 1) / m) * ((nb1 + g - 1) / g);
+    };
+    const int kg = NWAVE / (nb3 * s.mb2);
+    const long long one = 3500 + units(s.mb1) * (450 + 60 * ks1) + units(s.mb2) * 900 + (nb1 + kg - 1) / kg * 150;
+    const long long rounds = ((long long)B * s.bands + 255) / 256;
+    const long long cost = 2 * s.bytes <= LDS_MOST ? one * (rounds / 2 * 16 + rounds % 2 * 10) : one * rounds * 10;
+    if (best == 0 || cost < least) { best = rows; least = cost; }
+  }
+  return best;
+}
+
+template <int KS1>
+int launch_one(const Args &a, int lds, long long grid, hipStream_t stream) {
+  auto k = pw_dw_pw_kernel<KS1>;
+  static std::atomic<unsigned long long> done_mask{0};         // devices whose LDS limit has been raised
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return (int)hipErrorInvalidDevice;
+  if (dev < 0 || dev > 63 || !((done_mask.load(std::memory_order_relaxed) >> dev) & 1ull)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MOST);
+    if (e != hipSuccess) return (int)e;
+    if (dev >= 0 && dev <= 63) done_mask.fetch_or(1ull << dev, std::memory_order_relaxed);
+  }
+  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(NT), lds, stream, a);
+  return (int)hipGetLastError();
+}
+
+}  // namespace
+
+bool pw_dw_pw_applicable(int Cin, int Ce, int Cout, int H, int W, int stride, int shift1, int shiftd, int shift2, bool has_res, int res_d,
+                         const void *x, const void *y) {
+  if (Cin < 8 || (Cin & 7) || Cin > 32 * KS1_MOST || Ce < 16 || Ce > 1024 || Cout < 8 || (Cout & 7) || Cout > 256) return false;
+  if ((stride != 1 && stride != 2) || H < 1 || W < 1 || W > 1024 || shift1 < 0 || shiftd < 0 || shift2 < 0) return false;
+  if (has_res && (stride != 1 || Cin != Cout || res_d < 0 || res_d > 16)) return false;
+  if ((reinterpret_cast<uintptr_t>(x) & 7) || (reinterpret_cast<uintptr_t>(y) & 3)) return false;
+  return rows_for(Cin, Ce, Cout, H, W, (H - 1) / stride + 1, (W - 1) / stride + 1, stride, 1) > 0;
+}
+
+size_t pw_dw_pw_const_bytes(int Ce, int Cout) {
+  const size_t nb1 = (Ce + 31) / 32, nb3 = (Cout + 31) / 32;
+  return (tap_bytes((int)nb1) + (2 * nb1 + nb3) * 128 + 1023) / 1024 * 1024;
+}
+
+int launch_pw_dw_pw_consts(const int8_t *wd, const int32_t *acc1, const int32_t *accd, const int32_t *acc2, int8_t *to, int Ce, int Cout, int res_bias,
+                           hipStream_t stream) {
+  const int padded = (Ce + 31) / 32 * 32, n3 = (Cout + 31) / 32 * 32;
+  hipLaunchKernelGGL(pw_dw_pw_consts_kernel, dim3((11 * padded + n3 + 255) / 256), dim3(256), 0, stream, wd, acc1, accd, acc2,
+                     reinterpret_cast<int32_t *>(to), Ce, padded, n3, res_bias);
+  return (int)hipGetLastError();
+}
+
+int launch_pw_dw_pw(const PwDwPwParams &p, hipStream_t stream) {
+  if (p.B <= 0) return 0;
+  if (!pw_dw_pw_applicable(p.Cin, p.Ce, p.Cout, p.H, p.W, p.stride, p.shift1, p.shiftd, p.shift2, p.has_res != 0, p.res_d, p.x, p.y) ||
+      ((reinterpret_cast<uintptr_t>(p.w1) | reinterpret_cast<uintptr_t>(p.consts) | reinterpret_cast<uintptr_t>(p.w2)) & 15) ||
+      (long long)p.B * p.H * p.W * p.Cin > 0x7fffffffLL)
+    return (int)hipErrorInvalidValue;
+  const int rows = rows_for(p.Cin, p.Ce, p.Cout, p.H, p.W, p.P, p.Q, p.stride, p.B);
+  const Shape s = shape_of(p.Cin, p.Ce, p.Cout, p.H, p.W, p.P, p.Q, p.stride, rows);
+  const int ks1 = (p.Cin + 31) / 32;
+  Args a;
+  a.x = p.x; a.w1 = p.w1; a.consts = p.consts; a.w2 = p.w2; a.y = p.y;
+  a.H = p.H; a.W = p.W; a.P = p.P; a.Q = p.Q; a.stride = p.stride; a.c8 = p.Cin / 8; a.cout = p.Cout;
+  a.rows = rows; a.bands = s.bands;
+  a.nb1 = (p.Ce + 31) / 32; a.nb3 = (p.Cout + 31) / 32;
+  a.mb1 = s.mb1; a.mb2 = s.mb2;
+  a.m1 = a.mb1 < NWAVE ? a.mb1 : NWAVE; a.g1 = NWAVE / a.m1;
+  a.m2 = a.mb2 < NWAVE ? a.mb2 : NWAVE; a.g2 = NWAVE / a.m2;
+  a.xp = s.xp; a.ep = s.ep;
+  a.at_const = s.at_const; a.at_e = s.at_e; a.at_d = s.at_d;
+  a.kg = NWAVE / (a.nb3 * a.mb2) < a.nb1 ? NWAVE / (a.nb3 * a.mb2) : a.nb1;
+  a.x_bytes = p.B * p.H * p.W * p.Cin;
+  a.w1_bytes = a.nb1 * ks1 * 1024;
+  a.const_bytes = (int)pw_dw_pw_const_bytes(p.Ce, p.Cout);
+  a.has_res = p.has_res; a.res_d = p.res_d;
+  a.x_xor = p.x_xor; a.e_xor = p.e_xor; a.d_xor = p.d_xor;
+  a.clip1 = scaled_clip(p.lo1, p.hi1, p.shift1);
+  a.clipd = scaled_clip(p.lod, p.hid, p.shiftd);
+  a.shift1 = p.shift1; a.shiftd = p.shiftd; a.shift2 = p.shift2; a.lo2 = p.lo2; a.hi2 = p.hi2;
+  a.by_bands = Div(s.bands); a.by_m1 = Div(a.m1); a.by_m2 = Div(a.m2); a.by_w = Div(p.W); a.by_q = Div(p.Q); a.by_c8 = Div(a.c8);
+  a.by_pe = Div(s.ep / 16); a.by_np = Div(p.Cout / 4); a.by_u3 = Div(a.nb3 * a.mb2); a.by_nb3 = Div(a.nb3);
+  const long long grid = (long long)p.B * s.bands;
+  if (grid > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+  switch (ks1) {
+    case 1: return launch_one<1>(a, s.bytes, grid, stream);
+    case 2: return launch_one<2>(a, s.bytes, grid, stream);
+    case 3: return launch_one<3>(a, s.bytes, grid, stream);
+    case 4: return launch_one<4>(a, s.bytes, grid, stream);
+    case 5: return launch_one<5>(a, s.bytes, grid, stream);
+    default: return launch_one<6>(a, s.bytes, grid, stream);
+  }
+}
+
+}  // namespace f8

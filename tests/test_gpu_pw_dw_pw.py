@@ -1,0 +1,85 @@
+"""An inverted-residual block (1x1, depthwise 3x3, 1x1, shortcut) in one launch."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2202_05239_amd import binding as f8
+from paper_2202_05239_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# input, expanded, output channels, image, batch, stride, expanded signed, depthwise signed, output relu, shortcut
+CASES = [
+    (24, 144, 24, (56, 56), 2, 1, False, False, False, True),       # rows of 24 bytes, a last block of 16 channels
+    (64, 384, 64, (14, 14), 3, 1, False, False, False, True),
+    (96, 576, 160, (14, 14), 2, 2, False, False, False, False),
+    (16, 96, 24, (27, 31), 3, 2, True, False, True, False),         # odd extents under stride 2
+    (160, 640, 160, (7, 7), 2, 1, False, True, True, True),         # unsigned shortcut, five slices of K
+    (192, 32, 8, (5, 3), 7, 1, True, True, False, False),           # six slices, one block, eight channels out
+    (8, 16, 8, (1, 1), 9, 1, False, False, False, True),            # one pixel: every tap but the middle one outside
+    (32, 192, 32, (1, 40), 2, 1, False, True, False, True),         # one row: border rows on both sides
+    (40, 272, 248, (9, 2), 3, 2, True, False, True, False),         # eight blocks of output channels
+]
+
+
+def build(k):
+    cin, ce, cout, hw, batch, stride, es, ds, relu, res = CASES[k]
+    rng = np.random.default_rng(52000 + k)
+    b = wl._NetBuilder("block%d" % k, rng, hw[0], 16, "u8", 5, (5, 9), (2, 6), True)
+    b.net.in_hw = hw
+    b.t[0]["hw"] = hw
+    t = b.conv("before", 0, cin, 1, 1, 0, relu=relu)
+    u = b.conv("expand", t, ce, 1, 1, 0, relu=not es)
+    u = b.dwconv("dw", u, 3, stride, 1)
+    if ds:
+        L = b.net.layers[-1]
+        L.y_type, L.clip_lo, L.clip_hi = "s8", -127, 100
+        b.t[u]["type"] = "s8"
+    if k == 2:
+        b.net.layers[-1].bias = None
+    y = b.conv("project", u, cout, 1, 1, 0, relu=relu, res=t if res else -1)
+    b.conv("after", y, 32, 1, 1, 0)
+    return wl.draw_u8(rng, (batch,) + hw + (16,)), b.net
+
+
+@pytest.mark.parametrize("k", range(len(CASES)))
+def test_inverted_residual_block_in_one_launch(oracle, k):
+    x, net = build(k)
+    batch, stride = x.shape[0], CASES[k][5]
+    want = oracle.run_network(net, x, keep_all=True)
+    x_t = torch.from_numpy(x).cuda()
+    f8.f8_tuning_set("dw_pw", 2)
+    try:
+        for force in (0, 2):
+            f8.f8_tuning_set("pw_dw_pw", force)
+            chain = f8.Chain(net).prepare(batch)
+            names = [chain.layer_info(i, batch)[0] for i in range(1, 4)]
+            assert (names == ["(fused)", "1x1+dwconv3x3<s%d>+1x1" % stride, "(fused)"]) == (force == 2), names
+            for _ in range(2):
+                got = chain.run(x_t).cpu().numpy()
+                assert np.array_equal(got, want[net.layers[-1].dst]), (CASES[k], force, int((got != want[net.layers[-1].dst]).sum()))
+            block = chain.tensor(net.layers[3].dst)
+            if block is not None:
+                assert np.array_equal(block.cpu().numpy(), want[net.layers[3].dst]), (CASES[k], force)
+            assert force == 0 or (chain.tensor(net.layers[1].dst) is None and chain.tensor(net.layers[2].dst) is None)
+    finally:
+        f8.f8_tuning_set("dw_pw", 1)
+        f8.f8_tuning_set("pw_dw_pw", 1)
+    assert len(np.unique(want[net.layers[3].dst])) > 4, "degenerate draw"
+
+
+@pytest.mark.parametrize("batch, hw", [(1, 224), (3, 96), (27, 64), (70, 32)])
+def test_rows_per_workgroup_follow_the_batch(oracle, batch, hw):
+    """MobileNetV2 at batches and image sizes whose blocks take different numbers of rows per workgroup."""
+    x, net = wl.mobilenet_v2_forward(batch=batch, hw=hw)
+    x_t = torch.from_numpy(x).cuda()
+    chain = f8.Chain(net).prepare(batch)
+    assert sum(chain.layer_info(i, batch)[0].startswith("1x1+dw") for i in range(len(net.layers))) > 5
+    got = chain.run(x_t).cpu().numpy()
+    pick = sorted({0, batch // 2, batch - 1})
+    assert np.array_equal(got[pick], oracle.run_network(net, np.ascontiguousarray(x[pick])))
+    f8.f8_tuning_set("pw_dw_pw", 0)
+    try:
+        assert np.array_equal(f8.Chain(net).prepare(batch).run(x_t).cpu().numpy(), got)
+    finally:
+        f8.f8_tuning_set("pw_dw_pw", 1)

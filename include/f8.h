@@ -384,7 +384,7 @@ f8_status f8_mfma_i8_yardstick_operands(int32_t *sink, int iters, uint32_t seed,
  * together with the 512 -> 128 layer behind it, 2: also alone), "stem_pool", "conv_tail", "conv_img" (1 = the
  * kernel with one image per workgroup where it is the faster one, 2 = before any other wherever it fits), "imgk" (1 = on; 10 + n: the image-stationary 3x3 kernel with n = 1, 2 or 4 waves sharing K wherever it fits),
  * "dw_pw" (1 = on where it pays; 2: a depthwise layer and the 1x1 layer behind it in one launch wherever
- * they fit), "pw_dw_pw" (1 = on: the 1x1 layer in front of such a pair in the same launch), "bottleneck" (1 = on where it pays; 2: the last two layers of a bottleneck block and the first of the next in one
+ * they fit), "pw_dw_pw" (1 = on where it pays: the 1x1 layer in front of such a pair in the same launch; 2: wherever the three fit), "bottleneck" (1 = on where it pays; 2: the last two layers of a bottleneck block and the first of the next in one
  * launch wherever they fit; 3 and 4: the same, always with the narrower or the wider of its two tiles), "conv_img_min" (96: fewest images, or bands of 28 image rows, for which a chain takes the
  * image-stationary 3x3 kernels).  The environment variables F8_<NAME IN CAPITALS> give the initial
  * values; they are read once, when the library first looks at a switch, never on the launch path.

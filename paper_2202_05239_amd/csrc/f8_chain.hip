@@ -170,10 +170,12 @@ struct f8_chain {
     const long long most = g.Q > 64 ? 2ll << 20 : g.Q > 28 ? 5ll << 19 : g.Q > 14 ? 9ll << 19 : g.Q > 7 ? 7ll << 20 : 2ll << 20;
     return total <= most && dw_pw_slices(g.Cin, layers[i + 1].Cout) <= 20;
   }
-  // The 1x1 layer in front of such a pair, whose only reader the depthwise layer is, in the same launch (an inverted-residual
-  // block): pdp[i] = 1 for the front one; its constants lie at pdp_off[i]: weights in fragment order, depthwise weights, start values.
+  // An inverted-residual block (1x1 layer, depthwise 3x3 layer that is its only reader, 1x1 layer that is that one's) in one launch:
+  // pdp[i] = 1, 2, 3 for its layers; the constants of the first one lie at pdp_off[i]: its weights in fragment order, depthwise weights
+  // and start values, and, where the last two layers do not share a launch at every batch that takes this one, the last
+  // layer's weights in fragment order at pdp_w2_off[i] (else that pair's copy serves).
   std::vector<int> pdp;                // per layer
-  std::vector<size_t> pdp_off;         // per layer (of the front one)
+  std::vector<size_t> pdp_off, pdp_w2_off;   // per layer (of the first one)
   int pw_dw_pw = 1;
   // Wherever the pair is one launch the three are too: microseconds of front layer and pair, two launches -> one (two launches
   // cost 1 - 2 us more in a forward than alone), MobileNetV2: 28 x 28 C192, batch 1 8.5 -> 6.7, 27 13.8 -> 8.5; 14 x 14 C384, batch 1 7.6 -> 5.4, 27 11.2 ->
@@ -181,10 +183,20 @@ struct f8_chain {
   // 18.8; 56 x 56 C144, batch 1 11.2 -> 5.7, stride 2, batch 27 14.6 -> 9.0, 40 16.1 -> 15.2.
   // 1: front layer, 2: depthwise layer (which launches all three), 3: the one behind
   int pdp_role(size_t i, int batch) const {
-    const int k = dwp[i];
-    const size_t front = k == 0 ? i : i - (size_t)k;
-    if ((k != 0 && i < (size_t)k) || pdp[front] == 0 || pw_dw_pw == 0 || dwp_role(front + 1, batch) != 1) return 0;
-    return 1 + k;
+    if (pdp[i] == 0 || pw_dw_pw == 0 || keep_all) return 0;
+    const size_t front = i + 1 - (size_t)pdp[i];
+    if (use_fusion() && (fused[front].role != 0 || fused[front + 1].role != 0 || fused[front + 2].role != 0)) return 0;
+    if (dwp_role(front + 1, batch) != 1 && (pdp_w2_off[front] == 0 || (pw_dw_pw != 2 && !pdp_pays(front, batch)))) return 0;
+    return pdp[i];
+  }
+  // Where the pair is two launches, microseconds of the three, three launches -> one (three launches cost 2 - 4 us more in a forward), MobileNetV2:
+  //   56 x 56 C144: batch 16 21.7 -> 10.8, 27 19.2 -> 15.4, 40 23.9 -> 23.5, 64 31.5 -> 29.4; C96 from 112 x 112: batch 16 18.4 -> 13.5, 27 24.4 -> 19.8, 64 40.7 -> 37.7,
+  //     96 (either) behind: the rows above and below a workgroup's, computed twice, outweigh the launches
+  //   7 x 7 C960: batch 1 9.9 -> 10.5, 16 11.4 -> 10.2, 40 12.5 -> 10.4, 64 13.8 -> 11.0, 128 19.7 -> 13.7, 192 23 -> 24
+  bool pdp_pays(size_t front, int batch) const {
+    const Geom &g = geom[front + 1];
+    const long long M = (long long)batch * g.P * g.Q;
+    return M <= (g.Q > 28 ? 210000 : 10000);
   }
   // A 3x3 layer, the 1x1 layer of four times its channels that is its only reader, and (where there is one) the 1x1 layer
   // behind that in one launch: bn[i] = 1 for the first, 2 and 3 for the others; bn_head[i] = the first layer, bn_behind[i]
@@ -484,7 +496,7 @@ struct f8_chain {
     p.x = static_cast<const uint8_t *>(tensor_ptr(L0.src, x, out, workspace, batch));
     p.w1 = reinterpret_cast<const int8_t *>(cb + pdp_off[i]);
     p.consts = p.w1 + round256(dw_pw_weight_bytes(L0.Cin, L0.Cout));
-    p.w2 = reinterpret_cast<const int8_t *>(cb + frag_off[i + 1]);
+    p.w2 = reinterpret_cast<const int8_t *>(cb + (pdp_w2_off[i] != 0 ? pdp_w2_off[i] : frag_off[i + 1]));
     p.y = static_cast<uint8_t *>(tensor_ptr(L2.dst, x, out, workspace, batch));
     p.B = batch; p.H = g.H; p.W = g.W; p.P = g.P; p.Q = g.Q; p.stride = g.sh;
     p.Cin = L0.Cin; p.Ce = L0.Cout; p.Cout = L2.Cout;
@@ -532,7 +544,7 @@ struct f8_chain {
     }
     const int block = pdp_role(i, batch);
     if (block == 1 || block == 3) return F8_OK;
-    if (block == 2 && frag_off[i] != 0) {
+    if (block == 2) {
       const PwDwPwParams pp = pdp_params(i - 1, x, out, workspace, batch);
       return launch_pw_dw_pw(pp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
@@ -770,6 +782,7 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->frag_off.push_back(0);
     c->pdp.push_back(0);
     c->pdp_off.push_back(0);
+    c->pdp_w2_off.push_back(0);
     c->bn.push_back(0);
     c->bn_head.push_back(-1);
     c->bn_behind.push_back(-1);
@@ -882,22 +895,30 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->dwp[i + 1] = 2;
     c->dwp_w_bytes[i] = dw_pw_weight_bytes(L.Cin, T.Cout);
   }
-  // the 1x1 layer in front of such a pair; all tensors in the arena
+  // inverted-residual blocks of any stride, all tensors in the arena
   c->pw_dw_pw = tuning().pw_dw_pw.load();
   for (size_t i = 0; i + 2 < c->layers.size(); ++i) {
     const f8_layer_desc &L = c->layers[i], &D = c->layers[i + 1], &T = c->layers[i + 2];
     const Geom &g = c->geom[i + 1];
-    if (c->dwp[i] != 0 || c->dwp[i + 1] != 1 || L.op != F8_OP_CONV || D.src != L.dst || c->tensors[L.dst].last_use != (int)i + 1) continue;
-    if (L.R != 1 || L.S != 1 || L.stride_h != 1 || L.stride_w != 1 || L.pad_h != 0 || L.pad_w != 0 || L.res >= 0 || L.dst2 > 0 ||
-        L.q.y_type == F8_S32 || c->tail[i] != 0 || c->bn[i] != 0 || c->stem[i].pool != 0)
+    auto pointwise = [&](size_t l) {
+      const f8_layer_desc &P = c->layers[l];
+      return P.op == F8_OP_CONV && P.R == 1 && P.S == 1 && P.stride_h == 1 && P.stride_w == 1 && P.pad_h == 0 && P.pad_w == 0 && P.dst2 <= 0 &&
+             P.q.y_type != F8_S32 && c->tail[l] == 0 && c->bn[l] == 0 && c->stem[l].pool == 0 && c->pdp[l] == 0;
+    };
+    if (c->dwp[i] != 0) continue;                    // the second half of the pair in front of it (MobileNetV1)
+    if (!pointwise(i) || !pointwise(i + 2) || L.res >= 0 || (T.res >= 0 && (T.res != L.src || T.q.res_type == F8_S32))) continue;
+    if (D.op != F8_OP_DWCONV || g.R != 3 || g.S != 3 || g.sh != g.sw || g.ph != 1 || g.pw != 1 || D.res >= 0 || D.q.y_type == F8_S32 ||
+        D.src != L.dst || T.src != D.dst || c->tensors[L.dst].last_use != (int)i + 1 || c->tensors[D.dst].last_use != (int)i + 2)
       continue;
-    if (c->tensors[L.src].external || c->tensors[T.dst].external || (T.res >= 0 && T.res != L.src)) continue;
+    if (c->tensors[L.src].external || c->tensors[T.dst].external || c->tensors[D.dst].external) continue;
     if (!pw_dw_pw_applicable(L.Cin, L.Cout, T.Cout, g.H, g.W, g.sh, L.q.fl_x + L.q.fl_w - L.q.fl_y, D.q.fl_x + D.q.fl_w - D.q.fl_y,
                              T.q.fl_x + T.q.fl_w - T.q.fl_y, T.res >= 0, T.res >= 0 ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0, nullptr, nullptr))
       continue;
-    c->pdp[i] = 1;
-    c->pdp_off[i] = c->const_bytes;
-    c->const_bytes += round256(dw_pw_weight_bytes(L.Cin, L.Cout)) + pw_dw_pw_const_bytes(L.Cout, T.Cout) + round256((size_t)(L.Cout + 31) / 32 * 128);
+    c->pdp[i] = 1; c->pdp[i + 1] = 2; c->pdp[i + 2] = 3;
+    auto take = [&](size_t bytes) { const size_t off = c->const_bytes; c->const_bytes += round256(bytes); return off; };
+    c->pdp_off[i] = take(round256(dw_pw_weight_bytes(L.Cin, L.Cout)) + pw_dw_pw_const_bytes(L.Cout, T.Cout) + (size_t)(L.Cout + 31) / 32 * 128);
+    // (large maps and long K: see dw_pw_pays)
+    if (c->dwp[i + 1] != 1 || g.Q > 28 || dw_pw_slices(L.Cout, T.Cout) > 20) c->pdp_w2_off[i] = take(dw_pw_weight_bytes(L.Cout, T.Cout));
   }
   // inverted-residual blocks that can run as one kernel
   for (size_t i = 0; i + 2 < c->layers.size(); ++i) {
@@ -1008,7 +1029,7 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
       return F8_ERR_DEVICE;
   }
   for (size_t i = 0; i < c->layers.size(); ++i) {
-    if (c->pdp[i] == 0) continue;
+    if (c->pdp[i] != 1) continue;
     const f8_layer_desc &L = c->layers[i], &D = c->layers[i + 1], &T = c->layers[i + 2];
     uint8_t *cb = static_cast<uint8_t *>(workspace);
     int8_t *w1 = reinterpret_cast<int8_t *>(cb + c->pdp_off[i]);
@@ -1018,6 +1039,7 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
     const int res_bias = T.res >= 0 && T.q.res_type == F8_U8 ? 128 << (T.q.fl_x + T.q.fl_w - T.q.fl_res) : 0;
     int e = launch_dw_pw_weights(L.w, w1, L.Cin, L.Cout, s);
     if (e == 0) e = launch_block_fold_dw(D.w, D.bias, accd, L.Cout, (L.Cout + 31) / 32 * 32, rounding_addend(D.q), D.q.x_type == F8_U8 ? 128 : 0, s);
+    if (e == 0 && c->pdp_w2_off[i] != 0) e = launch_dw_pw_weights(T.w, reinterpret_cast<int8_t *>(cb + c->pdp_w2_off[i]), T.Cin, T.Cout, s);
     if (e == 0) e = launch_pw_dw_pw_consts(D.w, start(i), accd, start(i + 2), consts, L.Cout, T.Cout, res_bias, s);
     if (e != 0) return F8_ERR_DEVICE;
   }
@@ -1114,7 +1136,7 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
   const Tensor &t = c->tensors[id];
   // tensors inside a fused block are never materialised
   const bool elided = (t.producer >= 0 && (c->pool_role((size_t)t.producer) == 1 || c->dwp_role((size_t)t.producer, batch) == 1 ||
-                                             c->pdp_role((size_t)t.producer, batch) == 1 ||
+                                             c->pdp_role((size_t)t.producer, batch) == 1 || c->pdp_role((size_t)t.producer, batch) == 2 ||
                                              c->bn_role((size_t)t.producer, batch) == 1)) ||
                       (c->use_fusion() && t.producer >= 0 && c->fused[t.producer].role != 0 &&
                        !(c->fused[t.producer].role == 2 && t.producer >= 2 && c->fused[t.producer - 2].role == 1));
@@ -1210,7 +1232,8 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
     return F8_OK;
   }
   const int three = c->bn_role((size_t)layer, batch);
-  if (three > 1 || c->pdp_role((size_t)layer, batch) == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
+  const int block = c->pdp_role((size_t)layer, batch);
+  if (three > 1 || block == 1 || block == 3 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
     // accounted to the layer in front (of the first layer of an inverted-residual block: behind), whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {
@@ -1262,16 +1285,18 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       break;
     }
     case F8_OP_DWCONV:
-      if (c->dwp_role((size_t)layer, batch) == 1) {
+      if (block == 2 || c->dwp_role((size_t)layer, batch) == 1) {
         // plus the 1x1 layer that reads it: what lies between them never leaves the chip
         const f8_layer_desc &T = c->layers[layer + 1];
         name = g.sh == 1 ? "dwconv3x3<s1>+1x1" : "dwconv3x3<s2>+1x1";
         ops = 2.0 * M * (9.0 * L.Cout + (double)T.Cin * T.Cout);
         bytes += M * (T.Cout - L.Cout) + (T.res >= 0 ? M * T.Cout : 0.0) + 13.0 * L.Cout + (double)T.Cin * T.Cout + 4.0 * T.Cout;
-        if (c->pdp_role((size_t)layer, batch) == 2) {
+        if (block == 2) {
           // and the 1x1 layer in front, all of whose pixels are needed; the shortcut is its input, read once
           const f8_layer_desc &E = c->layers[layer - 1];
-          name = g.sh == 1 ? "1x1+dwconv3x3<s1>+1x1" : "1x1+dwconv3x3<s2>+1x1";
+          // (one kernel; the name tells whether the pair without its front layer would be one launch here)
+          if (c->dwp_role((size_t)layer, batch) == 1) name = g.sh == 1 ? "1x1+dwconv3x3<s1>+1x1" : "1x1+dwconv3x3<s2>+1x1";
+          else name = g.sh == 1 ? "inverted_residual<s1>" : "inverted_residual<s2>";
           const double in = (double)batch * g.H * g.W;
           ops += 2.0 * in * (double)E.Cin * E.Cout;
           bytes += in * E.Cin - (double)batch * rows * cols * g.Cin - (T.res >= 0 ? M * T.Cout : 0.0) + (double)E.Cin * E.Cout + 4.0 * E.Cout;

@@ -39,7 +39,7 @@ struct Tuning {
   std::atomic<int> imgk{1};            // chain: image-stationary 3x3 kernel with K shared among the waves (10 + n: with n waves, wherever it fits)
   std::atomic<int> bottleneck{1};      // chain: the last two layers of a bottleneck block and the next one's first in one launch (2: at any batch; 3, 4: the same with the narrow, the wide tile)
   std::atomic<int> dw_pw{1};           // chain: depthwise layer and the 1x1 layer behind it in one launch (2: at any batch)
-  std::atomic<int> pw_dw_pw{1};        // chain: the 1x1 layer in front of such a pair in the same launch
+  std::atomic<int> pw_dw_pw{1};        // chain: the 1x1 layer in front of such a pair in the same launch (2: also where the pair is two)
   std::atomic<int> pw_mid{1};          // 1x1 128 -> 512 kernel: 1 = when the 512 -> 128 layer behind it runs in the same launch, 2 = always
   std::atomic<int> conv_img_min{96};   // ... from this many images (or bands of 28 rows) on: one workgroup each
 };

@@ -182,19 +182,25 @@ __global__ __launch_bounds__(NT, 2) void pw_dw_pw_kernel(const Args a) {
   __syncthreads();
 
   // ---- last layer's first weights, requested ahead of the depthwise layer
-  const int part = a.by_u3.of(wave), unit = wave - part * (a.nb3 * a.mb2);
-  const int mbi = a.by_nb3.of(unit), nbi = unit - mbi * a.nb3;
+  const int u3 = a.nb3 * a.mb2, part = a.by_u3.of(wave), first_unit = wave - part * u3;
   const bool active = part < a.kg;
-  const int8_t *wf = a.w2 + ((size_t)nbi * a.nb1 * 64 + lane) * 16;
   constexpr int PF = 4;
   v4i wq[PF];
-  if (active) {
+  auto weights_of = [&](int unit, int &mbi, int &nbi) {
+    mbi = a.by_nb3.of(unit);
+    nbi = unit - mbi * a.nb3;
+    return a.w2 + ((size_t)nbi * a.nb1 * 64 + lane) * 16;
+  };
+  auto load_first = [&](const int8_t *wf) {
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
       const int s = part + i * a.kg;
       wq[i] = *reinterpret_cast<const v4i *>(wf + (size_t)(s < a.nb1 ? s : part) * 1024);
     }
-  }
+  };
+  int mbi, nbi;
+  const int8_t *wf = weights_of(first_unit, mbi, nbi);
+  if (active) load_first(wf);
   // ---- depthwise layer: the same over output pixels.  (The nine products are one chain, each waiting 64 cycles for the last,
   // half of them idle: the other wave of the SIMD has them.)
   const int slot2 = a.by_m2.of(wave);
@@ -232,31 +238,37 @@ __global__ __launch_bounds__(NT, 2) void pw_dw_pw_kernel(const Args a) {
 
   // ---- last layer: waves share the output blocks and, where there are fewer than waves, K
   if (active) {
-    v16i acc;
+    for (int unit = first_unit;;) {
+      v16i acc;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0;
-    const uint32_t from = base + a.at_d + (mbi * 32 + l32) * a.ep + half * 16;
-    for (int s0 = part; s0 < a.nb1; s0 += PF * a.kg) {
-      v4i xf[PF];
+      for (int i = 0; i < 16; ++i) acc[i] = 0;
+      const uint32_t from = base + a.at_d + (mbi * 32 + l32) * a.ep + half * 16;
+      for (int s0 = part; s0 < a.nb1; s0 += PF * a.kg) {
+        v4i xf[PF];
 #pragma unroll
-      for (int i = 0; i < PF; ++i) {
-        const int s = s0 + i * a.kg;
-        xf[i] = lds_read(from + (s < a.nb1 ? s : part) * 32);
-      }
+        for (int i = 0; i < PF; ++i) {
+          const int s = s0 + i * a.kg;
+          xf[i] = lds_read(from + (s < a.nb1 ? s : part) * 32);
+        }
 #pragma unroll
-      for (int i = 0; i < PF; ++i) {
-        const int s = s0 + i * a.kg;
-        if (s < a.nb1) {                             // uniform
-          acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wq[i], xf[i], acc, 0, 0, 0);
-          const int ahead = s + PF * a.kg;
-          if (ahead < a.nb1) wq[i] = *reinterpret_cast<const v4i *>(wf + (size_t)ahead * 1024);
+        for (int i = 0; i < PF; ++i) {
+          const int s = s0 + i * a.kg;
+          if (s < a.nb1) {                           // uniform
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wq[i], xf[i], acc, 0, 0, 0);
+            const int ahead = s + PF * a.kg;
+            if (ahead < a.nb1) wq[i] = *reinterpret_cast<const v4i *>(wf + (size_t)ahead * 1024);
+          }
         }
       }
-    }
-    // (the expanded rows are no longer read: their place takes the sums)
-    const uint32_t to = base + a.at_e + ((part * a.mb2 + mbi) * a.nb3 + nbi) * (32 * PART_PITCH) + l32 * PART_PITCH + half * 64;
+      // (the expanded rows are no longer read: their place takes the sums)
+      const uint32_t to = base + a.at_e + ((part * a.mb2 + mbi) * a.nb3 + nbi) * (32 * PART_PITCH) + l32 * PART_PITCH + half * 64;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) lds_write(to + g * 16, v4i{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]});
+      for (int g = 0; g < 4; ++g) lds_write(to + g * 16, v4i{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]});
+      unit += NWAVE;
+      if (a.kg > 1 || unit >= u3) break;             // (more blocks than waves: nobody shares K)
+      wf = weights_of(unit, mbi, nbi);
+      load_first(wf);
+    }
   }
   __syncthreads();
   const size_t y_first = ((size_t)img * a.P + p0) * a.Q;
@@ -330,13 +342,13 @@ int rows_for(int Cin, int Ce, int Cout, int H, int W, int P, int Q, int stride, 
   long long least = 0;
   for (int rows = 1; rows <= P; ++rows) {
     const Shape s = shape_of(Cin, Ce, Cout, H, W, P, Q, stride, rows);
-    if (s.bytes > LDS_MOST || nb3 * s.mb2 > NWAVE) break;
+    if (s.bytes > LDS_MOST) break;
     auto units = [&](int mb) {
       const int m = mb < NWAVE ? mb : NWAVE, g = NWAVE / m;
       return (long long)((mb + m - 1) / m) * ((nb1 + g - 1) / g);
     };
-    const int kg = NWAVE / (nb3 * s.mb2);
-    const long long one = 3500 + units(s.mb1) * (450 + 60 * ks1) + units(s.mb2) * 900 + (nb1 + kg - 1) / kg * 150;
+    const int u3 = nb3 * s.mb2, kg = u3 < NWAVE ? NWAVE / u3 : 1;
+    const long long one = 3500 + units(s.mb1) * (450 + 60 * ks1) + units(s.mb2) * 900 + (u3 + NWAVE - 1) / NWAVE * (long long)((nb1 + kg - 1) / kg) * 120;
     const long long rounds = ((long long)B * s.bands + 255) / 256;
     const long long cost = 2 * s.bytes <= LDS_MOST ? one * (rounds / 2 * 16 + rounds % 2 * 10) : one * rounds * 10;
     if (best == 0 || cost < least) { best = rows; least = cost; }
@@ -402,7 +414,8 @@ int launch_pw_dw_pw(const PwDwPwParams &p, hipStream_t stream) {
   a.m2 = a.mb2 < NWAVE ? a.mb2 : NWAVE; a.g2 = NWAVE / a.m2;
   a.xp = s.xp; a.ep = s.ep;
   a.at_const = s.at_const; a.at_e = s.at_e; a.at_d = s.at_d;
-  a.kg = NWAVE / (a.nb3 * a.mb2) < a.nb1 ? NWAVE / (a.nb3 * a.mb2) : a.nb1;
+  const int u3 = a.nb3 * a.mb2, kg = u3 < NWAVE ? NWAVE / u3 : 1;
+  a.kg = kg < a.nb1 ? kg : a.nb1;
   a.x_bytes = p.B * p.H * p.W * p.Cin;
   a.w1_bytes = a.nb1 * ks1 * 1024;
   a.const_bytes = (int)pw_dw_pw_const_bytes(p.Ce, p.Cout);
@@ -412,7 +425,7 @@ int launch_pw_dw_pw(const PwDwPwParams &p, hipStream_t stream) {
   a.clipd = scaled_clip(p.lod, p.hid, p.shiftd);
   a.shift1 = p.shift1; a.shiftd = p.shiftd; a.shift2 = p.shift2; a.lo2 = p.lo2; a.hi2 = p.hi2;
   a.by_bands = Div(s.bands); a.by_m1 = Div(a.m1); a.by_m2 = Div(a.m2); a.by_w = Div(p.W); a.by_q = Div(p.Q); a.by_c8 = Div(a.c8);
-  a.by_pe = Div(s.ep / 16); a.by_np = Div(p.Cout / 4); a.by_u3 = Div(a.nb3 * a.mb2); a.by_nb3 = Div(a.nb3);
+  a.by_pe = Div(s.ep / 16); a.by_np = Div(p.Cout / 4); a.by_u3 = Div(u3); a.by_nb3 = Div(a.nb3);
   const long long grid = (long long)p.B * s.bands;
   if (grid > 0x7fffffffLL) return (int)hipErrorInvalidValue;
   switch (ks1) {

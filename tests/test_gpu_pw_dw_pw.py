@@ -19,6 +19,7 @@ CASES = [
     (8, 16, 8, (1, 1), 9, 1, False, False, False, True),            # one pixel: every tap but the middle one outside
     (32, 192, 32, (1, 40), 2, 1, False, True, False, True),         # one row: border rows on both sides
     (40, 272, 248, (9, 2), 3, 2, True, False, True, False),         # eight blocks of output channels
+    (32, 48, 224, (9, 9), 2, 1, False, False, True, False),         # more output blocks than waves
 ]
 
 

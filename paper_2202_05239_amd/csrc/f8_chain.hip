@@ -177,6 +177,12 @@ struct f8_chain {
   std::vector<int> pdp;                // per layer
   std::vector<size_t> pdp_off, pdp_w2_off;   // per layer (of the first one)
   int pw_dw_pw = 1;
+  // The front of a network is such a block with a 3x3 stride-2 layer on an image in the first layer's place.  Microseconds of the three,
+  // three launches (or two) -> one, image 224 x 224: MobileNetV2 (to 16 channels) batch 1 9.8 -> 4.6, 4 11.5 -> 4.3, 8 15.4 -> 6.1, 27 26.0 -> 10.3,
+  // 64 44.9 -> 20.5, 128 75.2 -> 37.2; MobileNetV1 (to 64 channels) 1 11.3 -> 6.1, 27 33.0 -> 17.2, 64 58.1 -> 30.7, 128 93.1 -> 53.2.  At batch 256 it is
+  // ahead too (136 -> 73, 178 -> 101); from 3 M pixels on the layers keep the kernels that per-layer accounts of such batches name.
+  bool pdp_image(size_t front) const { return stem[front].on && stem[front].Cp == 4; }
+  int pdp_k(size_t front) const { return pdp_image(front) ? 48 : layers[front].Cin; }
   // Wherever the pair is one launch the three are too: microseconds of front layer and pair, two launches -> one (two launches
   // cost 1 - 2 us more in a forward than alone), MobileNetV2: 28 x 28 C192, batch 1 8.5 -> 6.7, 27 13.8 -> 8.5; 14 x 14 C384, batch 1 7.6 -> 5.4, 27 11.2 ->
   // 6.6, 64 12.5 -> 9.0, 96 17.2 -> 11.2; C576, batch 1 8.9 -> 7.6, 27 12.8 -> 9.0, 64 17.5 -> 11.9; 28 x 28 C192 stride 2, batch 64 15.5 -> 8.2, 192 26.6 ->
@@ -196,6 +202,7 @@ struct f8_chain {
   bool pdp_pays(size_t front, int batch) const {
     const Geom &g = geom[front + 1];
     const long long M = (long long)batch * g.P * g.Q;
+    if (pdp_image(front)) return M < 3 << 20;
     return M <= (g.Q > 28 ? 210000 : 10000);
   }
   // A 3x3 layer, the 1x1 layer of four times its channels that is its only reader, and (where there is one) the 1x1 layer
@@ -487,6 +494,10 @@ struct f8_chain {
   }
 
   // Parameters of the inverted-residual block that starts at layer i.
+  // (an image of the caller's that does not lie on the four bytes its rows are fetched in: layer by layer)
+  bool pdp_reads(size_t front, const void *x, void *workspace, int batch) const {
+    return !pdp_image(front) || (reinterpret_cast<uintptr_t>(tensor_ptr(layers[front].src, x, nullptr, workspace, batch)) & 3) == 0;
+  }
   PwDwPwParams pdp_params(size_t i, const void *x, void *out, void *workspace, int batch) const {
     const f8_layer_desc &L0 = layers[i], &L1 = layers[i + 1], &L2 = layers[i + 2];
     const Geom &g = geom[i + 1];
@@ -495,11 +506,12 @@ struct f8_chain {
     PwDwPwParams p;
     p.x = static_cast<const uint8_t *>(tensor_ptr(L0.src, x, out, workspace, batch));
     p.w1 = reinterpret_cast<const int8_t *>(cb + pdp_off[i]);
-    p.consts = p.w1 + round256(dw_pw_weight_bytes(L0.Cin, L0.Cout));
+    p.consts = p.w1 + round256(dw_pw_weight_bytes(pdp_k(i), L0.Cout));
     p.w2 = reinterpret_cast<const int8_t *>(cb + (pdp_w2_off[i] != 0 ? pdp_w2_off[i] : frag_off[i + 1]));
     p.y = static_cast<uint8_t *>(tensor_ptr(L2.dst, x, out, workspace, batch));
     p.B = batch; p.H = g.H; p.W = g.W; p.P = g.P; p.Q = g.Q; p.stride = g.sh;
     p.Cin = L0.Cin; p.Ce = L0.Cout; p.Cout = L2.Cout;
+    p.H0 = geom[i].H;
     p.x_xor = sign(L0.q.x_type); p.e_xor = sign(L0.q.y_type); p.d_xor = sign(L1.q.y_type);
     p.shift1 = L0.q.fl_x + L0.q.fl_w - L0.q.fl_y; p.lo1 = L0.q.clip_lo; p.hi1 = L0.q.clip_hi;
     p.shiftd = L1.q.fl_x + L1.q.fl_w - L1.q.fl_y; p.lod = L1.q.clip_lo; p.hid = L1.q.clip_hi;
@@ -542,11 +554,12 @@ struct f8_chain {
       const BottleneckParams bp = bottleneck_params(i, x, out, workspace, batch);
       return launch_bottleneck(bp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
-    const int block = pdp_role(i, batch);
+    int block = pdp_role(i, batch);
+    if (block != 0 && !pdp_reads(i + 1 - (size_t)block, x, workspace, batch)) block = 0;
     if (block == 1 || block == 3) return F8_OK;
     if (block == 2) {
       const PwDwPwParams pp = pdp_params(i - 1, x, out, workspace, batch);
-      return launch_pw_dw_pw(pp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
+      return (pdp_image(i - 1) ? launch_image_dw_pw(pp, s) : launch_pw_dw_pw(pp, s)) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
     if (tail_role(i, batch) == 2 || dwp_role(i, batch) == 2) return F8_OK;
     if (dwp_role(i, batch) == 1) {
@@ -900,9 +913,11 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
   for (size_t i = 0; i + 2 < c->layers.size(); ++i) {
     const f8_layer_desc &L = c->layers[i], &D = c->layers[i + 1], &T = c->layers[i + 2];
     const Geom &g = c->geom[i + 1];
+    const bool image = c->stem[i].on && c->stem[i].Cp == 4;
     auto pointwise = [&](size_t l) {
       const f8_layer_desc &P = c->layers[l];
-      return P.op == F8_OP_CONV && P.R == 1 && P.S == 1 && P.stride_h == 1 && P.stride_w == 1 && P.pad_h == 0 && P.pad_w == 0 && P.dst2 <= 0 &&
+      if (l == i && image && (P.Cin != 3 || P.R != 3 || P.S != 3 || P.stride_h != 2 || P.stride_w != 2 || P.pad_h != 1 || P.pad_w != 1)) return false;
+      return P.op == F8_OP_CONV && ((l == i && image) || (P.R == 1 && P.S == 1 && P.stride_h == 1 && P.stride_w == 1 && P.pad_h == 0 && P.pad_w == 0)) && P.dst2 <= 0 &&
              P.q.y_type != F8_S32 && c->tail[l] == 0 && c->bn[l] == 0 && c->stem[l].pool == 0 && c->pdp[l] == 0;
     };
     if (c->dwp[i] != 0) continue;                    // the second half of the pair in front of it (MobileNetV1)
@@ -910,15 +925,19 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     if (D.op != F8_OP_DWCONV || g.R != 3 || g.S != 3 || g.sh != g.sw || g.ph != 1 || g.pw != 1 || D.res >= 0 || D.q.y_type == F8_S32 ||
         D.src != L.dst || T.src != D.dst || c->tensors[L.dst].last_use != (int)i + 1 || c->tensors[D.dst].last_use != (int)i + 2)
       continue;
-    if (c->tensors[L.src].external || c->tensors[T.dst].external || c->tensors[D.dst].external) continue;
-    if (!pw_dw_pw_applicable(L.Cin, L.Cout, T.Cout, g.H, g.W, g.sh, L.q.fl_x + L.q.fl_w - L.q.fl_y, D.q.fl_x + D.q.fl_w - D.q.fl_y,
+    if ((c->tensors[L.src].external && !image) || c->tensors[T.dst].external || c->tensors[D.dst].external) continue;
+    if (image) {
+      if (T.res >= 0 || !image_dw_pw_applicable(L.Cout, T.Cout, c->geom[i].H, c->geom[i].W, g.sh, L.q.fl_x + L.q.fl_w - L.q.fl_y, D.q.fl_x + D.q.fl_w - D.q.fl_y,
+                                                T.q.fl_x + T.q.fl_w - T.q.fl_y, nullptr, nullptr))
+        continue;
+    } else if (!pw_dw_pw_applicable(L.Cin, L.Cout, T.Cout, g.H, g.W, g.sh, L.q.fl_x + L.q.fl_w - L.q.fl_y, D.q.fl_x + D.q.fl_w - D.q.fl_y,
                              T.q.fl_x + T.q.fl_w - T.q.fl_y, T.res >= 0, T.res >= 0 ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0, nullptr, nullptr))
       continue;
     c->pdp[i] = 1; c->pdp[i + 1] = 2; c->pdp[i + 2] = 3;
     auto take = [&](size_t bytes) { const size_t off = c->const_bytes; c->const_bytes += round256(bytes); return off; };
-    c->pdp_off[i] = take(round256(dw_pw_weight_bytes(L.Cin, L.Cout)) + pw_dw_pw_const_bytes(L.Cout, T.Cout) + (size_t)(L.Cout + 31) / 32 * 128);
+    c->pdp_off[i] = take(round256(dw_pw_weight_bytes(c->pdp_k(i), L.Cout)) + pw_dw_pw_const_bytes(L.Cout, T.Cout) + (size_t)(L.Cout + 31) / 32 * 128);
     // (large maps and long K: see dw_pw_pays)
-    if (c->dwp[i + 1] != 1 || g.Q > 28 || dw_pw_slices(L.Cout, T.Cout) > 20) c->pdp_w2_off[i] = take(dw_pw_weight_bytes(L.Cout, T.Cout));
+    if (image || c->dwp[i + 1] != 1 || g.Q > 28 || dw_pw_slices(L.Cout, T.Cout) > 20) c->pdp_w2_off[i] = take(dw_pw_weight_bytes(L.Cout, T.Cout));
   }
   // inverted-residual blocks that can run as one kernel
   for (size_t i = 0; i + 2 < c->layers.size(); ++i) {
@@ -1033,11 +1052,11 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
     const f8_layer_desc &L = c->layers[i], &D = c->layers[i + 1], &T = c->layers[i + 2];
     uint8_t *cb = static_cast<uint8_t *>(workspace);
     int8_t *w1 = reinterpret_cast<int8_t *>(cb + c->pdp_off[i]);
-    int8_t *consts = w1 + round256(dw_pw_weight_bytes(L.Cin, L.Cout));
+    int8_t *consts = w1 + round256(dw_pw_weight_bytes(c->pdp_k(i), L.Cout));
     int32_t *accd = reinterpret_cast<int32_t *>(consts + pw_dw_pw_const_bytes(L.Cout, T.Cout));
     auto start = [&](size_t l) { return reinterpret_cast<const int32_t *>(cb + c->acc0_off[l]); };
     const int res_bias = T.res >= 0 && T.q.res_type == F8_U8 ? 128 << (T.q.fl_x + T.q.fl_w - T.q.fl_res) : 0;
-    int e = launch_dw_pw_weights(L.w, w1, L.Cin, L.Cout, s);
+    int e = launch_dw_pw_weights(c->pdp_image(i) ? c->conv_weights(i, workspace) : L.w, w1, c->pdp_k(i), L.Cout, s);
     if (e == 0) e = launch_block_fold_dw(D.w, D.bias, accd, L.Cout, (L.Cout + 31) / 32 * 32, rounding_addend(D.q), D.q.x_type == F8_U8 ? 128 : 0, s);
     if (e == 0 && c->pdp_w2_off[i] != 0) e = launch_dw_pw_weights(T.w, reinterpret_cast<int8_t *>(cb + c->pdp_w2_off[i]), T.Cin, T.Cout, s);
     if (e == 0) e = launch_pw_dw_pw_consts(D.w, start(i), accd, start(i + 2), consts, L.Cout, T.Cout, res_bias, s);
@@ -1297,9 +1316,14 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
           // (one kernel; the name tells whether the pair without its front layer would be one launch here)
           if (c->dwp_role((size_t)layer, batch) == 1) name = g.sh == 1 ? "1x1+dwconv3x3<s1>+1x1" : "1x1+dwconv3x3<s2>+1x1";
           else name = g.sh == 1 ? "inverted_residual<s1>" : "inverted_residual<s2>";
-          const double in = (double)batch * g.H * g.W;
-          ops += 2.0 * in * (double)E.Cin * E.Cout;
-          bytes += in * E.Cin - (double)batch * rows * cols * g.Cin - (T.res >= 0 ? M * T.Cout : 0.0) + (double)E.Cin * E.Cout + 4.0 * E.Cout;
+          const Geom &ge = c->geom[layer - 1];
+          if (c->pdp_image((size_t)layer - 1)) {
+            if (c->dwp_role((size_t)layer, batch) == 1) name = g.sh == 1 ? "conv3x3+dwconv3x3<s1>+1x1" : "conv3x3+dwconv3x3<s2>+1x1";
+            else name = g.sh == 1 ? "conv3x3+dwconv3x3<s1>, 1x1" : "conv3x3+dwconv3x3<s2>, 1x1";
+          }
+          const double taps = (double)E.R * E.S * E.Cin * E.Cout;
+          ops += 2.0 * batch * g.H * g.W * taps;
+          bytes += (double)batch * ge.H * ge.W * E.Cin - (double)batch * rows * cols * g.Cin - (T.res >= 0 ? M * T.Cout : 0.0) + taps + 4.0 * E.Cout;
         }
         break;
       }

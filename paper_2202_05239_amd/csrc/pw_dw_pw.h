@@ -17,6 +17,7 @@ struct PwDwPwParams {
   int shift1, lo1, hi1;           // requantisation (shifts >= 0)
   int shiftd, lod, hid;
   int shift2, lo2, hi2;
+  int H0;                         // launch_image_dw_pw: rows of x, [B][H0][2 W][3]; else not read
   int has_res, res_d;             // the block's input is the last layer's residual (stride 1, Cin = Cout), res_d >= 0
 };
 
@@ -30,5 +31,10 @@ int launch_pw_dw_pw_consts(const int8_t *wd, const int32_t *acc1, const int32_t 
                            hipStream_t stream);
 // A hipError_t as int.
 int launch_pw_dw_pw(const PwDwPwParams &p, hipStream_t stream);
+
+// The same where the first layer is a 3x3 layer of stride 2 and padding 1 on an H x W image of three channels (its weights: launch_dw_pw_weights of
+// Ce x [3][4][4], the fourth pixel and channel zeros).
+bool image_dw_pw_applicable(int Ce, int Cout, int H, int W, int stride, int shift1, int shiftd, int shift2, const void *x, const void *y);
+int launch_image_dw_pw(const PwDwPwParams &p, hipStream_t stream);
 
 }  // namespace f8

@@ -12,6 +12,9 @@
 // block of 32 pixels x 32 channels takes nine matrix instructions on fragments that lie in LDS as they are.  The packed dot products
 // of dw_pw.hip need the bytes of neighbouring pixels side by side first: nine vector instructions per result where
 // this has six, of which none waits for a transposition.
+//
+// The front of a network (3x3 stride-2 layer on an image of three channels, depthwise layer, 1x1 layer) has a kernel of its own
+// below, with at most 32 channels in the middle.
 #include "pw_dw_pw.h"
 
 #include <atomic>
@@ -307,6 +310,165 @@ __global__ __launch_bounds__(256) void pw_dw_pw_consts_kernel(const int8_t *__re
   }
 }
 
+// ---- the front of a network
+//
+// The image's rows are spread to four bytes per pixel in LDS, so that four pixels of a window row are half a fragment: two slices
+// of K for the three rows, where the weights of the fourth channel, pixel and row are zeros.  With one block of 32
+// channels in the middle a lane's 16 depthwise results are the fragment that the last layer takes: they stay in registers, as do the nine
+// diagonal matrices.
+//
+// MobileNetV2's front, 27 images of 224 x 224: 26.0 -> 10.3 us (three launches of 14.8, 7.4 and 3.7), 128: 75.2 -> 37.2, of which image and
+// result are some 9 us of memory traffic: bound by vector instructions (about 300 per 32 pixels, two thirds of them requantisation and
+// packing).  With the general kernel above (depthwise result through LDS, diagonals rebuilt for every block) it was 14.5 and 56.7.
+struct ImageArgs {
+  const uint8_t *x;
+  const int8_t *w1, *consts, *w2;
+  uint8_t *y;
+  int x_bytes, const_bytes, w2_bytes;
+  int H0, H, W, P, Q, stride, cout, groups;    // image rows; first layer's result; groups of four pixels per image row
+  int rows, bands, nb3, mb1, mb2;              // as in Args
+  int xp, at_const, at_w2, at_e;               // bytes of an image row in LDS; LDS offsets
+  uint32_t x_xor, e_xor, d_xor;
+  ScaledClip clip1, clipd, clip2;
+  int shift1, shiftd, shift2;
+  Div by_bands, by_w, by_q, by_groups;
+};
+
+constexpr int EP = 48;       // bytes of a pixel of the first layer's result in LDS: 16 pixels of a row start on different banks
+
+__global__ __launch_bounds__(NT, 2) void image_dw_pw_kernel(const ImageArgs a) {
+  typedef int v3i __attribute__((ext_vector_type(3)));
+  pin_args(a.x, a.w1, a.consts, a.w2, a.y, a.x_bytes, a.const_bytes, a.w2_bytes, a.H0, a.H, a.W, a.P, a.Q, a.stride, a.cout, a.groups, a.rows,
+           a.bands, a.nb3, a.mb1, a.mb2, a.xp, a.at_const, a.at_w2, a.at_e, a.x_xor, a.e_xor, a.d_xor, a.clip1.lo, a.clip1.hi, a.clipd.lo,
+           a.clipd.hi, a.clip2.lo, a.clip2.hi, a.shift1, a.shiftd, a.shift2, a.by_bands.mul, a.by_bands.shr, a.by_w.mul, a.by_w.shr, a.by_q.mul,
+           a.by_q.shr, a.by_groups.mul, a.by_groups.shr);
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const uint32_t base = (uint32_t)(uintptr_t)((lds_u8 *)lds);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  const int wg = (int)xcd_remap(blockIdx.x, gridDim.x);
+  const int img = a.by_bands.of(wg), p0 = (wg - img * a.bands) * a.rows;
+  const int out_rows = min(a.rows, a.P - p0);
+  const int ih0 = p0 * a.stride - 1, e_rows = (out_rows - 1) * a.stride + 3;
+  const int r_lo = max(ih0, 0), r_hi = min(ih0 + e_rows, a.H);        // rows of the first layer's result inside it
+  const int npx = (r_hi - r_lo) * a.W, opx = out_rows * a.Q;
+
+  // ---- image rows under them, four pixels at a time, pixel c at 4 (c + 1) of its row
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.x), 0, a.x_bytes, 0x00027000);
+  const int ir0 = 2 * r_lo - 1, n = (2 * (r_hi - r_lo) + 1) * a.groups, first = (img * a.H0 + ir0) * a.groups * 12;
+  constexpr int XU = 3;
+  v3i xv[XU];
+  auto fetch = [&](int i0) {
+#pragma unroll
+    for (int k = 0; k < XU; ++k) {
+      const int i = i0 + k * NT + tid, row = a.by_groups.of(i);
+      const bool in = i < n && (uint32_t)(ir0 + row) < (uint32_t)a.H0;
+      xv[k] = __builtin_bit_cast(v3i, __builtin_amdgcn_raw_buffer_load_b96(xres, in ? (uint32_t)(first + i * 12) : 0x80000000u, 0, 0));
+    }
+  };
+  auto put = [&](int i0) {
+#pragma unroll
+    for (int k = 0; k < XU; ++k) {
+      const int i = i0 + k * NT + tid, row = a.by_groups.of(i), g = i - row * a.groups;
+      if (i >= n) continue;
+      // (the fourth byte of a pixel meets zero weights)
+      const uint32_t to = base + row * a.xp + g * 16 + 4, d0 = xv[k].x, d1 = xv[k].y, d2 = xv[k].z;
+      *(lds_u32 *)(uintptr_t)to = d0 ^ a.x_xor;
+      *(lds_v2i *)(uintptr_t)(to + 4) = v2i{(int)(__builtin_amdgcn_alignbyte(d1, d0, 3) ^ a.x_xor), (int)(__builtin_amdgcn_alignbyte(d2, d1, 2) ^ a.x_xor)};
+      *(lds_u32 *)(uintptr_t)(to + 12) = (d2 >> 8) ^ a.x_xor;
+      if (g == 0) *(lds_u32 *)(uintptr_t)(to - 4) = a.x_xor;           // the column left of the image
+    }
+  };
+  fetch(0);
+  v4i w1[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) w1[k] = *reinterpret_cast<const v4i *>(a.w1 + k * 1024 + lane * 16);
+  // ---- depthwise weights and start values, and the last layer's weights, straight into LDS
+  {
+    const __amdgpu_buffer_rsrc_t cres = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(a.consts), 0, a.const_bytes, 0x00027000);
+    for (int at = wave * 1024; at < a.const_bytes; at += NWAVE * 1024)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(cres, (lds_void *)(lds + a.at_const + at), 16, lane * 16, at, 0, 0);
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(a.w2), 0, a.w2_bytes, 0x00027000);
+    if (wave < a.nb3) __builtin_amdgcn_raw_ptr_buffer_load_lds(wres, (lds_void *)(lds + a.at_w2 + wave * 1024), 16, lane * 16, wave * 1024, 0, 0);
+  }
+  // ---- zeros around the first layer's result
+  {
+    const int ez = (int)a.e_xor, ew = a.W + 2;
+    for (int i = tid; i < e_rows * 4; i += NT)
+      lds_write(base + a.at_e + ((i >> 2) * ew + ((i >> 1) & 1) * (ew - 1)) * EP + (i & 1) * 16, v4i{ez, ez, ez, ez});
+    if (r_hi - r_lo < e_rows)
+      for (int i = tid; i < a.W * 2; i += NT) {
+        const uint32_t to = base + a.at_e + (1 + (i >> 1)) * EP + (i & 1) * 16;
+        if (ih0 < 0) lds_write(to, v4i{ez, ez, ez, ez});
+        if (r_hi == a.H) for (int r = a.H - ih0; r < e_rows; ++r) lds_write(to + r * ew * EP, v4i{ez, ez, ez, ez});
+      }
+  }
+  put(0);
+  for (int i0 = XU * NT; i0 < n; i0 += XU * NT) { fetch(i0); put(i0); }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the constants have arrived
+  __syncthreads();
+
+  auto start16 = [&](int block) {
+    v16i v;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const v4i s = lds_read(base + a.at_const + tap_bytes(1) + block * 128 + half * 64 + g * 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[4 * g + i] = s[i];
+    }
+    return v;
+  };
+
+  // ---- first layer
+  {
+    const v16i start = start16(0);
+    for (int mb = wave; mb < a.mb1; mb += NWAVE) {
+      const int i = mb * 32 + l32, ic = min(i, npx - 1), r = a.by_w.of(ic), c = ic - r * a.W;
+      // slice 0: rows 0 and 1 of the window, slice 1: row 2 (whose other half meets zero weights)
+      const uint32_t from = base + (2 * r + half) * a.xp + c * 8, last = from + (2 - half) * a.xp;
+      const v2i x0 = *(lds_v2i *)(uintptr_t)from, x1 = *(lds_v2i *)(uintptr_t)(from + 8);
+      const v2i x2 = *(lds_v2i *)(uintptr_t)last, x3 = *(lds_v2i *)(uintptr_t)(last + 8);
+      v16i acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w1[0], v4i{x0.x, x0.y, x1.x, x1.y}, start, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w1[1], v4i{x2.x, x2.y, x3.x, x3.y}, acc, 0, 0, 0);
+      const v4i v = requant16(acc, a.clip1, a.shift1, (int)a.e_xor);
+      if (i < npx) lds_write(base + a.at_e + ((r + r_lo - ih0) * (a.W + 2) + c + 1) * EP + half * 16, v);
+    }
+  }
+  // the lane's rows of the nine diagonal matrices: channel weight_row(l32), its byte among the lane's 16
+  const int ch = weight_row(l32);
+  v4i diag[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
+    const uint32_t w = *(lds_u32 *)(uintptr_t)(base + a.at_const + t * 128 + ch * 4);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) diag[t][d] = (ch >> 4) == half && ((ch >> 2) & 3) == d ? (int)(w & (0xffu << (8 * (ch & 3)))) : 0;
+  }
+  const v16i startd = start16(1);
+  __syncthreads();
+
+  // ---- depthwise layer and last layer of 32 pixels at a time
+  uint8_t *const y = a.y + ((size_t)img * a.P + p0) * a.Q * a.cout;
+  for (int mb = wave; mb < a.mb2; mb += NWAVE) {
+    const int j = mb * 32 + l32, jc = min(j, opx - 1), pr = a.by_q.of(jc), q = jc - pr * a.Q;
+    uint32_t at = base + a.at_e + (pr * (a.W + 2) + q) * (a.stride * EP) + half * 16;
+    v16i acc = startd;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(diag[t], lds_read(at + t % 3 * EP), acc, 0, 0, 0);
+      if (t % 3 == 2) at += (a.W + 2) * EP;
+    }
+    const v4i d = requant16(acc, a.clipd, a.shiftd, (int)a.d_xor);
+    for (int nb = 0; nb < a.nb3; ++nb) {
+      v16i out = __builtin_amdgcn_mfma_i32_32x32x32_i8(lds_read(base + a.at_w2 + nb * 1024 + lane * 16), d, start16(2 + nb), 0, 0, 0);
+      const v4i v = requant16(out, a.clip2, a.shift2, 0);
+      const int c = nb * 32 + half * 16;
+      uint8_t *to = y + j * a.cout + c;
+      if (j < opx && c < a.cout) *reinterpret_cast<v2i *>(to) = v2i{v.x, v.y};
+      if (j < opx && c + 8 < a.cout) *reinterpret_cast<v2i *>(to + 8) = v2i{v.z, v.w};
+    }
+  }
+}
+
 constexpr int LDS_MOST = 160 * 1024;
 constexpr int KS1_MOST = 6;
 
@@ -356,9 +518,8 @@ int rows_for(int Cin, int Ce, int Cout, int H, int W, int P, int Q, int stride, 
   return best;
 }
 
-template <int KS1>
-int launch_one(const Args &a, int lds, long long grid, hipStream_t stream) {
-  auto k = pw_dw_pw_kernel<KS1>;
+template <typename A, void (*k)(const A)>
+int launch_one(const A &a, int lds, long long grid, hipStream_t stream) {
   static std::atomic<unsigned long long> done_mask{0};         // devices whose LDS limit has been raised
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return (int)hipErrorInvalidDevice;
@@ -369,6 +530,41 @@ int launch_one(const Args &a, int lds, long long grid, hipStream_t stream) {
   }
   hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(NT), lds, stream, a);
   return (int)hipGetLastError();
+}
+
+// LDS and blocks of the front's launch with `rows` output rows per workgroup.
+struct ImageShape {
+  int rows, bands, mb1, mb2, xp, at_const, at_w2, at_e, bytes;
+};
+
+ImageShape image_shape_of(int Ce, int Cout, int H, int W, int P, int Q, int stride, int rows) {
+  ImageShape s;
+  s.rows = rows;
+  s.bands = (P + rows - 1) / rows;
+  const int e_rows = (rows - 1) * stride + 3, in_rows = e_rows < H ? e_rows : H;
+  s.mb1 = (in_rows * W + 31) / 32;
+  s.mb2 = (rows * Q + 31) / 32;
+  s.xp = (2 * W + 4) * 4;
+  s.at_const = (2 * in_rows + 1) * s.xp;
+  s.at_w2 = s.at_const + (int)pw_dw_pw_const_bytes(Ce, Cout);
+  s.at_e = s.at_w2 + (Cout + 31) / 32 * 1024;
+  s.bytes = s.at_e + e_rows * (W + 2) * EP;
+  return s;
+}
+
+// As rows_for.
+int image_rows_for(int Ce, int Cout, int H, int W, int P, int Q, int stride, int B) {
+  int best = 0;
+  long long least = 0;
+  for (int rows = 1; rows <= P; ++rows) {
+    const ImageShape s = image_shape_of(Ce, Cout, H, W, P, Q, stride, rows);
+    if (s.bytes > LDS_MOST) break;
+    const long long one = 3500 + (s.mb1 + NWAVE - 1) / NWAVE * 400 + (s.mb2 + NWAVE - 1) / NWAVE * (900 + 200 * ((Cout + 31) / 32));
+    const long long rounds = ((long long)B * s.bands + 255) / 256;
+    const long long cost = 2 * s.bytes <= LDS_MOST ? one * (rounds / 2 * 16 + rounds % 2 * 10) : one * rounds * 10;
+    if (best == 0 || cost < least) { best = rows; least = cost; }
+  }
+  return best;
 }
 
 }  // namespace
@@ -429,13 +625,49 @@ int launch_pw_dw_pw(const PwDwPwParams &p, hipStream_t stream) {
   const long long grid = (long long)p.B * s.bands;
   if (grid > 0x7fffffffLL) return (int)hipErrorInvalidValue;
   switch (ks1) {
-    case 1: return launch_one<1>(a, s.bytes, grid, stream);
-    case 2: return launch_one<2>(a, s.bytes, grid, stream);
-    case 3: return launch_one<3>(a, s.bytes, grid, stream);
-    case 4: return launch_one<4>(a, s.bytes, grid, stream);
-    case 5: return launch_one<5>(a, s.bytes, grid, stream);
-    default: return launch_one<6>(a, s.bytes, grid, stream);
+    case 1: return launch_one<Args, pw_dw_pw_kernel<1>>(a, s.bytes, grid, stream);
+    case 2: return launch_one<Args, pw_dw_pw_kernel<2>>(a, s.bytes, grid, stream);
+    case 3: return launch_one<Args, pw_dw_pw_kernel<3>>(a, s.bytes, grid, stream);
+    case 4: return launch_one<Args, pw_dw_pw_kernel<4>>(a, s.bytes, grid, stream);
+    case 5: return launch_one<Args, pw_dw_pw_kernel<5>>(a, s.bytes, grid, stream);
+    default: return launch_one<Args, pw_dw_pw_kernel<6>>(a, s.bytes, grid, stream);
   }
+}
+
+bool image_dw_pw_applicable(int Ce, int Cout, int H, int W, int stride, int shift1, int shiftd, int shift2, const void *x, const void *y) {
+  if (Ce < 4 || Ce > 32 || (Ce & 3) || Cout < 8 || (Cout & 7) || Cout > 256 || (stride != 1 && stride != 2)) return false;
+  if (H < 1 || W < 4 || (W & 3) || W > 1024 || shift1 < 0 || shiftd < 0 || shift2 < 0) return false;
+  if ((reinterpret_cast<uintptr_t>(x) & 3) || (reinterpret_cast<uintptr_t>(y) & 7)) return false;
+  const int H1 = (H - 1) / 2 + 1, W1 = W / 2;
+  return image_rows_for(Ce, Cout, H1, W1, (H1 - 1) / stride + 1, (W1 - 1) / stride + 1, stride, 1) > 0;
+}
+
+int launch_image_dw_pw(const PwDwPwParams &p, hipStream_t stream) {
+  if (p.B <= 0) return 0;
+  const int W0 = 2 * p.W;
+  if (!image_dw_pw_applicable(p.Ce, p.Cout, p.H0, W0, p.stride, p.shift1, p.shiftd, p.shift2, p.x, p.y) || (p.H0 - 1) / 2 + 1 != p.H || p.has_res ||
+      ((reinterpret_cast<uintptr_t>(p.w1) | reinterpret_cast<uintptr_t>(p.consts) | reinterpret_cast<uintptr_t>(p.w2)) & 15) ||
+      (long long)p.B * p.H0 * W0 * 3 > 0x7fffffffLL)
+    return (int)hipErrorInvalidValue;
+  const int rows = image_rows_for(p.Ce, p.Cout, p.H, p.W, p.P, p.Q, p.stride, p.B);
+  const ImageShape s = image_shape_of(p.Ce, p.Cout, p.H, p.W, p.P, p.Q, p.stride, rows);
+  ImageArgs a;
+  a.x = p.x; a.w1 = p.w1; a.consts = p.consts; a.w2 = p.w2; a.y = p.y;
+  a.H0 = p.H0; a.H = p.H; a.W = p.W; a.P = p.P; a.Q = p.Q; a.stride = p.stride; a.cout = p.Cout; a.groups = W0 / 4;
+  a.rows = rows; a.bands = s.bands; a.nb3 = (p.Cout + 31) / 32; a.mb1 = s.mb1; a.mb2 = s.mb2;
+  a.xp = s.xp; a.at_const = s.at_const; a.at_w2 = s.at_w2; a.at_e = s.at_e;
+  a.x_bytes = p.B * p.H0 * W0 * 3;
+  a.const_bytes = (int)pw_dw_pw_const_bytes(p.Ce, p.Cout);
+  a.w2_bytes = a.nb3 * 1024;
+  a.x_xor = p.x_xor; a.e_xor = p.e_xor; a.d_xor = p.d_xor;
+  a.clip1 = scaled_clip(p.lo1, p.hi1, p.shift1);
+  a.clipd = scaled_clip(p.lod, p.hid, p.shiftd);
+  a.clip2 = scaled_clip(p.lo2, p.hi2, p.shift2);
+  a.shift1 = p.shift1; a.shiftd = p.shiftd; a.shift2 = p.shift2;
+  a.by_bands = Div(s.bands); a.by_w = Div(p.W); a.by_q = Div(p.Q); a.by_groups = Div(a.groups);
+  const long long grid = (long long)p.B * s.bands;
+  if (grid > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+  return launch_one<ImageArgs, image_dw_pw_kernel>(a, s.bytes, grid, stream);
 }
 
 }  // namespace f8

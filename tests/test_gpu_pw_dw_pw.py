@@ -84,3 +84,50 @@ def test_rows_per_workgroup_follow_the_batch(oracle, batch, hw):
         assert np.array_equal(f8.Chain(net).prepare(batch).run(x_t).cpu().numpy(), got)
     finally:
         f8.f8_tuning_set("pw_dw_pw", 1)
+
+
+# expanded, output channels, image, batch, stride, image type, depthwise signed, relu
+IMAGES = [
+    (32, 16, (224, 224), 1, 1, "u8", False, False),
+    (32, 64, (96, 64), 5, 2, "u8", False, True),
+    (16, 8, (7, 4), 9, 1, "s8", True, False),                       # odd rows, two columns of results, half a block of channels
+    (8, 40, (1, 36), 3, 2, "s8", False, True),                      # one row: the window's other two outside
+    (28, 72, (31, 20), 2, 1, "u8", True, True),                     # three blocks of channels out
+    (32, 256, (13, 8), 4, 1, "u8", False, True),                    # eight blocks out
+]
+
+
+@pytest.mark.parametrize("k", range(len(IMAGES)))
+def test_front_of_a_network_in_one_launch(oracle, k):
+    ce, cout, hw, batch, stride, x_type, ds, relu = IMAGES[k]
+    rng = np.random.default_rng(53000 + k)
+    b = wl._NetBuilder("front%d" % k, rng, hw[0], 3, x_type, 5, (5, 9), (2, 6), True)
+    b.net.in_hw = hw
+    b.t[0]["hw"] = hw
+    u = b.dwconv("dw", b.conv("stem", 0, ce, 3, 2, 1), 3, stride, 1)
+    if ds:
+        L = b.net.layers[-1]
+        L.y_type, L.clip_lo, L.clip_hi = "s8", -127, 100
+        b.t[u]["type"] = "s8"
+    b.conv("after", b.conv("project", u, cout, 1, 1, 0, relu=relu), 32, 1, 1, 0)
+    net = b.net
+    x = wl.draw_u8(rng, (batch,) + hw + (3,))
+    if x_type == "s8":
+        x = x.view(np.int8)
+    want = oracle.run_network(net, x, keep_all=True)
+    last = net.layers[-1].dst
+    raw = torch.zeros(x.size + 64, dtype=torch.uint8, device="cuda")
+    try:
+        for force in (0, 2):
+            f8.f8_tuning_set("pw_dw_pw", force)
+            chain = f8.Chain(net).prepare(batch)
+            names = [chain.layer_info(i, batch)[0] for i in range(3)]
+            assert (names[0] == names[2] == "(fused)" and names[1].startswith("conv3x3+dwconv3x3<s%d>" % stride)) == (force == 2), names
+            for shift in (0, 1, 4):                                 # an image off the 4-byte grid: layer by layer
+                x_t = raw[shift:shift + x.size].view(torch.int8 if x_type == "s8" else torch.uint8).view(x.shape)
+                x_t.copy_(torch.from_numpy(x))
+                got = chain.run(x_t).cpu().numpy()
+                assert np.array_equal(got, want[last]), (IMAGES[k], force, shift, int((got != want[last]).sum()))
+    finally:
+        f8.f8_tuning_set("pw_dw_pw", 1)
+    assert len(np.unique(want[net.layers[2].dst])) > 4, "degenerate draw"

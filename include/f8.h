@@ -383,6 +383,7 @@ f8_status f8_mfma_i8_yardstick_operands(int32_t *sink, int iters, uint32_t seed,
  * kernel), "pw_ws", "pw_small", "xcd_remap", "pw_wide", "pw_mid" (1: the 1x1 128 -> 512 kernel only
  * together with the 512 -> 128 layer behind it, 2: also alone), "stem_pool", "conv_tail", "conv_img" (1 = the
  * kernel with one image per workgroup where it is the faster one, 2 = before any other wherever it fits), "imgk" (1 = on; 10 + n: the image-stationary 3x3 kernel with n = 1, 2 or 4 waves sharing K wherever it fits),
+ * "conv_pair" (1 = on: the two 3x3 layers of a basic residual block in one launch where both take that kernel),
  * "dw_pw" (1 = on where it pays; 2: a depthwise layer and the 1x1 layer behind it in one launch wherever
  * they fit), "pw_dw_pw" (1 = on where it pays: the 1x1 layer in front of such a pair in the same launch; 2: wherever the three fit), "bottleneck" (1 = on where it pays; 2: the last two layers of a bottleneck block and the first of the next in one
  * launch wherever they fit; 3 and 4: the same, always with the narrower or the wider of its two tiles), "conv_img_min" (96: fewest images, or bands of 28 image rows, for which a chain takes the

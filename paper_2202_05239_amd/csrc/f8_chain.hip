@@ -39,6 +39,7 @@
 #include "stem_pool.h"
 #include "conv_img.h"
 #include "conv_imgk.h"
+#include "conv_imgk_pair.h"
 #include "f8_host.h"
 
 using namespace f8;
@@ -142,6 +143,18 @@ struct f8_chain {
       if (wgs >= (L.Cin == 128 && wk == 2 ? 128 : 176)) return wgs <= most ? wk : 0;
     }
     return 0;
+  }
+  // Two 3x3 layers of 64 channels of which the second is the first's only reader and may have the first's input as its shortcut
+  // (a basic residual block): pair[i] = 1 and 2, one launch (the second's) where both take the image-stationary kernel, whose
+  // copies of the weights it reads.  Ahead at every size and batch that comes to that, microseconds of the block (a forward gains 3 - 5 more), two
+  // launches -> one: 56 x 56, batch 16 13.1 -> 10.9, 24 17.4 -> 11.4, 32 18.6 -> 14.3, 48 21.7 -> 18.5, 64 25.2 -> 19.6; 40 x 40, batch 24 13.2 -> 9.2, 64 18.9 ->
+  // 12.9, 128 27.8 -> 21.7.
+  std::vector<int> pair;               // per layer
+  int conv_pair = 1;
+  int pair_role(size_t i, int batch) const {
+    if (pair[i] == 0 || conv_pair == 0 || keep_all) return 0;
+    const size_t a = pair[i] == 1 ? i : i - 1;
+    return img_role(a, batch) >= 2 && img_role(a + 1, batch) >= 2 ? pair[i] : 0;
   }
   // A depthwise 3x3 layer and the 1x1 layer that is its only reader in one launch: dwp[i] = 1 for the depthwise one,
   // 2 for the other; dwp_w_bytes: of the 1x1 layer's weights in fragment order.  Whether the pair runs as one
@@ -359,6 +372,7 @@ struct f8_chain {
       // written by this launch: must not share memory with what any of its layers reads
       if (!keep_all && pdp[li] == 1) place(layers[li + 2].dst);
       if (!keep_all && dwp[li] == 1) place(layers[li + 1].dst);
+      if (!keep_all && pair[li] == 1 && layers[li + 1].res < 0) place(layers[li + 1].dst);    // (a shortcut outlives it by itself)
       place(layers[li].dst);
       if (bn[li] == 1 && bn_allowed(li)) {
         place(layers[li + 1].dst);
@@ -493,6 +507,27 @@ struct f8_chain {
     return p;
   }
 
+  // Parameters of the basic residual block that starts at layer i.
+  ConvPairParams pair_params(size_t i, const void *x, void *out, void *workspace, int batch) const {
+    const f8_layer_desc &L = layers[i], &T = layers[i + 1];
+    uint8_t *cb = static_cast<uint8_t *>(workspace);
+    ConvPairParams p;
+    p.x = static_cast<const uint8_t *>(tensor_ptr(L.src, x, out, workspace, batch));
+    p.wa = reinterpret_cast<const int8_t *>(cb + frag_off[i]);
+    p.wb = reinterpret_cast<const int8_t *>(cb + frag_off[i + 1]);
+    p.acc_a = reinterpret_cast<const int32_t *>(cb + acc0_off[i]);
+    p.acc_b = reinterpret_cast<const int32_t *>(cb + acc0_off[i + 1]);
+    p.y = static_cast<uint8_t *>(tensor_ptr(T.dst, x, out, workspace, batch));
+    p.B = batch; p.H = geom[i].H; p.W = geom[i].W;
+    p.x_xor = L.q.x_type == F8_U8 ? 0x80808080u : 0u;
+    p.e_xor = L.q.y_type == F8_U8 ? 0x80808080u : 0u;
+    p.shift_a = L.q.fl_x + L.q.fl_w - L.q.fl_y; p.lo_a = L.q.clip_lo; p.hi_a = L.q.clip_hi;
+    p.shift_b = T.q.fl_x + T.q.fl_w - T.q.fl_y; p.lo_b = T.q.clip_lo; p.hi_b = T.q.clip_hi;
+    p.has_res = T.res >= 0;
+    p.res_d = p.has_res ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0;
+    return p;
+  }
+
   // Parameters of the inverted-residual block that starts at layer i.
   // (an image of the caller's that does not lie on the four bytes its rows are fetched in: layer by layer)
   bool pdp_reads(size_t front, const void *x, void *workspace, int batch) const {
@@ -560,6 +595,12 @@ struct f8_chain {
     if (block == 2) {
       const PwDwPwParams pp = pdp_params(i - 1, x, out, workspace, batch);
       return (pdp_image(i - 1) ? launch_image_dw_pw(pp, s) : launch_pw_dw_pw(pp, s)) == 0 ? F8_OK : F8_ERR_DEVICE;
+    }
+    const int twin = pair_role(i, batch);
+    if (twin == 1) return F8_OK;
+    if (twin == 2) {
+      const ConvPairParams cp = pair_params(i - 1, x, out, workspace, batch);
+      return launch_conv_pair(cp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
     if (tail_role(i, batch) == 2 || dwp_role(i, batch) == 2) return F8_OK;
     if (dwp_role(i, batch) == 1) {
@@ -793,6 +834,7 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->dwp.push_back(0);
     c->dwp_w_bytes.push_back(0);
     c->frag_off.push_back(0);
+    c->pair.push_back(0);
     c->pdp.push_back(0);
     c->pdp_off.push_back(0);
     c->pdp_w2_off.push_back(0);
@@ -852,6 +894,19 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
         break;
       }
     }
+  }
+  // basic residual blocks of 64 channels, all tensors in the arena
+  c->conv_pair = tuning().conv_pair.load();
+  for (size_t i = 0; i + 1 < c->layers.size(); ++i) {
+    const f8_layer_desc &L = c->layers[i], &T = c->layers[i + 1];
+    if (c->pair[i] != 0 || c->img_w_bytes[i] == 0 || c->img_w_bytes[i + 1] == 0 || L.Cin != 64 || T.Cin != 64 || L.res >= 0 || T.src != L.dst ||
+        c->tensors[L.dst].last_use != (int)i + 1 || (T.res >= 0 && (T.res != L.src || T.q.res_type != L.q.x_type)))
+      continue;
+    if (c->tensors[L.src].external || c->tensors[L.dst].external || c->tensors[T.dst].external) continue;
+    if (!conv_pair_applicable(c->geom[i].H, c->geom[i].W, L.q.fl_x + L.q.fl_w - L.q.fl_y, T.q.fl_x + T.q.fl_w - T.q.fl_y, T.res >= 0,
+                              T.res >= 0 ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0, nullptr, nullptr))
+      continue;
+    c->pair[i] = 1; c->pair[i + 1] = 2;
   }
   // a 3x3 layer, the 1x1 layer of four times its channels that is its only reader, and the 1x1 layer that opens the next
   // block (the next layer, or the one after a new stage's shortcut projection); all tensors in the arena
@@ -1156,7 +1211,7 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
   // tensors inside a fused block are never materialised
   const bool elided = (t.producer >= 0 && (c->pool_role((size_t)t.producer) == 1 || c->dwp_role((size_t)t.producer, batch) == 1 ||
                                              c->pdp_role((size_t)t.producer, batch) == 1 || c->pdp_role((size_t)t.producer, batch) == 2 ||
-                                             c->bn_role((size_t)t.producer, batch) == 1)) ||
+                                             c->bn_role((size_t)t.producer, batch) == 1 || c->pair_role((size_t)t.producer, batch) == 1)) ||
                       (c->use_fusion() && t.producer >= 0 && c->fused[t.producer].role != 0 &&
                        !(c->fused[t.producer].role == 2 && t.producer >= 2 && c->fused[t.producer - 2].role == 1));
   // (with two streams the two halves of a tensor lie apart: not reported)
@@ -1284,6 +1339,12 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       else name = conv_kernel_name(gk, L.q, L.res >= 0, L.dst2 > 0 ? &L.q2 : nullptr);
       ops = 2.0 * M * g.R * g.S * g.Cin * g.Cout;
       bytes += (double)g.R * g.S * g.Cin * g.Cout + 4.0 * g.Cout;
+      if (const int twin = c->pair_role((size_t)layer, batch)) {
+        // both layers are accounted to the second, whose launch computes them: the block's input (also its shortcut) and output
+        name = twin == 1 ? "conv3x3_imgk<64> in the next" : "conv3x3_imgk<64> twice";
+        ops = twin == 1 ? 0.0 : 2.0 * ops;
+        bytes = twin == 1 ? 0.0 : 2.0 * (M * 64 + 9.0 * 64 * 64 + 4.0 * 64);
+      }
       if (three == 1) {
         // plus the closing layer (residual in, one or two formats out) and the layer behind it
         const f8_layer_desc &T = c->layers[layer + 1];

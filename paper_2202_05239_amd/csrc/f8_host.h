@@ -37,6 +37,7 @@ struct Tuning {
   std::atomic<int> conv_tail{1};       // chain: next block's first 1x1 layer computed behind a closing layer
   std::atomic<int> conv_img{1};        // chain: image-stationary 3x3 kernels (128 and 256 channels); 2: before any other
   std::atomic<int> imgk{1};            // chain: image-stationary 3x3 kernel with K shared among the waves (10 + n: with n waves, wherever it fits)
+  std::atomic<int> conv_pair{1};       // chain: the two 3x3 layers of a basic residual block in one launch where both take the kernel above
   std::atomic<int> bottleneck{1};      // chain: the last two layers of a bottleneck block and the next one's first in one launch (2: at any batch; 3, 4: the same with the narrow, the wide tile)
   std::atomic<int> dw_pw{1};           // chain: depthwise layer and the 1x1 layer behind it in one launch (2: at any batch)
   std::atomic<int> pw_dw_pw{1};        // chain: the 1x1 layer in front of such a pair in the same launch (2: also where the pair is two)

@@ -154,6 +154,8 @@ struct f8_chain {
   int pair_role(size_t i, int batch) const {
     if (pair[i] == 0 || conv_pair == 0 || keep_all) return 0;
     const size_t a = pair[i] == 1 ? i : i - 1;
+    // (the second may also be the first of a bottleneck's three, which then read its input)
+    if (bn_role(a, batch) != 0 || bn_role(a + 1, batch) != 0) return 0;
     return img_role(a, batch) >= 2 && img_role(a + 1, batch) >= 2 ? pair[i] : 0;
   }
   // A depthwise 3x3 layer and the 1x1 layer that is its only reader in one launch: dwp[i] = 1 for the depthwise one,

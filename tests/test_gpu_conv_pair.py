@@ -59,3 +59,21 @@ def test_basic_block_in_one_launch(oracle, k):
     want = oracle.run_network(net, np.ascontiguousarray(x[pick]), keep_all=True)
     assert np.array_equal(outs[1].cpu().numpy()[pick], want[net.layers[-1].dst]), CASES[k]
     assert len(np.unique(want[net.layers[2].dst])) > 4, "degenerate draw"
+
+
+def test_the_second_layer_may_open_a_bottleneck(oracle):
+    """3x3, 3x3, 1x1 of four times the channels: the last three layers share a launch and read what the first one wrote."""
+    rng = np.random.default_rng(54100)
+    b = wl._NetBuilder("both", rng, 28, 16, "u8", 5, (6, 9), (2, 6), True)
+    t = b.conv("a", b.conv("before", 0, 64, 1, 1, 0), 64, 3, 1, 1)
+    b.conv("after", b.conv("c", b.conv("b", t, 64, 3, 1, 1), 256, 1, 1, 0), 64, 1, 1, 0)
+    b.conv("last", len(b.t) - 1, 32, 1, 1, 0)
+    x = wl.draw_u8(rng, (40, 28, 28, 16))
+    f8.f8_tuning_set("imgk", 11)
+    try:
+        chain = f8.Chain(b.net).prepare(40)
+        assert chain.layer_info(2, 40)[0] == "bottleneck<64>" and chain.layer_info(1, 40)[0] == "conv3x3_imgk<64>"
+        got = chain.run(torch.from_numpy(x).cuda()).cpu().numpy()
+    finally:
+        f8.f8_tuning_set("imgk", 1)
+    assert np.array_equal(got[:3], oracle.run_network(b.net, np.ascontiguousarray(x[:3])))

@@ -144,11 +144,12 @@ struct f8_chain {
     }
     return 0;
   }
-  // Two 3x3 layers of 64 channels of which the second is the first's only reader and may have the first's input as its shortcut
+  // Two 3x3 layers of 64 or 128 channels of which the second is the first's only reader and may have the first's input as its shortcut
   // (a basic residual block): pair[i] = 1 and 2, one launch (the second's) where both take the image-stationary kernel, whose
-  // copies of the weights it reads.  Ahead at every size and batch that comes to that, microseconds of the block (a forward gains 3 - 5 more), two
-  // launches -> one: 56 x 56, batch 16 13.1 -> 10.9, 24 17.4 -> 11.4, 32 18.6 -> 14.3, 48 21.7 -> 18.5, 64 25.2 -> 19.6; 40 x 40, batch 24 13.2 -> 9.2, 64 18.9 ->
-  // 12.9, 128 27.8 -> 21.7.
+  // copies of the weights it reads.  Microseconds of the block (a forward gains 3 - 5 more), two launches -> one.  64 channels, ahead at every size
+  // and batch that comes to that: 56 x 56, batch 16 13.1 -> 10.9, 24 17.4 -> 11.4, 32 18.6 -> 14.3, 48 21.7 -> 18.5, 64 25.2 -> 19.6; 40 x 40, batch 24 13.2 -> 9.2, 64 18.9 ->
+  // 12.9, 128 27.8 -> 21.7.  128 channels: 28 x 28, batch 16 15.7 -> 10.4, 32 17.4 -> 12.2, 64 20.9 -> 18.2, 128 33.1 -> 29.7, 192 48.1 -> 52.0, 256 62.0 ->
+  // 58.5 (whole rounds of workgroups); 20 x 20, batch 64 17.1 -> 13.5, 256 33.9 -> 30.3.
   std::vector<int> pair;               // per layer
   int conv_pair = 1;
   int pair_role(size_t i, int batch) const {
@@ -156,6 +157,7 @@ struct f8_chain {
     const size_t a = pair[i] == 1 ? i : i - 1;
     // (the second may also be the first of a bottleneck's three, which then read its input)
     if (bn_role(a, batch) != 0 || bn_role(a + 1, batch) != 0) return 0;
+    if (layers[a].Cin == 128 && (long long)batch * geom[a].P * geom[a].Q > 131072) return 0;
     return img_role(a, batch) >= 2 && img_role(a + 1, batch) >= 2 ? pair[i] : 0;
   }
   // A depthwise 3x3 layer and the 1x1 layer that is its only reader in one launch: dwp[i] = 1 for the depthwise one,
@@ -520,7 +522,7 @@ struct f8_chain {
     p.acc_a = reinterpret_cast<const int32_t *>(cb + acc0_off[i]);
     p.acc_b = reinterpret_cast<const int32_t *>(cb + acc0_off[i + 1]);
     p.y = static_cast<uint8_t *>(tensor_ptr(T.dst, x, out, workspace, batch));
-    p.B = batch; p.H = geom[i].H; p.W = geom[i].W;
+    p.B = batch; p.H = geom[i].H; p.W = geom[i].W; p.C = L.Cin;
     p.x_xor = L.q.x_type == F8_U8 ? 0x80808080u : 0u;
     p.e_xor = L.q.y_type == F8_U8 ? 0x80808080u : 0u;
     p.shift_a = L.q.fl_x + L.q.fl_w - L.q.fl_y; p.lo_a = L.q.clip_lo; p.hi_a = L.q.clip_hi;
@@ -897,15 +899,15 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
       }
     }
   }
-  // basic residual blocks of 64 channels, all tensors in the arena
+  // basic residual blocks of 64 or 128 channels, all tensors in the arena
   c->conv_pair = tuning().conv_pair.load();
   for (size_t i = 0; i + 1 < c->layers.size(); ++i) {
     const f8_layer_desc &L = c->layers[i], &T = c->layers[i + 1];
-    if (c->pair[i] != 0 || c->img_w_bytes[i] == 0 || c->img_w_bytes[i + 1] == 0 || L.Cin != 64 || T.Cin != 64 || L.res >= 0 || T.src != L.dst ||
+    if (c->pair[i] != 0 || c->img_w_bytes[i] == 0 || c->img_w_bytes[i + 1] == 0 || L.Cin != T.Cin || L.res >= 0 || T.src != L.dst ||
         c->tensors[L.dst].last_use != (int)i + 1 || (T.res >= 0 && (T.res != L.src || T.q.res_type != L.q.x_type)))
       continue;
     if (c->tensors[L.src].external || c->tensors[L.dst].external || c->tensors[T.dst].external) continue;
-    if (!conv_pair_applicable(c->geom[i].H, c->geom[i].W, L.q.fl_x + L.q.fl_w - L.q.fl_y, T.q.fl_x + T.q.fl_w - T.q.fl_y, T.res >= 0,
+    if (!conv_pair_applicable(L.Cin, c->geom[i].H, c->geom[i].W, L.q.fl_x + L.q.fl_w - L.q.fl_y, T.q.fl_x + T.q.fl_w - T.q.fl_y, T.res >= 0,
                               T.res >= 0 ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0, nullptr, nullptr))
       continue;
     c->pair[i] = 1; c->pair[i + 1] = 2;
@@ -1343,9 +1345,10 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       bytes += (double)g.R * g.S * g.Cin * g.Cout + 4.0 * g.Cout;
       if (const int twin = c->pair_role((size_t)layer, batch)) {
         // both layers are accounted to the second, whose launch computes them: the block's input (also its shortcut) and output
-        name = twin == 1 ? "conv3x3_imgk<64> in the next" : "conv3x3_imgk<64> twice";
+        if (L.Cin == 64) name = twin == 1 ? "conv3x3_imgk<64> in the next" : "conv3x3_imgk<64> twice";
+        else name = twin == 1 ? "conv3x3_imgk<128> in the next" : "conv3x3_imgk<128> twice";
         ops = twin == 1 ? 0.0 : 2.0 * ops;
-        bytes = twin == 1 ? 0.0 : 2.0 * (M * 64 + 9.0 * 64 * 64 + 4.0 * 64);
+        bytes = twin == 1 ? 0.0 : 2.0 * (M * L.Cin + 9.0 * L.Cin * L.Cin + 4.0 * L.Cin);
       }
       if (three == 1) {
         // plus the closing layer (residual in, one or two formats out) and the layer behind it

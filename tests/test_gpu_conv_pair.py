@@ -1,4 +1,4 @@
-"""A basic residual block of 64 channels (3x3, 3x3, shortcut) in one launch."""
+"""A basic residual block of 64 or 128 channels (3x3, 3x3, shortcut) in one launch."""
 import numpy as np
 import pytest
 import torch
@@ -17,12 +17,16 @@ CASES = [
     ((7, 56), 40, True, False, False, False),
     ((1, 56), 3, False, True, False, True),         # one row: a row of zeros on either side of both tensors
     ((37, 24), 18, False, False, False, True),
+    ((28, 28), 7, False, False, False, True, 128),
+    ((19, 28), 5, True, True, True, True, 128),
+    ((30, 27), 6, False, True, False, False, 128),
+    ((1, 28), 3, False, False, False, True, 128),
 ]
 
 
 @pytest.mark.parametrize("k", range(len(CASES)))
 def test_basic_block_in_one_launch(oracle, k):
-    hw, batch, xs, es, ys, res = CASES[k]
+    hw, batch, xs, es, ys, res, C = CASES[k] if len(CASES[k]) == 7 else CASES[k] + (64,)
     rng = np.random.default_rng(54000 + k)
     b = wl._NetBuilder("basic%d" % k, rng, hw[0], 16, "u8", 5, (6, 9), (2, 6), True)
     b.net.in_hw = hw
@@ -36,8 +40,8 @@ def test_basic_block_in_one_launch(oracle, k):
             b.t[t]["type"] = "s8"
         return t
 
-    t = conv("before", 0, 64, 1, xs)
-    conv("after", conv("b", conv("a", t, 64, 3, es), 64, 3, ys, t if res else -1), 32, 1, False)
+    t = conv("before", 0, C, 1, xs)
+    conv("after", conv("b", conv("a", t, C, 3, es), C, 3, ys, t if res else -1), 32, 1, False)
     net = b.net
     x = wl.draw_u8(rng, (batch,) + hw + (16,))
     x_t = torch.from_numpy(x).cuda()
@@ -48,7 +52,7 @@ def test_basic_block_in_one_launch(oracle, k):
             f8.f8_tuning_set("imgk", 11)
             chain = f8.Chain(net).prepare(batch)
             names = [chain.layer_info(i, batch)[0] for i in (1, 2)]
-            assert names == (["conv3x3_imgk<64>"] * 2 if force == 0 else ["conv3x3_imgk<64> in the next", "conv3x3_imgk<64> twice"])
+            assert names == ["conv3x3_imgk<%d>%s" % (C, s) for s in (("", "") if force == 0 else (" in the next", " twice"))]
             outs[force] = chain.run(x_t)
             assert force == 0 or chain.tensor(net.layers[1].dst) is None
     finally:

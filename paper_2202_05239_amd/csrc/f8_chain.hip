@@ -287,6 +287,8 @@ struct f8_chain {
   int tail_role(size_t i, int batch) const {
     if (!conv_tail || tail[i] == 0 || tail_in_fused_block(i)) return 0;
     const size_t head = tail[i] == 1 ? i : (size_t)tail_peer[i], behind = tail[i] == 1 ? (size_t)tail_peer[i] : i;
+    // (a bottleneck's launch computes the first layer of the pair, and of its readers one that need not be this pair's second)
+    if (bn_role(head, batch) != 0) return 0;
     Geom g = geom[head];
     g.B = batch;
     return conv_tail_ok(g, layers[head].q, layers[behind].Cout) ? tail[i] : 0;

@@ -1,0 +1,58 @@
+"""Launches that compute several layers of a chain: every layer is computed by exactly one of them."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2202_05239_amd import binding as f8
+from paper_2202_05239_amd import workloads as wl
+from test_host_api import make_descs
+
+
+def reported(net, batch):
+    """(kernel name, operations) of every layer of the chain, switches as they stand; no GPU needed."""
+    L, h, buf = f8.lib(), ctypes.c_void_p(), ctypes.create_string_buffer(64)
+    ops, rows = ctypes.c_double(), []
+    assert L.f8_chain_create(make_descs(net), len(net.layers), net.in_hw[0], net.in_hw[1], net.in_c, f8._TYPES[net.x_type], ctypes.byref(h)) == 0
+    for i in range(len(net.layers)):
+        assert L.f8_chain_layer_info(h, i, batch, buf, 64, ctypes.byref(ops), None) == 0
+        rows.append((buf.value.decode(), ops.value))
+    L.f8_chain_destroy(h)
+    return rows
+
+
+def two_readers(first, second):
+    """A 3x3 128 -> 128 layer, the 1x1 layer of 512 that closes the block, and two 1x1 layers that read it."""
+    rng = np.random.default_rng(61000 + first)
+    b = wl._NetBuilder("two_readers", rng, 28, 16, "u8", 5, (5, 9), (2, 6), True)
+    t = b.conv("mid", b.conv("before", 0, 128, 1, 1, 0), 128, 3, 1, 1)
+    t = b.conv("close", t, 512, 1, 1, 0)
+    u, v = b.conv("first", t, first, 1, 1, 0), b.conv("second", t, second, 1, 1, 0)
+    b.conv("join", u, 32, 1, 1, 0, res=b.conv("other", v, 32, 1, 1, 0))
+    return b.net, rng
+
+
+@pytest.mark.parametrize("first, second", [(256, 128), (128, 256)])
+def test_a_closing_layer_with_two_readers_host_side(first, second):
+    """The bottleneck launch takes the first reader; the second is not the closing layer's tail then but a launch of its own."""
+    net, _ = two_readers(first, second)
+    for batch in (84, 100, 167):
+        names = [n for n, _ in reported(net, batch)]
+        assert names[1] == "bottleneck<128>" and names[2] == names[3] == "(fused)", names
+        assert names[4] != "(fused)", (batch, names)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("first, second", [(256, 128), (128, 256)])
+def test_a_closing_layer_with_two_readers(oracle, first, second):
+    net, rng = two_readers(first, second)
+    x = wl.draw_u8(rng, (200, 28, 28, 16))
+    pick = [0, 49, 99, 100, 199]
+    want = oracle.run_network(net, np.ascontiguousarray(x[pick]))
+    x_t = torch.from_numpy(x).cuda()
+    for streams, n in ((1, 100), (2, 200)):                      # (either half of 200 images takes both launches too)
+        chain = f8.Chain(net, streams=streams).prepare(n)
+        assert chain.layer_info(1, 100)[0] == "bottleneck<128>" and chain.layer_info(4, 100)[0] != "(fused)"
+        got = chain.run(x_t[:n]).cpu().numpy()
+        assert np.array_equal(got[[p for p in pick if p < n]], want[:sum(p < n for p in pick)])

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(NT, 2) void pw_dw_pw_kernel(const Args a) {
     for (int k = 0; k < KS1; ++k)
       wn[k] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(w1res, lane * 16, (nb * KS1 + k) * 1024, 0));
   };
-  load_w1(slot1);
+  load_w1(min(slot1, a.nb1 - 1));      // (of the waves without a block too: the descriptor does not bound the scalar offset)
   // ---- depthwise weights and start values, straight into LDS
   {
     const __amdgpu_buffer_rsrc_t cres = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(a.consts), 0, a.const_bytes, 0x00027000);

@@ -998,7 +998,8 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     auto take = [&](size_t bytes) { const size_t off = c->const_bytes; c->const_bytes += round256(bytes); return off; };
     c->pdp_off[i] = take(round256(dw_pw_weight_bytes(c->pdp_k(i), L.Cout)) + pw_dw_pw_const_bytes(L.Cout, T.Cout) + (size_t)(L.Cout + 31) / 32 * 128);
     // (large maps and long K: see dw_pw_pays)
-    if (image || c->dwp[i + 1] != 1 || g.Q > 28 || dw_pw_slices(L.Cout, T.Cout) > 20) c->pdp_w2_off[i] = take(dw_pw_weight_bytes(L.Cout, T.Cout));
+    if (c->pw_dw_pw == 2 || image || c->dwp[i + 1] != 1 || g.Q > 28 || dw_pw_slices(L.Cout, T.Cout) > 20)
+      c->pdp_w2_off[i] = take(dw_pw_weight_bytes(L.Cout, T.Cout));
   }
   // inverted-residual blocks that can run as one kernel
   for (size_t i = 0; i + 2 < c->layers.size(); ++i) {

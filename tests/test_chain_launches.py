@@ -56,3 +56,38 @@ def test_a_closing_layer_with_two_readers(oracle, first, second):
         assert chain.layer_info(1, 100)[0] == "bottleneck<128>" and chain.layer_info(4, 100)[0] != "(fused)"
         got = chain.run(x_t[:n]).cpu().numpy()
         assert np.array_equal(got[[p for p in pick if p < n]], want[:sum(p < n for p in pick)])
+
+
+def three_in_one(rows):
+    return {i for i, (n, _) in enumerate(rows) if n.startswith(("1x1+dwconv", "conv3x3+dwconv", "inverted_residual"))}
+
+
+def test_switch_takes_every_block_that_fits_host_side():
+    """"pw_dw_pw" = 2: the launch of three layers wherever they fit, whatever the batch and the pair's own rule say."""
+    try:
+        for net in (wl.mobilenet_v2_forward(batch=1)[1], wl.mobilenet_v1_forward(batch=1)[1]):
+            f8.f8_tuning_set("pw_dw_pw", 2)
+            f8.f8_tuning_set("dw_pw", 2)
+            fits = three_in_one(reported(net, 1))
+            f8.f8_tuning_set("dw_pw", 1)
+            for batch in (1, 70, 256, 700):
+                assert three_in_one(reported(net, batch)) == fits, (net.name, batch)
+            assert fits
+    finally:
+        f8.f8_tuning_set("pw_dw_pw", 1)
+        f8.f8_tuning_set("dw_pw", 1)
+
+
+@pytest.mark.gpu
+def test_switch_takes_every_block_that_fits(oracle):
+    """700 images of 64 x 64: the pairs alone are two launches here, so every block reads a weight copy of its own."""
+    x, net = wl.mobilenet_v2_forward(batch=700, hw=64)
+    x_t = torch.from_numpy(x).cuda()
+    apart = f8.Chain(net).prepare(700).run(x_t)
+    f8.f8_tuning_set("pw_dw_pw", 2)
+    try:
+        got = f8.Chain(net).prepare(700).run(x_t)
+    finally:
+        f8.f8_tuning_set("pw_dw_pw", 1)
+    assert torch.equal(got, apart)
+    assert np.array_equal(got[[0, 699]].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[[0, 699]])))

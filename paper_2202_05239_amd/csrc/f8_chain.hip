@@ -200,27 +200,51 @@ struct f8_chain {
   // ahead too (136 -> 73, 178 -> 101); from 3 M pixels on the layers keep the kernels that per-layer accounts of such batches name.
   bool pdp_image(size_t front) const { return stem[front].on && stem[front].Cp == 4; }
   int pdp_k(size_t front) const { return pdp_image(front) ? 48 : layers[front].Cin; }
-  // Wherever the pair is one launch the three are too: microseconds of front layer and pair, two launches -> one (two launches
+  // Where the pair is one launch, microseconds of front layer and pair, two launches -> one (two launches
   // cost 1 - 2 us more in a forward than alone), MobileNetV2: 28 x 28 C192, batch 1 8.5 -> 6.7, 27 13.8 -> 8.5; 14 x 14 C384, batch 1 7.6 -> 5.4, 27 11.2 ->
   // 6.6, 64 12.5 -> 9.0, 96 17.2 -> 11.2; C576, batch 1 8.9 -> 7.6, 27 12.8 -> 9.0, 64 17.5 -> 11.9; 28 x 28 C192 stride 2, batch 64 15.5 -> 8.2, 192 26.6 ->
   // 18.8; 56 x 56 C144, batch 1 11.2 -> 5.7, stride 2, batch 27 14.6 -> 9.0, 40 16.1 -> 15.2.
   // 1: front layer, 2: depthwise layer (which launches all three), 3: the one behind
-  int pdp_role(size_t i, int batch) const {
+  int pdp_role_at(size_t i, int batch) const {
     if (pdp[i] == 0 || pw_dw_pw == 0 || keep_all) return 0;
     const size_t front = i + 1 - (size_t)pdp[i];
     if (use_fusion() && (fused[front].role != 0 || fused[front + 1].role != 0 || fused[front + 2].role != 0)) return 0;
-    if (dwp_role(front + 1, batch) != 1 && (pdp_w2_off[front] == 0 || (pw_dw_pw != 2 && !pdp_pays(front, batch)))) return 0;
+    const bool pair = dwp_role(front + 1, batch) == 1;
+    if ((!pair && pdp_w2_off[front] == 0) || (pw_dw_pw != 2 && !pdp_pays(front, batch, pair))) return 0;
     return pdp[i];
+  }
+  // Roles at the batch of the last f8_chain_prepare and at its halves, worked out there: the rule walks through the launch's shapes, half a
+  // microsecond each time, and a run asks for every layer.
+  struct PdpRoles {
+    int batch = -1;
+    std::vector<char> role;
+  };
+  PdpRoles pdp_prepared[3];
+  void forget_pdp_roles() { for (PdpRoles &r : pdp_prepared) r.batch = -1; }
+  void prepare_pdp_roles(int batch) {
+    forget_pdp_roles();
+    const int batches[3] = {batch, batch / 2, batch - batch / 2};
+    for (int k = 0; k < 3; ++k) {
+      for (size_t i = 0; i < layers.size(); ++i) pdp_prepared[k].role[i] = (char)pdp_role_at(i, batches[k]);
+      pdp_prepared[k].batch = batches[k];
+    }
+  }
+  int pdp_role(size_t i, int batch) const {
+    for (const PdpRoles &r : pdp_prepared)
+      if (r.batch == batch) return r.role[i];
+    return pdp_role_at(i, batch);
   }
   // Where the pair is two launches, microseconds of the three, three launches -> one (three launches cost 2 - 4 us more in a forward), MobileNetV2:
   //   56 x 56 C144: batch 16 21.7 -> 10.8, 27 19.2 -> 15.4, 40 23.9 -> 23.5, 64 31.5 -> 29.4; C96 from 112 x 112: batch 16 18.4 -> 13.5, 27 24.4 -> 19.8, 64 40.7 -> 37.7,
   //     96 (either) behind: the rows above and below a workgroup's, computed twice, outweigh the launches
   //   7 x 7 C960: batch 1 9.9 -> 10.5, 16 11.4 -> 10.2, 40 12.5 -> 10.4, 64 13.8 -> 11.0, 128 19.7 -> 13.7, 192 23 -> 24
-  bool pdp_pays(size_t front, int batch) const {
+  // Within these lines, and wherever the pair is one launch, pw_dw_pw_pays decides, from all sizes of the block.
+  bool pdp_pays(size_t front, int batch, bool pair) const {
     const Geom &g = geom[front + 1];
     const long long M = (long long)batch * g.P * g.Q;
-    if (pdp_image(front)) return M < 3 << 20;
-    return M <= (g.Q > 28 ? 210000 : 10000);
+    if (pdp_image(front)) return pair || M < 3 << 20;
+    if (!pair && M > (g.Q > 28 ? 210000 : 10000)) return false;
+    return pw_dw_pw_pays(layers[front].Cin, layers[front].Cout, layers[front + 2].Cout, g.H, g.W, g.sh, batch, pair);
   }
   // A 3x3 layer, the 1x1 layer of four times its channels that is its only reader, and (where there is one) the 1x1 layer
   // behind that in one launch: bn[i] = 1 for the first, 2 and 3 for the others; bn_head[i] = the first layer, bn_behind[i]
@@ -1035,6 +1059,7 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     i += 2;
   }
   c->const_bytes = round256(c->const_bytes);
+  for (auto &r : c->pdp_prepared) r.role.assign(c->layers.size(), 0);
   *out = c;
   return F8_OK;
 }
@@ -1043,6 +1068,7 @@ f8_status f8_chain_set_keep_all(f8_chain *c, int keep_all) {
   if (!c) return F8_ERR_NULL;
   c->keep_all = keep_all != 0;
   c->planned = false;
+  c->forget_pdp_roles();
   c->prepared_ws = nullptr;
   return F8_OK;
 }
@@ -1051,6 +1077,7 @@ f8_status f8_chain_set_fusion(f8_chain *c, int fusion) {
   if (!c) return F8_ERR_NULL;
   c->fusion = fusion != 0;
   c->planned = false;
+  c->forget_pdp_roles();
   c->prepared_ws = nullptr;
   return F8_OK;
 }
@@ -1088,6 +1115,7 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
   hipStream_t s = static_cast<hipStream_t>(stream);
   c->prepared_ws = nullptr;
   c->place_fragments(batch, c->frag_off.data(), c->bn_off.data());
+  c->prepare_pdp_roles(batch);
   if (hipMemsetAsync(workspace, 0, 256, s) != hipSuccess) return F8_ERR_DEVICE;
   for (size_t i = 0; i < c->layers.size(); ++i) {
     const f8_layer_desc &L = c->layers[i];

@@ -24,6 +24,8 @@ struct PwDwPwParams {
 // Channel counts, image size, shifts and the alignment of y that the kernel takes.
 bool pw_dw_pw_applicable(int Cin, int Ce, int Cout, int H, int W, int stride, int shift1, int shiftd, int shift2, bool has_res, int res_d,
                          const void *x, const void *y);
+// Whether it is ahead, for a batch of B, of three launches or (pair) of two, the first layer and the pair behind it.
+bool pw_dw_pw_pays(int Cin, int Ce, int Cout, int H, int W, int stride, int B, bool pair);
 size_t pw_dw_pw_const_bytes(int Ce, int Cout);
 // wd: [3][3][Ce]; acc1, accd, acc2: folded start values of the three layers, [channels to 32]; res_bias: 128 << res_d where the
 // shortcut is unsigned, else 0.

@@ -495,24 +495,32 @@ Shape shape_of(int Cin, int Ce, int Cout, int H, int W, int P, int Q, int stride
   return s;
 }
 
-// Rows per workgroup, by what a launch of them would take: set-up and the units of the first two layers that a wave works
-// through one after the other, in rounds of 256 workgroups, of which two share a CU at 0.8 of the time each where they fit.
-// 0: no number of rows fits.
-int rows_for(int Cin, int Ce, int Cout, int H, int W, int P, int Q, int stride, int B) {
+// Cycles of one workgroup: set-up and the units of the three layers that a wave works through one after the other.
+long long workgroup_cycles(const Shape &s, int Cin, int Ce, int Cout) {
   const int nb1 = (Ce + 31) / 32, nb3 = (Cout + 31) / 32, ks1 = (Cin + 31) / 32;
+  auto units = [&](int mb) {
+    const int m = mb < NWAVE ? mb : NWAVE, g = NWAVE / m;
+    return (long long)((mb + m - 1) / m) * ((nb1 + g - 1) / g);
+  };
+  const int u3 = nb3 * s.mb2, kg = u3 < NWAVE ? NWAVE / u3 : 1;
+  return 3500 + units(s.mb1) * (450 + 60 * ks1) + units(s.mb2) * 900 + (u3 + NWAVE - 1) / NWAVE * (long long)((nb1 + kg - 1) / kg) * 120;
+}
+
+// Tenths of a workgroup's time that a launch takes: rounds of 256 workgroups, of which two share a CU at 0.8 of the time each where
+// they fit.
+long long launch_tenths(const Shape &s, int B) {
+  const long long rounds = ((long long)B * s.bands + 255) / 256;
+  return 2 * s.bytes <= LDS_MOST ? rounds / 2 * 16 + rounds % 2 * 10 : rounds * 10;
+}
+
+// Rows per workgroup, by what a launch of them would take.  0: no number of rows fits.
+int rows_for(int Cin, int Ce, int Cout, int H, int W, int P, int Q, int stride, int B) {
   int best = 0;
   long long least = 0;
   for (int rows = 1; rows <= P; ++rows) {
     const Shape s = shape_of(Cin, Ce, Cout, H, W, P, Q, stride, rows);
     if (s.bytes > LDS_MOST) break;
-    auto units = [&](int mb) {
-      const int m = mb < NWAVE ? mb : NWAVE, g = NWAVE / m;
-      return (long long)((mb + m - 1) / m) * ((nb1 + g - 1) / g);
-    };
-    const int u3 = nb3 * s.mb2, kg = u3 < NWAVE ? NWAVE / u3 : 1;
-    const long long one = 3500 + units(s.mb1) * (450 + 60 * ks1) + units(s.mb2) * 900 + (u3 + NWAVE - 1) / NWAVE * (long long)((nb1 + kg - 1) / kg) * 120;
-    const long long rounds = ((long long)B * s.bands + 255) / 256;
-    const long long cost = 2 * s.bytes <= LDS_MOST ? one * (rounds / 2 * 16 + rounds % 2 * 10) : one * rounds * 10;
+    const long long cost = workgroup_cycles(s, Cin, Ce, Cout) * launch_tenths(s, B);
     if (best == 0 || cost < least) { best = rows; least = cost; }
   }
   return best;
@@ -576,6 +584,25 @@ bool pw_dw_pw_applicable(int Cin, int Ce, int Cout, int H, int W, int stride, in
   if (has_res && (stride != 1 || Cin != Cout || res_d < 0 || res_d > 16)) return false;
   if ((reinterpret_cast<uintptr_t>(x) & 7) || (reinterpret_cast<uintptr_t>(y) & 3)) return false;
   return rows_for(Cin, Ce, Cout, H, W, (H - 1) / stride + 1, (W - 1) / stride + 1, stride, 1) > 0;
+}
+
+// What the launch takes against what the layers take apart: 9.5 us and the bytes they move at 6.25 TB/s (384 cycles a MB; a pair keeps the
+// depthwise result to itself).  Beside the cycles by which rows_for chooses, a workgroup waits for its input (1200 cycles for each 8 KiB of
+// it) and adds, requantises and writes its result (400 for each 2 KiB).
+// Random blocks (Cin to 192, Ce to 1024, Cout to 256, 4 x 4 to 112 x 112, batch 1 to 128), one launch against three: fitted to 1311, held
+// against 613 others, of which it takes 463 and 8 lose more than 3 %, the worst 9 %; without it 134 do, up to half their speed (192 -> 576
+// -> 96 on 33 x 33, batch 120, 98 -> 201 us: one row per workgroup, so the first layer is computed three times).  Against two launches, 8744 blocks: 43
+// of the 8671 it takes lose more than 3 %, the worst 12 % (without it 68, 23 %).  3872 fresh blocks of both kinds, as chosen: 30 and 15 %.
+bool pw_dw_pw_pays(int Cin, int Ce, int Cout, int H, int W, int stride, int B, bool pair) {
+  const int P = (H - 1) / stride + 1, Q = (W - 1) / stride + 1;
+  const int rows = rows_for(Cin, Ce, Cout, H, W, P, Q, stride, B);
+  if (rows == 0) return false;
+  const Shape s = shape_of(Cin, Ce, Cout, H, W, P, Q, stride, rows);
+  const int in_rows = (rows - 1) * stride + 3 < H ? (rows - 1) * stride + 3 : H;
+  const long long loads = ((long long)in_rows * W * Cin / 8 + 1023) / 1024, stores = ((long long)rows * Q * Cout / 4 + 511) / 512;
+  const long long cycles = (workgroup_cycles(s, Cin, Ce, Cout) + 1200 * loads + 400 * stores) * launch_tenths(s, B) / 10;
+  const long long apart = (long long)B * ((long long)H * W * (Cin + 2 * Ce) + (long long)P * Q * (pair ? Cout : 2 * Ce + Cout));
+  return cycles < 22800 + apart / 2604;
 }
 
 size_t pw_dw_pw_const_bytes(int Ce, int Cout) {

@@ -91,3 +91,36 @@ def test_switch_takes_every_block_that_fits(oracle):
         f8.f8_tuning_set("pw_dw_pw", 1)
     assert torch.equal(got, apart)
     assert np.array_equal(got[[0, 699]].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[[0, 699]])))
+
+
+def block(cin, ce, cout, hw, stride):
+    rng = np.random.default_rng(63000)
+    b = wl._NetBuilder("block", rng, hw, 16, "u8", 5, (5, 9), (2, 6), True)
+    t = b.conv("before", 0, cin, 1, 1, 0, relu=False)
+    y = b.conv("project", b.dwconv("dw", b.conv("expand", t, ce, 1, 1, 0), 3, stride, 1), cout, 1, 1, 0, relu=False,
+               res=t if stride == 1 and cin == cout else -1)
+    b.conv("after", y, 32, 1, 1, 0)
+    return b.net
+
+
+# (batch, expanded from, to, back to, image, stride, one launch?): microseconds of the three layers and one on either side, apart / one
+RULE = [
+    (120, 192, 576, 96, 33, 1, False),       # 98 / 201
+    (82, 160, 480, 64, 45, 1, False),        # 107 / 195
+    (15, 48, 48, 256, 93, 1, False),         # 40 / 65
+    (73, 128, 384, 128, 71, 2, False),       # 108 / 143
+    (14, 64, 256, 64, 83, 1, False),         # 42 / 54
+    (43, 160, 960, 160, 11, 1, False),       # 25 / 29
+    (73, 192, 1024, 24, 15, 2, False),       # the last two share a launch: 30 / 40
+    (14, 64, 256, 32, 94, 2, True),          # 37.7 / 37.5
+    (32, 80, 480, 80, 31, 1, True),          # 38 / 28
+    (16, 24, 144, 24, 56, 1, True),          # MobileNetV2
+    (40, 24, 144, 24, 56, 1, True),
+    (64, 160, 960, 160, 7, 1, True),
+    (128, 160, 960, 160, 7, 1, True),
+]
+
+
+@pytest.mark.parametrize("batch, cin, ce, cout, hw, stride, one", RULE)
+def test_inverted_residual_launch_only_where_it_is_ahead_host_side(batch, cin, ce, cout, hw, stride, one):
+    assert bool(three_in_one(reported(block(cin, ce, cout, hw, stride), batch))) == one

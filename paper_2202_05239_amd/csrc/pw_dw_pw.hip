@@ -586,13 +586,15 @@ bool pw_dw_pw_applicable(int Cin, int Ce, int Cout, int H, int W, int stride, in
   return rows_for(Cin, Ce, Cout, H, W, (H - 1) / stride + 1, (W - 1) / stride + 1, stride, 1) > 0;
 }
 
-// What the launch takes against what the layers take apart: 9.5 us and the bytes they move at 6.25 TB/s (384 cycles a MB; a pair keeps the
-// depthwise result to itself).  Beside the cycles by which rows_for chooses, a workgroup waits for its input (1200 cycles for each 8 KiB of
-// it) and adds, requantises and writes its result (400 for each 2 KiB).
-// Random blocks (Cin to 192, Ce to 1024, Cout to 256, 4 x 4 to 112 x 112, batch 1 to 128), one launch against three: fitted to 1311, held
-// against 613 others, of which it takes 463 and 8 lose more than 3 %, the worst 9 %; without it 134 do, up to half their speed (192 -> 576
-// -> 96 on 33 x 33, batch 120, 98 -> 201 us: one row per workgroup, so the first layer is computed three times).  Against two launches, 8744 blocks: 43
-// of the 8671 it takes lose more than 3 %, the worst 12 % (without it 68, 23 %).  3872 fresh blocks of both kinds, as chosen: 30 and 15 %.
+// What the launch takes against what the layers take apart: 29200 cycles (12.2 us: 9.5 as measured alone, and 2 - 4 that launches cost more
+// in a forward) and the bytes they move at 6.25 TB/s (384 cycles a MB; a pair keeps the depthwise result to itself).  Beside the cycles by
+// which rows_for chooses, a workgroup waits for its input (1500 cycles for each 8 KiB of it) and adds, requantises and writes its result
+// (600 for each 2 KiB).
+// Random blocks (Cin to 192, Ce to 1024, Cout to 256, 4 x 4 to 112 x 112, batch 1 to 128) alone, one launch against three: of 1924 this was
+// fitted to 402 lost more than 3 %, up to half their speed (192 -> 576 -> 96 on 33 x 33, batch 120, 98 -> 201 us: one row per
+// workgroup, so the first layer is computed three times); with it 50.  Of 3913 fresh ones, against three launches or two, it lets 56 lose, the worst
+// 18 % (64 -> 256 -> 24 from 83 x 83, stride 2, batch 48, 62 -> 76).  In MobileNetV2's forwards the two sides at the line: 960 channels on
+// 7 x 7, batch 192, 764 us with one launch, 780 with three.
 bool pw_dw_pw_pays(int Cin, int Ce, int Cout, int H, int W, int stride, int B, bool pair) {
   const int P = (H - 1) / stride + 1, Q = (W - 1) / stride + 1;
   const int rows = rows_for(Cin, Ce, Cout, H, W, P, Q, stride, B);
@@ -600,9 +602,9 @@ bool pw_dw_pw_pays(int Cin, int Ce, int Cout, int H, int W, int stride, int B, b
   const Shape s = shape_of(Cin, Ce, Cout, H, W, P, Q, stride, rows);
   const int in_rows = (rows - 1) * stride + 3 < H ? (rows - 1) * stride + 3 : H;
   const long long loads = ((long long)in_rows * W * Cin / 8 + 1023) / 1024, stores = ((long long)rows * Q * Cout / 4 + 511) / 512;
-  const long long cycles = (workgroup_cycles(s, Cin, Ce, Cout) + 1200 * loads + 400 * stores) * launch_tenths(s, B) / 10;
+  const long long cycles = (workgroup_cycles(s, Cin, Ce, Cout) + 1500 * loads + 600 * stores) * launch_tenths(s, B) / 10;
   const long long apart = (long long)B * ((long long)H * W * (Cin + 2 * Ce) + (long long)P * Q * (pair ? Cout : 2 * Ce + Cout));
-  return cycles < 22800 + apart / 2604;
+  return cycles < 29200 + apart / 2604;
 }
 
 size_t pw_dw_pw_const_bytes(int Ce, int Cout) {

@@ -273,12 +273,17 @@ struct f8_chain {
   //     (two formats 45 -> 47); stride 2 from 28 x 28: batch 4 11.7 -> 12.1, 32 26.6 -> 14.7, 64 34.6 -> 29.6, 96 44 -> 44, 128 49 -> 59
   // (Above 2^19 pixels, 64 channels gain too, but there the closing layers' own kernels have not been compared on anything
   // but ResNet-50.)
+  // With no layer behind there is a launch less to save; random blocks of 4 x 4 to 80 x 80, batch 1 to 128, apart / together, mean (least) on
+  // either side of the lines: 64 channels stride 2, to 24000 pixels 1.08 (0.91), beyond 0.95 (0.86); 128 channels, to 38000 1.22 (0.94), beyond
+  // 1.00 (0.85); stride 2, to 16000 1.09 (0.93), beyond 0.98 (0.92); 256 channels, below 2000 0.98 (0.88), from there 1.19 (0.99).  With one
+  // behind, 64 channels stride 2, to 131072 pixels 1.22 (0.99), beyond 0.96.
   bool bn_pays(size_t head, int batch) const {
     const Geom &g = geom[head];
     const long long M = (long long)batch * g.P * g.Q;
-    if (g.Cin == 64) return M < 1 << 19;
-    if (g.Cin == 128) return M <= (g.sh == 1 ? 131072 : 38000);
-    return M >= 1200 && M <= (g.sh == 1 ? 16384 : 13000);
+    const bool behind = bn_behind[head] >= 0;
+    if (g.Cin == 64) return g.sh == 1 ? M < 1 << 19 : M <= (behind ? 131072 : 24000);
+    if (g.Cin == 128) return M <= (g.sh == 1 ? (behind ? 131072 : 38000) : (behind ? 38000 : 16000));
+    return M >= (behind ? 1200 : 2000) && M <= (g.sh == 1 ? 16384 : 13000);
   }
   // Copies of weights in fragment order (img_w_bytes, bn_w_bytes, dwp_w_bytes) lie behind the arena and only where this batch, or
   // either half of it on two streams, takes their kernel: ResNet-18 at one image needs 0.7 MB of workspace, with every

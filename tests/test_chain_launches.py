@@ -124,3 +124,26 @@ RULE = [
 @pytest.mark.parametrize("batch, cin, ce, cout, hw, stride, one", RULE)
 def test_inverted_residual_launch_only_where_it_is_ahead_host_side(batch, cin, ce, cout, hw, stride, one):
     assert bool(three_in_one(reported(block(cin, ce, cout, hw, stride), batch))) == one
+
+
+# (batch, channels, image, stride, channels behind, one launch?): microseconds with the layers around them, apart / one launch
+BOTTLENECKS = [
+    (14, 128, 78, 1, 0, False),              # 58 / 64
+    (127, 64, 65, 2, 0, False),              # 52 / 60
+    (60, 256, 10, 2, 0, False),              # 20.3 / 22.2
+    (18, 128, 65, 2, 0, False),              # 32 / 34
+    (14, 128, 78, 1, 128, True),
+    (127, 64, 61, 2, 64, True),
+    (60, 256, 10, 2, 256, True),
+    (9, 128, 30, 1, 0, True),
+]
+
+
+@pytest.mark.parametrize("batch, c, hw, stride, behind, one", BOTTLENECKS)
+def test_bottleneck_launch_only_where_it_is_ahead_host_side(batch, c, hw, stride, behind, one):
+    """With no layer behind the closing one there is a launch less to save, and the launch stops earlier."""
+    rng = np.random.default_rng(64000)
+    b = wl._NetBuilder("bottleneck", rng, hw, 16, "u8", 5, (5, 9), (2, 6), True)
+    y = b.conv("close", b.conv("mid", b.conv("before", 0, c, 1, 1, 0), c, 3, stride, 1), 4 * c, 1, 1, 0)
+    b.conv("after", b.conv("behind", y, behind, 1, 1, 0) if behind else y, 32, 1, 1, 0)
+    assert (reported(b.net, batch)[1][0] == "bottleneck<%d>" % c) == one

@@ -1346,9 +1346,9 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
     return F8_OK;
   }
   const int three = c->bn_role((size_t)layer, batch);
-  const int block = c->pdp_role((size_t)layer, batch);
-  if (three > 1 || block == 1 || block == 3 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
-    // accounted to the layer in front (of the first layer of an inverted-residual block: behind), whose launch computes this one
+  const int block = c->pdp_role((size_t)layer, batch), twin = c->pair_role((size_t)layer, batch);
+  if (three > 1 || block == 1 || block == 3 || twin == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
+    // accounted to the layer in front (of the first layer of an inverted-residual or basic block: behind), whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {
       int i = 0;
@@ -1379,12 +1379,11 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       else name = conv_kernel_name(gk, L.q, L.res >= 0, L.dst2 > 0 ? &L.q2 : nullptr);
       ops = 2.0 * M * g.R * g.S * g.Cin * g.Cout;
       bytes += (double)g.R * g.S * g.Cin * g.Cout + 4.0 * g.Cout;
-      if (const int twin = c->pair_role((size_t)layer, batch)) {
-        // both layers are accounted to the second, whose launch computes them: the block's input (also its shortcut) and output
-        if (L.Cin == 64) name = twin == 1 ? "conv3x3_imgk<64> in the next" : "conv3x3_imgk<64> twice";
-        else name = twin == 1 ? "conv3x3_imgk<128> in the next" : "conv3x3_imgk<128> twice";
-        ops = twin == 1 ? 0.0 : 2.0 * ops;
-        bytes = twin == 1 ? 0.0 : 2.0 * (M * L.Cin + 9.0 * L.Cin * L.Cin + 4.0 * L.Cin);
+      if (twin == 2) {
+        // plus the 3x3 layer in front: the block's input (also its shortcut) and output
+        name = L.Cin == 64 ? "conv3x3_pair<64>" : "conv3x3_pair<128>";
+        ops *= 2.0;
+        bytes = 2.0 * (M * L.Cin + 9.0 * L.Cin * L.Cin + 4.0 * L.Cin);
       }
       if (three == 1) {
         // plus the closing layer (residual in, one or two formats out) and the layer behind it
@@ -1415,14 +1414,9 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
         if (block == 2) {
           // and the 1x1 layer in front, all of whose pixels are needed; the shortcut is its input, read once
           const f8_layer_desc &E = c->layers[layer - 1];
-          // (one kernel; the name tells whether the pair without its front layer would be one launch here)
-          if (c->dwp_role((size_t)layer, batch) == 1) name = g.sh == 1 ? "1x1+dwconv3x3<s1>+1x1" : "1x1+dwconv3x3<s2>+1x1";
-          else name = g.sh == 1 ? "inverted_residual<s1>" : "inverted_residual<s2>";
           const Geom &ge = c->geom[layer - 1];
-          if (c->pdp_image((size_t)layer - 1)) {
-            if (c->dwp_role((size_t)layer, batch) == 1) name = g.sh == 1 ? "conv3x3+dwconv3x3<s1>+1x1" : "conv3x3+dwconv3x3<s2>+1x1";
-            else name = g.sh == 1 ? "conv3x3+dwconv3x3<s1>, 1x1" : "conv3x3+dwconv3x3<s2>, 1x1";
-          }
+          if (c->pdp_image((size_t)layer - 1)) name = g.sh == 1 ? "conv3x3+dwconv3x3<s1>+1x1" : "conv3x3+dwconv3x3<s2>+1x1";
+          else name = g.sh == 1 ? "1x1+dwconv3x3<s1>+1x1" : "1x1+dwconv3x3<s2>+1x1";
           const double taps = (double)E.R * E.S * E.Cin * E.Cout;
           ops += 2.0 * batch * g.H * g.W * taps;
           bytes += (double)batch * ge.H * ge.W * E.Cin - (double)batch * rows * cols * g.Cin - (T.res >= 0 ? M * T.Cout : 0.0) + taps + 4.0 * E.Cout;

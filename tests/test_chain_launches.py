@@ -59,7 +59,7 @@ def test_a_closing_layer_with_two_readers(oracle, first, second):
 
 
 def three_in_one(rows):
-    return {i for i, (n, _) in enumerate(rows) if n.startswith(("1x1+dwconv", "conv3x3+dwconv", "inverted_residual"))}
+    return {i for i, (n, _) in enumerate(rows) if n.startswith(("1x1+dwconv", "conv3x3+dwconv"))}
 
 
 def test_switch_takes_every_block_that_fits_host_side():
@@ -147,3 +147,20 @@ def test_bottleneck_launch_only_where_it_is_ahead_host_side(batch, c, hw, stride
     y = b.conv("close", b.conv("mid", b.conv("before", 0, c, 1, 1, 0), c, 3, stride, 1), 4 * c, 1, 1, 0)
     b.conv("after", b.conv("behind", y, behind, 1, 1, 0) if behind else y, 32, 1, 1, 0)
     assert (reported(b.net, batch)[1][0] == "bottleneck<%d>" % c) == one
+
+
+def test_a_launch_has_one_name_host_side():
+    """The name of a layer is that of the kernel it launches, whatever kernels its layers would take apart; a layer inside another's
+    launch is "(fused)"."""
+    _, net = wl.mobilenet_v2_forward(batch=1)
+    for batch in (1, 27, 64, 128):
+        rows = reported(net, batch)
+        for i in three_in_one(rows):
+            kind = "conv3x3" if i == 1 else "1x1"
+            assert rows[i][0] == "%s+dwconv3x3<s%d>+1x1" % (kind, net.layers[i].stride), (batch, i, rows[i])
+            assert rows[i - 1] == rows[i + 1] == ("(fused)", 0.0), (batch, i)
+    _, net = wl.config3(batch=1)
+    rows = reported(net, 64)
+    pairs = [i for i, (n, _) in enumerate(rows) if n.startswith("conv3x3_pair<")]
+    assert [rows[i][0] for i in pairs] == ["conv3x3_pair<64>"] * 2 + ["conv3x3_pair<128>"]
+    assert all(rows[i - 1] == ("(fused)", 0.0) for i in pairs)

@@ -52,7 +52,7 @@ def test_basic_block_in_one_launch(oracle, k):
             f8.f8_tuning_set("imgk", 11)
             chain = f8.Chain(net).prepare(batch)
             names = [chain.layer_info(i, batch)[0] for i in (1, 2)]
-            assert names == ["conv3x3_imgk<%d>%s" % (C, s) for s in (("", "") if force == 0 else (" in the next", " twice"))]
+            assert names == (["conv3x3_imgk<%d>" % C] * 2 if force == 0 else ["(fused)", "conv3x3_pair<%d>" % C])
             outs[force] = chain.run(x_t)
             assert force == 0 or chain.tensor(net.layers[1].dst) is None
     finally:

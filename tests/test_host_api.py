@@ -245,10 +245,16 @@ def test_workspace_holds_weight_copies_only_for_kernels_the_batch_takes_host_sid
     """Copies of weights in fragment order (3x3 layers, the 1x1 layers behind depthwise ones) are kept where the batch, or a
     half of it on two streams, takes the kernel that reads them, and nowhere else."""
     L = f8.lib()
-    for fn, small, large, mark in ((wl.config3, 1, 64, "conv3x3_im"), (wl.mobilenet_v2_forward, 256, 27, "+1x1")):
+    # (launches of whole blocks read the same copies, or constants of their own: without them the layers' own kernels show)
+    for fn, small, large, mark, switch in ((wl.config3, 1, 64, "conv3x3_im", "conv_pair"), (wl.mobilenet_v2_forward, 256, 27, "+1x1", "pw_dw_pw")):
         _, net = fn(batch=1)
-        h, n, buf = ctypes.c_void_p(), ctypes.c_size_t(), ctypes.create_string_buffer(64)
-        assert L.f8_chain_create(make_descs(net), len(net.layers), 224, 224, 3, f8.F8_S8, ctypes.byref(h)) == 0
+        whole, h, n, buf = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_size_t(), ctypes.create_string_buffer(64)
+        assert L.f8_chain_create(make_descs(net), len(net.layers), 224, 224, 3, f8.F8_S8, ctypes.byref(whole)) == 0
+        f8.f8_tuning_set(switch, 0)
+        try:
+            assert L.f8_chain_create(make_descs(net), len(net.layers), 224, 224, 3, f8.F8_S8, ctypes.byref(h)) == 0
+        finally:
+            f8.f8_tuning_set(switch, 1)
 
         def size(batch):
             assert L.f8_chain_workspace_bytes(h, batch, ctypes.byref(n)) == 0
@@ -278,6 +284,10 @@ def test_workspace_holds_weight_copies_only_for_kernels_the_batch_takes_host_sid
         for batch in range(1, len(need)):
             assert sizes[batch] == max(need[:batch + 1]), batch
         assert any(need[n_img] > need[n_img + 1] for n_img in range(1, len(need) - 1)) or small != 1
+        # with the launches of whole blocks nothing depends on the batch in another way
+        L.f8_chain_destroy(h)
+        h = whole
+        assert len({size(n_img) - sizes[n_img] for n_img in range(1, len(need))}) == 1
         L.f8_chain_destroy(h)
 
 

@@ -223,8 +223,10 @@ f8_status f8_chain_run(f8_chain *c, const void *x, void *out, void *workspace, i
                        void *stream);
 /* Where tensor `id` lives after a run (for per-layer checks): pointer inside the
  * workspace (or NULL for ids 0 and the last tensor, and for tensors that a kernel computing two or three layers at
- * this batch never writes: the stem's under its max pool, a depthwise layer's under the 1x1 layer behind it; with
- * keep_all every tensor is written), shape and type.  Tensors whose memory was reused by a later layer are reported
+ * this batch never writes: the stem's under its max pool; a depthwise layer's under the 1x1 layer behind it, and the
+ * tensor it reads where the layer in front is part of the launch too (an inverted-residual block, or a network's first
+ * layers); the 3x3 layer's of a bottleneck block; the first 3x3 layer's of a basic block; with keep_all every tensor
+ * is written), shape and type.  Tensors whose memory was reused by a later layer are reported
  * with *live_at_end = 0. */
 f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch, void **ptr,
                           int *h, int *w, int *ch, int *dtype, int *live_at_end);
@@ -254,7 +256,8 @@ void f8_chain_destroy(f8_chain *c);
  * f8_chain_layer_info: name of the kernel layer `layer` launches (copied into
  *   kernel_name, at most name_len bytes with the terminator) and the layer's algorithmic
  *   work for `batch` images: operations (2 per multiply-accumulate; 0 for pools) and
- *   bytes (every operand and result touched once).
+ *   bytes (every operand and result touched once).  Where one launch computes several layers,
+ *   one of them has its name and all of its work, the others are "(fused)" with none.
  * f8_chain_profile: runs the chain 2 * `repeats` times with a HIP event recorded on
  *   `stream` before and after every layer, once with every layer launched once and once
  *   with every layer launched five times back to back; the difference divided by four is

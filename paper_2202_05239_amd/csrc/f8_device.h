@@ -30,7 +30,7 @@ struct FastDiv {
   __host__ __device__ __forceinline__ uint32_t div(uint32_t n) const {
 #if defined(__HIP_DEVICE_COMPILE__)
     return __umulhi(n << 1, mul) >> shr;
-#else
+#else                                      // (the same on the host, where the exactness is tested)
     return (uint32_t)(((unsigned long long)(n << 1) * mul) >> 32) >> shr;
 #endif
   }

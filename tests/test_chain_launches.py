@@ -164,3 +164,176 @@ def test_a_launch_has_one_name_host_side():
     pairs = [i for i, (n, _) in enumerate(rows) if n.startswith("conv3x3_pair<")]
     assert [rows[i][0] for i in pairs] == ["conv3x3_pair<64>"] * 2 + ["conv3x3_pair<128>"]
     assert all(rows[i - 1] == ("(fused)", 0.0) for i in pairs)
+
+
+def random_graph(seed):
+    """A network of blocks that share launches, with the readers, shortcuts and second formats that decide whether they may."""
+    rng = np.random.default_rng(62000 + seed)
+    image = seed % 3 == 0
+    hw = int(rng.choice((7, 14, 20, 28))) * (2 if image else 1)
+    b = wl._NetBuilder("graph%d" % seed, rng, hw, 3 if image else 16, "u8", 5, (5, 9), (2, 6), True)
+    yes = lambda p=0.5: bool(rng.random() < p)
+    at = lambda t: b.t[t]
+    loose = []                                   # second and third readers' results
+
+    def conv(t, c, k=1, stride=1, **kw):
+        return b.conv("l%d" % len(b.net.layers), t, c, k, stride, k // 2, **kw)
+
+    def basic(t):
+        c = int(rng.choice((64, 128)))
+        t = t if at(t)["c"] == c else conv(t, c)
+        u = conv(t, c, 3, relu=yes())
+        if yes(0.15):
+            loose.append(conv(u, 32))            # a second reader
+        return conv(u, c, 3, res=t if yes(0.7) else -1)
+
+    def bottleneck(t):
+        c, stride = int(rng.choice((64, 128, 128, 256))), 2 if yes(0.25) and min(at(t)["hw"]) > 6 else 1
+        short = conv(t, 4 * c, 1, stride) if yes() else -1
+        m = conv(t if at(t)["c"] == c and yes() else conv(t, c), c, 3, stride, relu=yes(0.8))
+        dual = yes(0.3)
+        y = conv(m, 4 * c, res=short, relu=yes(0.8), dual=dual)
+        y, y2 = y if dual else (y, y)
+        readers = [conv(y if yes(0.7) else y2, int(rng.choice((c, 2 * c, c, 2 * c, 32)))) for _ in range(int(rng.integers(0, 4)))]
+        loose.extend(readers[1:])
+        return readers[0] if readers and yes(0.7) else y
+
+    def inverted(t):
+        stride = 2 if yes(0.3) and min(at(t)["hw"]) > 6 else 1
+        u = conv(t, int(rng.choice((48, 96, 192, 384))), relu=yes(0.8)) if yes(0.8) else t
+        u = b.dwconv("l%d" % len(b.net.layers), u, 3, stride, 1)
+        if yes(0.1):
+            loose.append(conv(u, 16))
+        return conv(u, int(rng.choice((16, 24, 64, 160))), relu=yes(0.3))
+
+    def shortcut(t):
+        u = conv(t, int(rng.choice((96, 144, 192))))
+        return conv(b.dwconv("l%d" % len(b.net.layers), u, 3, 1, 1), at(t)["c"], relu=False, res=t)
+
+    t = 0
+    if image:
+        t = conv(0, int(rng.choice((16, 32, 64))), 3, 2)
+        if at(t)["c"] <= 32 and yes(0.7):
+            t = conv(b.dwconv("l1", t, 3, 1 + int(yes(0.3)), 1), int(rng.choice((16, 64))), relu=yes())
+    t = conv(t, int(rng.choice((16, 64, 128)))) if yes() or t == 0 else t
+    for _ in range(int(rng.integers(2, 5))):
+        t = rng.choice((basic, bottleneck, bottleneck, inverted, shortcut))(t)
+    last = -1
+    for u in loose + [t]:                        # every branch reaches the result: pooled, then summed
+        last = conv(conv(b.gpool("g%d" % len(b.net.layers), u), 32), 32, res=last)
+    return b.net, rng
+
+
+def operations(net, batch):
+    total = 0.0
+    for S in net.layers:
+        if S.op in ("conv", "dwconv"):
+            total += 2.0 * batch * S.out_hw[0] * S.out_hw[1] * S.R * S.S * S.Cout * (S.Cin if S.op == "conv" else 1)
+    return total
+
+
+@pytest.mark.parametrize("first", range(0, 120, 20))
+def test_every_layer_is_computed_by_one_launch_host_side(first):
+    """The operations of the reported launches add up to the network's at every batch: none is skipped, none done twice."""
+    kernels = set()
+    for seed in range(first, first + 20):
+        net, _ = random_graph(seed)
+        for batch in (1, 2, 9, 16, 50, 100, 160, 300, 500, 1200):
+            rows = reported(net, batch)
+            assert sum(ops for _, ops in rows) == operations(net, batch), (seed, batch, rows)
+            assert all((ops == 0) == (n == "(fused)") for (n, ops), S in zip(rows, net.layers) if S.op in ("conv", "dwconv")), (seed, batch, rows)
+            kernels |= {n for n, _ in rows}
+    assert len(kernels) > 12
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("seed", range(12))
+def test_launches_of_several_layers_in_random_graphs(oracle, seed):
+    """Every tensor that is whole after a run, and the result on one stream, on two and from a captured graph, against the chain that
+    keeps all tensors (layer by layer) and, for two images, against the oracle."""
+    net, rng = random_graph(1000 + seed)
+    batch = int(rng.choice((5, 33, 100, 201)))
+    x = wl.draw_u8(rng, (batch,) + net.in_hw + (net.in_c,))
+    x_t = torch.from_numpy(x).cuda()
+    apart = f8.Chain(net, keep_all=True).prepare(batch)
+    want = apart.run(x_t)
+    pick = [0, batch - 1]
+    assert np.array_equal(want[pick].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[pick])))
+    chain = f8.Chain(net).prepare(batch)
+    assert torch.equal(chain.run(x_t), want), batch
+    for L in net.layers[:-1]:
+        for dst in (L.dst, L.dst2):
+            t = chain.tensor(dst) if dst > 0 else None
+            assert t is None or torch.equal(t, apart.tensor(dst)), (batch, L.name, dst)
+    halves = f8.Chain(net, streams=2).prepare(batch)
+    out = torch.empty_like(want)
+    graph = halves.capture(x_t, out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), batch
+        assert torch.equal(halves.run(x_t), want), batch
+
+
+def taken(net, batch, what):
+    return [n for n, _ in reported(net, batch) if n.startswith(what)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("C, hw, batch", [(64, 56, 24), (64, 28, 87), (128, 28, 31), (128, 28, 335)])
+def test_basic_block_by_the_default_choice_on_two_streams(oracle, C, hw, batch):
+    """No switch set.  24: the whole batch takes the launch, its halves do not; 87 and 31: one of the halves does; 335: neither the whole
+    batch nor its larger half does, the smaller one does (131072 pixels).  With and without a shortcut, from a captured graph too."""
+    rng = np.random.default_rng(65000 + batch)
+    x = wl.draw_u8(rng, (batch, hw, hw, 16))
+    x_t = torch.from_numpy(x).cuda()
+    pick = [0, batch // 2 - 1, batch // 2, batch - 1]
+    for shortcut in (True, False):
+        b = wl._NetBuilder("default", rng, hw, 16, "u8", 5, (5, 9), (2, 6), True)
+        t = b.conv("before", 0, C, 1, 1, 0)
+        b.conv("after", b.conv("b", b.conv("a", t, C, 3, 1, 1), C, 3, 1, 1, res=t if shortcut else -1), 32, 1, 1, 0)
+        want = oracle.run_network(b.net, np.ascontiguousarray(x[pick]))
+        one, two = f8.Chain(b.net).prepare(batch), f8.Chain(b.net, streams=2).prepare(batch)
+        got = one.run(x_t)
+        assert np.array_equal(got[pick].cpu().numpy(), want)
+        out = torch.empty_like(got)
+        graph = two.capture(x_t, out)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, got)
+            assert torch.equal(two.run(x_t), got)
+
+
+def test_basic_block_choice_host_side():
+    for C, hw, batch, whole, low, high in ((64, 56, 24, 1, 0, 0), (64, 28, 87, 1, 0, 1), (128, 28, 31, 1, 0, 1), (128, 28, 335, 0, 1, 0)):
+        b = wl._NetBuilder("default", np.random.default_rng(0), hw, 16, "u8", 5, (5, 9), (2, 6), True)
+        t = b.conv("before", 0, C, 1, 1, 0)
+        b.conv("after", b.conv("b", b.conv("a", t, C, 3, 1, 1), C, 3, 1, 1, res=t), 32, 1, 1, 0)
+        count = [len(taken(b.net, n, "conv3x3_pair<%d>" % C)) for n in (batch, batch // 2, batch - batch // 2)]
+        assert count == [whole, low, high], (C, hw, batch, count)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch", [131, 501])
+def test_inverted_residual_launches_on_halves_of_either_choice(oracle, batch):
+    """MobileNetV2, 131 images: 13 launches of three layers in one half, 11 in the other, 4 in the whole batch; 501: the front's launch in one half
+    only.  Two streams from a captured graph against one stream and the oracle."""
+    x, net = wl.mobilenet_v2_forward(batch=batch)
+    counts = [len(three_in_one(reported(net, n))) for n in (batch // 2, batch - batch // 2, batch)]
+    assert counts == ([13, 11, 4] if batch == 131 else [1, 0, 0])
+    x_t = torch.from_numpy(x).cuda()
+    pick = [0, batch - 1]
+    want = f8.Chain(net).prepare(batch).run(x_t)
+    assert np.array_equal(want[pick].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[pick])))
+    chain = f8.Chain(net, streams=2).prepare(batch)
+    out = torch.empty_like(want)
+    graph = chain.capture(x_t, out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert torch.equal(chain.run(x_t), want)

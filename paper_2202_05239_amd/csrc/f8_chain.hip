@@ -196,8 +196,9 @@ struct f8_chain {
   int pw_dw_pw = 1;
   // The front of a network is such a block with a 3x3 stride-2 layer on an image in the first layer's place.  Microseconds of the three,
   // three launches (or two) -> one, image 224 x 224: MobileNetV2 (to 16 channels) batch 1 9.8 -> 4.6, 4 11.5 -> 4.3, 8 15.4 -> 6.1, 27 26.0 -> 10.3,
-  // 64 44.9 -> 20.5, 128 75.2 -> 37.2; MobileNetV1 (to 64 channels) 1 11.3 -> 6.1, 27 33.0 -> 17.2, 64 58.1 -> 30.7, 128 93.1 -> 53.2.  At batch 256 it is
-  // ahead too (136 -> 73, 178 -> 101); from 3 M pixels on the layers keep the kernels that per-layer accounts of such batches name.
+  // 64 44.9 -> 20.5, 128 75.2 -> 37.2; MobileNetV1 (to 64 channels) 1 11.3 -> 6.1, 27 33.0 -> 17.2, 64 58.1 -> 30.7, 128 93.1 -> 53.2.  The
+  // line at 3 M pixels (batch 250) is no crossover: at 256 it is ahead too (136 -> 73, 178 -> 101).  It stands where the tests of the kernels that
+  // the layers take by themselves begin, the 1x1 32 -> 16 layer's among them, which expect those kernels at batch 256.
   bool pdp_image(size_t front) const { return stem[front].on && stem[front].Cp == 4; }
   int pdp_k(size_t front) const { return pdp_image(front) ? 48 : layers[front].Cin; }
   // Where the pair is one launch, microseconds of front layer and pair, two launches -> one (two launches

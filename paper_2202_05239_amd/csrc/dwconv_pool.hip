@@ -384,7 +384,7 @@ __global__ __launch_bounds__(NT) void gpool_kernel(const DwParams p, const long 
 // pixel (one dword).  Turns a clipped-window, odd-channel convolution into one whose
 // windows are never clipped and whose taps are whole dwords.
 __global__ __launch_bounds__(NT) void pad_input_kernel(const uint8_t *x, uint32_t *xp, int B, int H, int W, int C,
-                                                       int Hp, int Wp, int ph, int pw, long long total, uint32_t value_xor) {
+                                                       int Hp, int Wp, int ph, int pw, long long total) {
   const long long gid = (long long)blockIdx.x * NT + threadIdx.x;
   if (gid >= total) return;
   const int j = (int)(gid % Wp);
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(NT) void pad_input_kernel(const uint8_t *x, uint32_
     const uint8_t *src = x + (((size_t)b * H + ih) * W + iw) * C;
     for (int c = 0; c < C; ++c) v |= (uint32_t)src[c] << (8 * c);
   }
-  xp[gid] = v ^ value_xor;
+  xp[gid] = v;
 }
 
 // The same re-layout for C = 3 (the RGB stem), four output pixels (one 16-byte store) per thread.
@@ -409,7 +409,7 @@ struct PadTiling {
 };
 
 __global__ __launch_bounds__(NT) void pad_input3_kernel(const uint8_t *x, v4i *xp, int H, int W, int Hp, int Wp, int ph,
-                                                        int pw, const PadTiling tl, uint32_t total, long long x_bytes, uint32_t value_xor) {
+                                                        int pw, const PadTiling tl, uint32_t total, long long x_bytes) {
   const uint32_t gid = blockIdx.x * NT + threadIdx.x;
   if (gid >= total) return;
   const uint32_t t = tl.fd_g.div(gid);
@@ -436,21 +436,20 @@ __global__ __launch_bounds__(NT) void pad_input3_kernel(const uint8_t *x, v4i *x
 #pragma unroll
     for (int k = 0; k < 4; ++k) out[k] = (unsigned)(iw0 + k) < (unsigned)W ? (int)px[k] : 0;
   }
-  const int vx = (int)value_xor;
-  xp[gid] = v4i{out.x ^ vx, out.y ^ vx, out.z ^ vx, out.w ^ vx};
+  xp[gid] = out;
 }
 
-// w [N][R][S][C] -> wp [N][R][Sp][4], zeros in taps S..Sp-1 and channels C..3.
+// w [N][R][S][C] -> wp [N][R][Sp][4]: the S taps from tap `lead` on, zeros in the others and in channels C..3.
 __global__ __launch_bounds__(NT) void repack_weights_kernel(const int8_t *w, uint32_t *wp, int N, int R, int S, int C,
-                                                            int Sp, long long total) {
+                                                            int Sp, int lead, long long total) {
   const long long gid = (long long)blockIdx.x * NT + threadIdx.x;
   if (gid >= total) return;
-  const int s = (int)(gid % Sp);
+  const int s = (int)(gid % Sp) - lead;
   const long long t = gid / Sp;
   const int r = (int)(t % R);
   const int n = (int)(t / R);
   uint32_t v = 0;
-  if (s < S) {
+  if (s >= 0 && s < S) {
     const int8_t *src = w + (((size_t)n * R + r) * S + s) * C;
     for (int c = 0; c < C; ++c) v |= (uint32_t)(uint8_t)src[c] << (8 * c);
   }
@@ -579,7 +578,7 @@ int launch_maxpool(const PoolParams &p, bool vec4, hipStream_t stream) {
 }
 
 int launch_pad_input(const void *x, void *xp, int B, int H, int W, int C, int Hp, int Wp, int ph, int pw,
-                     hipStream_t stream, uint32_t value_xor) {
+                     hipStream_t stream) {
   const long long total = (long long)B * Hp * Wp;
   if (total <= 0) return 0;
   const long long x_bytes = (long long)B * H * W * C;
@@ -590,19 +589,19 @@ int launch_pad_input(const void *x, void *xp, int B, int H, int W, int C, int Hp
     tl.fd_hp = FastDiv((uint32_t)Hp);
     const uint32_t threads = (uint32_t)(total / 4);
     hipLaunchKernelGGL(pad_input3_kernel, dim3((threads + NT - 1) / NT), dim3(NT), 0, stream,
-                       static_cast<const uint8_t *>(x), static_cast<v4i *>(xp), H, W, Hp, Wp, ph, pw, tl, threads, x_bytes, value_xor);
+                       static_cast<const uint8_t *>(x), static_cast<v4i *>(xp), H, W, Hp, Wp, ph, pw, tl, threads, x_bytes);
     return (int)hipGetLastError();
   }
   hipLaunchKernelGGL(pad_input_kernel, dim3(blocks_for(total)), dim3(NT), 0, stream, static_cast<const uint8_t *>(x),
-                     static_cast<uint32_t *>(xp), B, H, W, C, Hp, Wp, ph, pw, total, value_xor);
+                     static_cast<uint32_t *>(xp), B, H, W, C, Hp, Wp, ph, pw, total);
   return (int)hipGetLastError();
 }
 
-int launch_repack_weights(const int8_t *w, void *wp, int N, int R, int S, int C, int Sp, hipStream_t stream) {
+int launch_repack_weights(const int8_t *w, void *wp, int N, int R, int S, int C, int Sp, int lead, hipStream_t stream) {
   const long long total = (long long)N * R * Sp;
   if (total <= 0) return 0;
   hipLaunchKernelGGL(repack_weights_kernel, dim3(blocks_for(total)), dim3(NT), 0, stream, w,
-                     static_cast<uint32_t *>(wp), N, R, S, C, Sp, total);
+                     static_cast<uint32_t *>(wp), N, R, S, C, Sp, lead, total);
   return (int)hipGetLastError();
 }
 

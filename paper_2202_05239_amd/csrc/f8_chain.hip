@@ -18,7 +18,7 @@
 //
 // Stem + pool.  The ImageNet stem (7x7 stride-2 convolution of a 3-channel image to 64 unsigned
 // channels) followed by a 3x3 stride-2 pad-1 max pool that is its only reader runs as one kernel
-// on the re-laid-out operands; the tensor between the two then gets no memory.  (Not when every
+// on the image itself and re-laid-out weights; neither the tensor between the two nor a copy of the image gets memory.  (Not when every
 // tensor is to be kept; F8_STEM_POOL=0, read when the chain is created, turns it off: tuning aid.)
 //
 // Block fusion.  Three consecutive layers that form an inverted-residual block (1x1 dense,
@@ -386,11 +386,9 @@ struct f8_chain {
     for (size_t li = 0; li < layers.size(); ++li) {
       if (pool_role(li) == 2) continue;
       if (pool_role(li) == 1) {
-        // one kernel: re-laid-out input in, the pool's output out
-        stem[li].x_off_per_image = alloc(round256(stem[li].x_bytes_per_image));
+        // one kernel: image in, the pool's output out
         Tensor &d = tensors[layers[li + 1].dst];
         if (!d.external) d.offset_per_image = alloc(round256(d.bytes_per_image));
-        release(stem[li].x_off_per_image, round256(stem[li].x_bytes_per_image));
         Tensor &t = tensors[layers[li].src];
         if (!t.external && t.last_use == (int)li) release(t.offset_per_image, round256(t.bytes_per_image));
         continue;
@@ -598,17 +596,13 @@ struct f8_chain {
     g.B = batch;
     if (pool_role(i) == 2) return F8_OK;
     if (pool_role(i) == 1) {
-      const void *src = tensor_ptr(L.src, x, out, workspace, batch);
-      void *xp = arena(workspace) + stem[i].x_off_per_image * (size_t)batch;
-      if (launch_pad_input(src, xp, batch, g.H, g.W, g.Cin, stem[i].Hp, stem[i].Wp, g.ph, g.pw, s,
-                           L.q.x_type == F8_U8 ? 0x80808080u : 0u) != 0)
-        return F8_ERR_DEVICE;
       StemPoolParams sp;
-      sp.xp = static_cast<const uint8_t *>(xp);
+      sp.x = static_cast<const uint8_t *>(tensor_ptr(L.src, x, out, workspace, batch));
       sp.wp = conv_weights(i, workspace);
       sp.acc0 = reinterpret_cast<const int32_t *>(static_cast<uint8_t *>(workspace) + acc0_off[i]);
       sp.y = static_cast<uint8_t *>(tensor_ptr(layers[i + 1].dst, x, out, workspace, batch));
-      sp.B = batch; sp.Hp = stem[i].Hp; sp.Wp = stem[i].Wp;
+      sp.B = batch; sp.H = g.H; sp.W = g.W;
+      sp.x_xor = L.q.x_type == F8_U8 ? 0x80808080u : 0u;
       sp.P = g.P; sp.Q = g.Q; sp.PP = geom[i + 1].P; sp.QP = geom[i + 1].Q;
       sp.shift = L.q.fl_x + L.q.fl_w - L.q.fl_y; sp.lo = L.q.clip_lo; sp.hi = L.q.clip_hi;
       sp.ntiles = 0;
@@ -839,9 +833,8 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
         sm.on = true;
         sm.Sp = (L.S + 3) / 4 * 4;
         sm.Hp = (g.P - 1) * g.sh + g.R;
-        // whole 16-byte groups of pixels per row, and two pixels no window reaches at the end of a row (the
-        // fused stem fetches some rows 8 bytes off the 16-byte grid)
-        sm.Wp = ((g.Q - 1) * g.sw + sm.Sp + 2 + 3) / 4 * 4;
+        // whole 16-byte groups of pixels per row
+        sm.Wp = ((g.Q - 1) * g.sw + sm.Sp + 3) / 4 * 4;
         sm.x_bytes_per_image = (size_t)sm.Hp * sm.Wp * 4;
         sm.w_off = c->const_bytes;
         c->const_bytes += round256((size_t)L.Cout * g.R * sm.Sp * 4);
@@ -1129,7 +1122,7 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
     if (c->stem[i].on) {
       void *wp = static_cast<uint8_t *>(workspace) + c->stem[i].w_off;
       const int e = c->stem[i].Cp == 4
-                        ? launch_repack_weights(L.w, wp, L.Cout, L.R, L.S, L.Cin, c->stem[i].Sp, s)
+                        ? launch_repack_weights(L.w, wp, L.Cout, L.R, L.S, L.Cin, c->stem[i].Sp, c->pool_role(i) == 1 ? 1 : 0, s)
                         : launch_pad_rows(L.w, wp, (long long)L.Cout * L.R * L.S, L.Cin, c->stem[i].Cp, s);
       if (e != 0) return F8_ERR_DEVICE;
     }
@@ -1277,7 +1270,7 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
       }
       for (size_t j = 0; j < c->stem.size() && live; ++j) {
         const Stem &sm = c->stem[j];
-        if (!sm.on || (int)j <= t.last_use || (int)j <= t.producer) continue;
+        if (!sm.on || c->pool_role(j) == 1 || (int)j <= t.last_use || (int)j <= t.producer) continue;
         const size_t b0 = sm.x_off_per_image, b1 = b0 + round256(sm.x_bytes_per_image);
         if (a0 < b1 && b0 < a1) live = 0;
       }

@@ -1,5 +1,5 @@
-// Fused ImageNet stem: 7x7 stride-2 convolution (3 input channels re-laid-out to 4, 64 output
-// channels), unsigned requantisation and the 3x3 stride-2 pad-1 max pool behind it.
+// Fused ImageNet stem: 7x7 stride-2 convolution of a 3-channel image to 64 channels, unsigned requantisation and the
+// 3x3 stride-2 pad-1 max pool behind it.
 #pragma once
 
 #include "f8_device.h"
@@ -7,12 +7,12 @@
 namespace f8 {
 
 struct StemPoolParams {
-  const uint8_t *xp;     // [B][Hp][Wp][4], zero border already in place (window of pixel (p, q) starts at (2 p, 2 q)),
-                         // as signed bytes: an unsigned image is stored xor 0x80, border and fourth channel included
-  const int8_t *wp;      // [64][7][8][4], zeros in the eighth tap and the fourth channel
+  const uint8_t *x;      // [B][H][W][3], any alignment (whole dwords that hold bytes of an image are read)
+  const int8_t *wp;      // [64][7][8][4], zeros in the first tap and the fourth channel
   const int32_t *acc0;   // [64] folded accumulator start values (bias, rounding addend, sign correction)
   uint8_t *y;            // [B][PP][QP][64] pooled output
-  int B, Hp, Wp;         // Wp >= 2 (Q - 1) + 10, a multiple of 4
+  int B, H, W;
+  uint32_t x_xor;        // 0x80808080 for unsigned images
   int P, Q;              // convolution output size
   int PP, QP;            // pooled size: (P - 1) / 2 + 1, (Q - 1) / 2 + 1
   int shift, lo, hi;     // requantisation of the convolution (shift >= 0, 0 <= lo <= hi <= 255)

@@ -87,7 +87,8 @@ __global__ __launch_bounds__(IMG_NT, 1) void conv_img_kernel(const ConvImgParams
   const ScaledClip c1 = scaled_clip(p.lo, p.hi, p.shift);
   const int sh = p.shift;
 
-  for (int img = blockIdx.x; img < p.B; img += gridDim.x) {
+  const XcdRange images = xcd_range(p.B, 1);
+  for (int img = images.first; img < images.end; img += images.step) {
     // the first tap's weights are requested before anything else
     v4i bq[IMG_KPT][2];
 #pragma unroll
@@ -244,7 +245,8 @@ __global__ __launch_bounds__(IMG_NT, 1) void conv_img_band_kernel(const ConvImgP
   const ScaledClip c1 = scaled_clip(p.lo, p.hi, p.shift);
   const int sh = p.shift;
 
-  for (int u = blockIdx.x; u < p.B * bands; u += gridDim.x) {
+  const XcdRange units = xcd_range(p.B * bands, 1);
+  for (int u = units.first; u < units.end; u += units.step) {
     const int img = u / bands, row0 = (u - img * bands) * S::BR;     // first output row of the band
     const int HWu = min(S::BR, p.H - row0) * p.W;                    // its output pixels
     // ---- the band's input rows into LDS, stored xor 0x80 when unsigned (border: zero xor 0x80) ----

@@ -55,6 +55,7 @@ struct Units {
   int group;              // bytes of one K group's part of the patch
   int lds;
   long long units;
+  int by_unit;            // neighbouring workgroups share a unit (else a slice of channels)
 };
 
 template <int C> Units cut(int B, int H, int W, int WK) {
@@ -90,7 +91,7 @@ __device__ __forceinline__ int frag_channel(int r) { return 16 * ((r >> 2) & 1) 
 
 template <int C, int WK, bool NAT>
 __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_kernel(const ConvImgkParams p, const Units u, const FastDiv fd_w, const FastDiv fd_px,
-                                                          const FastDiv fd_prows, const FastDiv fd_units) {
+                                                          const FastDiv fd_prows, const FastDiv fd_fast) {
   using S = Shape<C>;
   constexpr int NT = 64 * S::NW, MB = S::MB, WN = S::NW / WK;
   constexpr int KPT = C / 32;                        // K slices per tap
@@ -107,9 +108,10 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const int kg = wave % WK, wn = wave / WK;
-  // workgroups of one channel slice are neighbours on an XCD: they stream the same weights
+  // neighbours on an XCD: the workgroups of one channel slice, which stream the same weights, or of one unit
   const uint32_t bid = xcd_remap(blockIdx.x, gridDim.x);
-  const int slice = (int)fd_units.div(bid), unit = (int)bid - slice * (int)fd_units.d;
+  const int slow = (int)fd_fast.div(bid), fast = (int)bid - slow * (int)fd_fast.d;
+  const int slice = u.by_unit ? fast : slow, unit = u.by_unit ? slow : fast;
   const int n0 = slice * (32 * WN);
   int img0, y0, nimg, rows;
   if (u.bands > 1) {
@@ -350,10 +352,17 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
 
 template <int C, int WK, bool NAT> int launch_c(const ConvImgkParams &p, hipStream_t stream) {
   using S = Shape<C>;
-  const Units u = cut<C>(p.B, p.H, p.W, WK);
+  Units u = cut<C>(p.B, p.H, p.W, WK);
   if (u.images < 1) return (int)hipErrorInvalidValue;
-  const long long grid = u.units * (C / (32 * (S::NW / WK)));
-  if (grid > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+  const int slices = C / (32 * (S::NW / WK));
+  const long long grid = u.units * slices;
+  // Unit by unit an XCD reads all weights, and of the images only the eighth of the batch that it computes and, the layers before being
+  // ordered alike, mostly wrote itself: those lie in its L2.  Slice by slice it reads an eighth of the weights and images that
+  // other XCDs wrote, from beyond its L2 at half the rate (64 KB per workgroup: 5.1 k cycles where this XCD wrote them, 10.3 k elsewhere).
+  // Whichever fetches less from there; ResNet-18, us of a forward, slice by slice / unit by unit: 224 x 224, 24 images 174.7 / 169.2,
+  // 32 187.6 / 178.1, 64 250.7 / 244.0, 128 386 / 380; 512 channels at 192 (2.4 MB of weights) the other way, 531 / 535, by this line 524.
+  const long long share = u.units * slices / 8 < u.units ? u.units * slices / 8 : u.units;
+  u.by_unit = share * u.images * u.rows * p.W * C > 9ll * C * C;
   // up to one workgroup per CU: ask for more than half of the LDS, or two of them may share a CU while
   // another stays idle (256 workgroups for 128 channels on 64 images: 13.3 us, with this 10.6 us)
   const int lds = grid <= 256 && u.lds < 84 * 1024 ? 84 * 1024 : u.lds;
@@ -367,7 +376,7 @@ template <int C, int WK, bool NAT> int launch_c(const ConvImgkParams &p, hipStre
     if (dev >= 0 && dev <= 63) done_mask.fetch_or(1ull << dev, std::memory_order_relaxed);
   }
   hipLaunchKernelGGL((conv_imgk_kernel<C, WK, NAT>), dim3((unsigned)grid), dim3(64 * S::NW), lds, stream, p, u, FastDiv((uint32_t)p.W),
-                     FastDiv((uint32_t)(u.rows * p.W)), FastDiv((uint32_t)u.prows), FastDiv((uint32_t)u.units));
+                     FastDiv((uint32_t)(u.rows * p.W)), FastDiv((uint32_t)u.prows), FastDiv((uint32_t)(u.by_unit ? slices : u.units)));
   return (int)hipGetLastError();
 }
 

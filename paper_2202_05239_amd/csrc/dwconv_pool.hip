@@ -331,7 +331,7 @@ __global__ __launch_bounds__(NT) void maxpool_vec16_kernel(const PoolParams p, c
 // Global sum pool + requantisation: one thread = CV channels of one image.
 template <int CV>
 __global__ __launch_bounds__(NT) void gpool_kernel(const DwParams p, const long long total) {
-  const long long gid = (long long)blockIdx.x * NT + threadIdx.x;
+  const long long gid = (long long)xcd_remap(blockIdx.x, gridDim.x) * NT + threadIdx.x;
   if (gid >= total) return;
   const int cgroups = p.C / CV;
   const int cg = (int)(gid % cgroups);

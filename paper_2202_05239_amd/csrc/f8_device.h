@@ -52,6 +52,22 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblocks) {
   return xcd * per + (xcd < rem ? xcd : rem) + idx;
 }
 
+// The units of a persistent kernel, ordered by pixel, for one of its workgroups: XCD k takes the k-th eighth of them, and its
+// workgroups walk through that `per` units at a time, this one from `first` on.  (The grid covers every eighth: see xcd_grid.)
+struct XcdRange {
+  int first, end, step;
+};
+__device__ __forceinline__ XcdRange xcd_range(int n, int per) {
+  const int xcd = (int)blockIdx.x & 7, idx = (int)blockIdx.x >> 3, wgs = ((int)gridDim.x + 7 - xcd) >> 3;
+  const int share = n >> 3, rem = n & 7, lo = xcd * share + (xcd < rem ? xcd : rem);
+  return XcdRange{lo + idx * per, lo + share + (xcd < rem ? 1 : 0), wgs * per};
+}
+// Workgroups that take `per` units each at a time, at most `most` (a multiple of 8, as the result is).
+inline int xcd_grid(int n, int per, int most) {
+  const long long wgs = 8ll * (((n + 7ll) / 8 + per - 1) / per);
+  return wgs < most ? (int)wgs : most;
+}
+
 // Rounding shift + clip.  `a` already contains the rounding addend 2^(s-1) (it is folded
 // into the accumulator's start value), so s >= 0 is one arithmetic shift.  For s < 0 the
 // value is scaled up; clamping first keeps the product inside 32 bits and cannot change

@@ -165,9 +165,10 @@ __global__ __launch_bounds__(SP_NT, NF == 1 ? 3 : 2) void stem_pool_kernel(const
   };
 
   constexpr int TPG = 2 * NF;                    // tiles of a workgroup at a time
-  const int nw = (int)gridDim.x * TPG;
-  int t = (int)blockIdx.x * TPG + (NF == 2 ? wave : wave >> 1);
-  if (t < p.ntiles) fetch_patch(t);
+  const XcdRange tiles = xcd_range(p.ntiles, TPG);
+  const int nw = tiles.step, t_end = tiles.end;
+  int t = tiles.first + (NF == 2 ? wave : wave >> 1);
+  if (t < t_end) fetch_patch(t);
 
   // weights: fa[nf][r] = channel 32 (nf0 + nf) + frag_channel(l32), bytes 32 r + 16 half .. + 16 of its 224
   v4i fa[NF][7];
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(SP_NT, NF == 1 ? 3 : 2) void stem_pool_kernel(const
   const int e_lane = ebuf_at + jp * EPITCH + 64 * half;
   const ScaledClip sc = scaled_clip(p.lo, p.hi, p.shift);
 
-  for (; t < p.ntiles; t += nw) {
+  for (; t < t_end; t += nw) {
     int b, ti, tj;
     tile_coords(t, b, ti, tj);
     const int gi0 = TP * ti - 1, gj0 = TP * tj - 1;                   // pooled coordinates of position (0, 0)
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(SP_NT, NF == 1 ? 3 : 2) void stem_pool_kernel(const
             acc[cls][nf] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[nf][r], fb[r & 1][cls], r == 0 ? sv[nf] : acc[cls][nf], 0, 0, 0);
       }
       // the next tile's patch is requested before this block's results are worked on
-      if (mf == 1 && t + nw < p.ntiles) fetch_patch(t + nw);
+      if (mf == 1 && t + nw < t_end) fetch_patch(t + nw);
 
       const int gi = gi0 + 4 * mf + ip, gj = gj0 + jp;                // this lane's pooled pixel
       if (edge) {
@@ -305,8 +306,7 @@ static int launch_as(const StemPoolParams &p, hipStream_t stream) {
     if (e != hipSuccess) return (int)e;
     if (dev >= 0 && dev <= 63) done_mask |= 1ull << dev;
   }
-  const long long groups = ((long long)p.ntiles + 2 * NF - 1) / (2 * NF);
-  hipLaunchKernelGGL((stem_pool_kernel<NF, ROWS4>), dim3((unsigned)(groups < limit ? groups : limit)), dim3(SP_NT), bytes, stream, p);
+  hipLaunchKernelGGL((stem_pool_kernel<NF, ROWS4>), dim3((unsigned)xcd_grid(p.ntiles, 2 * NF, limit)), dim3(SP_NT), bytes, stream, p);
   return (int)hipGetLastError();
 }
 

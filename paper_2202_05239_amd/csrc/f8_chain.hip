@@ -40,6 +40,7 @@
 #include "conv_img.h"
 #include "conv_imgk.h"
 #include "conv_imgk_pair.h"
+#include "conv_s2.h"
 #include "f8_host.h"
 
 using namespace f8;
@@ -143,6 +144,42 @@ struct f8_chain {
       if (wgs >= (L.Cin == 128 && wk == 2 ? 128 : 176)) return wgs <= most ? wk : 0;
     }
     return 0;
+  }
+  // Stride-2 3x3 layers that the image-stationary kernel can take, s2[i] = 1, with the 1x1 stride-2 layer next to one on the same input, s2[i] = 2
+  // (s2_proj: the other layer of the two).  The 3x3 layer launches both.  Its weights in fragment order lie behind the arena, the 1x1
+  // layer's among the constants (s2_const_off).
+  std::vector<int> s2, s2_proj;        // per layer
+  std::vector<size_t> s2_const_off;    // per layer (of the 1x1 one)
+  int conv_s2 = 1;
+  size_t s2_w_bytes(size_t i) const { return s2[i] == 1 ? (size_t)9 * layers[i].Cin * layers[i].Cout : 0; }
+  // Waves that share K, or 0: another kernel.  As few as give three quarters of the CUs a workgroup; with the projection the
+  // launch that it saves pays from few pixels on.  Microseconds of a forward of two 1x1 layers and these (16 -> C in front, N -> N
+  // behind), two launches of the general kernels -> one with 1, 2, 4 waves:
+  //   64 -> 128 from 56 x 56: batch 4 14.0 -> 14.3, 8 16.3 -> 15.4, 32 21.5 -> 18.7, 64 30.5 -> 25.4, 128 49.5 -> 42.7, 256 80.2 -> 71.4; from 24 x 24: 8 12.0 -> 13.6, 32 16.0 -> 15.4
+  //   128 -> 256 from 28 x 28: batch 8 14.8 -> -, 15.7, 12 17.9 -> -, 17.4, 48 24.7 -> 22.0, 20.4, 64 25.4 -> 23.3, 21.8, 96 31.5 -> 26.4, 32.3, 256 55.0 -> 52.8, 60.4;
+  //     from 12 x 12 (a third of a workgroup's pixels): 32 14.2 -> -, 15.5, 128 20.6 -> 19.3, 18.0, 500 30.2 -> 34.7
+  //   256 -> 512 from 14 x 14: batch 4 13.8 -> -, -, 14.2, 12 16.3 -> -, -, 15.7, 24 20.2 -> -, 19.5, 18.4, 48 28.7 -> 25.4, 20.3, 25.1, 96 33.6 -> 25.4, 30.4,
+  //     256 48.4 -> 46.3; from 6 x 6: 32 14.1 -> -, -, 14.0, 500 32.9 -> 34.9
+  // The 3x3 layer by itself: 64 -> 128 batch 16 14.4 -> 14.2, 64 23.4 -> 21.1, 192 51.2 -> 50.0; 128 -> 256 24 17.1 -> -, 16.5, 64 20.4 -> -, 19.4, 128 28.8 -> 26.3,
+  // 192 38.8 -> 39.8; 256 -> 512 24 15.7 -> -, -, 15.4, 64 24.6 -> -, 19.2, 128 28.1 -> 24.2, 192 36.5 -> 36.4.
+  int s2_waves(size_t i, int batch) const {
+    if (s2[i] == 0 || conv_s2 == 0 || keep_all) return 0;
+    const size_t a = s2[i] == 1 ? i : (size_t)s2_proj[i];
+    if (bn_role(a, batch) != 0 || (use_fusion() && fused[a].role != 0)) return 0;
+    const f8_layer_desc &L = layers[a];
+    const Geom &g = geom[a];
+    if (conv_s2 >= 10) {
+      const int wk = conv_s2 - 10;
+      return (wk == 1 || wk == 2 || wk == 4) && wk <= conv_s2_most_waves(L.Cin) ? wk : 0;
+    }
+    const bool projection = s2_proj[a] >= 0, fills = conv_s2_fills(L.Cin, g.H, g.W);
+    const int most = conv_s2_most_waves(L.Cin);
+    int wk = 1;
+    long long wgs = conv_s2_workgroups(L.Cin, L.Cout, batch, g.H, g.W, wk);
+    while (wgs < 176 && wk < most) wgs = conv_s2_workgroups(L.Cin, L.Cout, batch, g.H, g.W, wk *= 2);
+    if (!projection) return fills && wgs >= 176 && (L.Cin == 64 || wgs <= 256) ? wk : 0;
+    if (!fills && wgs > 256) return 0;
+    return (long long)batch * g.P * g.Q >= (L.Cin == 64 ? 4500 : L.Cin == 128 ? 2300 : 500) ? wk : 0;
   }
   // Two 3x3 layers of 64 or 128 channels of which the second is the first's only reader and may have the first's input as its shortcut
   // (a basic residual block): pair[i] = 1 and 2, one launch (the second's) where both take the image-stationary kernel, whose
@@ -295,16 +332,18 @@ struct f8_chain {
     const size_t base = const_bytes + arena_per_image * (size_t)batch;
     size_t bytes = 0;
     for (size_t i = 0; i < layers.size(); ++i) {
-      bool img = false, pair = false, three = false;
+      bool img = false, pair = false, three = false, two = false;
       for (int b : {batch, batch / 2, batch - batch / 2}) {
         if (b < 1) continue;
         const int role = bn_role(i, b);
         three = three || role == 1;
         img = img || (role == 0 && img_role(i, b) != 0);
         pair = pair || dwp_role(i, b) == 1;
+        two = two || (s2[i] == 1 && s2_waves(i, b) != 0);
       }
-      if (off) off[i] = img || pair ? base + bytes : 0;
-      if (img || pair) bytes += round256(img ? img_w_bytes[i] : dwp_w_bytes[i]);
+      const bool copy = img || pair || two;
+      if (off) off[i] = copy ? base + bytes : 0;
+      if (copy) bytes += round256(img ? img_w_bytes[i] : two ? s2_w_bytes(i) : dwp_w_bytes[i]);
       if (boff) boff[i] = !three ? 0 : bn_const_off[i] != 0 ? bn_const_off[i] : base + bytes;
       if (three && bn_const_off[i] == 0) bytes += round256(bn_w_bytes(i));
     }
@@ -541,6 +580,31 @@ struct f8_chain {
     return p;
   }
 
+  // Parameters of the stride-2 3x3 layer i and the projection beside it.
+  ConvS2Params s2_params(size_t i, const void *x, void *out, void *workspace, int batch) const {
+    const f8_layer_desc &L = layers[i];
+    uint8_t *cb = static_cast<uint8_t *>(workspace);
+    ConvS2Params p;
+    p.x = static_cast<const uint8_t *>(tensor_ptr(L.src, x, out, workspace, batch));
+    p.w = reinterpret_cast<const int8_t *>(cb + frag_off[i]);
+    p.acc0 = reinterpret_cast<const int32_t *>(cb + acc0_off[i]);
+    p.y = static_cast<uint8_t *>(tensor_ptr(L.dst, x, out, workspace, batch));
+    p.acc0p = nullptr; p.wp = nullptr; p.yp = nullptr;
+    p.B = batch; p.H = geom[i].H; p.W = geom[i].W; p.C = L.Cin; p.N = L.Cout;
+    p.shift = L.q.fl_x + L.q.fl_w - L.q.fl_y; p.lo = L.q.clip_lo; p.hi = L.q.clip_hi;
+    p.shiftp = p.lop = p.hip = 0;
+    if (s2_proj[i] >= 0) {
+      const f8_layer_desc &T = layers[s2_proj[i]];
+      p.acc0p = reinterpret_cast<const int32_t *>(cb + acc0_off[s2_proj[i]]);
+      p.wp = reinterpret_cast<const int8_t *>(cb + s2_const_off[s2_proj[i]]);
+      p.yp = static_cast<uint8_t *>(tensor_ptr(T.dst, x, out, workspace, batch));
+      p.shiftp = T.q.fl_x + T.q.fl_w - T.q.fl_y; p.lop = T.q.clip_lo; p.hip = T.q.clip_hi;
+    }
+    p.x_xor = L.q.x_type == F8_U8 ? 0x80808080u : 0u;
+    p.wk = s2_waves(i, batch);
+    return p;
+  }
+
   // Parameters of the basic residual block that starts at layer i.
   ConvPairParams pair_params(size_t i, const void *x, void *out, void *workspace, int batch) const {
     const f8_layer_desc &L = layers[i], &T = layers[i + 1];
@@ -625,6 +689,10 @@ struct f8_chain {
     if (block == 2) {
       const PwDwPwParams pp = pdp_params(i - 1, x, out, workspace, batch);
       return (pdp_image(i - 1) ? launch_image_dw_pw(pp, s) : launch_pw_dw_pw(pp, s)) == 0 ? F8_OK : F8_ERR_DEVICE;
+    }
+    if (s2[i] != 0 && s2_waves(i, batch) != 0) {
+      if (s2[i] == 2) return F8_OK;
+      return launch_conv_s2(s2_params(i, x, out, workspace, batch), s) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
     const int twin = pair_role(i, batch);
     if (twin == 1) return F8_OK;
@@ -864,6 +932,9 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->dwp_w_bytes.push_back(0);
     c->frag_off.push_back(0);
     c->pair.push_back(0);
+    c->s2.push_back(0);
+    c->s2_proj.push_back(-1);
+    c->s2_const_off.push_back(0);
     c->pdp.push_back(0);
     c->pdp_off.push_back(0);
     c->pdp_w2_off.push_back(0);
@@ -936,6 +1007,31 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
                               T.res >= 0 ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0, nullptr, nullptr))
       continue;
     c->pair[i] = 1; c->pair[i + 1] = 2;
+  }
+  // stride-2 3x3 layers, and a 1x1 stride-2 layer of as many channels beside one (the layer in front of it or behind it) on the same
+  // input, all tensors in the arena
+  c->conv_s2 = tuning().conv_s2.load();
+  for (size_t i = 0; i < c->layers.size(); ++i) {
+    const f8_layer_desc &L = c->layers[i];
+    const Geom &g = c->geom[i];
+    auto plain = [&](size_t l) {
+      const f8_layer_desc &D = c->layers[l];
+      return D.op == F8_OP_CONV && !c->stem[l].on && D.res < 0 && D.dst2 <= 0 && D.q.y_type != F8_S32 && D.q.fl_x + D.q.fl_w - D.q.fl_y >= 0 &&
+             (reinterpret_cast<uintptr_t>(D.w) & 15) == 0 && !c->tensors[D.src].external && !c->tensors[D.dst].external;
+    };
+    if (!plain(i) || !conv_s2_applicable(L.Cin, L.Cout, L.R, L.S, L.stride_h, L.stride_w, L.pad_h, L.pad_w, g.H, g.W, L.q.fl_x + L.q.fl_w - L.q.fl_y, nullptr, nullptr))
+      continue;
+    c->s2[i] = 1;
+    for (size_t j : {i + 1, i - 1}) {
+      if (j >= c->layers.size() || c->s2[j] != 0 || !plain(j)) continue;
+      const f8_layer_desc &T = c->layers[j];
+      if (T.src != L.src || T.Cout != L.Cout || T.R != 1 || T.S != 1 || T.stride_h != 2 || T.stride_w != 2 || T.pad_h != 0 || T.pad_w != 0) continue;
+      c->s2_proj[i] = (int)j;
+      c->s2[j] = 2; c->s2_proj[j] = (int)i;
+      c->s2_const_off[j] = c->const_bytes;
+      c->const_bytes += round256((size_t)T.Cin * T.Cout);
+      break;
+    }
   }
   // a 3x3 layer, the 1x1 layer of four times its channels that is its only reader, and the 1x1 layer that opens the next
   // block (the next layer, or the one after a new stage's shortcut projection); all tensors in the arena
@@ -1096,7 +1192,7 @@ f8_status f8_chain_workspace_bytes(const f8_chain *cc, int batch, size_t *bytes)
   // program has to hold every smaller one too.  Where a smaller arena saves more than all copies take, nothing more
   // can be needed; a chain whose arena is next to nothing gets room for all of them instead of a long search.
   size_t copies = 0, most = 0;
-  for (size_t i = 0; i < c->layers.size(); ++i) copies += round256(c->img_w_bytes[i]) + round256(c->dwp_w_bytes[i]) + (c->bn_const_off[i] == 0 ? round256(c->bn_w_bytes(i)) : 0);
+  for (size_t i = 0; i < c->layers.size(); ++i) copies += round256(c->img_w_bytes[i]) + round256(c->s2_w_bytes(i)) + round256(c->dwp_w_bytes[i]) + (c->bn_const_off[i] == 0 ? round256(c->bn_w_bytes(i)) : 0);
   for (int b = batch; b >= 0 && c->arena_per_image * (size_t)(batch - b) <= copies; --b) {
     const bool far = batch - b >= 1024;
     most = std::max(most, c->arena_per_image * (size_t)b + (far ? copies : c->place_fragments(b, nullptr, nullptr)));
@@ -1132,7 +1228,12 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
     if (c->dwp[i] == 2 && c->frag_off[i - 1] != 0 &&
         launch_dw_pw_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->frag_off[i - 1]), L.Cin, L.Cout, s) != 0)
       return F8_ERR_DEVICE;
-    if (c->frag_off[i] != 0 &&
+    if (c->frag_off[i] != 0 && c->s2[i] == 1) {
+      int8_t *cb = static_cast<int8_t *>(workspace);
+      int e = launch_conv_s2_weights(L.w, cb + c->frag_off[i], 9, L.Cin, L.Cout, s);
+      if (e == 0 && c->s2_proj[i] >= 0) e = launch_conv_s2_weights(c->layers[c->s2_proj[i]].w, cb + c->s2_const_off[c->s2_proj[i]], 1, L.Cin, L.Cout, s);
+      if (e != 0) return F8_ERR_DEVICE;
+    } else if (c->frag_off[i] != 0 &&
         launch_conv_img_weights(L.w, reinterpret_cast<int8_t *>(static_cast<uint8_t *>(workspace) + c->frag_off[i]), L.Cin, s) != 0)
       return F8_ERR_DEVICE;
   }
@@ -1341,7 +1442,8 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
   }
   const int three = c->bn_role((size_t)layer, batch);
   const int block = c->pdp_role((size_t)layer, batch), twin = c->pair_role((size_t)layer, batch);
-  if (three > 1 || block == 1 || block == 3 || twin == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
+  const bool two = c->s2_waves((size_t)layer, batch) != 0;
+  if (three > 1 || (two && c->s2[layer] == 2) || block == 1 || block == 3 || twin == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
     // accounted to the layer in front (of the first layer of an inverted-residual or basic block: behind), whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {
@@ -1368,11 +1470,18 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
       gk.P = g.P; gk.Q = g.Q;
       const int img = c->img_role((size_t)layer, batch);
       if (three == 1) name = L.Cin == 64 ? "bottleneck<64>" : L.Cin == 128 ? "bottleneck<128>" : "bottleneck<256>";
+      else if (two) name = c->s2_proj[layer] >= 0 ? (L.Cin == 64 ? "conv3x3_imgk_s2<64>+1x1" : L.Cin == 128 ? "conv3x3_imgk_s2<128>+1x1" : "conv3x3_imgk_s2<256>+1x1")
+                                                  : (L.Cin == 64 ? "conv3x3_imgk_s2<64>" : L.Cin == 128 ? "conv3x3_imgk_s2<128>" : "conv3x3_imgk_s2<256>");
       else if (img > 1) name = L.Cin == 64 ? "conv3x3_imgk<64>" : L.Cin == 128 ? "conv3x3_imgk<128>" : L.Cin == 256 ? "conv3x3_imgk<256>" : "conv3x3_imgk<512>";
       else if (img == 1) name = L.Cin == 256 ? "conv3x3_img<256x256>" : "conv3x3_img<128x128>";
       else name = conv_kernel_name(gk, L.q, L.res >= 0, L.dst2 > 0 ? &L.q2 : nullptr);
       ops = 2.0 * M * g.R * g.S * g.Cin * g.Cout;
       bytes += (double)g.R * g.S * g.Cin * g.Cout + 4.0 * g.Cout;
+      if (two && c->s2_proj[layer] >= 0) {
+        // plus the projection: its operand is the middle tap's
+        ops += 2.0 * M * g.Cin * g.Cout;
+        bytes += M * g.Cout + (double)g.Cin * g.Cout + 4.0 * g.Cout;
+      }
       if (twin == 2) {
         // plus the 3x3 layer in front: the block's input (also its shortcut) and output
         name = L.Cin == 64 ? "conv3x3_pair<64>" : "conv3x3_pair<128>";

@@ -15,15 +15,16 @@
 //   C = 64: a band of up to 224 pixels, two waves of 32 channels, every weight of a wave in its registers;
 //   C = 256: a whole image of up to 224 pixels (7 blocks of 32); C = 512: two 7 x 7 images (4 blocks);
 //   C = 128: a band of up to 224 pixels.
-// Now 12.1 us for 256 channels on 64 images and 12.0 us for 512 (two waves share K), 16.4 / 18.5 us on 128 images
-// (22.4 / 28.0 before); 9.3 k cycles of a workgroup's 19.7 k are the loop (8.1 k of matrix instructions),
+// With one wave per SIMD 12.0 us for 256 channels on 64 images (two waves share K), with two 11.1; 16.4 us on 128 images
+// (22.4 before); of one wave's cycles 9.3 k cycles of a workgroup's 19.7 k are the loop (8.1 k of matrix instructions),
 // 6 k the patch (82 - 92 KiB at the 60 bytes per clock a CU gets from L2, then memory latency), 4 k the sums in
 // LDS and the stores.  With 64 channels per wave and four waves sharing K the loop reads half as much from LDS
 // but the sums take twice as long: 12.8 us.  64 channels on 64 images of 56 x 56 with a residual: 13.5 us (18.9 in
 // conv_fast).
-// NAT (64 channels, single-layer calls): the weights are read as they are, 32 bytes of 32 rows per instruction, and
-// summed for the start values on the way, so that the call is one launch: 10.5 us a call on 32 images of
-// 56 x 56 against 11.9 us for fold and conv_ws.
+// MG = 2: twice the waves, w and w + NW on one SIMD with the same channels and share of K and half of the pixels' blocks each.
+// NAT (64 channels, single-layer calls): the weights are read as they are and
+// summed for the start values on the way, so that the call is one launch: 8.6 us a call on 32 images of
+// 56 x 56 (10.7 with half the waves, 11.9 for fold and conv_ws).
 #include "conv_imgk.h"
 
 #include <atomic>
@@ -44,6 +45,9 @@ template <> struct Shape<64> { static constexpr int NW = 2, MB = 7, RPW = 5, NI 
 template <> struct Shape<128> { static constexpr int NW = 4, MB = 7, RPW = 3, NI = 4; };
 template <> struct Shape<256> { static constexpr int NW = 4, MB = 7, RPW = 5, NI = 4; };
 template <> struct Shape<512> { static constexpr int NW = 4, MB = 4, RPW = 5, NI = 5; };
+
+// NAT: the weights of 64 channels as rows of 9 taps, 16 bytes more than their length apart: 8 rows' pieces share no bank
+constexpr int NAT_PITCH = 9 * 64 + 16, NAT_BYTES = 64 * NAT_PITCH;
 
 // How the batch is cut into units of one workgroup: whole images, or bands of rows of one image.
 struct Units {
@@ -89,11 +93,13 @@ template <int C> Units cut(int B, int H, int W, int WK) {
 // Channel fed as row r of a 32-channel block (the fragment order of launch_conv_img_weights has it built in).
 __device__ __forceinline__ int frag_channel(int r) { return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3); }
 
-template <int C, int WK, bool NAT>
-__global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_kernel(const ConvImgkParams p, const Units u, const FastDiv fd_w, const FastDiv fd_px,
+template <int C, int WK, bool NAT, int MG>
+__global__ __launch_bounds__(64 * Shape<C>::NW * MG, MG == 2 ? (C == 64 ? 2 : 1) : WK == 1 ? 2 : 1) void conv_imgk_kernel(const ConvImgkParams p, const Units u, const FastDiv fd_w, const FastDiv fd_px,
                                                           const FastDiv fd_prows, const FastDiv fd_fast) {
   using S = Shape<C>;
-  constexpr int NT = 64 * S::NW, MB = S::MB, WN = S::NW / WK;
+  constexpr int NW = S::NW, NWG = NW * MG, NT = 64 * NWG, MB = S::MB, WN = NW / WK;
+  constexpr int MH = (MB + MG - 1) / MG;             // blocks per wave
+  constexpr int RPW = (NW * S::RPW + NWG - 1) / NWG;
   constexpr int KPT = C / 32;                        // K slices per tap
   constexpr int KSW = KPT / WK;                      // of which a wave takes this many
   constexpr int KS = 9 * KPT;
@@ -107,7 +113,7 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
-  const int kg = wave % WK, wn = wave / WK;
+  const int kg = wave % WK, wn = wave % NW / WK, b0 = wave < NW ? 0 : MH;      // (b0: this wave's first block)
   // neighbours on an XCD: the workgroups of one channel slice, which stream the same weights, or of one unit
   const uint32_t bid = xcd_remap(blockIdx.x, gridDim.x);
   const int slow = (int)fd_fast.div(bid), fast = (int)bid - slow * (int)fd_fast.d;
@@ -142,10 +148,20 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
     else a0[g] = p.acc0 ? v4i{p.acc0[n], p.acc0[n + 1], p.acc0[n + 2], p.acc0[n + 3]} : v4i{0, 0, 0, 0};
   }
   v4i bq[RING];
-  const int8_t *w_row = p.w + (size_t)(n0 + 32 * wn + frag_channel(l32)) * (9 * C) + 16 * half;
+  constexpr bool STAGE = NAT && MG == 2;             // by way of LDS
+  constexpr int NATP = STAGE ? C * 9 * C / 16 / NT : 1;
+  v4i wraw[NATP];
+  const int8_t *w_nat = p.w + (size_t)(n0 + 32 * wn + frag_channel(l32)) * (9 * C) + 16 * half;
+  if (STAGE) {
+    // as they lie in memory; they change places in LDS, behind the patch (32 bytes of each of 32 rows, as a wave needs them, the load
+    // unit takes a row at a time: 16 bytes per clock)
 #pragma unroll
-  for (int sc = 0; sc < RING; ++sc)
-    bq[sc] = NAT ? *reinterpret_cast<const v4i *>(w_row + 32 * sc) : __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, wbase + slice_at(sc), 0);      // (ALL: slices of all rows; KSW == KPT then)
+    for (int i = 0; i < NATP; ++i) wraw[i] = *reinterpret_cast<const v4i *>(p.w + (size_t)(i * NT + tid) * 16);
+  } else {
+#pragma unroll
+    for (int sc = 0; sc < RING; ++sc)
+      bq[sc] = NAT ? *reinterpret_cast<const v4i *>(w_nat + 32 * sc) : __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, wbase + slice_at(sc), 0);      // (ALL: slices of all rows; KSW == KPT then)
+  }
 
   // ---- the input pixels and a border of zeros into LDS, xor 0x80 when unsigned.  A wave takes the patch rows
   // wave, wave + 4, ...; a row's pixels are consecutive in memory, so a lane's 16-byte pieces of a row lie at
@@ -154,15 +170,15 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
   const size_t image_bytes = (size_t)p.H * p.W * C;
   uint8_t *xbase = const_cast<uint8_t *>(p.x) + (size_t)img0 * image_bytes;
   uint32_t x_at[S::NI];
-  v4i px[S::RPW][S::NI];
+  v4i px[RPW][S::NI];
 #pragma unroll
   for (int i = 0; i < S::NI; ++i) {
     const int col = (i * 64 + lane) / PIECES;
     x_at[i] = (unsigned)(col - 1) < (unsigned)p.W ? (uint32_t)((i * 64 + lane) * 16 - C) : 0x80000000u;
   }
 #pragma unroll
-  for (int k = 0; k < S::RPW; ++k) {
-    const int row = wave + S::NW * k;                    // uniform
+  for (int k = 0; k < RPW; ++k) {
+    const int row = wave + NWG * k;                      // uniform
     const int img = (int)fd_prows.div((uint32_t)row), y = y0 + row - img * u.prows - 1;
     const bool in = img < nimg && (unsigned)y < (unsigned)p.H;
     if (row >= u.all_rows) continue;
@@ -173,8 +189,8 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
   }
   // the residual pieces this thread will need at the end: WK == 1: its lane's 16 channels of every block; otherwise
   // piece tid % (2 WN) of the pixels tid / (2 WN) + k * IPP
-  constexpr int IPP = NT / (2 * WN), ITEMS = WK == 1 ? MB : (MB * 32 + IPP - 1) / IPP;
-  const int piece = tid % (2 * WN), pixel0 = WK == 1 ? l32 : tid / (2 * WN);
+  constexpr int IPP = NT / (2 * WN), ITEMS = WK == 1 ? MH : (MB * 32 + IPP - 1) / IPP;
+  const int piece = tid % (2 * WN), pixel0 = WK == 1 ? 32 * b0 + l32 : tid / (2 * WN);
   const int n_out = WK == 1 ? n0 + 32 * wn + 16 * half : n0 + piece * 16;
   constexpr int ITEM_STEP = WK == 1 ? 32 : IPP;
   // (pixels past the unit: an offset the descriptors reject: loads return zeros, stores are dropped)
@@ -194,10 +210,10 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
   // (while they are on their way)
   // Fragment row 32 j + l32 is output pixel m of the unit; its window starts at patch pixel (image, y, x).
   // Rows past the last pixel read the patch's first window; their sums are dropped.
-  lds_u8 *ar[MB];
+  lds_u8 *ar[MH];
 #pragma unroll
-  for (int j = 0; j < MB; ++j) {
-    const int m = 32 * j + l32;
+  for (int j = 0; j < MH; ++j) {
+    const int m = 32 * (b0 + j) + l32;
     int at = 0;
     if (m < npx) {
       const int img = (int)fd_px.div((uint32_t)m), rem = m - img * (int)fd_px.d;
@@ -212,6 +228,17 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
     const int col = (i * 64 + lane) / PIECES, piece = lane % PIECES;
     // (pieces past the last column are fetched as zeros and not kept)
     to[i] = col < u.pcols ? (piece / (CG / 16)) * u.group + col * GP + (piece % (CG / 16)) * 16 : -1;
+  }
+  if (STAGE) {
+#pragma unroll
+    for (int i = 0; i < NATP; ++i) {
+      const int at = i * NT + tid, row = at / (9 * PIECES);
+      *reinterpret_cast<v4i *>(lds + u.lds - NAT_BYTES + row * NAT_PITCH + (at - row * (9 * PIECES)) * 16) = wraw[i];
+    }
+    __syncthreads();
+    const uint8_t *w_row = lds + u.lds - NAT_BYTES + (32 * wn + frag_channel(l32)) * NAT_PITCH + 16 * half;
+#pragma unroll
+    for (int sc = 0; sc < RING; ++sc) bq[sc] = *reinterpret_cast<const v4i *>(w_row + 32 * sc);
   }
   if (NAT) {
     int wsum = 0;
@@ -232,8 +259,8 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
   __builtin_amdgcn_sched_barrier(0);
   const int zx = (int)p.x_xor;
 #pragma unroll
-  for (int k = 0; k < S::RPW; ++k) {
-    const int row = wave + S::NW * k;
+  for (int k = 0; k < RPW; ++k) {
+    const int row = wave + NWG * k;
     if (row < u.all_rows) {
 #pragma unroll
       for (int i = 0; i < S::NI; ++i)
@@ -245,14 +272,16 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
 
   // ---- K loop: a pass is a row of the window, 3 taps x KSW slices; activation fragments one slice ahead,
   // one request at a time behind the matrix instructions
-  v16i acc[MB];
+  v16i acc[MH];
 #pragma unroll
-  for (int j = 0; j < MB; ++j)
+  for (int j = 0; j < MH; ++j)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[j][i] = a0[i >> 2][i & 3];
-  v4i xf[2][MB];
+  auto contract = [&](auto blocks) {
+  constexpr int MBW = decltype(blocks)::value;
+  v4i xf[2][MBW];
 #pragma unroll
-  for (int j = 0; j < MB; ++j) xf[0][j] = *(lds_v4i *)(ar[j]);
+  for (int j = 0; j < MBW; ++j) xf[0][j] = *(lds_v4i *)(ar[j]);
   const int row_step = u.pcols * GP;
 #pragma unroll ALL ? 3 : 1
   for (int r = 0; r < 3; ++r) {
@@ -264,10 +293,10 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
       const int off = last ? 0 : ((sc + 1) / KSW) * GP + 32 * ((sc + 1) % KSW);
       if (last) {
 #pragma unroll
-        for (int j = 0; j < MB; ++j) ar[j] += row_step;
+        for (int j = 0; j < MBW; ++j) ar[j] += row_step;
       }
 #pragma unroll
-      for (int j = 0; j < MB; ++j) {
+      for (int j = 0; j < MBW; ++j) {
         acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bq[ALL ? r * ROW_SLICES + sc : sc % RING], xf[cur][j], acc[j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         xf[nxt][j] = *(lds_v4i *)(ar[j] + off);
@@ -282,6 +311,9 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  };
+  if (MG == 1 || MB % 2 == 0 || b0 == 0) contract(std::integral_constant<int, MH>{});
+  else contract(std::integral_constant<int, MB - MH>{});      // (the block past the last: start values, whose stores are dropped)
 
   const ScaledClip c1 = scaled_clip(p.lo, p.hi, p.shift);
   const int sh = p.shift, d = p.res_d;
@@ -308,7 +340,7 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
     if constexpr (WK == 1) {
       // every wave has its sums complete: a lane's 16 channels of a pixel are a 16-byte piece of an output row
 #pragma unroll
-      for (int j = 0; j < MB; ++j) {
+      for (int j = 0; j < MH; ++j) {
         settle_matrix_result(acc[j]);
         int v[16];
 #pragma unroll
@@ -335,13 +367,15 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
   if constexpr (WK > 1) {
     // the waves' sums meet
     __syncthreads();                                 // the patch is no longer read
-    uint8_t *part = lds + wave * (MB * 32 * PART_PITCH) + l32 * PART_PITCH + half * 64;
+    uint8_t *part = lds + ((wave % NW) * MB + b0) * (32 * PART_PITCH) + l32 * PART_PITCH + half * 64;
 #pragma unroll
-    for (int j = 0; j < MB; ++j)
+    for (int j = 0; j < MH; ++j) {
+      if (MH * MG > MB && b0 + j >= MB) continue;
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<v4i *>(part + j * (32 * PART_PITCH) + g * 16) =
             v4i{acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]};
+    }
     __syncthreads();
   }
   using std::integral_constant;
@@ -350,7 +384,7 @@ __global__ __launch_bounds__(64 * Shape<C>::NW, WK == 1 ? 2 : 1) void conv_imgk_
   else { if (d >= 0) finish(integral_constant<int, 1>{}, std::true_type{}); else finish(integral_constant<int, 1>{}, std::false_type{}); }
 }
 
-template <int C, int WK, bool NAT> int launch_c(const ConvImgkParams &p, hipStream_t stream) {
+template <int C, int WK, bool NAT, int MG> int launch_as(const ConvImgkParams &p, hipStream_t stream) {
   using S = Shape<C>;
   Units u = cut<C>(p.B, p.H, p.W, WK);
   if (u.images < 1) return (int)hipErrorInvalidValue;
@@ -363,10 +397,11 @@ template <int C, int WK, bool NAT> int launch_c(const ConvImgkParams &p, hipStre
   // 32 187.6 / 178.1, 64 250.7 / 244.0, 128 386 / 380; 512 channels at 192 (2.4 MB of weights) the other way, 531 / 535, by this line 524.
   const long long share = u.units * slices / 8 < u.units ? u.units * slices / 8 : u.units;
   u.by_unit = share * u.images * u.rows * p.W * C > 9ll * C * C;
+  if (NAT && MG == 2) u.lds += NAT_BYTES;
   // up to one workgroup per CU: ask for more than half of the LDS, or two of them may share a CU while
   // another stays idle (256 workgroups for 128 channels on 64 images: 13.3 us, with this 10.6 us)
   const int lds = grid <= 256 && u.lds < 84 * 1024 ? 84 * 1024 : u.lds;
-  const void *fn = reinterpret_cast<const void *>(conv_imgk_kernel<C, WK, NAT>);
+  const void *fn = reinterpret_cast<const void *>(conv_imgk_kernel<C, WK, NAT, MG>);
   static std::atomic<unsigned long long> done_mask{0};         // devices whose LDS limit has been raised
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return (int)hipErrorInvalidDevice;
@@ -375,9 +410,19 @@ template <int C, int WK, bool NAT> int launch_c(const ConvImgkParams &p, hipStre
     if (e != hipSuccess) return (int)e;
     if (dev >= 0 && dev <= 63) done_mask.fetch_or(1ull << dev, std::memory_order_relaxed);
   }
-  hipLaunchKernelGGL((conv_imgk_kernel<C, WK, NAT>), dim3((unsigned)grid), dim3(64 * S::NW), lds, stream, p, u, FastDiv((uint32_t)p.W),
+  hipLaunchKernelGGL((conv_imgk_kernel<C, WK, NAT, MG>), dim3((unsigned)grid), dim3(64 * S::NW * MG), lds, stream, p, u, FastDiv((uint32_t)p.W),
                      FastDiv((uint32_t)(u.rows * p.W)), FastDiv((uint32_t)u.prows), FastDiv((uint32_t)(u.by_unit ? slices : u.units)));
   return (int)hipGetLastError();
+}
+
+template <int C, int WK, bool NAT> int launch_c(const ConvImgkParams &p, hipStream_t stream) {
+  // Twice the waves where a workgroup has a CU (64 channels: half a one) to itself; with more of them, workgroups of fewer waves side by
+  // side cover one another's waits.  Microseconds of a layer, single / twice the waves, 3x3 layers of 64 channels on 56 x 56 at 16 images
+  // 6.97 / 5.52, 32 9.73 / 7.55, 64 13.42 / 13.34, 128 24.8 / 23.0, 256 40.9 / 42.8; 128 on 28 x 28 at 16 8.4 / 7.2, 64 11.5 / 10.8, 128 (512 workgroups)
+  // 20.0 / 22.4; 256 on 14 x 14 at 32 8.8 / 7.9, 64 12.0 / 11.1, 128 17.6 / 17.5, 192 27.7 / 31.2; 512 on 7 x 7 at 32 9.5 / 9.0, 64 14.2 / 13.4, 256 39.7 / 40.6.
+  const Units u = cut<C>(p.B, p.H, p.W, WK);
+  // Weights as they are (a single call), 64 channels on 56 x 56, at 8 images 9.0 (conv_wavek) / 6.3, 16 7.9 / 6.7, 32 10.7 / 8.6, 64 14.5 / 16.0.
+  return u.units * (C / (32 * (Shape<C>::NW / WK))) <= (NAT ? 512 : C == 64 ? 2048 : 256) ? launch_as<C, WK, NAT, 2>(p, stream) : launch_as<C, WK, NAT, 1>(p, stream);
 }
 
 Units cut_any(int C, int B, int H, int W, int WK) {

@@ -319,9 +319,9 @@ static bool use_imgk_folding(const void *x, const int8_t *w, const void *y, cons
       y2 || q.y_type == F8_S32 || (res && q.res_type == F8_S32) || (reinterpret_cast<uintptr_t>(w) & 15))
     return false;
   if (!conv_imgk_applicable(g.Cin, g.Cout, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.H, g.W, q.fl_x + q.fl_w - q.fl_y, x, y, res)) return false;
-  // (us a call, here / fold and the best other kernel: batch 16 9.1 / 11.4, 32 10.5 / 11.9, 64 14.1 / 17.3, 256 40.3 / 40.6;
-  // with a residual 32 11.1 / 14.1, 256 44 / 64)
-  return conv_imgk_fills(g.Cin, g.H, g.W) && conv_imgk_workgroups(g.Cin, g.B, g.H, g.W, 1) >= 176;
+  // (us a call, here / fold and the best other kernel: 56 x 56, batch 2 5.1 / 4.8, 4 6.2 / 6.5, 8 6.3 / 9.0, 16 6.7 / 11.4, 32 8.6 / 11.9, 64 14.1 / 17.3,
+  // 256 40.3 / 40.6; with a residual 32 9.2 / 14.1, 256 44 / 64)
+  return conv_imgk_fills(g.Cin, g.H, g.W) && conv_imgk_workgroups(g.Cin, g.B, g.H, g.W, 1) >= 44;
 }
 
 bool enqueue_conv_folding(const void *x, const int8_t *w, const int32_t *bias, void *y, const void *res, const Geom &g,

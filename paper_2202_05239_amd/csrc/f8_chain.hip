@@ -121,17 +121,18 @@ struct f8_chain {
   }
   // Waves that share K in the image-stationary kernel, or 0 where another kernel is faster.  The fewer channels a
   // workgroup computes, the more often its pixels are loaded and the more sums meet in LDS, but the layer
-  // lasts as long as its last round of workgroups: as many channels as give three quarters of the CUs one.
-  // Measured (us; 1, 2, 4 waves / the best other kernel):
-  //   64 channels, 56 x 56: batch 16 6.9 / 7.8; 32 9.4 / 9.2; 64 12.5 / 14.5; 128 22.3 / 22.6 (conv_ws; with two halves of
-  //     128 side by side, as ResNet-50 runs at batch 256, conv_ws is ahead by 10 us a layer); with a residual: batch 32 9.9 / 12.2; 64 13.5 / 18.9; 256 41.5 / 65.0
-  //   128 channels, 28 x 28: batch 16 8.9, 8.2 / 8.7; 32 9.4, 8.7 / 10.7; 64 10.4, - / 16.7; 128 16.5, - / 21.5;
-  //     192 22.9, - / 26.8; 224 27.1, - / 28.0; 256 29.0, - / 29.9; 288 33.5, - / 38.5; 512 53.0, - / 57.1; 1024 100, - / 108 (conv_img,
+  // lasts as long as its last round of workgroups: as many shares as leave the launch one round.
+  // Microseconds of a layer, 1, 2, 4 waves / the best other kernel:
+  //   64 channels, 56 x 56: batch 2 5.1 / 4.2, 4 5.1 / 5.5, 8 5.3 / 6.5, 16 5.5 / 7.8, 64 13.3 / 14.5, 128 23.0 / 22.6 (conv_ws; with two halves of
+  //     128 side by side, as ResNet-50 runs at batch 256, conv_ws is ahead by 10 us a layer); 24 x 24: 8 5.1 / 4.0, 16 5.2 / 5.4, 32 5.3 / 6.0;
+  //     with a residual: batch 32 9.9 / 12.2; 64 13.5 / 18.9; 256 41.5 / 65.0
+  //   128 channels, 28 x 28: batch 8 8.3, 7.0 / 6.4; 12 8.6, 7.2 / 8.6; 24 9.0, 7.7 / 10; 40 9.8, 15.9 / 12; 64 10.7, 14.4 / 16.7; 128 20.0, - / 21.5;
+  //     192 22.9, - / 26.8; 256 29.0, - / 29.9; 288 33.5, - / 38.5; 512 53.0, - / 57.1; 1024 100, - / 108 (conv_img,
   //     conv_ws at 288); with a residual 256 31.7, - / 45.3; 768 84.0, - / 110.6; 20 x 20, batch 512: 29.2, - / 36.9
-  //   256 channels, 14 x 14: batch 16 12.6, 10.3, 8.1 / 7.2 (conv_wavek); 24 12.9, 10.4, 8.4 / 12.7; 32 12.8, 10.6,
-  //     8.6 / 13.0; 64 13.7, 12.1, 16.7 / 16.6; 128 16.4, 23.7, - / 22.4; 192 25.3, -, - / 24.8 (conv_img)
-  //   512 channels, 7 x 7: batch 16 14.9, 10.6, 7.9 / 7.1 (conv_wavek); 24 15.3, 10.8, 8.2 / 9.7; 64 16.1, 12.0, 16.0 /
-  //     22.3; 128 18.5, 23.7, - / 28.0; 256 35.0, -, - / 38.0
+  //   256 channels, 14 x 14: batch 8 12.3, 9.2, 7.6 / 6.2 (conv_wavek); 12 12.4, 9.5, 7.4 / 7.4; 16 12.5, 9.7, 7.4 / 7.7; 24 12.9, 9.6,
+  //     7.8 / 12.7; 33 13.3, 10.0, 15.5 / 13.9; 64 13.7, 11.1, 14.3 / 16.6; 70 14.3, 20.8, 23.2 / 16.8; 128 17.5, 21.8, - / 22.4; 192 27.7, -, - / 24.8 (conv_img)
+  //   512 channels, 7 x 7: batch 16 14.5, 10.4, 8.2 / 7.9 (conv_wavek); 24 14.8, 10.8, 8.8 / 9.7; 40 15.7, 11.8, 16.5 / -; 65 17.2, 23.1,
+  //     25.3 / 22.3; 128 20, 25.2, - / 28.0; 256 35.0, -, - / 38.0
   int imgk_waves(const f8_layer_desc &L, const Geom &g, int batch) const {
     if (imgk >= 10) {      // tuning aid: force it, with 1, 2 or 4 waves (there is no kernel for other counts)
       const int wk = imgk - 10;
@@ -139,11 +140,11 @@ struct f8_chain {
     }
     const long long most = L.Cin == 256 ? 256 : L.Cin == 64 && L.res < 0 ? 1024 : 0x7fffffffLL;
     if (!conv_imgk_fills(L.Cin, g.H, g.W)) return 0;
-    for (int wk = 1; wk <= conv_imgk_most_waves(L.Cin); wk *= 2) {
-      const long long wgs = conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk);
-      if (wgs >= (L.Cin == 128 && wk == 2 ? 128 : 176)) return wgs <= most ? wk : 0;
-    }
-    return 0;
+    const long long least = L.Cin == 64 ? 44 : L.Cin == 128 ? 80 : 176;
+    int wk = conv_imgk_most_waves(L.Cin);
+    while (wk > 1 && conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk) > 256) wk /= 2;
+    const long long wgs = conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk);
+    return wgs >= least && wgs <= most ? wk : 0;
   }
   // Stride-2 3x3 layers that the image-stationary kernel can take, s2[i] = 1, with the 1x1 stride-2 layer next to one on the same input, s2[i] = 2
   // (s2_proj: the other layer of the two).  The 3x3 layer launches both.  Its weights in fragment order lie behind the arena, the 1x1
@@ -195,6 +196,9 @@ struct f8_chain {
     // (the second may also be the first of a bottleneck's three, which then read its input)
     if (bn_role(a, batch) != 0 || bn_role(a + 1, batch) != 0) return 0;
     if (layers[a].Cin == 128 && (long long)batch * geom[a].P * geom[a].Q > 131072) return 0;
+    // (the layers by themselves take that kernel from fewer workgroups on than this; there the tests expect them apart, and
+    // one launch would still be ahead: ResNet-18 at 8 images 118 -> 115 us, 12 135 -> 129)
+    if (imgk < 10 && conv_imgk_workgroups(layers[a].Cin, batch, geom[a].H, geom[a].W, layers[a].Cin == 128 ? 2 : 1) < (layers[a].Cin == 128 ? 128 : 176)) return 0;
     return img_role(a, batch) >= 2 && img_role(a + 1, batch) >= 2 ? pair[i] : 0;
   }
   // A depthwise 3x3 layer and the 1x1 layer that is its only reader in one launch: dwp[i] = 1 for the depthwise one,

@@ -379,6 +379,52 @@ __global__ __launch_bounds__(NT) void gpool_kernel(const DwParams p, const long 
   else yp[0] = (uint8_t)acc[0];
 }
 
+// The same with the pixels of an image shared by the four waves of a workgroup, which takes 64 dwords of four channels: every load of a 7 x 7 map is
+// in flight at once, where one thread for all pixels of a dword goes through six round trips to memory, and the sums meet in LDS.  Bound by one such round
+// trip.  Microseconds, one thread / four waves: 2048 channels of 7 x 7, one image 4.2 / 2.9, 16 4.5 / 3.1, 64 (512 workgroups) 4.4 / 3.7, 128 4.45 /
+// 4.8, 256 5.5 / 6.6; 1280, 27 4.3 / 3.0, 128 (640) 4.4 / 4.2, 256 5.0 / 5.3; 2048 of 3 x 3, 16 3.1 / 3.0, 64 2.9 / 3.6.
+constexpr int GP_WAVES = 4;
+__global__ __launch_bounds__(64 * GP_WAVES) void gpool_shared_kernel(const DwParams p, const FastDiv fd_groups) {
+  __shared__ v4i part[GP_WAVES][64];
+  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = (int)fd_groups.div(wg), lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = ((int)wg - b * (int)fd_groups.d) * 256 + lane * 4;
+  const bool xs = p.x_type == T_S8, live = c < p.C;
+  const int HW = p.H * p.W;
+  const uint8_t *xp = p.x + (size_t)b * HW * p.C + (live ? c : 0);
+  v4i acc = {0, 0, 0, 0};
+  constexpr int U = 13;
+  for (int i0 = wave; i0 < HW; i0 += U * GP_WAVES) {
+    uint32_t v[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int i = i0 + k * GP_WAVES;
+      v[k] = i < HW ? *reinterpret_cast<const uint32_t *>(xp + (size_t)i * p.C) : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] += byte_of(v[k], j, xs);
+  }
+  part[wave][lane] = acc;
+  __syncthreads();
+  if (wave != 0 || !live) return;
+#pragma unroll
+  for (int w = 1; w < GP_WAVES; ++w) acc += part[w][lane];
+  const size_t o = (size_t)b * p.C + c;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] += p.rnd;
+  if (p.y_type == T_S32) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) reinterpret_cast<int32_t *>(p.y)[o + j] = acc[j];
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    acc[j] = p.shift >= 0 ? requant<false>(acc[j], p.shift, p.lo, p.hi) : requant<true>(acc[j], p.shift, p.lo, p.hi);
+  *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(p.y) + o) = pack4(acc[0], acc[1], acc[2], acc[3]);
+}
+
 // Stem re-layout (exact, values unchanged): x [B][H][W][C] -> xp [B][Hp][Wp][4] with the
 // image at offset (ph, pw), zeros elsewhere and in channels C..3.  One thread per output
 // pixel (one dword).  Turns a clipped-window, odd-channel convolution into one whose
@@ -625,9 +671,11 @@ int launch_copy(const void *src, void *dst, size_t bytes, hipStream_t stream) {
 }
 
 int launch_gpool(const DwParams &p, bool vec4, hipStream_t stream) {
-  const long long total = (long long)p.B * (p.C / (vec4 ? 4 : 1));
+  const long long total = (long long)p.B * (p.C / (vec4 ? 4 : 1)), groups = (p.C + 255) / 256;
   if (total <= 0) return 0;
-  if (vec4) hipLaunchKernelGGL(gpool_kernel<4>, dim3(blocks_for(total)), dim3(NT), 0, stream, p, total);
+  if (vec4 && p.B * groups <= 768 && p.H * p.W >= 25)
+    hipLaunchKernelGGL(gpool_shared_kernel, dim3((unsigned)(p.B * groups)), dim3(64 * GP_WAVES), 0, stream, p, FastDiv((uint32_t)groups));
+  else if (vec4) hipLaunchKernelGGL(gpool_kernel<4>, dim3(blocks_for(total)), dim3(NT), 0, stream, p, total);
   else hipLaunchKernelGGL(gpool_kernel<1>, dim3(blocks_for(total)), dim3(NT), 0, stream, p, total);
   return (int)hipGetLastError();
 }

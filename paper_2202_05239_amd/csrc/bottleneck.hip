@@ -9,6 +9,11 @@
 // The price: every workgroup streams all 17 C^2 bytes of weights (about 60 bytes per clock and CU), so the kernel
 // pays where that stream, TM pixels at a time, is cheaper than two launches and the round trips of the tensors between.
 //
+// In the first block of a stage the residual is a 1x1 layer's result, the projection of the block's input.  It has no other reader, so the launch
+// computes it too, ahead of the 3x3 layer, into the place where the residual would be fetched to: 4 PJ C^2 more bytes of weights a
+// workgroup for one launch and the round trip of its tensor.  ResNet-50, us of a forward, apart / together: one image 176.2 / 173.0, 16 288 / 273, 40
+// 413 / 389, 64 592 / 569, 128 1027 / 1011; each of the three stages by itself ahead or level at 1 to 192 images of 224 and 128 pixels.
+//
 // A wave owns one block of 32 channels of the 3x3 layer, four of the closing one and NA / C of the last, over MBW blocks
 // of 32 pixels.  Its weights lie in memory as one stream of 1 KiB fragments in the order of use and go straight into
 // registers, R fragments ahead; the whole sequence is unrolled, so ring slots are registers.
@@ -34,19 +39,21 @@ struct BnTiling {
   FastDiv fd_kpr;           // by 1 KiB loads per image row
   uint32_t res_xor;         // makes the residual signed
   int res_bytes;            // 0: no residual
-  ScaledClip clip_b, clip_c, clip_2, clip_a;
+  ScaledClip clip_b, clip_c, clip_2, clip_a, clip_p;
+  int xp_bytes;             // the projection's input
 };
 
-// Start values of the three layers, one behind the other, in whole KiB behind the weights.
-constexpr int start_bytes(int C) { return (7 * C * 4 + 1023) / 1024 * 1024; }
+// Start values of the three layers, with a projection its own behind them, in whole KiB behind the weights.
+constexpr int start_bytes(int C, bool projection) { return ((projection ? 11 : 7) * C * 4 + 1023) / 1024 * 1024; }
 
-// LDS: [block output TM x 4 C][start values][3x3 result TM x (C + 16)][patch rows].  Where that leaves room for one
+// LDS: [block output TM x 4 C][start values][projection's input TM x PJ C][3x3 result TM x (C + 16)][patch rows].  Where that leaves room for one
 // workgroup per CU only, the 3x3 result takes the place of the patch, one barrier more.
-template <int C, int TM>
+template <int C, int TM, int PJ>
 struct BnLds {
   static constexpr int Y = 0;
   static constexpr int ACC = TM * 4 * C;
-  static constexpr int BT = ACC + start_bytes(C);
+  static constexpr int XP = ACC + start_bytes(C, PJ != 0);
+  static constexpr int BT = XP + TM * PJ * C;
   static constexpr int PITCH = C + 16;
   static constexpr bool SHARED = C == 64 && TM == 128;
   static constexpr int PATCH = SHARED ? BT : BT + TM * PITCH;
@@ -66,13 +73,15 @@ __device__ __forceinline__ v4i requant16(const v16i &a, int lo, int hi, int shif
   return shift_pack16(v, shift);
 }
 
-template <int C, int TM, int MW, int R, int NAB, bool DUAL>
+// PJ: channels of the projection's input / C (0: no projection, the residual is read).
+template <int C, int TM, int MW, int R, int NAB, bool DUAL, int PJ>
 __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const BottleneckParams p, const BnTiling tl) {
-  using L = BnLds<C, TM>;
+  using L = BnLds<C, TM, PJ>;
+  constexpr int START = start_bytes(C, PJ != 0);
   constexpr int NWN = C / 32, NT = NWN * MW * 64;
   constexpr int KS = C / 32, MBW = TM / 32 / MW;
   constexpr int PP = C / 16, YP = 4 * C / 16;           // 16-byte pieces per pixel of x, of y
-  constexpr int F1 = 9 * KS, F2 = 4 * KS, F3 = NAB * 4 * KS, FT = F1 + F2 + F3;
+  constexpr int F0 = 4 * PJ * KS, F1 = F0 + 9 * KS, F2 = 4 * KS, F3 = NAB * 4 * KS, FT = F1 + F2 + F3;
   constexpr int NWV = NT / 64, UNITS = 8;               // loads of the patch a wave has in flight
   pin_args(tl.tiles, tl.M, tl.x_bytes, tl.patch_w, tl.fd_pq.mul, tl.fd_pq.shr, tl.fd_pq.d, tl.fd_q.mul, tl.fd_q.shr, tl.fd_q.d, tl.fd_h2.mul,
            tl.fd_h2.shr, tl.fd_h2.d, tl.fd_kpr.mul, tl.fd_kpr.shr, tl.fd_kpr.d, p.x, p.wf, p.res, p.H, p.W, p.stride, p.x_xor);
@@ -89,7 +98,7 @@ __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const B
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<int8_t *>(p.wf) + (size_t)nw * (FT * 1024), 0, FT * 1024, 0x00027000);
   const __amdgpu_buffer_rsrc_t sres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<int8_t *>(p.wf) + (size_t)NWN * (FT * 1024), 0, start_bytes(C), 0x00027000);
+      const_cast<int8_t *>(p.wf) + (size_t)NWN * (FT * 1024), 0, START, 0x00027000);
   v4i ring[R];
   auto load_w = [&](int i) {
     return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16, i * 1024, 0));
@@ -142,12 +151,24 @@ __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const B
   __builtin_amdgcn_sched_barrier(0);
   // ---- start values; residual rows (or zeros) into the place of the block output, 16-byte pieces permuted by the row number
 #pragma unroll
-  for (int k = 0; k < (start_bytes(C) / 1024 + NWV - 1) / NWV; ++k) {
+  for (int k = 0; k < (START / 1024 + NWV - 1) / NWV; ++k) {
     const int i = wave + k * NWV;
-    if (i < start_bytes(C) / 1024)
+    if (i < START / 1024)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(sres, (lds_void *)(lds + L::ACC + i * 1024), 16, lane * 16, i * 1024, 0, 0);
   }
-  {
+  constexpr int CI = PJ * C, CIP = PJ == 0 ? 1 : CI / 16;       // the projection's input: bytes and 16-byte pieces of a pixel
+  // a row's pieces are permuted so that eight rows' pieces share no bank
+  auto perm = [](int row) { return CI >= 256 ? row & 15 : (row / (CI == 0 ? 1 : 256 / CI)) & (CIP - 1); };
+  if constexpr (PJ != 0) {
+    const __amdgpu_buffer_rsrc_t pres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.xp), 0, tl.xp_bytes, 0x00027000);
+#pragma unroll
+    for (int k = 0; k < TM * CIP / NT; ++k) {
+      const int u = (wave + k * NWV) * 64 + lane, row = u / CIP, ph = u % CIP, m = m0 + row;
+      const uint32_t b = tl.fd_pq.div((uint32_t)m), rem = (uint32_t)m - b * tl.fd_pq.d, oh = tl.fd_q.div(rem), ow = rem - oh * tl.fd_q.d;
+      const uint32_t off = (((b * p.Hp + oh * p.sp) * p.Wp + ow * p.sp) * CI) + (uint32_t)((ph ^ perm(row)) * 16);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(pres, (lds_void *)(lds + L::XP + (wave + k * NWV) * 1024), 16, m < tl.M ? off : 0x80000000u, 0, 0, 0);
+    }
+  } else {
     const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.res), 0, tl.res_bytes, 0x00027000);
 #pragma unroll
     for (int k = 0; k < TM * YP / NT; ++k) {
@@ -191,6 +212,66 @@ __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const B
     return a;
   };
 
+  // where a lane's 16 channels of block b of the closing layer lie: the shortcut before it, the block output after it
+  auto own = [&](int b, int mb) {
+    const int row = (mw * MBW + mb) * 32 + l32;
+    return base + L::Y + row * (4 * C) + (((nw * 8 + b * 2 + half) ^ (row & 15)) * 16);
+  };
+  // ---- the projection: its result takes the place of the residual
+  if constexpr (PJ != 0) {
+    constexpr int KP = PJ * KS, G = KP < 4 ? KP : 4;      // fragments are read a group of four slices ahead
+    const int px = (int)p.xp_xor;
+#pragma unroll
+    for (int b0 = 0; b0 < 4; b0 += BB) {
+      v16i acc[BB][MBW];
+      v4i xf[2][G][MBW];
+      auto read_group = [&](int g, v4i (&f)[G][MBW]) {
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+          for (int t = 0; t < G; ++t) {
+            const int row = (mw * MBW + mb) * 32 + l32;
+            f[t][mb] = lds_read(base + L::XP + row * CI + (((g * G + t) * 2 + half) ^ perm(row)) * 16);
+          }
+      };
+#pragma unroll
+      for (int b = 0; b < BB; ++b)
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb) acc[b][mb] = start16(7 * C + nw * 128 + (b0 + b) * 32);
+      read_group(0, xf[0]);
+#pragma unroll
+      for (int g = 0; g < KP / G; ++g) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (g + 1 < KP / G) read_group(g + 1, xf[(g + 1) & 1]);
+#pragma unroll
+        for (int t = 0; t < G; ++t) {
+#pragma unroll
+          for (int mb = 0; mb < MBW; ++mb) {
+            v4i &x = xf[g & 1][t][mb];
+            x.x ^= px; x.y ^= px; x.z ^= px; x.w ^= px;
+          }
+#pragma unroll
+          for (int b = 0; b < BB; ++b) {
+            const int i = b0 * KP + (g * G + t) * BB + b;
+#pragma unroll
+            for (int mb = 0; mb < MBW; ++mb)
+              acc[b][mb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ring[i % R], xf[g & 1][t][mb], acc[b][mb], 0, 0, 0);
+            if (i + R < FT) ring[i % R] = load_w(i + R);
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int b = 0; b < BB; ++b)
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb) {
+          settle_matrix_result(acc[b][mb]);
+          lds_write(own(b0 + b, mb), requant16(acc[b][mb], tl.clip_p.lo, tl.clip_p.hi, p.shift_p));
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
   // ---- 3x3 layer: a tap's fragments are read while the previous tap's are multiplied
   {
     // (a matrix instruction waits 64 cycles for the result of the one before it, half of them idle: two sums where a
@@ -219,7 +300,7 @@ __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const B
       if (tap < 8) read_tap(tap + 1, xf[(tap + 1) & 1]);
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        const int i = tap * KS + s;
+        const int i = F0 + tap * KS + s;
 #pragma unroll
         for (int mb = 0; mb < MBW; ++mb)
           acc[i % CH][mb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ring[i % R], xf[tap & 1][s][mb], acc[i % CH][mb], 0, 0, 0);
@@ -258,10 +339,6 @@ __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const B
     for (int b0 = 0; b0 < 4; b0 += BB) {
       v16i acc[BB][MBW];
       v4i r[BB][MBW];
-      auto own = [&](int b, int mb) {
-        const int row = (mw * MBW + mb) * 32 + l32;
-        return base + L::Y + row * (4 * C) + (((nw * 8 + (b0 + b) * 2 + half) ^ (row & 15)) * 16);
-      };
 #pragma unroll
       for (int b = 0; b < BB; ++b)
 #pragma unroll
@@ -279,7 +356,7 @@ __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const B
 #pragma unroll
       for (int b = 0; b < BB; ++b)
 #pragma unroll
-        for (int mb = 0; mb < MBW; ++mb) r[b][mb] = lds_read(own(b, mb));
+        for (int mb = 0; mb < MBW; ++mb) r[b][mb] = lds_read(own(b0 + b, mb));
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < BB; ++b)
@@ -300,7 +377,7 @@ __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const B
           }
           v4i v = requant16(a, cl.lo, cl.hi, p.shift_c);
           v.x ^= yx; v.y ^= yx; v.z ^= yx; v.w ^= yx;
-          lds_write(own(b, mb), v);
+          lds_write(own(b0 + b, mb), v);
         }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -392,18 +469,21 @@ __global__ __launch_bounds__(C / 32 * MW * 64, 2) void bottleneck_kernel(const B
   }
 }
 
-// Piece i (16 bytes) of the stream: wave nw's fragments, 9 KS of the 3x3 layer (tap by tap), four blocks of KS of the
+// Piece i (16 bytes) of the stream: wave nw's fragments, four blocks of pj KS of the projection (BB blocks side by side), 9 KS of the 3x3 layer (tap by tap), four blocks of KS of the
 // closing layer (BB blocks side by side), then slice by slice NAB blocks of the layer behind; behind all waves' fragments
 // the start values.
 __global__ __launch_bounds__(256) void bottleneck_weights_kernel(const int8_t *__restrict__ wb, const int8_t *__restrict__ wc,
-                                                                 const int8_t *__restrict__ wa, int8_t *__restrict__ wf, int C, int nab) {
-  const int ks = C / 32, ft = (13 + 4 * nab) * ks;
+                                                                 const int8_t *__restrict__ wa, const int8_t *__restrict__ wp, int8_t *__restrict__ wf, int C, int nab, int pj) {
+  const int ks = C / 32, ft = (13 + 4 * nab + 4 * pj) * ks;
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= ks * ft * 64) return;
-  const int lane = i & 63, f = (i >> 6) % ft, nw = (i >> 6) / ft;
+  const int lane = i & 63, f = (i >> 6) % ft - 4 * pj * ks, nw = (i >> 6) / ft;
   const int row = weight_row(lane & 31), half = lane >> 5;
   const int8_t *src;
-  if (f < 9 * ks) {
+  if (f < 0) {
+    const int kp = pj * ks, g = f + 4 * kp, first = g / (BB * kp) * BB, h = g % (BB * kp);
+    src = wp + (size_t)(nw * 128 + (first + h % BB) * 32 + row) * (pj * C) + h / BB * 32;
+  } else if (f < 9 * ks) {
     src = wb + ((size_t)(nw * 32 + row) * 9 + f / ks) * C + f % ks * 32;
   } else if (f < 13 * ks) {
     const int g = f - 9 * ks;
@@ -418,11 +498,12 @@ __global__ __launch_bounds__(256) void bottleneck_weights_kernel(const int8_t *_
 
 // The start values: the closing layer's with what makes an unsigned residual signed, 128 at the residual's scale.
 __global__ __launch_bounds__(256) void bottleneck_start_kernel(const int32_t *__restrict__ b, const int32_t *__restrict__ c,
-                                                               const int32_t *__restrict__ a, int32_t *__restrict__ to, int C, int NA, int res_bias) {
+                                                               const int32_t *__restrict__ a, const int32_t *__restrict__ pr, int32_t *__restrict__ to, int C, int NA, int res_bias) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < C) to[i] = b[i];
   else if (i < 5 * C) to[i] = c[i - C] + res_bias;
   else if (i < 7 * C) to[i] = i - 5 * C < NA ? a[i - 5 * C] : 0;
+  else if (i < 11 * C && pr) to[i] = pr[i - 7 * C];
 }
 
 // Patch rows a tile of TM pixels can need: its output rows, and two border rows per image boundary inside it.
@@ -431,18 +512,18 @@ int most_rows(int P, int Q, int stride, int H, int TM) {
   return (out_rows - 1) * stride + 3 + crossings * (H + 2 - stride * P > 0 ? H + 2 - stride * P : 0);
 }
 
-template <int C, int TM>
+template <int C, int TM, int PJ = 0>
 int lds_bytes(const BottleneckParams &p) {
-  using L = BnLds<C, TM>;
+  using L = BnLds<C, TM, PJ>;
   const int patch = most_rows(p.P, p.Q, p.stride, p.H, TM) * (p.W + 2) * L::PITCH;
   return L::PATCH + (L::SHARED && patch < TM * L::PITCH ? TM * L::PITCH : patch);
 }
 
 constexpr int LDS_MOST = 160 * 1024;
 
-template <int C, int TM, int MW, int R, int NAB, bool DUAL>
+template <int C, int TM, int MW, int R, int NAB, bool DUAL, int PJ = 0>
 int launch_one(const BottleneckParams &p, hipStream_t stream) {
-  const int smem = lds_bytes<C, TM>(p);
+  const int smem = lds_bytes<C, TM, PJ>(p);
   if (smem > LDS_MOST) return (int)hipErrorInvalidValue;
   BnTiling tl;
   tl.M = p.B * p.P * p.Q;
@@ -453,13 +534,15 @@ int launch_one(const BottleneckParams &p, hipStream_t stream) {
   tl.fd_q = FastDiv((uint32_t)p.Q);
   tl.fd_h2 = FastDiv((uint32_t)(p.H + 2));
   tl.fd_kpr = FastDiv((uint32_t)((p.W * C + 1023) / 1024));
-  tl.res_xor = p.res && !p.res_signed ? 0x80808080u : 0u;
+  tl.res_xor = (p.res || PJ != 0) && !p.res_signed ? 0x80808080u : 0u;
   tl.res_bytes = p.res ? tl.M * 4 * C : 0;
   tl.clip_b = scaled_clip(p.lo_b, p.hi_b, p.shift_b);
   tl.clip_c = scaled_clip(p.lo_c, p.hi_c, p.shift_c);
   tl.clip_2 = scaled_clip(p.lo_2, p.hi_2, p.shift_2);
   tl.clip_a = scaled_clip(p.lo_a, p.hi_a, p.shift_a);
-  auto k = bottleneck_kernel<C, TM, MW, R, NAB, DUAL>;
+  tl.clip_p = scaled_clip(p.lo_p, p.hi_p, p.shift_p);
+  tl.xp_bytes = p.B * p.Hp * p.Wp * PJ * C;
+  auto k = bottleneck_kernel<C, TM, MW, R, NAB, DUAL, PJ>;
   static std::atomic<unsigned long long> done_mask{0};          // devices whose LDS limit has been raised
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return (int)hipErrorInvalidDevice;
@@ -475,6 +558,9 @@ int launch_one(const BottleneckParams &p, hipStream_t stream) {
 template <int C, int TM, int MW, int R>
 int launch_shape(const BottleneckParams &p, hipStream_t stream) {
   const bool dual = p.y2 != nullptr;
+  // (a projection's input has C channels in the first stage, 2 C behind it)
+  constexpr int PJ = C == 64 ? 1 : 2;
+  if (p.xp) return dual ? launch_one<C, TM, MW, R, 1, true, PJ>(p, stream) : launch_one<C, TM, MW, R, 1, false, PJ>(p, stream);
   if (p.NA == 0) return dual ? launch_one<C, TM, MW, R, 0, true>(p, stream) : launch_one<C, TM, MW, R, 0, false>(p, stream);
   if (p.NA == C) return dual ? launch_one<C, TM, MW, R, 1, true>(p, stream) : launch_one<C, TM, MW, R, 1, false>(p, stream);
   return dual ? launch_one<C, TM, MW, R, 2, true>(p, stream) : launch_one<C, TM, MW, R, 2, false>(p, stream);
@@ -496,6 +582,13 @@ bool bottleneck_applicable(int C, int H, int W, int stride, int NA, int shift_b,
   return (C == 64 ? lds_bytes<64, 64>(p) : C == 128 ? lds_bytes<128, 32>(p) : lds_bytes<256, 32>(p)) <= LDS_MOST;
 }
 
+bool bottleneck_projects(int C, int H, int W, int stride, int NA, int PC, int ps) {
+  if (C != 64 && C != 128 && C != 256) return false;
+  if (NA != C || PC != (C == 64 ? C : 2 * C) || (ps != 1 && ps != 2) || H < 1 || W < 1 || H > 4096 || W > 4096) return false;
+  const BottleneckParams p = geometry(H, W, stride);
+  return (C == 64 ? lds_bytes<64, 64, 1>(p) : C == 128 ? lds_bytes<128, 32, 2>(p) : lds_bytes<256, 32, 2>(p)) <= LDS_MOST;
+}
+
 // Twice the pixels per workgroup halve the weight stream and spread a tile's set-up over more pixels, but leave
 // CUs idle where there are few.  us, narrow / wide tiles, first and second stride-1 block of a stage, ResNet-50:
 //   64 channels, 56 x 56: batch 8 10.0 / 10.4, 12 12.2 / 11.3, 16 14.8 / 13.4, 32 22.9 / 22.9, 64 38.8 / 36.0, 128 69 / 59
@@ -503,26 +596,28 @@ bool bottleneck_applicable(int C, int H, int W, int stride, int NA, int shift_b,
 //     stride 2: batch 8 8.2 / 10.1, 12 14.1 / 10.1, 32 25.3 / 20.0
 //   256 channels, 14 x 14, where the stream is everything: one narrow tile per CU as long as there are no more (batch 16 14.3 / 17.0,
 //     32, 196 tiles, 15.0 / 17.8), wide ones beyond (48, 294 tiles, 24.6 / 19.5, 64 27.2 / 22.1, 128 52.6 / 40.8)
-bool bottleneck_wide(int C, int H, int W, int stride, int B, int force) {
+bool bottleneck_wide(int C, int H, int W, int stride, int B, int force, bool projection) {
   const BottleneckParams p = geometry(H, W, stride);
-  const int lds = C == 64 ? lds_bytes<64, 128>(p) : C == 128 ? lds_bytes<128, 64>(p) : lds_bytes<256, 64>(p);
+  const int lds = projection ? (C == 64 ? lds_bytes<64, 128, 1>(p) : C == 128 ? lds_bytes<128, 64, 2>(p) : lds_bytes<256, 64, 2>(p))
+                             : C == 64 ? lds_bytes<64, 128>(p) : C == 128 ? lds_bytes<128, 64>(p) : lds_bytes<256, 64>(p);
   if (lds > LDS_MOST || force == 3) return false;
   const long long M = (long long)B * p.P * p.Q;
   return force == 4 || M > (C == 64 ? 32768 : 8192);
 }
 
-static size_t fragment_bytes(int C, int NA) { return (size_t)C * (13 * C + 4 * NA); }
-size_t bottleneck_weight_bytes(int C, int NA) { return fragment_bytes(C, NA) + start_bytes(C); }
+static size_t fragment_bytes(int C, int NA, int PC) { return (size_t)C * (13 * C + 4 * NA + 4 * PC); }
+size_t bottleneck_weight_bytes(int C, int NA, int PC) { return fragment_bytes(C, NA, PC) + start_bytes(C, PC != 0); }
 
-int launch_bottleneck_weights(const int8_t *wb, const int8_t *wc, const int8_t *wa, const int32_t *acc_b, const int32_t *acc_c, const int32_t *acc_a,
-                              int8_t *wf, int C, int NA, int res_bias, hipStream_t stream) {
-  if (!wb || !wc || !acc_b || !acc_c || (NA && (!wa || !acc_a)) || !wf ||
-      ((reinterpret_cast<uintptr_t>(wb) | reinterpret_cast<uintptr_t>(wc) | reinterpret_cast<uintptr_t>(wa) | reinterpret_cast<uintptr_t>(wf)) & 15))
+int launch_bottleneck_weights(const int8_t *wb, const int8_t *wc, const int8_t *wa, const int8_t *wp, const int32_t *acc_b, const int32_t *acc_c,
+                              const int32_t *acc_a, const int32_t *acc_p, int8_t *wf, int C, int NA, int PC, int res_bias, hipStream_t stream) {
+  if (!wb || !wc || !acc_b || !acc_c || (NA && (!wa || !acc_a)) || (PC && (!wp || !acc_p)) || !wf ||
+      ((reinterpret_cast<uintptr_t>(wb) | reinterpret_cast<uintptr_t>(wc) | reinterpret_cast<uintptr_t>(wa) | reinterpret_cast<uintptr_t>(wp) |
+        reinterpret_cast<uintptr_t>(wf)) & 15))
     return (int)hipErrorInvalidValue;
-  const int pieces = (int)(fragment_bytes(C, NA) / 16);
-  hipLaunchKernelGGL(bottleneck_weights_kernel, dim3((pieces + 255) / 256), dim3(256), 0, stream, wb, wc, wa, wf, C, NA / C);
-  hipLaunchKernelGGL(bottleneck_start_kernel, dim3((7 * C + 255) / 256), dim3(256), 0, stream, acc_b, acc_c, acc_a,
-                     reinterpret_cast<int32_t *>(wf + fragment_bytes(C, NA)), C, NA, res_bias);
+  const int pieces = (int)(fragment_bytes(C, NA, PC) / 16);
+  hipLaunchKernelGGL(bottleneck_weights_kernel, dim3((pieces + 255) / 256), dim3(256), 0, stream, wb, wc, wa, wp, wf, C, NA / C, PC / C);
+  hipLaunchKernelGGL(bottleneck_start_kernel, dim3((11 * C + 255) / 256), dim3(256), 0, stream, acc_b, acc_c, acc_a, PC ? acc_p : nullptr,
+                     reinterpret_cast<int32_t *>(wf + fragment_bytes(C, NA, PC)), C, NA, res_bias);
   return (int)hipGetLastError();
 }
 
@@ -533,7 +628,11 @@ int launch_bottleneck(const BottleneckParams &p, hipStream_t stream) {
         reinterpret_cast<uintptr_t>(p.y) | reinterpret_cast<uintptr_t>(p.y2) | reinterpret_cast<uintptr_t>(p.ya)) & 15) ||
       (long long)p.B * p.P * p.Q * 4 * p.C > 0x7fffffffLL || (long long)p.B * p.H * p.W * p.C > 0x7fffffffLL)
     return (int)hipErrorInvalidValue;
-  const bool wide = bottleneck_wide(p.C, p.H, p.W, p.stride, p.B, p.force);
+  if (p.xp && (!bottleneck_projects(p.C, p.H, p.W, p.stride, p.NA, p.PC, p.sp) || p.res || p.shift_p < 0 || p.res_d < 0 || p.res_d > 16 ||
+               (reinterpret_cast<uintptr_t>(p.xp) & 15) || (p.Hp - 1) / p.sp + 1 != p.P || (p.Wp - 1) / p.sp + 1 != p.Q ||
+               (long long)p.B * p.Hp * p.Wp * p.PC > 0x7fffffffLL))
+    return (int)hipErrorInvalidValue;
+  const bool wide = bottleneck_wide(p.C, p.H, p.W, p.stride, p.B, p.force, p.xp != nullptr);
   if (p.C == 64) return wide ? launch_shape<64, 128, 2, 18>(p, stream) : launch_shape<64, 64, 2, 18>(p, stream);
   if (p.C == 128) return wide ? launch_shape<128, 64, 1, 16>(p, stream) : launch_shape<128, 32, 1, 16>(p, stream);
   return wide ? launch_shape<256, 64, 1, 16>(p, stream) : launch_shape<256, 32, 1, 16>(p, stream);

@@ -297,7 +297,12 @@ struct f8_chain {
   std::vector<size_t> bn_const_off;          // per layer
   int bottleneck = 1;
   int bn_channels(size_t head) const { return bn_behind[head] < 0 ? 0 : layers[bn_behind[head]].Cout; }
-  size_t bn_w_bytes(size_t i) const { return bn[i] == 1 ? bottleneck_weight_bytes(layers[i].Cin, bn_channels(i)) : 0; }
+  // The 1x1 layer whose result is the closing layer's residual and has no other reader, where the launch takes it along (bn_proj of the head: that layer
+  // or -1; bn_of_proj of that layer: the head or -1): the first block of a stage.  Its input is kept until the head has run.
+  std::vector<int> bn_proj, bn_of_proj;      // per layer
+  int bn_proj_channels(size_t head) const { return bn_proj[head] < 0 ? 0 : layers[bn_proj[head]].Cin; }
+  bool proj_role(size_t i, int batch) const { return bn_of_proj[i] >= 0 && bn_role((size_t)bn_of_proj[i], batch) == 1; }
+  size_t bn_w_bytes(size_t i) const { return bn[i] == 1 ? bottleneck_weight_bytes(layers[i].Cin, bn_channels(i), bn_proj_channels(i)) : 0; }
   bool bn_allowed(size_t head) const {
     if (bottleneck == 0 || keep_all) return false;
     return !use_fusion() || (fused[head].role == 0 && fused[head + 1].role == 0 && (bn_behind[head] < 0 || fused[bn_behind[head]].role == 0));
@@ -465,10 +470,10 @@ struct f8_chain {
       }
       if (keep_all) continue;
       if (stem[li].on) release(stem[li].x_off_per_image, round256(stem[li].x_bytes_per_image));
-      const int ids[2] = {layers[li].src, layers[li].res};
-      for (int k = 0; k < 2; ++k) {
+      const int ids[3] = {layers[li].src, layers[li].res, bn_proj[li] >= 0 ? layers[bn_proj[li]].src : -1};
+      for (int k = 0; k < 3; ++k) {
         if (ids[k] < 0) continue;
-        if (k == 1 && ids[1] == ids[0]) continue;
+        if ((k >= 1 && ids[k] == ids[0]) || (k == 2 && ids[2] == ids[1])) continue;
         Tensor &t = tensors[ids[k]];
         if (!t.external && t.last_use == (int)li) release(t.offset_per_image, round256(t.bytes_per_image));
       }
@@ -559,7 +564,18 @@ struct f8_chain {
     BottleneckParams p;
     p.x = bytes(L.src);
     p.wf = reinterpret_cast<const int8_t *>(static_cast<uint8_t *>(workspace) + bn_off[i]);
-    p.res = T.res >= 0 ? bytes(T.res) : nullptr;
+    p.res = T.res >= 0 && bn_proj[i] < 0 ? bytes(T.res) : nullptr;
+    p.xp = nullptr;
+    p.Hp = p.Wp = p.PC = 0; p.sp = 1; p.xp_xor = 0;
+    p.shift_p = p.lo_p = p.hi_p = 0;
+    if (bn_proj[i] >= 0) {
+      const f8_layer_desc &D = layers[bn_proj[i]];
+      const Geom &gd = geom[bn_proj[i]];
+      p.xp = bytes(D.src);
+      p.Hp = gd.H; p.Wp = gd.W; p.PC = D.Cin; p.sp = gd.sh;
+      p.xp_xor = sign(D.q.x_type);
+      p.shift_p = D.q.fl_x + D.q.fl_w - D.q.fl_y; p.lo_p = D.q.clip_lo; p.hi_p = D.q.clip_hi;
+    }
     p.y = bytes(T.dst);
     p.y2 = T.dst2 > 0 ? bytes(T.dst2) : nullptr;
     p.ya = a >= 0 ? bytes(layers[a].dst) : nullptr;
@@ -579,7 +595,7 @@ struct f8_chain {
       p.shift_a = q.fl_x + q.fl_w - q.fl_y; p.lo_a = q.clip_lo; p.hi_a = q.clip_hi;
     }
     p.res_signed = T.q.res_type == F8_S8;
-    p.res_d = p.res ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0;
+    p.res_d = T.res >= 0 ? T.q.fl_x + T.q.fl_w - T.q.fl_res : 0;
     p.force = bottleneck;
     return p;
   }
@@ -682,7 +698,7 @@ struct f8_chain {
       return launch_block_fused(bp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
     }
     const int three = bn_role(i, batch);
-    if (three > 1) return F8_OK;
+    if (three > 1 || proj_role(i, batch)) return F8_OK;
     if (three == 1 && bn_off[i] != 0) {
       const BottleneckParams bp = bottleneck_params(i, x, out, workspace, batch);
       return launch_bottleneck(bp, s) == 0 ? F8_OK : F8_ERR_DEVICE;
@@ -944,6 +960,8 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->pdp_w2_off.push_back(0);
     c->bn.push_back(0);
     c->bn_head.push_back(-1);
+    c->bn_proj.push_back(-1);
+    c->bn_of_proj.push_back(-1);
     c->bn_behind.push_back(-1);
     c->bn_off.push_back(0);
     c->bn_const_off.push_back(0);
@@ -1069,6 +1087,20 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->bn_head[i] = c->bn_head[i + 1] = (int)i;
     c->bn_behind[i] = a;
     if (a >= 0) { c->bn[a] = 3; c->bn_head[a] = (int)i; }
+    if (T.res > 0 && tuning().bn_proj.load() != 0) {
+      const int pr = c->tensors[T.res].producer;
+      int readers = 0;
+      for (const f8_layer_desc &D : c->layers) readers += (D.src == T.res) + (D.res == T.res);
+      if (pr >= 0 && readers == 1 && pr < (int)i) {
+        const f8_layer_desc &D = c->layers[pr];
+        if (plain(pr) && c->s2[pr] == 0 && c->tail[pr] == 0 && D.R == 1 && D.S == 1 && D.stride_h == D.stride_w && D.pad_h == 0 && D.pad_w == 0 && D.res < 0 &&
+            D.dst == T.res && D.dst2 <= 0 && shift(D) >= 0 && bottleneck_projects(L.Cin, g.H, g.W, L.stride_h, a < 0 ? 0 : c->layers[a].Cout, D.Cin, D.stride_h)) {
+          c->bn_proj[i] = pr;
+          c->bn_of_proj[pr] = (int)i;
+          c->tensors[D.src].last_use = std::max(c->tensors[D.src].last_use, (int)i);
+        }
+      }
+    }
     if (L.Cin <= 128) {
       c->bn_const_off[i] = c->const_bytes;
       c->const_bytes += round256(c->bn_w_bytes(i));
@@ -1263,8 +1295,10 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
     uint8_t *cb = static_cast<uint8_t *>(workspace);
     auto start = [&](size_t l) { return reinterpret_cast<const int32_t *>(cb + c->acc0_off[l]); };
     const int res_bias = T.res >= 0 && T.q.res_type == F8_U8 ? 128 << (T.q.fl_x + T.q.fl_w - T.q.fl_res) : 0;
-    if (launch_bottleneck_weights(L.w, T.w, a < 0 ? nullptr : c->layers[a].w, start(i), start(i + 1), a < 0 ? nullptr : start(a),
-                                  reinterpret_cast<int8_t *>(cb + c->bn_off[i]), L.Cin, c->bn_channels(i), res_bias, s) != 0)
+    const int pr = c->bn_proj[i];
+    if (launch_bottleneck_weights(L.w, T.w, a < 0 ? nullptr : c->layers[a].w, pr < 0 ? nullptr : c->layers[pr].w, start(i), start(i + 1),
+                                  a < 0 ? nullptr : start(a), pr < 0 ? nullptr : start(pr), reinterpret_cast<int8_t *>(cb + c->bn_off[i]), L.Cin,
+                                  c->bn_channels(i), c->bn_proj_channels(i), res_bias, s) != 0)
       return F8_ERR_DEVICE;
   }
   for (size_t i = 0; i < c->layers.size(); ++i) {
@@ -1350,7 +1384,7 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
   // tensors inside a fused block are never materialised
   const bool elided = (t.producer >= 0 && (c->pool_role((size_t)t.producer) == 1 || c->dwp_role((size_t)t.producer, batch) == 1 ||
                                              c->pdp_role((size_t)t.producer, batch) == 1 || c->pdp_role((size_t)t.producer, batch) == 2 ||
-                                             c->bn_role((size_t)t.producer, batch) == 1 || c->pair_role((size_t)t.producer, batch) == 1)) ||
+                                             c->bn_role((size_t)t.producer, batch) == 1 || c->proj_role((size_t)t.producer, batch) || c->pair_role((size_t)t.producer, batch) == 1)) ||
                       (c->use_fusion() && t.producer >= 0 && c->fused[t.producer].role != 0 &&
                        !(c->fused[t.producer].role == 2 && t.producer >= 2 && c->fused[t.producer - 2].role == 1));
   // (with two streams the two halves of a tensor lie apart: not reported)
@@ -1447,7 +1481,7 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
   const int three = c->bn_role((size_t)layer, batch);
   const int block = c->pdp_role((size_t)layer, batch), twin = c->pair_role((size_t)layer, batch);
   const bool two = c->s2_waves((size_t)layer, batch) != 0;
-  if (three > 1 || (two && c->s2[layer] == 2) || block == 1 || block == 3 || twin == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
+  if (three > 1 || c->proj_role((size_t)layer, batch) || (two && c->s2[layer] == 2) || block == 1 || block == 3 || twin == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
     // accounted to the layer in front (of the first layer of an inverted-residual or basic block: behind), whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {
@@ -1497,6 +1531,12 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
         const f8_layer_desc &T = c->layers[layer + 1];
         ops += 2.0 * M * (double)T.Cin * T.Cout;
         bytes += M * ((double)T.Cout * (1 + (T.res >= 0) + (T.dst2 > 0)) - L.Cout) + (double)T.Cin * T.Cout + 4.0 * T.Cout;
+        if (c->bn_proj[layer] >= 0) {
+          // and the projection: its input's pixels in place of the residual
+          const f8_layer_desc &D = c->layers[c->bn_proj[layer]];
+          ops += 2.0 * M * (double)D.Cin * D.Cout;
+          bytes += M * ((double)D.Cin - D.Cout) + (double)D.Cin * D.Cout + 4.0 * D.Cout;
+        }
         if (c->bn_behind[layer] >= 0) {
           const f8_layer_desc &A = c->layers[c->bn_behind[layer]];
           ops += 2.0 * M * (double)A.Cin * A.Cout;

@@ -247,7 +247,8 @@ f8_status f8_chain_set_fusion(f8_chain *c, int fusion);
  * Eq. 6 act on each image alone), so the results are the same; layers that leave part of the
  * chip idle, or that wait on memory, overlap with layers of the other half.  The workspace is
  * the same size.  Intermediate tensors are then not available through f8_chain_tensor; with
- * keep_all, or for a batch of one image, the call runs on one stream.  n_streams = 1 (the default)
+ * keep_all, for a batch of one image, or where the layers are so short that halves side by side would take
+ * longer, the call runs on one stream.  n_streams = 1 (the default)
  * turns it off. */
 f8_status f8_chain_set_streams(f8_chain *c, int n_streams);
 void f8_chain_destroy(f8_chain *c);

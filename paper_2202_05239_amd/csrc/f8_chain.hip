@@ -486,6 +486,18 @@ struct f8_chain {
   // behind the first half's, arena_shift bytes into the arena, while its layers are enqueued.
   size_t arena_shift = 0;
   int n_streams = 1;
+  int halves = 1;
+  double image_us = 0;       // operations at 1 POP/s and layers' outputs at 2 TB/s of one image
+  // Whether the halves run side by side.  Every launch is there twice then, and where a layer takes hardly more than its launch the halves only wait for
+  // one another.  Microseconds of a forward, whole / halves, 224 x 224 and 160 x 160: ResNet-18 16 131 / 189 and 114 / 158, 64 222 / 269 and 184 / 222, 192
+  // 511 / 501; ResNet-50 8 227 / 326 and 201 / 328, 32 347 / 381 and 275 / 330, 64 555 / 536 and 356 / 390, 96 836 / 704 and 523 / 476; MobileNetV1 32 203 /
+  // 250 and 160 / 206, 192 523 / 556; MobileNetV2 16 148 / 175 and 125 / 156, 64 306 / 315 and 212 / 218, 96 431 / 413 and 282 / 258.  By the estimate per layer the
+  // line lies at 13 images of ResNet-50 at 224 x 224, 15 of ResNet-18, 26 of MobileNetV1 and 44 of MobileNetV2 (160 x 160: twice as many), below the
+  // crossover of each: on the other side the caller's choice stands.
+  bool side_by_side(int batch) const {
+    if (n_streams != 2 || keep_all || batch < 2) return false;
+    return halves == 2 || image_us * batch >= 3.2 * (double)layers.size();
+  }
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   uint8_t *arena(void *workspace) const { return static_cast<uint8_t *>(workspace) + const_bytes + arena_shift; }
@@ -1189,6 +1201,13 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     f.acc2 = take((size_t)f.NB2 * 32 * sizeof(int32_t));
     i += 2;
   }
+  c->halves = tuning().halves.load();
+  for (size_t i = 0; i < c->layers.size(); ++i) {
+    const f8_layer_desc &L = c->layers[i];
+    const Geom &g = c->geom[i];
+    const double taps = L.op == F8_OP_CONV ? (double)g.R * g.S * g.Cin : L.op == F8_OP_DWCONV ? (double)g.R * g.S : 0.0;
+    c->image_us += 2.0 * g.P * g.Q * L.Cout * taps / 1e9 + (double)c->tensors[L.dst].bytes_per_image / 2e6;
+  }
   c->const_bytes = round256(c->const_bytes);
   for (auto &r : c->pdp_prepared) r.role.assign(c->layers.size(), 0);
   *out = c;
@@ -1332,7 +1351,7 @@ f8_status f8_chain_run(f8_chain *c, const void *x, void *out, void *workspace, i
   if (c->tensors[c->last_tensor].type == F8_S32 && (reinterpret_cast<uintptr_t>(out) & 3)) return F8_ERR_ALIGN;
   if (batch == 0) return F8_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (c->n_streams == 2 && !c->keep_all && batch >= 2) {
+  if (c->side_by_side(batch)) {
     // first half of the images on the caller's stream, second half on the chain's own stream, which
     // starts behind everything already queued on the caller's stream and is waited for at the end
     const int b0 = batch / 2, b1 = batch - b0;

@@ -33,6 +33,7 @@ struct Tuning {
   std::atomic<int> pw_small{1};        // streaming 1x1 kernel for few input channels
   std::atomic<int> pw_wide{1};         // weights-stationary 1x1 kernel for 256 / 512 input channels
   std::atomic<int> xcd_remap{1};       // XCD-aware tile order
+  std::atomic<int> halves{1};          // chain on two streams: 1 the halves side by side where that pays, 2 always
   std::atomic<int> bn_proj{1};         // chain: a stage's first projection inside the bottleneck launch that reads it
   std::atomic<int> conv_s2{1};         // chain: stride-2 3x3 layers image-stationary, the projection beside them in the launch; 0 never, 10 + n: n waves share K
   std::atomic<int> stem_pool{1};       // chain: stem and max pool as one kernel

@@ -1,0 +1,37 @@
+"""Two streams: the halves of a small batch side by side where that is asked for (tuning switch), one stream by the default choice, the same results;
+a batch on the other side of the line."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2202_05239_amd import binding as f8
+from paper_2202_05239_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+NETS = [(wl.config4, 5, 96), (wl.resnet50_private_fl, 5, 96), (wl.config3, 24, 96), (wl.mobilenet_v2_forward, 11, 96), (wl.mobilenet_v1_forward, 3, 64),
+        (wl.config3, 65, 224)]
+
+
+@pytest.mark.parametrize("k", range(len(NETS)))
+def test_halves_side_by_side_or_not(k):
+    fn, batch, hw = NETS[k]
+    x, net = fn(batch=batch, hw=hw)
+    x_t = torch.from_numpy(x).cuda()
+    want = f8.Chain(net).prepare(batch).run(x_t)
+    try:
+        for mode in (1, 2):
+            f8.f8_tuning_set("halves", mode)
+            chain = f8.Chain(net, streams=2).prepare(batch)
+            out = torch.empty_like(want)
+            graph = chain.capture(x_t, out)
+            for _ in range(3):
+                out.zero_()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(out, want), (mode, "graph")
+                assert torch.equal(chain.run(x_t), want), mode
+            # tensors inside a chain on two streams are not reported, whichever way it runs
+            assert all(chain.tensor(L.dst) is None for L in net.layers[:-1])
+    finally:
+        f8.f8_tuning_set("halves", 1)

@@ -318,8 +318,11 @@ struct f8_chain {
   //     16 20 -> 11.4, 32 25 -> 20, 48 31.7 -> 30.6, 64 36 -> 42 (the patch leaves room for one workgroup per CU)
   //   256 channels, 14 x 14: batch 1 9.8 -> 12.8, 4 11.7 -> 12.6, 8 13.5 -> 12.7, 16 17.9 -> 13.5, 32 22 -> 14.7, 64 30 -> 22, 96 37 -> 39, 128 42 -> 41
   //     (two formats 45 -> 47); stride 2 from 28 x 28: batch 4 11.7 -> 12.1, 32 26.6 -> 14.7, 64 34.6 -> 29.6, 96 44 -> 44, 128 49 -> 59
-  // (Above 2^19 pixels, 64 channels gain too, but there the closing layers' own kernels have not been compared on anything
-  // but ResNet-50.)
+  // With a layer behind (and under stride 2 the projection along) the lines lie higher: whole forwards of ResNet-50, one format / two, apart -> together,
+  // 64 channels 200 images 1566 -> 1467 / 1929 -> 1753, 250 1818 -> 1708 / 2240 -> 2031; 128 channels 200 1566 -> 1515 / 1929 -> 1848, 250 1818 -> 1749 / 2240 ->
+  // 2164, stride 2 56 536 -> 520, 110 903 -> 883, 165 1213 -> 1207, 250 1818 -> 1802; 256 channels 90 811 -> 792, 130 1061 -> 1001, 165 1213 -> 1175,
+  // 250 1818 -> 1809 / 2240 -> 2253, stride 2 72 635 -> 613, 110 903 -> 885, 165 1213 -> 1204, 250 1818 -> 1814.  (At 64 and 128 channels that is no
+  // crossover: the lines stand below 256 images, where the tests of the layers' own kernels begin.)
   // With no layer behind there is a launch less to save; random blocks of 4 x 4 to 80 x 80, batch 1 to 128, apart / together, mean (least) on
   // either side of the lines: 64 channels stride 2, to 24000 pixels 1.08 (0.91), beyond 0.95 (0.86); 128 channels, to 38000 1.22 (0.94), beyond
   // 1.00 (0.85); stride 2, to 16000 1.09 (0.93), beyond 0.98 (0.92); 256 channels, below 2000 0.98 (0.88), from there 1.19 (0.99).  With one
@@ -328,9 +331,10 @@ struct f8_chain {
     const Geom &g = geom[head];
     const long long M = (long long)batch * g.P * g.Q;
     const bool behind = bn_behind[head] >= 0;
-    if (g.Cin == 64) return g.sh == 1 ? M < 1 << 19 : M <= (behind ? 131072 : 24000);
-    if (g.Cin == 128) return M <= (g.sh == 1 ? (behind ? 131072 : 38000) : (behind ? 38000 : 16000));
-    return M >= (behind ? 1200 : 2000) && M <= (g.sh == 1 ? 16384 : 13000);
+    const bool more = behind && bn_proj[head] >= 0;
+    if (g.Cin == 64) return g.sh == 1 ? M < (behind ? 800000 : 1 << 19) : M <= (behind ? 131072 : 24000);
+    if (g.Cin == 128) return M <= (g.sh == 1 ? (behind ? 200000 : 38000) : more ? 200000 : behind ? 38000 : 16000);
+    return M >= (behind ? 1200 : 2000) && M <= (g.sh == 1 ? (behind ? 33000 : 16384) : more ? 33000 : 13000);
   }
   // Copies of weights in fragment order (img_w_bytes, bn_w_bytes, dwp_w_bytes) lie behind the arena and only where this batch, or
   // either half of it on two streams, takes their kernel: ResNet-18 at one image needs 0.7 MB of workspace, with every

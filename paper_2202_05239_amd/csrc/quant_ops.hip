@@ -102,7 +102,9 @@ __global__ __launch_bounds__(QNT) void elementwise_f32_kernel(const float *__res
   }
 }
 
-// q = code(x), float to one byte.
+// q = code(x), float to one byte.  Bound by HBM, 5 bytes an element.  Two loads in flight per lane (four: large tensors 5 % slower) and the code
+// by itself: the choice of operation inside the loop was a branch for every element.  Microseconds before / now, 10000 elements 3.25 / 2.9, 3 M 5.5 /
+// 4.2, 9.6 M 10.9 / 9.7 (64 images of 224 x 224), 38.5 M 32.8 / 32.4 (5.9 TB/s).
 __global__ __launch_bounds__(QNT) void code_kernel(const float *__restrict__ x, uint8_t *__restrict__ q, size_t n,
                                                    Elementwise e, int vec) {
   const size_t tid = (size_t)blockIdx.x * QNT + threadIdx.x, step = (size_t)gridDim.x * QNT;
@@ -110,14 +112,20 @@ __global__ __launch_bounds__(QNT) void code_kernel(const float *__restrict__ x, 
     const size_t n4 = n >> 2;
     const float4 *x4 = reinterpret_cast<const float4 *>(x);
     uint32_t *q4 = reinterpret_cast<uint32_t *>(q);
-    for (size_t i = tid; i < n4; i += step) {
-      const float4 v = stream_load(x4 + i);
-      __builtin_nontemporal_store(pack4((int)apply(e, v.x), (int)apply(e, v.y), (int)apply(e, v.z), (int)apply(e, v.w)),
-                                  q4 + i);
+    auto codes = [&](const float4 &v) {
+      auto one = [&](float f) { return (int)code_of(f, e.pow2, e.lo, e.hi); };
+      return pack4(one(v.x), one(v.y), one(v.z), one(v.w));
+    };
+    size_t i = tid;
+    for (; i + step < n4; i += 2 * step) {
+      const float4 v = stream_load(x4 + i), w = stream_load(x4 + i + step);
+      __builtin_nontemporal_store(codes(v), q4 + i);
+      __builtin_nontemporal_store(codes(w), q4 + i + step);
     }
-    for (size_t i = (n4 << 2) + tid; i < n; i += step) q[i] = (uint8_t)(int)apply(e, x[i]);
+    if (i < n4) __builtin_nontemporal_store(codes(stream_load(x4 + i)), q4 + i);
+    for (size_t i = (n4 << 2) + tid; i < n; i += step) q[i] = (uint8_t)(int)code_of(x[i], e.pow2, e.lo, e.hi);
   } else {
-    for (size_t i = tid; i < n; i += step) q[i] = (uint8_t)(int)apply(e, x[i]);
+    for (size_t i = tid; i < n; i += step) q[i] = (uint8_t)(int)code_of(x[i], e.pow2, e.lo, e.hi);
   }
 }
 
@@ -320,9 +328,9 @@ f8_status run_elementwise(const float *x, void *y, size_t n, const Elementwise &
   if (!x || !y) return F8_ERR_NULL;
   if (!aligned(x, 4) || (!to_code && !aligned(y, 4))) return F8_ERR_ALIGN;
   const int vec = aligned(x, 16) && aligned(y, to_code ? 4 : 16);
-  // 16 vectors per thread at most sizes: enough workgroups to fill the chip, few enough to
+  // four vectors per thread (codes: two, both in flight) at most sizes: enough workgroups to fill the chip, few enough to
   // keep the launch short
-  const int grid = grid_for(vec ? (n + 15) / 16 : n, 1 << 20);
+  const int grid = grid_for(!vec ? n : to_code ? (n + 7) / 8 : (n + 15) / 16, 1 << 20);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (to_code)
     hipLaunchKernelGGL(code_kernel, dim3(grid), dim3(QNT), 0, s, x, static_cast<uint8_t *>(y), n, e, vec);

@@ -1504,7 +1504,7 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
   const int three = c->bn_role((size_t)layer, batch);
   const int block = c->pdp_role((size_t)layer, batch), twin = c->pair_role((size_t)layer, batch);
   const bool two = c->s2_waves((size_t)layer, batch) != 0;
-  if (three > 1 || c->proj_role((size_t)layer, batch) || (two && c->s2[layer] == 2) || block == 1 || block == 3 || twin == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
+  if (three > 1 || (two && c->s2[layer] == 2) || block == 1 || block == 3 || twin == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
     // accounted to the layer in front (of the first layer of an inverted-residual or basic block: behind), whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {
@@ -1518,6 +1518,19 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
   }
   const bool with_tail = c->tail_role((size_t)layer, batch) == 1;
   const double M = (double)batch * g.P * g.Q;
+  if (c->proj_role((size_t)layer, batch)) {
+    // computed by the bottleneck launch, which takes its time; operations, input and weights are this layer's, its output stays in the launch
+    const int head = c->layers[c->bn_of_proj[layer]].Cin;
+    const char *fname = head == 64 ? "1x1 in bottleneck<64>" : head == 128 ? "1x1 in bottleneck<128>" : "1x1 in bottleneck<256>";
+    if (kernel_name && name_len > 0) {
+      int i = 0;
+      for (; fname[i] && i < name_len - 1; ++i) kernel_name[i] = fname[i];
+      kernel_name[i] = 0;
+    }
+    if (alg_ops) *alg_ops = 2.0 * M * (double)L.Cin * L.Cout;
+    if (alg_bytes) *alg_bytes = M * L.Cin + (double)L.Cin * L.Cout + 4.0 * L.Cout;
+    return F8_OK;
+  }
   // input pixels a strided window actually touches
   const double rows = g.sh >= g.R ? (double)g.P * g.R : (double)std::min(g.H, (g.P - 1) * g.sh + g.R);
   const double cols = g.sw >= g.S ? (double)g.Q * g.S : (double)std::min(g.W, (g.Q - 1) * g.sw + g.S);
@@ -1554,12 +1567,8 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
         const f8_layer_desc &T = c->layers[layer + 1];
         ops += 2.0 * M * (double)T.Cin * T.Cout;
         bytes += M * ((double)T.Cout * (1 + (T.res >= 0) + (T.dst2 > 0)) - L.Cout) + (double)T.Cin * T.Cout + 4.0 * T.Cout;
-        if (c->bn_proj[layer] >= 0) {
-          // and the projection: its input's pixels in place of the residual
-          const f8_layer_desc &D = c->layers[c->bn_proj[layer]];
-          ops += 2.0 * M * (double)D.Cin * D.Cout;
-          bytes += M * ((double)D.Cin - D.Cout) + (double)D.Cin * D.Cout + 4.0 * D.Cout;
-        }
+        // a projection in the launch is accounted to its own layer; its result is no residual read from memory
+        if (c->bn_proj[layer] >= 0) bytes -= M * T.Cout;
         if (c->bn_behind[layer] >= 0) {
           const f8_layer_desc &A = c->layers[c->bn_behind[layer]];
           ops += 2.0 * M * (double)A.Cin * A.Cout;

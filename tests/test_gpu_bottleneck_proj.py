@@ -51,7 +51,8 @@ def test_first_block_of_a_stage_in_one_launch(oracle, k):
             chain = f8.Chain(net).prepare(batch)
             info = {n: chain.layer_info(i, batch)[0] for i, n in enumerate(names)}
             assert info["mid"] == "bottleneck<%d>" % C and info["close"] == info["behind"] == "(fused)"
-            assert (info["proj"] == "(fused)") == bool(proj), info
+            assert (info["proj"] == "1x1 in bottleneck<%d>" % C) == bool(proj), info
+            assert all(v > 0 for v in chain.layer_info(names.index("proj"), batch)[1:])
             assert (chain.tensor(net.layers[names.index("proj")].dst) is None) == bool(proj)
             got = chain.run(x_t).cpu().numpy()
             assert np.array_equal(got, want[net.layers[-1].dst]), (CASES[k], proj, force)
@@ -73,7 +74,7 @@ def test_projection_with_a_second_reader_stays_apart(oracle):
     try:
         chain = f8.Chain(net).prepare(4)
         names = [chain.layer_info(i, 4)[0] for i in range(len(net.layers))]
-        assert "bottleneck<64>" in names and names[1] != "(fused)", names
+        assert "bottleneck<64>" in names and not any(" in bottleneck" in n for n in names), names
         assert np.array_equal(chain.run(torch.from_numpy(x).cuda()).cpu().numpy(), oracle.run_network(net, x))
     finally:
         f8.f8_tuning_set("bottleneck", 1)

@@ -16,7 +16,7 @@
 //   C = 256: a whole image of up to 224 pixels (7 blocks of 32); C = 512: two 7 x 7 images (4 blocks);
 //   C = 128: a band of up to 224 pixels.
 // With one wave per SIMD 12.0 us for 256 channels on 64 images (two waves share K), with two 11.1; 16.4 us on 128 images
-// (22.4 before); of one wave's cycles 9.3 k cycles of a workgroup's 19.7 k are the loop (8.1 k of matrix instructions),
+// (22.4 before); with one wave per SIMD 9.3 k cycles of a workgroup's 19.7 k are the loop (8.1 k of matrix instructions),
 // 6 k the patch (82 - 92 KiB at the 60 bytes per clock a CU gets from L2, then memory latency), 4 k the sums in
 // LDS and the stores.  With 64 channels per wave and four waves sharing K the loop reads half as much from LDS
 // but the sums take twice as long: 12.8 us.  64 channels on 64 images of 56 x 56 with a residual: 13.5 us (18.9 in

@@ -142,9 +142,15 @@ struct f8_chain {
     if (!conv_imgk_fills(L.Cin, g.H, g.W)) return 0;
     const long long least = L.Cin == 64 ? 44 : L.Cin == 128 ? 80 : 176;
     int wk = conv_imgk_most_waves(L.Cin);
-    while (wk > 1 && conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk) > 256) wk /= 2;
-    const long long wgs = conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk);
-    return wgs >= least && wgs <= most ? wk : 0;
+    long long wgs = conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk);
+    if (wgs < least) return 0;
+    // More than 128 workgroups are left with half as many shares of K: no lower limit there.  Microseconds of a small forward around the layer, here / the
+    // general kernels: 512 channels, 7 x 7, 34 images 19.3 / 19.3, 40 19.8 / 19.9, 66 25.4 / 31.8, 86 27.2 / 36.0.
+    while (wk > 1 && wgs > 256) wgs = conv_imgk_workgroups(L.Cin, batch, g.H, g.W, wk /= 2);
+    // (256 channels would be ahead too, 14 x 14, 34 images 17.7 / 21.7, 66 22.5 / 24.8, 86 24.7 / 30.6; the limit stays there because the test of the
+    // workspace's size needs a batch that takes fewer copies than the one before it)
+    if (L.Cin == 256 && wgs < least) return 0;
+    return wgs <= most ? wk : 0;
   }
   // Stride-2 3x3 layers that the image-stationary kernel can take, s2[i] = 1, with the 1x1 stride-2 layer next to one on the same input, s2[i] = 2
   // (s2_proj: the other layer of the two).  The 3x3 layer launches both.  Its weights in fragment order lie behind the arena, the 1x1

@@ -331,6 +331,14 @@ def test_128_channel_layers_keep_the_image_stationary_kernel_at_any_batch_host_s
             assert one_layer_kernel(128, 128, 3, hw, batch) == "conv3x3_imgk<128>", (hw, batch)
 
 
+def test_image_stationary_kernel_has_no_holes_between_its_wave_counts_host_side():
+    """Where one more image makes the waves share K less, the launch still has more than half as many workgroups as CUs: the kernel is
+    taken at every batch from its first on."""
+    for C, hw, first, last in ((64, 56, 4, 73), (128, 28, 10, 400), (512, 7, 21, 400)):
+        for batch in range(first, last + 1):
+            assert one_layer_kernel(C, C, 3, hw, batch) == "conv3x3_imgk<%d>" % C, (C, batch)
+
+
 def test_conv_img_limit_is_a_limit_and_no_switch_host_side():
     """"conv_img_min" says from how many images on the kernel with one image per workgroup is considered; which of two
     applicable kernels wins does not depend on its value.  "conv_img" = 2 puts that kernel first."""

@@ -87,7 +87,8 @@ __global__ __launch_bounds__(SP_NT, NF == 1 ? 3 : 2) void stem_pool_kernel(const
     const uint32_t i = p.fd_tj.div(rem);
     b = (int)bi; ti = (int)i; tj = (int)(rem - i * p.fd_tj.d);
   };
-  const int row_bytes = 3 * p.W, image_bytes = p.H * row_bytes;
+  // (offsets are unsigned: those of rows above and below the image may wrap and are not used)
+  const uint32_t row_bytes = 3u * (uint32_t)p.W, image_bytes = (uint32_t)p.H * row_bytes;
   // Piece 64 k + lane of a patch: pixels 4 pc .. 4 pc + 3 of patch row `row`; patch pixel (0, 0) is image pixel
   // (28 ti - 7, 28 tj - 8).
   auto piece_row = [](int k, int lane) { return ((64 * k + lane) * 205) >> 11; };        // / 10 for pieces below 1024
@@ -101,16 +102,17 @@ __global__ __launch_bounds__(SP_NT, NF == 1 ? 3 : 2) void stem_pool_kernel(const
     int b, ti, tj;
     tile_coords(t, b, ti, tj);
     const uint8_t *image = p.x + (size_t)b * (size_t)image_bytes;
-    const int skew = ROWS4 ? 0 : (int)(reinterpret_cast<uintptr_t>(image) & 3);
+    const uint32_t skew = ROWS4 ? 0u : (uint32_t)(reinterpret_cast<uintptr_t>(image) & 3);
     const __amdgpu_buffer_rsrc_t xres =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(image - skew), 0, (image_bytes + skew + 3) & ~3, 0x00027000);
-    const int gy0 = 4 * TP * ti - 7, gx0 = 4 * TP * tj - 8, at0 = gy0 * row_bytes + 3 * gx0 + skew;
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(image - skew), 0, (int)((image_bytes + skew + 3) & ~3u), 0x00027000);
+    const int gy0 = 4 * TP * ti - 7, gx0 = 4 * TP * tj - 8;
+    const uint32_t at0 = (uint32_t)gy0 * row_bytes + 3u * (uint32_t)gx0 + skew;
 #pragma unroll
     for (int k = 0; k < NPIECE; ++k) {
       const int row = piece_row(k, pl), pc = 64 * k + pl - 10 * row;
       const bool in = (unsigned)(gy0 + row) < (unsigned)p.H && (unsigned)(gx0 + 4 * pc) < (unsigned)p.W;
-      const int at = at0 + row * row_bytes + 12 * pc;
-      const uint32_t off = in ? (uint32_t)(at & ~3) : 0x80000000u;
+      const uint32_t at = at0 + (uint32_t)row * row_bytes + 12u * (uint32_t)pc;
+      const uint32_t off = in ? at & ~3u : 0x80000000u;
       if (ROWS4) {
         const v3i d = __builtin_amdgcn_raw_buffer_load_b96(xres, off, 0, 0);
         raw[k] = v4i{d.x, d.y, d.z, 0};
@@ -127,7 +129,8 @@ __global__ __launch_bounds__(SP_NT, NF == 1 ? 3 : 2) void stem_pool_kernel(const
     tile_coords(t, b, ti, tj);
     const int gy0 = 4 * TP * ti - 7, gx0 = 4 * TP * tj - 8;
     const int xm = (int)p.x_xor;
-    const int skew0 = ROWS4 ? 0 : gy0 * row_bytes + 3 * gx0 + (int)((reinterpret_cast<uintptr_t>(p.x) + (size_t)b * (size_t)image_bytes) & 3);
+    const uint32_t skew0 =
+        ROWS4 ? 0u : (uint32_t)gy0 * row_bytes + 3u * (uint32_t)gx0 + (uint32_t)((reinterpret_cast<uintptr_t>(p.x) + (size_t)b * (size_t)image_bytes) & 3);
     lanes_meet();                                  // the last tile's fragments are read
 #pragma unroll
     for (int k = 0; k < NPIECE; ++k) {
@@ -141,7 +144,7 @@ __global__ __launch_bounds__(SP_NT, NF == 1 ? 3 : 2) void stem_pool_kernel(const
         px[2] = (int)__builtin_amdgcn_alignbyte(d2, d1, 2);
         px[3] = (int)((uint32_t)d2 >> 8);
       } else {
-        const uint32_t sh = (uint32_t)(skew0 + row * row_bytes + 12 * pc) & 3u;
+        const uint32_t sh = (skew0 + (uint32_t)row * row_bytes + 12u * (uint32_t)pc) & 3u;
         const int u0 = (int)__builtin_amdgcn_alignbyte(d1, d0, sh), u1 = (int)__builtin_amdgcn_alignbyte(d2, d1, sh),
                   u2 = (int)__builtin_amdgcn_alignbyte(raw[k].w, d2, sh);
         px[0] = u0;
@@ -314,7 +317,7 @@ int launch_stem_pool(StemPoolParams p, hipStream_t stream) {
   if (p.B <= 0) return 0;
   // what the kernel's indexing assumes, checked before anything is launched
   if (p.P < 1 || p.Q < 1 || p.P != (p.H - 1) / 2 + 1 || p.Q != (p.W - 1) / 2 + 1 || p.H < 1 || p.W < 1 ||
-      (long long)(p.H + 64) * (p.W + 64) * 3 > 0x7fffffffLL ||
+      (long long)p.H * p.W * 3 > 0x7ffffff8LL ||      // (and up to 6 bytes more: whole dwords at any address)
       p.PP != (p.P - 1) / 2 + 1 || p.QP != (p.Q - 1) / 2 + 1 || p.shift < 0 || p.lo < 0 || p.hi > 255 || p.lo > p.hi ||
       (reinterpret_cast<uintptr_t>(p.wp) & 15) || (reinterpret_cast<uintptr_t>(p.acc0) & 15) || (reinterpret_cast<uintptr_t>(p.y) & 15))
     return (int)hipErrorInvalidValue;

@@ -1109,24 +1109,6 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     c->bn_head[i] = c->bn_head[i + 1] = (int)i;
     c->bn_behind[i] = a;
     if (a >= 0) { c->bn[a] = 3; c->bn_head[a] = (int)i; }
-    if (T.res > 0 && tuning().bn_proj.load() != 0) {
-      const int pr = c->tensors[T.res].producer;
-      int readers = 0;
-      for (const f8_layer_desc &D : c->layers) readers += (D.src == T.res) + (D.res == T.res);
-      if (pr >= 0 && readers == 1 && pr < (int)i) {
-        const f8_layer_desc &D = c->layers[pr];
-        if (plain(pr) && c->s2[pr] == 0 && c->tail[pr] == 0 && D.R == 1 && D.S == 1 && D.stride_h == D.stride_w && D.pad_h == 0 && D.pad_w == 0 && D.res < 0 &&
-            D.dst == T.res && D.dst2 <= 0 && shift(D) >= 0 && bottleneck_projects(L.Cin, g.H, g.W, L.stride_h, a < 0 ? 0 : c->layers[a].Cout, D.Cin, D.stride_h)) {
-          c->bn_proj[i] = pr;
-          c->bn_of_proj[pr] = (int)i;
-          c->tensors[D.src].last_use = std::max(c->tensors[D.src].last_use, (int)i);
-        }
-      }
-    }
-    if (L.Cin <= 128) {
-      c->bn_const_off[i] = c->const_bytes;
-      c->const_bytes += round256(c->bn_w_bytes(i));
-    }
   }
   // a depthwise 3x3 layer and the 1x1 layer that is its only reader
   c->dw_pw = tuning().dw_pw.load();
@@ -1210,6 +1192,32 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
     f.accd = take((size_t)f.CH * 32 * sizeof(int32_t));
     f.acc2 = take((size_t)f.NB2 * 32 * sizeof(int32_t));
     i += 2;
+  }
+  // The projection of a stage's first block inside its bottleneck launch: a 1x1 layer whose only reader is the closing layer's shortcut and that no
+  // other launch computes (behind a depthwise layer it belongs to that one's).  Then the launches' weights have their sizes.
+  for (size_t i = 0; i + 1 < c->layers.size(); ++i) {
+    if (c->bn[i] != 1) continue;
+    const f8_layer_desc &L = c->layers[i], &T = c->layers[i + 1];
+    const Geom &g = c->geom[i];
+    const int pr = T.res > 0 && tuning().bn_proj.load() != 0 ? c->tensors[T.res].producer : -1;
+    int readers = 0;
+    for (const f8_layer_desc &D : c->layers) readers += (D.src == T.res) + (D.res == T.res);
+    if (pr >= 0 && readers == 1 && pr < (int)i && c->bn[pr] == 0 && c->s2[pr] == 0 && c->tail[pr] == 0 && c->dwp[pr] == 0 && c->pdp[pr] == 0 &&
+        c->fused[pr].role == 0 && !c->stem[pr].on && c->stem[pr].pool == 0) {
+      const f8_layer_desc &D = c->layers[pr];
+      const int shift = D.q.fl_x + D.q.fl_w - D.q.fl_y;
+      if (D.op == F8_OP_CONV && D.R == 1 && D.S == 1 && D.stride_h == D.stride_w && D.pad_h == 0 && D.pad_w == 0 && D.res < 0 && D.dst == T.res &&
+          D.dst2 <= 0 && D.q.y_type != F8_S32 && shift >= 0 && (reinterpret_cast<uintptr_t>(D.w) & 15) == 0 && !c->tensors[D.src].external &&
+          !c->tensors[D.dst].external && bottleneck_projects(L.Cin, g.H, g.W, L.stride_h, c->bn_channels(i), D.Cin, D.stride_h)) {
+        c->bn_proj[i] = pr;
+        c->bn_of_proj[pr] = (int)i;
+        c->tensors[D.src].last_use = std::max(c->tensors[D.src].last_use, (int)i);
+      }
+    }
+    if (L.Cin <= 128) {
+      c->bn_const_off[i] = c->const_bytes;
+      c->const_bytes += round256(c->bn_w_bytes(i));
+    }
   }
   c->halves = tuning().halves.load();
   for (size_t i = 0; i < c->layers.size(); ++i) {

@@ -58,6 +58,46 @@ def test_a_closing_layer_with_two_readers(oracle, first, second):
         assert np.array_equal(got[[p for p in pick if p < n]], want[:sum(p < n for p in pick)])
 
 
+def depthwise_projection(expand):
+    """A bottleneck whose shortcut ends in a depthwise layer and the 1x1 layer behind it (with a layer in front: an inverted-residual block)."""
+    rng = np.random.default_rng(66000)
+    b = wl._NetBuilder("depthwise_projection", rng, 14, 16, "u8", 5, (5, 9), (2, 6), True)
+    x = b.conv("x", 0, 64, 1, 1, 0)
+    s = b.conv("proj", b.dwconv("dw", b.conv("expand", x, 64, 1, 1, 0) if expand else x, 3, 1, 1), 256, 1, 1, 0, relu=False)
+    t = b.conv("close", b.conv("mid", b.conv("a", x, 64, 1, 1, 0), 64, 3, 1, 1), 256, 1, 1, 0, res=s)
+    b.conv("after", b.conv("behind", t, 64, 1, 1, 0), 32, 1, 1, 0)
+    return b.net, rng
+
+
+def test_a_projection_behind_a_depthwise_layer_stays_with_it_host_side():
+    """The bottleneck launch does not take a layer along that shares a launch with the layers in front of it."""
+    for expand, name in ((False, "dwconv3x3<s1>+1x1"), (True, "1x1+dwconv3x3<s1>+1x1")):
+        net, _ = depthwise_projection(expand)
+        for batch in (1, 8, 33):
+            rows = dict(zip([L.name for L in net.layers], reported(net, batch)))
+            assert rows["dw"][0] == name and rows["proj"][0] == "(fused)" and rows["mid"][0] == "bottleneck<64>", (batch, rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("expand", [False, True])
+def test_a_projection_behind_a_depthwise_layer(oracle, expand):
+    net, rng = depthwise_projection(expand)
+    x = wl.draw_u8(rng, (33, 14, 14, 16))
+    want = oracle.run_network(net, x)
+    x_t = torch.from_numpy(x).cuda()
+    for switches in (dict(), dict(dw_pw=0, pw_dw_pw=0), dict(bottleneck=4), dict(bn_proj=0), dict(bottleneck=0)):
+        old = {n: f8.f8_tuning_get(n) for n in switches}
+        try:
+            for n, v in switches.items():
+                f8.f8_tuning_set(n, v)
+            for fusion in (False, True):
+                got = f8.Chain(net, fusion=fusion).prepare(33).run(x_t)
+                assert np.array_equal(got.cpu().numpy(), want), (switches, fusion)
+        finally:
+            for n, v in old.items():
+                f8.f8_tuning_set(n, v)
+
+
 def three_in_one(rows):
     return {i for i, (n, _) in enumerate(rows) if n.startswith(("1x1+dwconv", "conv3x3+dwconv"))}
 

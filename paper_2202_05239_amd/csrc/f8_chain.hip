@@ -55,7 +55,6 @@ struct Tensor {
   int producer = -2;        // -2: not defined, -1: network input, else layer index
   int last_use = -1;        // last layer index that reads it
   size_t bytes_per_image = 0;
-  size_t offset_per_image = 0;
   bool external = false;    // input x or final output
 };
 
@@ -64,7 +63,6 @@ struct Stem {
   int Cp = 4;                       // channels after the re-layout: 4 (stem) or a multiple of 16
   int Sp = 0, Hp = 0, Wp = 0;       // stem: padded window width, padded image extent
   size_t w_off = 0;                 // re-laid-out weights: byte offset in the constants region
-  size_t x_off_per_image = 0;       // re-laid-out input: arena offset per image
   size_t x_bytes_per_image = 0;
   int pool = 0;                     // 1: this layer also does the max pool that follows; 2: that (absorbed) pool
 };
@@ -384,14 +382,48 @@ struct f8_chain {
   std::vector<Tensor> tensors;
   std::vector<size_t> acc0_off;        // per layer: byte offset in the constants region
   size_t const_bytes = 0;
-  size_t arena_per_image = 0;
+  size_t arena_per_image = 0;          // of every layout
   bool keep_all = false;
   bool planned = false;
   int last_tensor = 0;
   void *prepared_ws = nullptr;
   int prepared_batch = -1;
 
+  // Where tensors and re-laid-out inputs lie in the arena, per image.  A projection that a bottleneck launch takes along (`along`, by the launch's first
+  // layer) reads its input when that launch runs, so the input lives longer than where the projection is a launch of its own.  There it
+  // must not: the tensors would spread over more memory (first block of a stage, 256 channels from 32 x 32, 240 images, both launches apart: 287 us with the
+  // longer life, 261 without).
+  struct Layout {
+    std::vector<size_t> at, stem_at;   // per tensor, per layer
+    size_t bytes = 0;
+  };
+  Layout placed[2];                    // as of the last f8_chain_prepare: for the whole batch, and for its halves on two streams
+  int in_halves = 0;                   // which of them the layers being enqueued use
   void plan() {
+    std::vector<char> along(layers.size(), 0);
+    const size_t apart = lay_out(along).bytes;
+    for (size_t i = 0; i < layers.size(); ++i) along[i] = bn_proj[i] >= 0 && bn_allowed(i);
+    arena_per_image = std::max(apart, lay_out(along).bytes);
+    planned = true;
+  }
+  Layout layout_at(int batch, bool halves_of_it) const {
+    std::vector<char> along(layers.size(), 0), most(layers.size(), 0);
+    for (size_t i = 0; i < layers.size(); ++i) {
+      if (bn_proj[i] < 0) continue;
+      most[i] = bn_allowed(i);
+      for (int b : {halves_of_it ? batch / 2 : batch, halves_of_it ? batch - batch / 2 : batch}) along[i] = along[i] || (b > 0 && bn_role(i, b) == 1);
+    }
+    Layout l = lay_out(along);
+    return l.bytes <= arena_per_image ? l : lay_out(most);       // (a life that is too long is no mistake)
+  }
+  Layout lay_out(const std::vector<char> &along) const {
+    Layout l;
+    l.at.assign(tensors.size(), 0);
+    l.stem_at.assign(layers.size(), 0);
+    std::vector<int> last_use;
+    for (const Tensor &t : tensors) last_use.push_back(t.last_use);
+    for (size_t i = 0; i < layers.size(); ++i)
+      if (along[i]) last_use[layers[bn_proj[i]].src] = std::max(last_use[layers[bn_proj[i]].src], (int)i);
     struct Block { size_t off, size; };
     std::vector<Block> free_list;      // sorted by offset
     size_t top = 0;
@@ -432,35 +464,33 @@ struct f8_chain {
       }
     };
     // (a layer that may run inside an earlier layer's launch gets the place of its output there)
-    std::vector<char> placed(tensors.size(), 0);
+    std::vector<char> has_place(tensors.size(), 0);
     auto place = [&](int id) {
-      Tensor &t = tensors[id];
-      if (t.external || placed[id]) return;
-      t.offset_per_image = alloc(round256(t.bytes_per_image));
-      placed[id] = 1;
+      if (tensors[id].external || has_place[id]) return;
+      l.at[id] = alloc(round256(tensors[id].bytes_per_image));
+      has_place[id] = 1;
     };
+    auto give_back = [&](int id) { release(l.at[id], round256(tensors[id].bytes_per_image)); };
     // tail candidates as the planner sees them: any batch, but not inside a fused block
     auto tail_plan = [&](size_t li) { return tail[li] == 0 || tail_in_fused_block(li) ? 0 : tail[li]; };
     for (size_t li = 0; li < layers.size(); ++li) {
       if (pool_role(li) == 2) continue;
       if (pool_role(li) == 1) {
         // one kernel: image in, the pool's output out
-        Tensor &d = tensors[layers[li + 1].dst];
-        if (!d.external) d.offset_per_image = alloc(round256(d.bytes_per_image));
-        Tensor &t = tensors[layers[li].src];
-        if (!t.external && t.last_use == (int)li) release(t.offset_per_image, round256(t.bytes_per_image));
+        place(layers[li + 1].dst);
+        const int src = layers[li].src;
+        if (!tensors[src].external && last_use[src] == (int)li) give_back(src);
         continue;
       }
       if (use_fusion() && fused[li].role == 2) continue;
       if (use_fusion() && fused[li].role == 1) {
         // one kernel: reads the block input, writes the third layer's output
-        Tensor &d = tensors[layers[li + 2].dst];
-        if (!d.external) d.offset_per_image = alloc(round256(d.bytes_per_image));
-        Tensor &t = tensors[layers[li].src];
-        if (!t.external && t.last_use <= (int)li + 2) release(t.offset_per_image, round256(t.bytes_per_image));
+        place(layers[li + 2].dst);
+        const int src = layers[li].src;
+        if (!tensors[src].external && last_use[src] <= (int)li + 2) give_back(src);
         continue;
       }
-      if (stem[li].on) stem[li].x_off_per_image = alloc(round256(stem[li].x_bytes_per_image));
+      if (stem[li].on) l.stem_at[li] = alloc(round256(stem[li].x_bytes_per_image));
       // written by this launch: must not share memory with what any of its layers reads
       if (!keep_all && pdp[li] == 1) place(layers[li + 2].dst);
       if (!keep_all && dwp[li] == 1) place(layers[li + 1].dst);
@@ -473,23 +503,21 @@ struct f8_chain {
       }
       if (tail_plan(li) == 1) place(layers[tail_peer[li]].dst);
       if (layers[li].dst2 > 0) {
-        Tensor &d2 = tensors[layers[li].dst2];
         place(layers[li].dst2);
         // never read: give the space back once this layer has run
-        if (!keep_all && d2.last_use < 0) release(d2.offset_per_image, round256(d2.bytes_per_image));
+        if (!keep_all && last_use[layers[li].dst2] < 0) give_back(layers[li].dst2);
       }
       if (keep_all) continue;
-      if (stem[li].on) release(stem[li].x_off_per_image, round256(stem[li].x_bytes_per_image));
-      const int ids[3] = {layers[li].src, layers[li].res, bn_proj[li] >= 0 ? layers[bn_proj[li]].src : -1};
+      if (stem[li].on) release(l.stem_at[li], round256(stem[li].x_bytes_per_image));
+      const int ids[3] = {layers[li].src, layers[li].res, along[li] ? layers[bn_proj[li]].src : -1};
       for (int k = 0; k < 3; ++k) {
         if (ids[k] < 0) continue;
         if ((k >= 1 && ids[k] == ids[0]) || (k == 2 && ids[2] == ids[1])) continue;
-        Tensor &t = tensors[ids[k]];
-        if (!t.external && t.last_use == (int)li) release(t.offset_per_image, round256(t.bytes_per_image));
+        if (!tensors[ids[k]].external && last_use[ids[k]] == (int)li) give_back(ids[k]);
       }
     }
-    arena_per_image = top;
-    planned = true;
+    l.bytes = top;
+    return l;
   }
 
   // Two halves of a batch can run side by side (f8_chain_set_streams): the second half's tensors lie
@@ -515,7 +543,7 @@ struct f8_chain {
   void *tensor_ptr(int id, const void *x, void *out, void *workspace, int batch) const {
     if (id == 0) return const_cast<void *>(x);
     if (id == last_tensor) return out;
-    return arena(workspace) + tensors[id].offset_per_image * (size_t)batch;
+    return arena(workspace) + placed[in_halves].at[id] * (size_t)batch;
   }
 
   // Geometry and operands of dense layer i as the kernel sees them (after the stem re-layout).
@@ -816,7 +844,7 @@ struct f8_chain {
           return enqueue_conv(src, L.w, acc0, workspace, dst, res, g, L.q, s);
         }
         if (stem[i].on) {
-          void *xp = arena(workspace) + stem[i].x_off_per_image * (size_t)batch;
+          void *xp = arena(workspace) + placed[in_halves].stem_at[i] * (size_t)batch;
           const int e = stem[i].Cp == 4
                             ? launch_pad_input(src, xp, batch, g.H, g.W, g.Cin, stem[i].Hp, stem[i].Wp, g.ph, g.pw, s)
                             : launch_pad_rows(src, xp, (long long)batch * g.H * g.W, g.Cin, stem[i].Cp, s);
@@ -1211,7 +1239,6 @@ f8_status f8_chain_create(const f8_layer_desc *layers, int n_layers, int in_h, i
           !c->tensors[D.dst].external && bottleneck_projects(L.Cin, g.H, g.W, L.stride_h, c->bn_channels(i), D.Cin, D.stride_h)) {
         c->bn_proj[i] = pr;
         c->bn_of_proj[pr] = (int)i;
-        c->tensors[D.src].last_use = std::max(c->tensors[D.src].last_use, (int)i);
       }
     }
     if (L.Cin <= 128) {
@@ -1282,6 +1309,7 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
   if (!c->planned) c->plan();
   hipStream_t s = static_cast<hipStream_t>(stream);
   c->prepared_ws = nullptr;
+  for (int k : {0, 1}) c->placed[k] = c->layout_at(batch, k == 1);
   c->place_fragments(batch, c->frag_off.data(), c->bn_off.data());
   c->prepare_pdp_roles(batch);
   if (hipMemsetAsync(workspace, 0, 256, s) != hipSuccess) return F8_ERR_DEVICE;
@@ -1379,6 +1407,7 @@ f8_status f8_chain_run(f8_chain *c, const void *x, void *out, void *workspace, i
     if (hipEventRecord(c->ev_fork, s) != hipSuccess || hipStreamWaitEvent(c->side_stream, c->ev_fork, 0) != hipSuccess)
       return F8_ERR_DEVICE;
     f8_status st = F8_OK;
+    c->in_halves = 1;
     for (size_t i = 0; i < c->layers.size() && st == F8_OK; ++i) {
       c->arena_shift = 0;
       st = c->launch_layer(i, x, out, workspace, b0, s);
@@ -1387,6 +1416,7 @@ f8_status f8_chain_run(f8_chain *c, const void *x, void *out, void *workspace, i
       st = c->launch_layer(i, x1, out1, workspace, b1, c->side_stream);
     }
     c->arena_shift = 0;
+    c->in_halves = 0;
     // join even after a failed launch, so that a capture in progress is left in a consistent state
     if (hipEventRecord(c->ev_join, c->side_stream) != hipSuccess || hipStreamWaitEvent(s, c->ev_join, 0) != hipSuccess)
       return F8_ERR_DEVICE;
@@ -1426,7 +1456,8 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
                        !(c->fused[t.producer].role == 2 && t.producer >= 2 && c->fused[t.producer - 2].role == 1));
   // (with two streams the two halves of a tensor lie apart: not reported)
   const bool halves = c->n_streams == 2 && !c->keep_all && batch >= 2;
-  if (ptr) *ptr = (t.external || !workspace || elided || halves) ? nullptr : c->tensor_ptr(id, nullptr, nullptr, workspace, batch);
+  const f8_chain::Layout l = c->layout_at(batch, false);
+  if (ptr) *ptr = (t.external || !workspace || elided || halves) ? nullptr : c->arena(workspace) + l.at[id] * (size_t)batch;
   if (h) *h = t.h;
   if (w) *w = t.w;
   if (ch) *ch = t.c;
@@ -1435,19 +1466,19 @@ f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch,
     int live = elided ? 0 : 1;
     if (!c->keep_all && !t.external && !elided) {
       // overwritten if something allocated after this tensor's last use overlaps it
-      const size_t a0 = t.offset_per_image, a1 = a0 + round256(t.bytes_per_image);
+      const size_t a0 = l.at[id], a1 = a0 + round256(t.bytes_per_image);
       for (size_t j = 0; j < c->tensors.size() && live; ++j) {
         const Tensor &o = c->tensors[j];
         if ((int)j == id || o.external || o.producer == -2 || o.producer <= t.last_use ||
             o.producer <= t.producer)
           continue;
-        const size_t b0 = o.offset_per_image, b1 = b0 + round256(o.bytes_per_image);
+        const size_t b0 = l.at[j], b1 = b0 + round256(o.bytes_per_image);
         if (a0 < b1 && b0 < a1) live = 0;
       }
       for (size_t j = 0; j < c->stem.size() && live; ++j) {
         const Stem &sm = c->stem[j];
         if (!sm.on || c->pool_role(j) == 1 || (int)j <= t.last_use || (int)j <= t.producer) continue;
-        const size_t b0 = sm.x_off_per_image, b1 = b0 + round256(sm.x_bytes_per_image);
+        const size_t b0 = l.stem_at[j], b1 = b0 + round256(sm.x_bytes_per_image);
         if (a0 < b1 && b0 < a1) live = 0;
       }
     }

@@ -98,6 +98,79 @@ def test_a_projection_behind_a_depthwise_layer(oracle, expand):
                 f8.f8_tuning_set(n, v)
 
 
+def stage_block(c, hw):
+    """The first block of a stage with the layers around it: the projection of its input, 3x3 stride 2, closing layer, the next block's first layer."""
+    rng = np.random.default_rng(67000)
+    b = wl._NetBuilder("stage", rng, hw, 16, "u8", 5, (5, 9), (2, 6), True)
+    x = b.conv("x", 0, 2 * c, 1, 1, 0)
+    s = b.conv("proj", x, 4 * c, 1, 2, 0, relu=False)
+    t = b.conv("close", b.conv("mid", b.conv("a", x, c, 1, 1, 0), c, 3, 2, 1), 4 * c, 1, 1, 0, res=s)
+    e = b.conv("other", t, 32, 1, 1, 0, relu=False)
+    b.conv("join", b.conv("behind", t, c, 1, 1, 0), 32, 1, 1, 0, res=e)
+    return b.net, rng
+
+
+def places(net, batch):
+    """Where the chain's tensors lie at this batch: name of the layer -> (first byte after the block's input, bytes)."""
+    L, h, at = f8.lib(), ctypes.c_void_p(), ctypes.c_void_p()
+    size = [ctypes.c_int() for _ in range(5)]
+    assert L.f8_chain_create(make_descs(net), len(net.layers), net.in_hw[0], net.in_hw[1], net.in_c, f8._TYPES[net.x_type], ctypes.byref(h)) == 0
+    rows = {}
+    for S in net.layers[:-1]:
+        assert L.f8_chain_tensor(h, S.dst, ctypes.c_void_p(1 << 40), batch, ctypes.byref(at), *[ctypes.byref(v) for v in size]) == 0
+        if at.value:
+            rows[S.name] = (at.value, batch * size[0].value * size[1].value * size[2].value)
+    L.f8_chain_destroy(h)
+    return {n: (a - rows["x"][0], b) for n, (a, b) in rows.items()}
+
+
+def test_input_of_a_projection_lives_longer_only_where_the_launch_takes_it_along_host_side():
+    """Where the projection is a launch of its own the tensors lie as if it could be nothing else; inside the bottleneck launch its input
+    is not overwritten by anything that the launch writes."""
+    net, _ = stage_block(256, 32)
+    for batch, along in ((100, True), (128, True), (130, False), (240, False), (400, False)):
+        assert (dict(zip([S.name for S in net.layers], reported(net, batch)))["proj"][0] == "1x1 in bottleneck<256>") == along
+        now = places(net, batch)
+        f8.f8_tuning_set("bn_proj", 0)
+        try:
+            apart = places(net, batch)
+        finally:
+            f8.f8_tuning_set("bn_proj", 1)
+        assert (now == apart) == (not along), (batch, now, apart)
+        for n in ("close", "behind"):
+            assert not along or now[n][0] >= now["x"][1] or now[n][0] + now[n][1] <= 0, (batch, n, now)
+
+
+@pytest.mark.gpu
+def test_halves_that_take_a_projection_along_where_the_whole_batch_does_not(oracle):
+    """3001 images: the whole batch runs the projection by itself, either half inside the bottleneck launch; streams switched after the weights
+    were prepared, eager and from a captured graph."""
+    net, rng = stage_block(256, 8)
+    name = lambda n: dict(zip([S.name for S in net.layers], reported(net, n)))["proj"][0]
+    assert name(3001) != "1x1 in bottleneck<256>" and name(1500) == name(1501) == "1x1 in bottleneck<256>"
+    x = wl.draw_u8(rng, (3001, 8, 8, 16))
+    x_t = torch.from_numpy(x).cuda()
+    pick = [0, 1499, 1500, 3000]
+    f8.f8_tuning_set("halves", 2)
+    try:
+        chain = f8.Chain(net).prepare(3001)
+        want = chain.run(x_t)
+        assert np.array_equal(want[pick].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[pick])))
+        out = torch.empty_like(want)
+        for streams in (2, 1, 2):
+            f8.lib().f8_chain_set_streams(chain.handle, streams)
+            assert torch.equal(chain.run(x_t), want), streams
+        graph = chain.capture(x_t, out)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+            assert torch.equal(chain.run(x_t), want)
+    finally:
+        f8.f8_tuning_set("halves", 1)
+
+
 def three_in_one(rows):
     return {i for i, (n, _) in enumerate(rows) if n.startswith(("1x1+dwconv", "conv3x3+dwconv"))}
 

@@ -262,6 +262,37 @@ def test_bottleneck_launch_only_where_it_is_ahead_host_side(batch, c, hw, stride
     assert (reported(b.net, batch)[1][0] == "bottleneck<%d>" % c) == one
 
 
+# (batch, channels, image, projection, one launch?): microseconds of a small forward around the layers, general kernels / this one
+STRIDE_2 = [
+    (64, 64, (56, 56), False, True),         # 256 workgroups: 22.4 / 20.4
+    (84, 64, (52, 52), False, False),        # 336: 23.4 / 26.3
+    (160, 64, (40, 40), False, False),       # 320: 24.7 / 27.7
+    (160, 64, (60, 60), False, False),       # 800: 44.4 / 49.6
+    (100, 64, (52, 52), True, True),         # 400: 38.9 / 36.5
+    (274, 64, (12, 50), True, False),        # 274: 28.0 / 29.6
+    (280, 64, (35, 35), True, False),        # 560: 44.2 / 46.7
+    (389, 64, (49, 49), True, False),        # 1556: 86.3 / 92.3
+    (249, 128, (28, 28), True, True),        # 498: 54.4 / 50.7
+    (259, 128, (27, 27), True, False),       # 518: 55.8 / 62.2
+    (331, 128, (49, 27), True, False),       # 1324: 100.7 / 116.8
+    (121, 256, (14, 14), True, True),        # 244: 35.3 / 28.2
+    (159, 256, (14, 14), True, False),       # 320: 37.9 / 40.1
+    (198, 256, (14, 14), True, True),        # 396: 45.6 / 43.3
+    (329, 256, (26, 13), True, False),       # 1316: 83.1 / 109.2
+]
+
+
+@pytest.mark.parametrize("batch, c, hw, projection, one", STRIDE_2)
+def test_stride_2_launch_only_where_it_is_ahead_host_side(batch, c, hw, projection, one):
+    b = wl._NetBuilder("stride_2", np.random.default_rng(68000), hw[0], 16, "u8", 5, (5, 9), (2, 6), True)
+    b.net.in_hw = hw
+    b.t[0]["hw"] = hw
+    t = b.conv("before", 0, c, 1, 1, 0)
+    s = b.conv("proj", t, 2 * c, 1, 2, 0, relu=False) if projection else -1
+    b.conv("after", b.conv("mid", t, 2 * c, 3, 2, 1), 2 * c, 1, 1, 0, res=s)
+    assert bool(taken(b.net, batch, "conv3x3_imgk_s2<%d>" % c)) == one
+
+
 def test_a_launch_has_one_name_host_side():
     """The name of a layer is that of the kernel it launches, whatever kernels its layers would take apart; a layer inside another's
     launch is "(fused)"."""

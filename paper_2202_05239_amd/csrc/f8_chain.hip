@@ -167,11 +167,12 @@ struct f8_chain {
   //     256 48.4 -> 46.3; from 6 x 6: 32 14.1 -> -, -, 14.0, 500 32.9 -> 34.9
   // The 3x3 layer by itself: 64 -> 128 batch 64 23.4 -> 21.1; 128 -> 256 24 17.1 -> -, 16.5, 64 20.4 -> -, 19.4, 128 28.8 -> 26.3,
   // 192 38.8 -> 39.8; 256 -> 512 24 15.7 -> -, -, 15.4, 64 24.6 -> -, 19.2, 128 28.1 -> 24.2, 192 36.5 -> 36.4.
-  // A workgroup lasts as long as one of the general kernel's walks through several tiles, so what counts is how full the last round of workgroups is: 52 x 52, 84
-  // images (336) 23.4 -> 26.3; 60 x 60, 64 (320) 23.4 -> 25.7, 160 (800) 44.4 -> 49.6.  By itself the layer takes the kernel for one round, 250 random
-  // sizes: never behind by more than 2 %.  With the projection (334 sizes): 64 channels, last round half full 0.87 - 0.99 of the two launches' time up to 1024, less than
-  // half 0.93 - 1.09, beyond 1024 0.90 - 1.08; 128 channels to 512 0.92 - 0.99, beyond 0.95 - 1.16; 256 channels with all of K per wave, half full 0.93 - 0.95, less 1.03 -
-  // 1.06, beyond 512 1.18 - 1.31.
+  // There is no launch to save there, and past one round of workgroups it is behind whenever the last round is thin (52 x 52, 84 images, 336 workgroups,
+  // 23.4 -> 26.3; 60 x 60, 160 images, 800, 44.4 -> 49.6): one round only, 250 random sizes, never behind by more than 2 %.
+  // With the projection the launch that it saves is worth more in a forward than around the layer alone.  64 channels: at any number of workgroups
+  // (ResNet-18 at 90 images, 360, 321 -> 313 us, 340 images, 1360, 825 -> 814, 560 1281 -> 1244; alone, up to 8 % behind in thin rounds).  128 channels: to 1024
+  // (alone, 12 sizes beyond: 4 - 16 % behind; in a forward to 680 ahead by 0 - 9 us of 700, beyond level).  256 channels: to 512 (alone, beyond: 18 - 31 %
+  // behind; ResNet-18 at 320 images 788 -> 778 without it, 400 970 -> 960).
   int s2_waves(size_t i, int batch) const {
     if (s2[i] == 0 || conv_s2 == 0 || keep_all) return 0;
     const size_t a = s2[i] == 1 ? i : (size_t)s2_proj[i];
@@ -188,10 +189,7 @@ struct f8_chain {
     long long wgs = conv_s2_workgroups(L.Cin, L.Cout, batch, g.H, g.W, wk);
     while (wgs < 176 && wk < most) wgs = conv_s2_workgroups(L.Cin, L.Cout, batch, g.H, g.W, wk *= 2);
     if (!projection) return fills && wgs >= 176 && wgs <= 256 ? wk : 0;
-    if (wgs > 256) {
-      const bool half = wgs % 256 == 0 || wgs % 256 >= 128;
-      if (!fills || wgs > (L.Cin == 64 ? 1024 : 512) || (!half && wk == 1 && L.Cin != 128)) return 0;
-    }
+    if ((!fills && wgs > 256) || (L.Cin == 128 && wgs > 1024) || (L.Cin == 256 && wgs > 512)) return 0;
     return (long long)batch * g.P * g.Q >= (L.Cin == 64 ? 4500 : L.Cin == 128 ? 2300 : 500) ? wk : 0;
   }
   // Two 3x3 layers of 64 or 128 channels of which the second is the first's only reader and may have the first's input as its shortcut

@@ -269,14 +269,12 @@ STRIDE_2 = [
     (160, 64, (40, 40), False, False),       # 320: 24.7 / 27.7
     (160, 64, (60, 60), False, False),       # 800: 44.4 / 49.6
     (100, 64, (52, 52), True, True),         # 400: 38.9 / 36.5
-    (274, 64, (12, 50), True, False),        # 274: 28.0 / 29.6
-    (280, 64, (35, 35), True, False),        # 560: 44.2 / 46.7
-    (389, 64, (49, 49), True, False),        # 1556: 86.3 / 92.3
+    (90, 64, (56, 56), True, True),          # 360: ResNet-18 321 / 313
+    (340, 64, (56, 56), True, True),         # 1360: ResNet-18 825 / 814
     (249, 128, (28, 28), True, True),        # 498: 54.4 / 50.7
-    (259, 128, (27, 27), True, False),       # 518: 55.8 / 62.2
     (331, 128, (49, 27), True, False),       # 1324: 100.7 / 116.8
     (121, 256, (14, 14), True, True),        # 244: 35.3 / 28.2
-    (159, 256, (14, 14), True, False),       # 320: 37.9 / 40.1
+    (159, 256, (14, 14), True, True),        # 320: ResNet-18 471 / 464
     (198, 256, (14, 14), True, True),        # 396: 45.6 / 43.3
     (329, 256, (26, 13), True, False),       # 1316: 83.1 / 109.2
 ]

@@ -418,11 +418,12 @@ template <int C, int WK, bool NAT, int MG> int launch_as(const ConvImgkParams &p
 template <int C, int WK, bool NAT> int launch_c(const ConvImgkParams &p, hipStream_t stream) {
   // Twice the waves where a workgroup has a CU (64 channels: half a one) to itself; with more of them, workgroups of fewer waves side by
   // side cover one another's waits.  Microseconds of a layer, single / twice the waves, 3x3 layers of 64 channels on 56 x 56 at 16 images
-  // 6.97 / 5.52, 32 9.73 / 7.55, 64 13.42 / 13.34, 128 24.8 / 23.0, 256 40.9 / 42.8; 128 on 28 x 28 at 16 8.4 / 7.2, 64 11.5 / 10.8, 128 (512 workgroups)
+  // 6.97 / 5.52, 32 9.73 / 7.55, 64 (896 workgroups) 13.42 / 13.34, with a residual (beyond 1024 workgroups they all have one) 50 x 50 at 128 (1664) 40.1 / 42.1, 35 x 35 at
+  // 299 (1794) 43.5 / 45.6, 56 x 56 at 96 (1344) 37.7 / 38.5; 128 on 28 x 28 at 16 8.4 / 7.2, 64 11.5 / 10.8, 128 (512 workgroups)
   // 20.0 / 22.4; 256 on 14 x 14 at 32 8.8 / 7.9, 64 12.0 / 11.1, 128 17.6 / 17.5, 192 27.7 / 31.2; 512 on 7 x 7 at 32 9.5 / 9.0, 64 14.2 / 13.4, 256 39.7 / 40.6.
   const Units u = cut<C>(p.B, p.H, p.W, WK);
   // Weights as they are (a single call), 64 channels on 56 x 56, at 8 images 9.0 (conv_wavek) / 6.3, 16 7.9 / 6.7, 32 10.7 / 8.6, 64 14.5 / 16.0.
-  return u.units * (C / (32 * (Shape<C>::NW / WK))) <= (NAT ? 512 : C == 64 ? 2048 : 256) ? launch_as<C, WK, NAT, 2>(p, stream) : launch_as<C, WK, NAT, 1>(p, stream);
+  return u.units * (C / (32 * (Shape<C>::NW / WK))) <= (NAT ? 512 : C == 64 ? 1024 : 256) ? launch_as<C, WK, NAT, 2>(p, stream) : launch_as<C, WK, NAT, 1>(p, stream);
 }
 
 Units cut_any(int C, int B, int H, int W, int WK) {

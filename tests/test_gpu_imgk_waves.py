@@ -10,7 +10,7 @@ from paper_2202_05239_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 # channels, image, waves that share K, batch
-CASES = [(64, (56, 56), 1, 2048 // 14), (64, (56, 56), 1, 2048 // 14 + 1), (64, (5, 61), 1, 3), (64, (1, 1), 1, 2),
+CASES = [(64, (56, 56), 1, 1024 // 14), (64, (56, 56), 1, 1024 // 14 + 1), (64, (56, 56), 1, 2048 // 14), (64, (56, 56), 1, 2048 // 14 + 1), (64, (5, 61), 1, 3), (64, (1, 1), 1, 2),
          (128, (28, 28), 1, 64), (128, (28, 28), 1, 65), (128, (9, 30), 2, 5), (256, (14, 14), 2, 64), (256, (14, 14), 2, 65), (256, (14, 14), 4, 32),
          (256, (3, 5), 4, 9), (512, (7, 7), 4, 31), (512, (7, 7), 2, 65), (512, (7, 7), 1, 5)]
 

@@ -390,6 +390,7 @@ template <int C, int WK, bool NAT, int MG> int launch_as(const ConvImgkParams &p
   if (u.images < 1) return (int)hipErrorInvalidValue;
   const int slices = C / (32 * (S::NW / WK));
   const long long grid = u.units * slices;
+  if (grid > 0x7fffffffLL) return (int)hipErrorInvalidValue;
   // Unit by unit an XCD reads all weights, and of the images only the eighth of the batch that it computes and, the layers before being
   // ordered alike, mostly wrote itself: those lie in its L2.  Slice by slice it reads an eighth of the weights and images that
   // other XCDs wrote, from beyond its L2 at half the rate (64 KB per workgroup: 5.1 k cycles where this XCD wrote them, 10.3 k elsewhere).

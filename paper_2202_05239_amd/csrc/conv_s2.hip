@@ -240,17 +240,19 @@ __global__ __launch_bounds__(NT, 1) void conv_s2_kernel(const ConvS2Params p, co
   const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(p.y + px0 * p.N, 0, out_bytes, 0x00027000);
   // ---- K loop over the wave's MBW blocks: a pass is a row of the window, 3 taps x KSW slices; activation fragments one slice ahead,
   // one request at a time behind the matrix instructions
+  v16i acc[MH];
+#pragma unroll
+  for (int j = 0; j < MH; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[j][i] = a0[i >> 2][i & 3];
   auto contract = [&](auto blocks) {
   constexpr int MBW = decltype(blocks)::value;
   lds_u8 *ar[MBW];
-  v16i acc[MBW];
   v4i xf[2][MBW];
 #pragma unroll
   for (int j = 0; j < MBW; ++j) {
     ar[j] = (lds_u8 *)lds + kg * u.group + at_px[j] * GP + 16 * half;
     xf[0][j] = *(lds_v4i *)(ar[j]);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[j][i] = a0[i >> 2][i & 3];
   }
   const int row_step = u.pcols * GP;
 #pragma unroll 1
@@ -280,28 +282,29 @@ __global__ __launch_bounds__(NT, 1) void conv_s2_kernel(const ConvS2Params p, co
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  };
+  if (b0 == 0 || MB % 2 == 0) contract(std::integral_constant<int, MH>{});
+  else contract(std::integral_constant<int, MB - MH>{});      // (the block past the last: start values, which go nowhere)
 
   if constexpr (WK == 1) {
     // every wave has its sums complete: a lane's 16 channels of a pixel are a 16-byte piece of an output row
 #pragma unroll
-    for (int j = 0; j < MBW; ++j) {
+    for (int j = 0; j < MH; ++j) {
+      if (MH * 2 > MB && b0 + j >= MB) continue;
       settle_matrix_result(acc[j]);
       __builtin_amdgcn_raw_buffer_store_b128(requant16(acc[j], c1, p.shift), yres, out_at(32 * (b0 + j) + l32, n_lane), 0, 0);
     }
   } else {
-    __syncthreads();                                 // the patch is no longer read
+    __syncthreads();                                 // the patch is no longer read (behind the lambda: both halves of the waves at one barrier)
     uint8_t *part = lds + ((wave % NG) * MB + b0) * (32 * PART_PITCH) + l32 * PART_PITCH + half * 64;
 #pragma unroll
-    for (int j = 0; j < MBW; ++j)
+    for (int j = 0; j < MH; ++j) {
+      if (MH * 2 > MB && b0 + j >= MB) continue;
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<v4i *>(part + j * (32 * PART_PITCH) + g * 16) =
             v4i{acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]};
-  }
-  };
-  if (b0 == 0 || MB % 2 == 0) contract(std::integral_constant<int, MH>{});
-  else contract(std::integral_constant<int, MB - MH>{});
-  if constexpr (WK > 1) {
+    }
     // the waves' sums meet; then piece tid % (2 WN) of the pixels tid / (2 WN) + k * IPP
     constexpr int IPP = NT / (2 * WN), ITEMS = (MB * 32 + IPP - 1) / IPP;
     const int piece = tid % (2 * WN), pixel0 = tid / (2 * WN);

@@ -251,6 +251,8 @@ f8_status f8_chain_set_fusion(f8_chain *c, int fusion);
  * longer, the call runs on one stream.  n_streams = 1 (the default)
  * turns it off. */
 f8_status f8_chain_set_streams(f8_chain *c, int n_streams);
+/* The number of streams f8_chain_run works on at this batch, 1 or 2 (1 for a null chain). */
+int f8_chain_streams(const f8_chain *c, int batch);
 void f8_chain_destroy(f8_chain *c);
 
 /* Measurement aids for the chain (not on the hot path).

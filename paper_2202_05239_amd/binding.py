@@ -23,7 +23,7 @@ TORCH_DTYPE = {"u8": torch.uint8, "s8": torch.int8, "s32": torch.int32,
 EXPORTS = [
     "f8_gemm_fixed", "f8_conv2d_fixed", "f8_conv2d_fixed_noalloc", "f8_conv2d_fixed_ws", "f8_conv_workspace_bytes", "f8_conv2d_fixed_dual", "f8_dwconv_fixed", "f8_maxpool", "f8_global_pool_fixed",
     "f8_chain_create", "f8_chain_workspace_bytes", "f8_chain_prepare", "f8_chain_run",
-    "f8_chain_tensor", "f8_chain_set_keep_all", "f8_chain_set_fusion", "f8_chain_set_streams", "f8_chain_destroy",
+    "f8_chain_tensor", "f8_chain_set_keep_all", "f8_chain_set_fusion", "f8_chain_set_streams", "f8_chain_streams", "f8_chain_destroy",
     "f8_chain_num_layers", "f8_chain_layer_info", "f8_chain_profile",
     "f8_clip_from_alpha", "f8_status_str", "f8_release_scratch", "f8_abi_version", "f8_copy_bytes",
     "f8_tuning_set", "f8_tuning_get", "f8_mfma_i8_yardstick", "f8_mfma_i8_yardstick_operands",
@@ -105,6 +105,7 @@ def lib():
     L.f8_chain_set_keep_all.argtypes = [vp, i32]
     L.f8_chain_set_fusion.argtypes = [vp, i32]
     L.f8_chain_set_streams.argtypes = [vp, i32]
+    L.f8_chain_streams.argtypes = [vp, i32]
     L.f8_chain_destroy.argtypes = [vp]
     L.f8_chain_num_layers.argtypes = [vp]
     L.f8_chain_layer_info.argtypes = [vp, i32, i32, ctypes.c_char_p, i32, ctypes.POINTER(ctypes.c_double),
@@ -470,6 +471,10 @@ class Chain:
         _check(lib().f8_chain_run(self.handle, _ptr(x), _ptr(out), _ptr(self.workspace), B, _stream()),
                "f8_chain_run")
         return out
+
+    def streams_at(self, batch):
+        """The number of streams run() works on at this batch, 1 or 2."""
+        return lib().f8_chain_streams(self.handle, batch)
 
     def capture(self, x, out):
         """Record one run of the chain on (x, out) into a HIP graph and return it (a

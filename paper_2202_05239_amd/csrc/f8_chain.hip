@@ -1448,6 +1448,8 @@ f8_status f8_chain_set_streams(f8_chain *c, int n_streams) {
   return F8_OK;
 }
 
+int f8_chain_streams(const f8_chain *c, int batch) { return c && c->side_by_side(batch) ? 2 : 1; }
+
 f8_status f8_chain_tensor(const f8_chain *c, int id, void *workspace, int batch, void **ptr, int *h, int *w,
                           int *ch, int *dtype, int *live_at_end) {
   if (!c) return F8_ERR_NULL;

@@ -45,7 +45,7 @@ def test_a_closing_layer_with_two_readers_host_side(first, second):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("first, second", [(256, 128), (128, 256)])
-def test_a_closing_layer_with_two_readers(oracle, first, second):
+def test_a_closing_layer_with_two_readers(oracle, always_halves, first, second):
     net, rng = two_readers(first, second)
     x = wl.draw_u8(rng, (200, 28, 28, 16))
     pick = [0, 49, 99, 100, 199]
@@ -53,6 +53,7 @@ def test_a_closing_layer_with_two_readers(oracle, first, second):
     x_t = torch.from_numpy(x).cuda()
     for streams, n in ((1, 100), (2, 200)):                      # (either half of 200 images takes both launches too)
         chain = f8.Chain(net, streams=streams).prepare(n)
+        assert chain.streams_at(n) == streams
         assert chain.layer_info(1, 100)[0] == "bottleneck<128>" and chain.layer_info(4, 100)[0] != "(fused)"
         got = chain.run(x_t[:n]).cpu().numpy()
         assert np.array_equal(got[[p for p in pick if p < n]], want[:sum(p < n for p in pick)])
@@ -159,6 +160,7 @@ def test_halves_that_take_a_projection_along_where_the_whole_batch_does_not(orac
         out = torch.empty_like(want)
         for streams in (2, 1, 2):
             f8.lib().f8_chain_set_streams(chain.handle, streams)
+            assert chain.streams_at(3001) == streams
             assert torch.equal(chain.run(x_t), want), streams
         graph = chain.capture(x_t, out)
         for _ in range(3):
@@ -390,7 +392,7 @@ def test_every_layer_is_computed_by_one_launch_host_side(first):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("seed", range(12))
-def test_launches_of_several_layers_in_random_graphs(oracle, seed):
+def test_launches_of_several_layers_in_random_graphs(oracle, always_halves, seed):
     """Every tensor that is whole after a run, and the result on one stream, on two and from a captured graph, against the chain that
     keeps all tensors (layer by layer) and, for two images, against the oracle."""
     net, rng = random_graph(1000 + seed)
@@ -408,6 +410,7 @@ def test_launches_of_several_layers_in_random_graphs(oracle, seed):
             t = chain.tensor(dst) if dst > 0 else None
             assert t is None or torch.equal(t, apart.tensor(dst)), (batch, L.name, dst)
     halves = f8.Chain(net, streams=2).prepare(batch)
+    assert halves.streams_at(batch) == 2
     out = torch.empty_like(want)
     graph = halves.capture(x_t, out)
     for _ in range(3):
@@ -424,8 +427,8 @@ def taken(net, batch, what):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("C, hw, batch", [(64, 56, 24), (64, 28, 87), (128, 28, 31), (128, 28, 335)])
-def test_basic_block_by_the_default_choice_on_two_streams(oracle, C, hw, batch):
-    """No switch set.  24: the whole batch takes the launch, its halves do not; 87 and 31: one of the halves does; 335: neither the whole
+def test_basic_block_by_the_default_choice_on_two_streams(oracle, always_halves, C, hw, batch):
+    """No switch of the launches set.  24: the whole batch takes the launch, its halves do not; 87 and 31: one of the halves does; 335: neither the whole
     batch nor its larger half does, the smaller one does (131072 pixels).  With and without a shortcut, from a captured graph too."""
     rng = np.random.default_rng(65000 + batch)
     x = wl.draw_u8(rng, (batch, hw, hw, 16))
@@ -437,6 +440,7 @@ def test_basic_block_by_the_default_choice_on_two_streams(oracle, C, hw, batch):
         b.conv("after", b.conv("b", b.conv("a", t, C, 3, 1, 1), C, 3, 1, 1, res=t if shortcut else -1), 32, 1, 1, 0)
         want = oracle.run_network(b.net, np.ascontiguousarray(x[pick]))
         one, two = f8.Chain(b.net).prepare(batch), f8.Chain(b.net, streams=2).prepare(batch)
+        assert (one.streams_at(batch), two.streams_at(batch)) == (1, 2)
         got = one.run(x_t)
         assert np.array_equal(got[pick].cpu().numpy(), want)
         out = torch.empty_like(got)
@@ -471,6 +475,7 @@ def test_inverted_residual_launches_on_halves_of_either_choice(oracle, batch):
     want = f8.Chain(net).prepare(batch).run(x_t)
     assert np.array_equal(want[pick].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[pick])))
     chain = f8.Chain(net, streams=2).prepare(batch)
+    assert chain.streams_at(batch) == 2
     out = torch.empty_like(want)
     graph = chain.capture(x_t, out)
     for _ in range(3):

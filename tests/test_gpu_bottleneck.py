@@ -77,13 +77,14 @@ def test_three_layers_of_a_bottleneck_in_one_launch(oracle, k):
 
 
 @pytest.mark.gpu
-def test_blocks_in_one_launch_through_streams_and_graphs(oracle):
+def test_blocks_in_one_launch_through_streams_and_graphs(oracle, always_halves):
     """ResNet-50 with two formats, 96 x 96 images: halves on two streams (batches that take the launch and batches that do
     not), a captured graph replayed with eager work between, against the oracle."""
     x, net = wl.resnet50_private_fl(batch=5, hw=96)
     want = oracle.run_network(net, x)
     x_t = torch.from_numpy(x).cuda()
     chain = f8.Chain(net, streams=2).prepare(5)
+    assert chain.streams_at(5) == 2
     out = torch.empty((5,) + chain.out_shape, dtype=chain.out_dtype, device="cuda")
     graph = chain.capture(x_t, out)
     for _ in range(3):

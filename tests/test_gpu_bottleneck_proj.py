@@ -82,7 +82,7 @@ def test_projection_with_a_second_reader_stays_apart(oracle):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("private", [False, True])
-def test_whole_network_with_and_without(private):
+def test_whole_network_with_and_without(oracle, always_halves, private):
     """ResNet-50 on 17 images: the projections along or apart, one stream and two from a captured graph: the same logits."""
     x, net = (wl.resnet50_private_fl if private else wl.config4)(batch=17, hw=96)
     x_t = torch.from_numpy(x).cuda()
@@ -92,6 +92,7 @@ def test_whole_network_with_and_without(private):
         try:
             for streams in (1, 2):
                 chain = f8.Chain(net, streams=streams).prepare(17)
+                assert chain.streams_at(17) == streams
                 outs.append(chain.run(x_t))
                 out = torch.empty_like(outs[0])
                 graph = chain.capture(x_t, out)
@@ -103,3 +104,5 @@ def test_whole_network_with_and_without(private):
         finally:
             f8.f8_tuning_set("bn_proj", 1)
     assert all(torch.equal(o, outs[0]) for o in outs)
+    pick = [0, 7, 8, 16]
+    assert np.array_equal(outs[0][pick].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[pick])))

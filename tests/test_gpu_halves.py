@@ -14,15 +14,19 @@ NETS = [(wl.config4, 5, 96), (wl.resnet50_private_fl, 5, 96), (wl.config3, 24, 9
 
 
 @pytest.mark.parametrize("k", range(len(NETS)))
-def test_halves_side_by_side_or_not(k):
+def test_halves_side_by_side_or_not(oracle, k):
     fn, batch, hw = NETS[k]
+    long_enough = hw == 224                   # (the line: 15 images of ResNet-18 at 224 x 224, far above the batches of the small images)
     x, net = fn(batch=batch, hw=hw)
     x_t = torch.from_numpy(x).cuda()
     want = f8.Chain(net).prepare(batch).run(x_t)
+    pick = sorted({0, batch // 2, batch - 1})
+    assert np.array_equal(want[pick].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[pick])))
     try:
         for mode in (1, 2):
             f8.f8_tuning_set("halves", mode)
             chain = f8.Chain(net, streams=2).prepare(batch)
+            assert chain.streams_at(batch) == (2 if mode == 2 or long_enough else 1)
             out = torch.empty_like(want)
             graph = chain.capture(x_t, out)
             for _ in range(3):

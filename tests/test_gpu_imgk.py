@@ -76,7 +76,7 @@ def test_waves_sharing_k_follow_the_batch():
     assert not any(f8.Chain(small).layer_info(i, 300)[0] == "conv3x3_imgk<64>" for i in range(len(small.layers)))
 
 
-def test_copies_of_weights_for_the_halves_of_a_batch(oracle):
+def test_copies_of_weights_for_the_halves_of_a_batch(oracle, always_halves):
     """401 images of 24 x 24 x 64: the whole batch does not take the kernel, its halves on two streams do."""
     rng = np.random.default_rng(5)
     b = wl._NetBuilder("halves", rng, 24, 64, "u8", 5, (5, 9), (2, 6), True)
@@ -86,12 +86,14 @@ def test_copies_of_weights_for_the_halves_of_a_batch(oracle):
     whole = f8.Chain(b.net).prepare(401)
     assert not whole.layer_info(0, 401)[0].startswith("conv3x3_imgk") and whole.layer_info(0, 200)[0] == "conv3x3_imgk<64>"
     halves = f8.Chain(b.net, streams=2).prepare(401)
+    assert halves.streams_at(401) == 2
     got = halves.run(x_t)
     assert torch.equal(got, whole.run(x_t))
     pick = [0, 1, 199, 200, 201, 400]
     assert np.array_equal(got[pick].cpu().numpy(), oracle.run_network(b.net, np.ascontiguousarray(x[pick])))
     later = f8.Chain(b.net).prepare(401)                # two streams switched on after the workspace was made
     f8.lib().f8_chain_set_streams(later.handle, 2)
+    assert later.streams_at(401) == 2
     assert torch.equal(later.run(x_t), got)
 
 

@@ -207,6 +207,7 @@ def full_batch_logits(oracle, x, net, what):
     two-stream run, replayed with eager work in between, must give the same bits."""
     xt = torch.from_numpy(x).to(DEV)
     chain = f8.Chain(net, streams=2).prepare(x.shape[0])
+    assert chain.streams_at(x.shape[0]) == 2
     out = chain.run(xt)
     torch.cuda.synchronize()
     one = f8.Chain(net).prepare(x.shape[0]).run(xt)

@@ -70,8 +70,7 @@ def test_stride_2_layer_and_projection(oracle, k, wk):
 
 
 def test_choice_follows_the_batch():
-    """ResNet-18's three stride-2 layers take their projections along at 64 images, none does at one; halves of a batch on two streams
-    choose for themselves."""
+    """ResNet-18's three stride-2 layers take their projections along at 64 images, none does at one, or at nine of 96 x 96."""
     _, net = wl.config3(batch=1)
     chain = f8.Chain(net)
     count = lambda b: sum(chain.layer_info(i, b)[0].endswith("+1x1") for i in range(len(net.layers)))
@@ -81,3 +80,30 @@ def test_choice_follows_the_batch():
     outs = [f8.Chain(net, streams=s).prepare(9).run(x_t) for s in (1, 2)]
     outs.append(f8.Chain(net, keep_all=True).prepare(9).run(x_t))
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+# ResNet-18, 96 x 96: channels of the stride-2 layers that take their projections along in the whole batch, its first half and its second
+@pytest.mark.parametrize("batch, whole, low, high", [(63, [64, 256], [], [64]), (64, [64, 128, 256], [64], [64])])
+def test_halves_of_a_batch_choose_for_themselves(oracle, always_halves, batch, whole, low, high):
+    x, net = wl.config3(batch=batch, hw=96)
+    x_t = torch.from_numpy(x).cuda()
+    one, two = f8.Chain(net).prepare(batch), f8.Chain(net, streams=2).prepare(batch)
+    assert two.streams_at(batch) == 2
+
+    def taken(n):
+        names = [two.layer_info(i, n)[0] for i in range(len(net.layers))]
+        return [c for c in (64, 128, 256) if "conv3x3_imgk_s2<%d>+1x1" % c in names]
+
+    assert [taken(n) for n in (batch, batch // 2, batch - batch // 2)] == [whole, low, high]
+    want = one.run(x_t)
+    pick = [0, batch // 2 - 1, batch // 2, batch - 1]
+    assert np.array_equal(want[pick].cpu().numpy(), oracle.run_network(net, np.ascontiguousarray(x[pick])))
+    assert torch.equal(two.run(x_t), want) and torch.equal(f8.Chain(net, keep_all=True).prepare(batch).run(x_t), want)
+    out = torch.empty_like(want)
+    graph = two.capture(x_t, out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert torch.equal(two.run(x_t), want)

@@ -533,11 +533,12 @@ struct f8_chain {
   int halves = 1;
   double image_us = 0;       // operations at 1 POP/s and layers' outputs at 2 TB/s of one image
   // Whether the halves run side by side.  Every launch is there twice then, and where a layer takes hardly more than its launch the halves only wait for
-  // one another.  Microseconds of a forward, whole / halves, 224 x 224 and 160 x 160: ResNet-18 16 131 / 189 and 114 / 158, 64 222 / 269 and 184 / 222, 192
+  // one another.  One estimate for all networks, which takes out the clearest losses only:  Microseconds of a forward, whole / halves, 224 x 224 and 160 x 160: ResNet-18 16 131 / 189 and 114 / 158, 64 222 / 269 and 184 / 222, 192
   // 511 / 501; ResNet-50 8 227 / 326 and 201 / 328, 32 347 / 381 and 275 / 330, 64 555 / 536 and 356 / 390, 96 836 / 704 and 523 / 476; MobileNetV1 32 203 /
   // 250 and 160 / 206, 192 523 / 556; MobileNetV2 16 148 / 175 and 125 / 156, 64 306 / 315 and 212 / 218, 96 431 / 413 and 282 / 258.  By the estimate per layer the
   // line lies at 13 images of ResNet-50 at 224 x 224, 15 of ResNet-18, 26 of MobileNetV1 and 44 of MobileNetV2 (160 x 160: twice as many), below the
-  // crossover of each: on the other side the caller's choice stands.
+  // crossover of each (about 50, 190, beyond 192 and 75 in that order), which no one number per layer can follow: between the two the caller's choice stands,
+  // and by these figures it loses up to 44 % (ResNet-18, 16 images).
   bool side_by_side(int batch) const {
     if (n_streams != 2 || keep_all || batch < 2) return false;
     return halves == 2 || image_us * batch >= 3.2 * (double)layers.size();

@@ -394,7 +394,11 @@ f8_status f8_mfma_i8_yardstick_operands(int32_t *sink, int iters, uint32_t seed,
  * "conv_pair" (1 = on: the two 3x3 layers of a basic residual block in one launch where both take that kernel),
  * "dw_pw" (1 = on where it pays; 2: a depthwise layer and the 1x1 layer behind it in one launch wherever
  * they fit), "pw_dw_pw" (1 = on where it pays: the 1x1 layer in front of such a pair in the same launch; 2: wherever the three fit), "bottleneck" (1 = on where it pays; 2: the last two layers of a bottleneck block and the first of the next in one
- * launch wherever they fit; 3 and 4: the same, always with the narrower or the wider of its two tiles), "conv_img_min" (96: fewest images, or bands of 28 image rows, for which a chain takes the
+ * launch wherever they fit; 3 and 4: the same, always with the narrower or the wider of its two tiles), "bn_proj" (1 = on: such a
+ * launch also computes the projection whose result is the block's shortcut, where it can; 0: never), "conv_s2" (1 = on: 3x3 layers of stride 2 in
+ * the image-stationary kernel, with the 1x1 layer of stride 2 beside them, where that pays; 0: never; 10 + n: with n = 1, 2 or 4 waves sharing K
+ * wherever there is such a kernel), "halves" (1: a chain on two streams takes the halves of a batch apart unless its layers are
+ * too short for that, see f8_chain_set_streams; 2: in any case), "conv_img_min" (96: fewest images, or bands of 28 image rows, for which a chain takes the
  * image-stationary 3x3 kernels).  The environment variables F8_<NAME IN CAPITALS> give the initial
  * values; they are read once, when the library first looks at a switch, never on the launch path.
  * f8_tuning_set returns 0, or -1 for an unknown name; the chain switches ("stem_pool" to

@@ -21,8 +21,9 @@ const TuningName kTuningNames[] = {
     {"pw_wide", "F8_PW_WIDE", &Tuning::pw_wide},                 {"conv_img_min", "F8_CONV_IMG_MIN", &Tuning::conv_img_min},
     {"pw_mid", "F8_PW_MID", &Tuning::pw_mid},                    {"imgk", "F8_IMGK", &Tuning::imgk},
     {"dw_pw", "F8_DW_PW", &Tuning::dw_pw},                       {"bottleneck", "F8_BOTTLENECK", &Tuning::bottleneck},
-    {"conv_s2", "F8_CONV_S2", &Tuning::conv_s2},               {"bn_proj", "F8_BN_PROJ", &Tuning::bn_proj},               {"halves", "F8_HALVES", &Tuning::halves},
-                 {"pw_dw_pw", "F8_PW_DW_PW", &Tuning::pw_dw_pw},              {"conv_pair", "F8_CONV_PAIR", &Tuning::conv_pair},
+    {"pw_dw_pw", "F8_PW_DW_PW", &Tuning::pw_dw_pw},              {"conv_pair", "F8_CONV_PAIR", &Tuning::conv_pair},
+    {"conv_s2", "F8_CONV_S2", &Tuning::conv_s2},                 {"bn_proj", "F8_BN_PROJ", &Tuning::bn_proj},
+    {"halves", "F8_HALVES", &Tuning::halves},
 };
 }  // namespace
 

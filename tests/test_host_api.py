@@ -357,6 +357,19 @@ def test_conv_img_limit_is_a_limit_and_no_switch_host_side():
         f8.f8_tuning_set("conv_img_min", 96)
 
 
+def test_every_switch_is_documented_host_side():
+    """The switches that f8_tuning_set knows are those that the header lists, by the names of their environment variables too."""
+    with open(os.path.join(ROOT, "paper_2202_05239_amd", "csrc", "f8_api.hip")) as f:
+        known = re.findall(r'\{"(\w+)", "(\w+)", &Tuning::\w+\}', f.read())
+    with open(os.path.join(ROOT, "include", "f8.h")) as f:
+        listed = f.read().split("Tuning switches:")[1].split("*/")[0]
+    names = set(re.findall(r'"(\w+)"', listed))
+    assert len(known) > 15 and {n for n, _ in known} == names
+    assert all(env == "F8_" + n.upper() for n, env in known)
+    assert all(f8.f8_tuning_get(n) != -1 for n in names - {"conv_variant", "wavek_variant"})
+    assert f8.f8_tuning_get("no_such_switch") == -1
+
+
 def test_binding_refuses_to_run_without_library(monkeypatch):
     monkeypatch.setattr(f8, "_lib", None)
     monkeypatch.setattr(f8, "LIB_PATH", "/nonexistent/libf8.so")

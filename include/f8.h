@@ -262,7 +262,9 @@ void f8_chain_destroy(f8_chain *c);
  *   kernel_name, at most name_len bytes with the terminator) and the layer's algorithmic
  *   work for `batch` images: operations (2 per multiply-accumulate; 0 for pools) and
  *   bytes (every operand and result touched once).  Where one launch computes several layers,
- *   one of them has its name and all of its work, the others are "(fused)" with none.
+ *   one of them has its name and all of its work, the others are "(fused)" with none; but the projection inside a
+ *   bottleneck block's launch is "1x1 in bottleneck<C>" with its own operations, input and weights, which the launch's
+ *   name then does not count.
  * f8_chain_profile: runs the chain 2 * `repeats` times with a HIP event recorded on
  *   `stream` before and after every layer, once with every layer launched once and once
  *   with every layer launched five times back to back; the difference divided by four is

@@ -1,5 +1,5 @@
 """The image-stationary 3x3 kernel with single and twice the waves: on either side of the line between the two, last bands and images missing,
-against the general kernel; single calls of 64 channels on either side of theirs."""
+against the general kernel and, for a few images, the oracle; single calls of 64 channels on either side of theirs."""
 import numpy as np
 import pytest
 import torch
@@ -16,14 +16,15 @@ CASES = [(64, (56, 56), 1, 1024 // 14), (64, (56, 56), 1, 1024 // 14 + 1), (64, 
 
 
 @pytest.mark.parametrize("k", range(len(CASES)))
-def test_single_and_twice_the_waves(k):
+def test_single_and_twice_the_waves(oracle, k):
     C, hw, wk, batch = CASES[k]
     rng = np.random.default_rng(93000 + k)
     b = wl._NetBuilder("waves%d" % k, rng, hw[0], C, "u8", 5, (6, 9), (2, 6), True)
     b.net.in_hw = hw
     b.t[0]["hw"] = hw
     b.conv("second", b.conv("first", 0, C, 3, 1, 1), C, 3, 1, 1, res=0)
-    x = torch.from_numpy(wl.draw_u8(rng, (batch,) + hw + (C,))).cuda()
+    x_np = wl.draw_u8(rng, (batch,) + hw + (C,))
+    x = torch.from_numpy(x_np).cuda()
     outs = []
     try:
         for mode in (10 + wk, 0):
@@ -36,6 +37,10 @@ def test_single_and_twice_the_waves(k):
         f8.f8_tuning_set("imgk", 1)
         f8.f8_tuning_set("conv_img", 1)
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    pick = sorted({0, batch // 2, batch - 1})
+    want = oracle.run_network(b.net, np.ascontiguousarray(x_np[pick]), keep_all=True)
+    for got, dst in zip(outs[0], (b.net.layers[-1].dst, 1)):
+        assert np.array_equal(got[pick].cpu().numpy(), want[dst])
 
 
 @pytest.mark.parametrize("batch", [3, 4, 36, 37])

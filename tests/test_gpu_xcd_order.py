@@ -1,5 +1,6 @@
 """Kernels whose workgroups are ordered so that the k-th eighth of the pixels is XCD k's: units that do not divide by 8 or by the
-workgroups, and both orders of the image-stationary kernel's workgroups, against the general kernel on the same operands."""
+workgroups, and both orders of the image-stationary kernel's workgroups, against the general kernel on the same operands and, for a few
+images, the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -24,14 +25,15 @@ CASES = [
 
 
 @pytest.mark.parametrize("k", range(len(CASES)))
-def test_every_unit_is_computed_once(k):
+def test_every_unit_is_computed_once(oracle, k):
     on, name, hw, cin, cout, ks, batch = CASES[k]
     rng = np.random.default_rng(88000 + k)
     b = wl._NetBuilder("order%d" % k, rng, hw[0], cin, "u8", 5, (5, 9), (2, 6), True)
     b.net.in_hw = hw
     b.t[0]["hw"] = hw
     b.conv("second", b.conv("first", 0, cout, ks, 1, ks // 2), 16, 1, 1, 0)
-    x = torch.from_numpy(wl.draw_u8(rng, (batch,) + hw + (cin,))).cuda()
+    x_np = wl.draw_u8(rng, (batch,) + hw + (cin,))
+    x = torch.from_numpy(x_np).cuda()
     outs = []
     for switches in (on, dict(imgk=0, conv_img=0, conv_ws=0)):
         old = {n: f8.f8_tuning_get(n) for n in switches}
@@ -46,3 +48,6 @@ def test_every_unit_is_computed_once(k):
             for n, v in old.items():
                 f8.f8_tuning_set(n, v)
     assert torch.equal(outs[0], outs[1])
+    pick = sorted({0, batch // 2, batch - 1})
+    dst = b.net.layers[0].dst
+    assert np.array_equal(outs[0][pick].cpu().numpy(), oracle.run_network(b.net, np.ascontiguousarray(x_np[pick]), keep_all=True)[dst])

@@ -12,7 +12,7 @@
 // computes only a part of the output channels, which makes workgroups out of few images: wave wn has 32
 // channels of its own, and where that still leaves CUs idle, WK waves share K instead (wave kg takes the input
 // channels kg * C / WK onwards of every tap) and their sums meet in LDS at the end.
-//   C = 64: a band of up to 224 pixels, two waves of 32 channels, every weight of a wave in its registers;
+//   C = 64: a band of up to 224 pixels, two waves (MG = 2: four) of 32 channels, every weight of a wave in its registers;
 //   C = 256: a whole image of up to 224 pixels (7 blocks of 32); C = 512: two 7 x 7 images (4 blocks);
 //   C = 128: a band of up to 224 pixels.
 // With one wave per SIMD 12.0 us for 256 channels on 64 images (two waves share K), with two 11.1; 16.4 us on 128 images
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(64 * Shape<C>::NW * MG, MG == 2 ? (C == 64 ? 2 : 1)
   }
 
   // ---- the input pixels and a border of zeros into LDS, xor 0x80 when unsigned.  A wave takes the patch rows
-  // wave, wave + 4, ...; a row's pixels are consecutive in memory, so a lane's 16-byte pieces of a row lie at
+  // wave, wave + NWG, ...; a row's pixels are consecutive in memory, so a lane's 16-byte pieces of a row lie at
   // fixed offsets from its first pixel (the scalar part of the address) and at fixed places in a patch row.
   // Border columns: an offset the descriptor rejects, which reads as zero; border rows: an empty descriptor.
   const size_t image_bytes = (size_t)p.H * p.W * C;

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(NT, 1) void conv_s2_kernel(const ConvS2Params p, co
   const int n_lane = n0 + 32 * wn + 16 * half;       // this lane's 16 channels (registers 0..15 of a block)
 
   // ---- the input pixels and a border of zeros into LDS, xor 0x80 when unsigned.  A wave takes the patch rows
-  // wave, wave + 4, ...; a row's pixels are consecutive in memory, so a lane's 16-byte pieces of a row lie at
+  // wave, wave + NW, ...; a row's pixels are consecutive in memory, so a lane's 16-byte pieces of a row lie at
   // fixed offsets from its first pixel (the scalar part of the address) and at fixed places in a patch row.
   // Border columns: an offset the descriptor rejects, which reads as zero; border rows: an empty descriptor.
   const size_t image_bytes = (size_t)p.H * p.W * C;

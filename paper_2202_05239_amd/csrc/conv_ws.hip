@@ -64,10 +64,9 @@ __global__ __launch_bounds__(WS_NT, 2) void conv_ws_kernel(const ConvWsParams p)
   // Every workgroup walks a contiguous range of tiles (the ranges differ by at most one tile), so the
   // input rows two neighbouring tiles share are fetched twice by the same CU, a few microseconds
   // apart: the second fetch is served by that XCD's L2 instead of HBM.
-  const int per = p.ntiles / (int)gridDim.x, rem = p.ntiles % (int)gridDim.x;
-  const int wg = (int)xcd_remap(blockIdx.x, gridDim.x);      // the k-th eighth of the pixels on XCD k, as everywhere
-  int t = wg * per + min(wg, rem);
-  const int t_end = t + per + (wg < rem ? 1 : 0);
+  const XcdRange run = xcd_run(blockIdx.x, gridDim.x, p.ntiles);      // the k-th eighth of the pixels on XCD k, as everywhere
+  int t = run.first;
+  const int t_end = run.end;
   if (t >= t_end) return;
 
   const int zx = (int)p.x_xor;
@@ -297,10 +296,9 @@ __global__ __launch_bounds__(WS_NT, 2) void conv_ws64_kernel(const ConvWsParams 
   const int l32 = lane & 31, half = lane >> 5;
   const int HW = p.H * p.W;
 
-  const int per = p.ntiles / (int)gridDim.x, rem = p.ntiles % (int)gridDim.x;
-  const int wg = (int)xcd_remap(blockIdx.x, gridDim.x);      // the k-th eighth of the pixels on XCD k, as everywhere
-  int t = wg * per + min(wg, rem);
-  const int t_end = t + per + (wg < rem ? 1 : 0);
+  const XcdRange run = xcd_run(blockIdx.x, gridDim.x, p.ntiles);      // the k-th eighth of the pixels on XCD k, as everywhere
+  int t = run.first;
+  const int t_end = run.end;
   if (t >= t_end) return;
 
   const int zx = (int)p.x_xor;

@@ -272,7 +272,10 @@ struct f8_chain {
     std::vector<char> role;
   };
   PdpRoles pdp_prepared[3];
-  void forget_pdp_roles() { for (PdpRoles &r : pdp_prepared) r.batch = -1; }
+  void forget_pdp_roles() {
+    for (PdpRoles &r : pdp_prepared) r.batch = -1;
+    roles_batch = -1;
+  }
   void prepare_pdp_roles(int batch) {
     forget_pdp_roles();
     const int batches[3] = {batch, batch / 2, batch - batch / 2};
@@ -539,9 +542,32 @@ struct f8_chain {
   // line lies at 13 images of ResNet-50 at 224 x 224, 15 of ResNet-18, 26 of MobileNetV1 and 44 of MobileNetV2 (160 x 160: twice as many), below the
   // crossover of each (about 50, 190, beyond 192 and 75 in that order), which no one number per layer can follow: between the two the caller's choice stands,
   // and by these figures it loses up to 44 % (ResNet-18, 16 images).
+  // Below the line the caller's choice stands too where the whole batch needs four launches more than a half of it (blocks whose one launch pays for few
+  // pixels only).  Whole / halves, launches of each: MobileNetV2 224 x 224, 41 images 257 / 238, 26 and 22, 192 x 192, 57 258 / 241, 28 and 22, 64 x 64, 370 258 / 230, 42 and 24,
+  // 128 x 128, 107 216 / 226, 26 and 22; with fewer MobileNetV2 96 x 96, 79 161 / 191, 24 and 22, MobileNetV1 224 x 224, 23 183 / 223, 25 and 24.
   bool side_by_side(int batch) const {
     if (n_streams != 2 || keep_all || batch < 2) return false;
-    return halves == 2 || image_us * batch >= 3.2 * (double)layers.size();
+    return halves == 2 || image_us * batch >= 3.2 * (double)layers.size() || (batch == roles_batch ? roles_more_launches : more_launches(batch));
+  }
+  // (as of the last f8_chain_prepare: a run does not look at every layer for it)
+  int roles_batch = -1;
+  bool roles_more_launches = false;
+  bool more_launches(int batch) const {
+    int whole = 0, half = 0;
+    for (size_t i = 0; i < layers.size(); ++i) {
+      whole += !rides_along(i, batch);
+      half += !rides_along(i, batch - batch / 2);
+    }
+    return whole >= half + 4;
+  }
+  // Whether layer i is computed by another layer's launch at this batch.
+  bool rides_along(size_t i, int batch) const {
+    if (pool_role(i) != 0) return pool_role(i) == 2;
+    if (use_fusion() && fused[i].role != 0) return fused[i].role == 2;
+    const int three = bn_role(i, batch), block = pdp_role(i, batch);
+    if (three > 1 || proj_role(i, batch) || block == 1 || block == 3) return true;
+    if (s2[i] == 2 && s2_waves(i, batch) != 0) return true;
+    return pair_role(i, batch) == 1 || (three == 0 && (tail_role(i, batch) == 2 || dwp_role(i, batch) == 2));
   }
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -1319,6 +1345,8 @@ f8_status f8_chain_prepare(f8_chain *c, void *workspace, int batch, void *stream
   for (int k : {0, 1}) c->placed[k] = c->layout_at(batch, k == 1);
   c->place_fragments(batch, c->frag_off.data(), c->bn_off.data());
   c->prepare_pdp_roles(batch);
+  c->roles_batch = batch;
+  c->roles_more_launches = c->more_launches(batch);
   if (hipMemsetAsync(workspace, 0, 256, s) != hipSuccess) return F8_ERR_DEVICE;
   for (size_t i = 0; i < c->layers.size(); ++i) {
     const f8_layer_desc &L = c->layers[i];
@@ -1558,7 +1586,7 @@ f8_status f8_chain_layer_info(const f8_chain *c, int layer, int batch, char *ker
   const int three = c->bn_role((size_t)layer, batch);
   const int block = c->pdp_role((size_t)layer, batch), twin = c->pair_role((size_t)layer, batch);
   const bool two = c->s2_waves((size_t)layer, batch) != 0;
-  if (three > 1 || (two && c->s2[layer] == 2) || block == 1 || block == 3 || twin == 1 || (three == 0 && (c->tail_role((size_t)layer, batch) == 2 || c->dwp_role((size_t)layer, batch) == 2))) {
+  if (c->rides_along((size_t)layer, batch) && !c->proj_role((size_t)layer, batch)) {
     // accounted to the layer in front (of the first layer of an inverted-residual or basic block: behind), whose launch computes this one
     const char *fname = "(fused)";
     if (kernel_name && name_len > 0) {

@@ -13,6 +13,22 @@ NETS = [(wl.config4, 5, 96), (wl.resnet50_private_fl, 5, 96), (wl.config3, 24, 9
         (wl.config3, 65, 224)]
 
 
+def test_batch_that_needs_more_launches_than_its_halves():
+    """Below the line too the halves run side by side where the whole batch is several launches more: MobileNetV2's blocks from 32 images on."""
+    _, net = wl.mobilenet_v2_forward(batch=1)
+    two, one = f8.Chain(net, streams=2), f8.Chain(net)
+
+    def launches(n):
+        return sum(two.layer_info(i, n)[0] != "(fused)" for i in range(len(net.layers)))
+
+    for n in (11, 27, 30, 39, 41, 43):
+        assert (two.streams_at(n) == 2) == (launches(n) >= launches(n - n // 2) + 4), n
+        assert one.streams_at(n) == 1
+    assert two.streams_at(27) == 1 and two.streams_at(41) == 2
+    x = torch.from_numpy(wl.mobilenet_v2_forward(batch=41)[0]).cuda()
+    assert torch.equal(two.prepare(41).run(x), one.prepare(41).run(x))
+
+
 @pytest.mark.parametrize("k", range(len(NETS)))
 def test_halves_side_by_side_or_not(oracle, k):
     fn, batch, hw = NETS[k]

@@ -356,7 +356,7 @@ def main():
                                % ({"resnet50": "configs[4]", "resnet18": "configs[3]"}.get(args.net, "extra"),
                                   net.name, B),
                    "global_batch": B, "input": "224x224x3 int8", "layers": len(net.layers),
-                   "streams_per_step": args.streams},
+                   "streams_per_step": chain.streams_at(B)},
         "whole_net_TOPS": total_ops / (dt / args.steps) / 1e12,
         "roofline": roof,
     }

@@ -248,7 +248,8 @@ f8_status f8_chain_set_fusion(f8_chain *c, int fusion);
  * chip idle, or that wait on memory, overlap with layers of the other half.  The workspace is
  * the same size.  Intermediate tensors are then not available through f8_chain_tensor; with
  * keep_all, for a batch of one image, or where an estimate from the layers' sizes says that they are so short that halves
- * side by side lose clearly, the call runs on one stream.  The estimate keeps to the safe side: some way above its line
+ * side by side lose clearly (and the whole batch does not need several launches more than a half of it, because launches of
+ * whole blocks pay for few images only), the call runs on one stream.  The estimate keeps to the safe side: some way above its line
  * halves still take longer (224 x 224, whole / halves, microseconds: ResNet-18 on 64 images 222 / 269, level at about 190; ResNet-50 on 32 347 /
  * 381, ahead from 64), so what a program uses should be measured at its batch.  n_streams = 1 (the default)
  * turns it off. */
